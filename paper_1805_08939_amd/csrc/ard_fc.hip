@@ -413,14 +413,14 @@ int fc_fwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const vo
   const bool a_vec = vec_rows(g.a.ld, sizeof(T));
   const bool b_vec = vec_rows(s.B, sizeof(T));
   if (s.input_major) {  // A(m, k) = W^T[in(k)][m]: m-contiguous
-    if (fast_ok<true, true>(g, sizeof(T))) {
-      ARD_HIP_CHECK((run_fast_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, wv.partial)));
+    if (any_ok<true, true>(g, sizeof(T))) {
+      ARD_HIP_CHECK((run_strided_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, wv.partial)));
     } else {
       ARD_HIP_CHECK((run_gemm<T, T, MC_VEC, MC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
           g, 1, a_vec, b_vec, stream, wv.partial)));
     }
-  } else if (fast_ok<false, true>(g, sizeof(T))) {
-    ARD_HIP_CHECK((run_fast_gemm<T, false, true, T, EPI_FWD>(g, 1, stream, wv.partial)));
+  } else if (any_ok<false, true>(g, sizeof(T))) {
+    ARD_HIP_CHECK((run_strided_gemm<T, false, true, T, EPI_FWD>(g, 1, stream, wv.partial)));
   } else {
     ARD_HIP_CHECK((run_gemm<T, T, KC_VEC, KC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
         g, 1, a_vec, b_vec, stream, wv.partial)));
@@ -537,8 +537,8 @@ int run_bwd_data(const ard_fc_desc* d, const FcShape& s, const GemmArgs& g, cons
   const bool a_vec = vec_rows(g.a.ld, sizeof(T));
   const bool b_vec = vec_rows(s.B, sizeof(T));
   if (s.input_major) {  // A(m, t) = W^T[in(m)][t]: k-contiguous rows
-    if (fast_ok<false, true>(g, sizeof(T))) {
-      ARD_HIP_CHECK((run_fast_gemm<T, false, true, T, EPI_FWD>(g, 1, stream, partial)));
+    if (any_ok<false, true>(g, sizeof(T))) {
+      ARD_HIP_CHECK((run_strided_gemm<T, false, true, T, EPI_FWD>(g, 1, stream, partial)));
     } else if (gated) {
       ARD_HIP_CHECK((run_gemm<T, T, KC_VEC, KC_ELEM, MC_VEC, MC_ELEM, false, true, EPI_FWD>(
           g, 1, a_vec, b_vec, stream, partial)));
@@ -546,8 +546,8 @@ int run_bwd_data(const ard_fc_desc* d, const FcShape& s, const GemmArgs& g, cons
       ARD_HIP_CHECK((run_gemm<T, T, KC_VEC, KC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
           g, 1, a_vec, b_vec, stream, partial)));
     }
-  } else if (fast_ok<true, true>(g, sizeof(T))) {
-    ARD_HIP_CHECK((run_fast_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, partial)));
+  } else if (any_ok<true, true>(g, sizeof(T))) {
+    ARD_HIP_CHECK((run_strided_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, partial)));
   } else if (gated) {
     ARD_HIP_CHECK((run_gemm<T, T, MC_VEC, MC_ELEM, MC_VEC, MC_ELEM, false, true, EPI_FWD>(
         g, 1, a_vec, b_vec, stream, partial)));
@@ -578,8 +578,8 @@ int fc_bwd_weight_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, c
                       : nullptr;
   bool dbias_done = false;
   if (s.input_major) {  // the bias gradient from dbias_kernel (G is the B operand here)
-    if (fast_ok<false, false>(g, sizeof(T))) {
-      ARD_HIP_CHECK((run_fast_gemm<T, false, false, float, EPI_FWD>(g, 1, stream, partial)));
+    if (any_ok<false, false>(g, sizeof(T))) {
+      ARD_HIP_CHECK((run_strided_gemm<T, false, false, float, EPI_FWD>(g, 1, stream, partial)));
     } else if (gated) {
       ARD_HIP_CHECK((run_gemm<T, float, KC_VEC, KC_ELEM, KC_VEC, KC_ELEM, false, true, EPI_FWD>(
           g, 1, v, v, stream, partial)));
@@ -587,13 +587,13 @@ int fc_bwd_weight_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, c
       ARD_HIP_CHECK((run_gemm<T, float, KC_VEC, KC_ELEM, KC_VEC, KC_ELEM, false, false, EPI_FWD>(
           g, 1, v, v, stream, partial)));
     }
-  } else if (fast_ok<false, false>(g, sizeof(T))) {
+  } else if (any_ok<false, false>(g, sizeof(T))) {
     // dbias = scale * G 1: the row sums of A, taken by the same kernel
     if (dbias) {
       g.rsum = dbias + s.out_offset;
       g.rsum_ld = s.out_period;
     }
-    ARD_HIP_CHECK((run_fast_gemm<T, false, false, float, EPI_FWD, true>(g, 1, stream, partial, &dbias_done)));
+    ARD_HIP_CHECK((run_strided_gemm<T, false, false, float, EPI_FWD, true>(g, 1, stream, partial, &dbias_done)));
   } else if (gated) {
     ARD_HIP_CHECK((run_gemm<T, float, KC_VEC, KC_ELEM, KC_VEC, KC_ELEM, true, false, EPI_FWD>(
         g, 1, v, v, stream, partial)));
@@ -618,17 +618,27 @@ int fc_bwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const vo
   if (st != ARD_OK) return st;
   const GemmArgs gd = bwd_data_args<T>(d, s, dYt, Yt, wv.op, dXt, Xgate);
   GemmArgs gw = bwd_weight_args<T>(d, s, Xt, dYt, Yt, dW);
-  if (!s.input_major && fast_ok<true, true>(gd, sizeof(T)) && fast_ok<false, false>(gw, sizeof(T)) &&
-      fast_pair_ok<T>(gd, gw)) {
+  const bool fast = fast_ok<true, true>(gd, sizeof(T)) && fast_ok<false, false>(gw, sizeof(T));
+  // both on register loads: neither is split off to the direct loads of a call of its own
+  const bool any = !fast && !fast_ok<true, true>(gd, sizeof(T)) && !fast_ok<false, false>(gw, sizeof(T)) &&
+                   any_ok<true, true>(gd, sizeof(T)) && any_ok<false, false>(gw, sizeof(T));
+  if (!s.input_major && ((fast && fast_pair_ok<T>(gd, gw)) || (any && any_pair_ok<T>(gd, gw)))) {
     if (dbias) {
       gw.rsum = dbias + s.out_offset;
       gw.rsum_ld = s.out_period;
+    }
+    if (fast && dbias)
       ARD_HIP_CHECK((launch_fast_pair<T, true, true, T, EPI_FWD, false, false, false, float, EPI_FWD, true>(
           gd, gw, stream)));
-    } else {
+    else if (fast)
       ARD_HIP_CHECK((launch_fast_pair<T, true, true, T, EPI_FWD, false, false, false, float, EPI_FWD, false>(
           gd, gw, stream)));
-    }
+    else if (dbias)
+      ARD_HIP_CHECK((launch_fast_pair<T, true, true, T, EPI_FWD, false, false, false, float, EPI_FWD, true, true>(
+          gd, gw, stream)));
+    else
+      ARD_HIP_CHECK((launch_fast_pair<T, true, true, T, EPI_FWD, false, false, false, float, EPI_FWD, false, true>(
+          gd, gw, stream)));
     if ((st = zero_dropped_inputs<T>(d, s, dXt, stream)) != ARD_OK) return st;
     return finish_bwd_weight<T>(d, s, dYt, Yt, dW, dbias, dbias != nullptr, stream);
   }

@@ -510,6 +510,168 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
   wait_vm<0>();  // no direct load may still write LDS past this point
 }
 
+// ------------------------------------------------------------------------
+// The same GEMM for views whose rows start at any element (a batch or a row
+// length that is no multiple of 16 bytes). A direct load moves whole 16-byte
+// aligned chunks only, so here the slab passes through registers: every lane
+// loads its chunks with 16-byte loads of element alignment (whole lines all
+// the same: consecutive lanes read consecutive chunks) and writes them to the
+// LDS position that the direct load would have filled. Two slabs are in
+// flight in registers while a third is computed from LDS. A chunk that
+// reaches past the extent is loaded element by element and padded with zeros:
+// nothing past a row's last valid element is read, and no zeroing pass over a
+// partial slab is needed.
+// Bound by the latency of a slab's loads at small sizes, like the direct-load
+// kernels. It replaced the general kernel's element loads (one load
+// instruction per element instead of one per 4 fp32 or 8 bf16, with 64-bit
+// address arithmetic in each). One layer's forward and backward on MI355X:
+// bf16 batch 100, 1023 -> 1537: 63 -> 42 us; fp32 batch 330, 6566 -> 114:
+// 126 -> 55 us; bf16 batch 860, 1586 -> 408: 83 -> 32 us.
+
+// Sixteen bytes at an address aligned to ES bytes only.
+template <int ES>
+__device__ __forceinline__ u32x4 load16_any(const char* p) {
+  typedef u32x4 u32x4_a2 __attribute__((aligned(2), may_alias));
+  typedef u32x4 u32x4_a4 __attribute__((aligned(4), may_alias));
+  if constexpr (ES == 2)
+    return *reinterpret_cast<const u32x4_a2*>(p);
+  else
+    return *reinterpret_cast<const u32x4_a4*>(p);
+}
+
+// The first n (< 16 / ES) elements at p, zeros behind them.
+template <int ES>
+__device__ __forceinline__ u32x4 load16_part(const char* p, int n) {
+  u32x4 x = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int e = 0; e < 16 / ES; ++e) {
+    if (e < n) {
+      if constexpr (ES == 4)
+        x[e] = *reinterpret_cast<const uint32_t*>(p + 4 * e);
+      else
+        x[e / 2] |= static_cast<uint32_t>(*reinterpret_cast<const uint16_t*>(p + 2 * e)) << (16 * (e & 1));
+    }
+  }
+  return x;
+}
+
+// DmaSrc's chunk-to-LDS assignment with loads into registers.
+template <class Cfg, int R, bool MC>
+struct RegSrc {
+  static constexpr int ES = Cfg::ES, EPC = 16 / ES;
+  static constexpr int CPR = MC ? R * ES / 16 : Cfg::BK * ES / 16;
+  static constexpr int PER_WAVE = R * Cfg::BK * ES / 1024 / Cfg::NW;
+  uint32_t off[PER_WAVE];  // byte offset of the lane's chunk from the slab base
+  int k[PER_WAVE];         // the chunk's first k (KC) or its k-row (MC) within the slab
+  int nv[PER_WAVE];        // MC: valid columns of the chunk, <= 0 none
+
+  __device__ __forceinline__ void init(int64_t ld, int r0, int rext, int wave) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) {
+      const int pos = (wave * PER_WAVE + i) * 64 + lane;
+      if constexpr (!MC) {
+        const int r = pos / CPR;
+        const int c = (pos % CPR) ^ kc_swz<CPR>(r);
+        const int row = r0 + r < rext ? r0 + r : rext - 1;  // past the extent: a valid row, its results are discarded
+        off[i] = static_cast<uint32_t>(row * ld * ES) + static_cast<uint32_t>(c * 16);
+        k[i] = c * EPC;
+      } else {
+        const int kk = pos / CPR;
+        const int c = (pos % CPR) ^ mc_swz<CPR, ES>(kk);
+        const int col = r0 + c * EPC;
+        off[i] = static_cast<uint32_t>(kk * ld * ES) + static_cast<uint32_t>(col * ES);
+        k[i] = kk;
+        nv[i] = rext - col;
+      }
+    }
+  }
+
+  // The slab whose first element is at base, of which the first kv k (k-rows) are valid.
+  __device__ __forceinline__ void load(const char* base, int kv, u32x4 (&v)[PER_WAVE]) const {
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) {
+      const int n = MC ? (k[i] < kv ? nv[i] : 0) : kv - k[i];
+      if (n >= EPC)
+        v[i] = load16_any<ES>(base + off[i]);
+      else
+        v[i] = load16_part<ES>(base + off[i], n);
+    }
+  }
+
+  __device__ __forceinline__ void store(char* region, int wave, const u32x4 (&v)[PER_WAVE]) const {
+    char* p = region + wave * PER_WAVE * 1024 + (threadIdx.x & 63) * 16;
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) *reinterpret_cast<u32x4*>(p + i * 1024) = v[i];
+  }
+};
+
+// SlabLoader's walk over the slabs with register loads.
+template <class Cfg, bool AMC, bool BMC>
+struct RegLoader {
+  using SrcA = RegSrc<Cfg, Cfg::BM, AMC>;
+  using SrcB = RegSrc<Cfg, Cfg::BN, BMC>;
+  struct Regs {
+    u32x4 a[SrcA::PER_WAVE], b[SrcB::PER_WAVE];
+  };
+  SrcA da;
+  SrcB db;
+  const char* na;
+  const char* nb;
+  int64_t a_step, b_step, a_wrap, b_wrap;
+  int K, ik, wv;
+
+  __device__ __forceinline__ void load(Regs& r) {  // the next slab, then the advance
+    da.load(na, K - ik, r.a);
+    db.load(nb, K - ik, r.b);
+    na += a_step;
+    nb += b_step;
+    ik += Cfg::BK;
+    if (ik >= K) ik = 0, na += a_wrap, nb += b_wrap;
+  }
+  __device__ __forceinline__ void store(char* stage, const Regs& r) const {
+    da.store(stage, wv, r.a);
+    db.store(stage + Cfg::ABYTES, wv, r.b);
+  }
+};
+
+// The slab pipeline on register loads: slab q is computed from LDS stage
+// q % 2 while slabs q + 1 and q + 2 are on their way in registers; one
+// barrier per slab.
+template <class Cfg, bool AMC, bool BMC, bool RSUM>
+__device__ __forceinline__ void run_slabs_reg(RegLoader<Cfg, AMC, BMC>& ld, int nslab,
+                                              f32x16 (&acc)[Cfg::FM][Cfg::FN], int wm, int wn, int kw0, char* smem,
+                                              float* rs) {
+  using Frags = StepFrags<Cfg, AMC, BMC>;
+  constexpr int STEPS = Cfg::KW / Frags::KSTEP;
+  static_assert(Cfg::STAGES >= 2, "two LDS stages");
+  if (nslab <= 0) return;
+  typename RegLoader<Cfg, AMC, BMC>::Regs buf[2];
+  ld.load(buf[0]);
+  if (nslab > 1) ld.load(buf[1]);
+  ld.store(smem, buf[0]);
+  if (nslab > 2) ld.load(buf[0]);
+  lds_barrier();
+  auto slab = [&](int q, int par) {  // par = q % 2, a constant where it is used
+    const char* st = smem + par * Cfg::STAGE;
+    Frags fr[2];
+    fr[0].load(st, wm, wn, kw0);
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      if (s + 1 < STEPS) fr[(s + 1) & 1].load(st, wm, wn, kw0 + (s + 1) * Frags::KSTEP);
+      fr[s & 1].mma(acc);
+      if constexpr (RSUM) fr[s & 1].rowsum(*reinterpret_cast<float(*)[Cfg::FM]>(rs));
+    }
+    if (q + 1 < nslab) ld.store(smem + (par ^ 1) * Cfg::STAGE, buf[par ^ 1]);
+    if (q + 3 < nslab) ld.load(buf[par ^ 1]);
+    lds_barrier();  // slab q + 1 is in LDS; no wave reads slab q any more
+  };
+  for (int q = 0; q < nslab; q += 2) {
+    slab(q, 0);
+    if (q + 1 < nslab) slab(q + 1, 1);
+  }
+}
+
 // Output of one wave's accumulator tile. Each block row of 32 rows passes
 // through the wave's own LDS region in fp32 (epilogue applied on the way in),
 // and every lane then writes 4 consecutive values of one output row (16 bytes
@@ -644,7 +806,8 @@ __device__ __forceinline__ void fast_store(const GemmArgs& g, f32x16 (&acc)[Cfg:
 // row 32 i + l % 32, the waves of a k split are added in LDS in split order.
 // One workgroup's output tile: position bid of an nx x ny tile grid in the
 // grouped order, batch-and-split index bzs.
-template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false>
+// ANY: the operands' rows start at any element (register loads).
+template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false, bool ANY = false>
 __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, int tile_col, int bzs, char* smem) {
   using T = typename Cfg::T;
   const int n0 = tile_col * Cfg::BN;
@@ -679,9 +842,9 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
   }
 
   // slabs q0 .. q1 - 1 of this split
-  SlabLoader<Cfg, AMC, BMC> ld;
+  using Loader = typename std::conditional<ANY, RegLoader<Cfg, AMC, BMC>, SlabLoader<Cfg, AMC, BMC>>::type;
+  Loader ld;
   ld.wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  ld.lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
   static_assert(DmaSrc<Cfg, Cfg::BM, AMC>::PER_WAVE + DmaSrc<Cfg, Cfg::BN, BMC>::PER_WAVE == Cfg::LPW, "load count");
   if (q0 < q1) {
     ld.da.init(g.a.ld, m0, g.M, ld.wv);
@@ -695,14 +858,19 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
   ld.b_wrap = g.b.kbstride * ES - nks * ld.b_step;
   const int ib = q0 == 0 ? 0 : q0 / (nks > 0 ? nks : 1);
   ld.ik = (q0 - ib * nks) * Cfg::BK;
-  ld.is = 0;
-  ld.left = q1 - q0 - 1;
   ld.na = uniform_ptr(reinterpret_cast<const char*>(abase) + (ib * g.a.kbstride) * ES + ld.ik / Cfg::BK * ld.a_step);
   ld.nb = uniform_ptr(reinterpret_cast<const char*>(bbase) + (ib * g.b.kbstride) * ES + ld.ik / Cfg::BK * ld.b_step);
   float rs[Cfg::FM];
 #pragma unroll
   for (int i = 0; i < Cfg::FM; ++i) rs[i] = 0.0f;
-  run_slabs<Cfg, AMC, BMC, true, RSUM>(ld, q1 - q0, g.K, ld.ik, acc, wm, wn, ks * Cfg::KW, smem, rs);
+  if constexpr (ANY) {
+    run_slabs_reg<Cfg, AMC, BMC, RSUM>(ld, q1 - q0, acc, wm, wn, ks * Cfg::KW, smem, rs);
+  } else {
+    ld.lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
+    ld.is = 0;
+    ld.left = q1 - q0 - 1;
+    run_slabs<Cfg, AMC, BMC, true, RSUM>(ld, q1 - q0, g.K, ld.ik, acc, wm, wn, ks * Cfg::KW, smem, rs);
+  }
   const int rlane = threadIdx.x & 63;
   if constexpr (RSUM) {
 #pragma unroll
@@ -789,7 +957,7 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
 // holding a few tiles of every slice. When an operand is shared by the batch
 // entries (batch stride 0), positions run within each slice: XCD x then holds
 // the same tiles of every entry and the shared panels stay in its L2.
-template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false>
+template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false, bool ANY = false>
 __global__ void __launch_bounds__(Cfg::NT) fast_gemm_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nx = gridDim.x, ny = gridDim.y, nxy = nx * ny;
@@ -803,7 +971,7 @@ __global__ void __launch_bounds__(Cfg::NT) fast_gemm_kernel(GemmArgs g) {
     grouped_order(t % nxy, nx, ny, tile_row, tile_col);
     z = t / nxy;
   }
-  fast_gemm_tile<Cfg, AMC, BMC, OutT, EPI, RSUM>(g, tile_row, tile_col, z, smem);
+  fast_gemm_tile<Cfg, AMC, BMC, OutT, EPI, RSUM, ANY>(g, tile_row, tile_col, z, smem);
 }
 
 // Two independent GEMMs of one configuration in one launch (no batch, no k
@@ -811,7 +979,7 @@ __global__ void __launch_bounds__(Cfg::NT) fast_gemm_kernel(GemmArgs g) {
 // One launch instead of two saves a kernel's fixed start and drain time, and
 // two problems too small to fill the chip alone run side by side.
 template <class Cfg, bool AMC1, bool BMC1, typename OutT1, int EPI1, bool RSUM1, bool AMC2, bool BMC2,
-          typename OutT2, int EPI2, bool RSUM2>
+          typename OutT2, int EPI2, bool RSUM2, bool ANY = false>
 __global__ void __launch_bounds__(Cfg::NT) fast_gemm_pair_kernel(GemmArgs g1, GemmArgs g2) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nx1 = (g1.N + Cfg::BN - 1) / Cfg::BN, ny1 = (g1.M + Cfg::BM - 1) / Cfg::BM;
@@ -819,11 +987,11 @@ __global__ void __launch_bounds__(Cfg::NT) fast_gemm_pair_kernel(GemmArgs g1, Ge
   int row, col;
   if (b < nx1 * ny1) {
     grouped_tile(b, nx1, ny1, row, col);
-    fast_gemm_tile<Cfg, AMC1, BMC1, OutT1, EPI1, RSUM1>(g1, row, col, 0, smem);
+    fast_gemm_tile<Cfg, AMC1, BMC1, OutT1, EPI1, RSUM1, ANY>(g1, row, col, 0, smem);
   } else {
     const int nx2 = (g2.N + Cfg::BN - 1) / Cfg::BN, ny2 = (g2.M + Cfg::BM - 1) / Cfg::BM;
     grouped_tile(b - nx1 * ny1, nx2, ny2, row, col);
-    fast_gemm_tile<Cfg, AMC2, BMC2, OutT2, EPI2, RSUM2>(g2, row, col, 0, smem);
+    fast_gemm_tile<Cfg, AMC2, BMC2, OutT2, EPI2, RSUM2, ANY>(g2, row, col, 0, smem);
   }
 }
 
@@ -843,6 +1011,20 @@ inline bool fast_ok(const GemmArgs& g, size_t esize) {
     const int64_t span = mc ? e + 256 * o.ld : (e - 1) * o.ld + 256;
     return o.ridx == nullptr && o.cidx == nullptr && o.y == nullptr && o.ld % epc == 0 && o.bstride % epc == 0 &&
            o.kbstride % epc == 0 && (reinterpret_cast<uintptr_t>(o.p) & 15u) == 0 && o.ld >= 0 &&
+           span * static_cast<int64_t>(esize) < (int64_t{1} << 31);
+  };
+  return ok(g.a, g.M, AMC) && ok(g.b, g.N, BMC);
+}
+
+// Whether a problem can run on the register-load variant: plain strided views
+// (no gather, no load-time gate) with the same bound on a slab's span, rows
+// starting at any element.
+template <bool AMC, bool BMC>
+inline bool any_ok(const GemmArgs& g, size_t esize) {
+  auto ok = [esize](const GemmOperand& o, int ext, bool mc) {
+    const int64_t e = ext > 0 ? ext : 1;
+    const int64_t span = mc ? e + 256 * o.ld : (e - 1) * o.ld + 256;
+    return o.ridx == nullptr && o.cidx == nullptr && o.y == nullptr && o.ld >= 0 &&
            span * static_cast<int64_t>(esize) < (int64_t{1} << 31);
   };
   return ok(g.a, g.M, AMC) && ok(g.b, g.N, BMC);
@@ -998,10 +1180,10 @@ inline size_t fast_partial_floats(int M, int N, int K, int kbatch, int batch) {
   return p.splits > 1 ? static_cast<size_t>(p.splits) * batch * M * N : 0;
 }
 
-template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false>
+template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false, bool ANY = false>
 inline hipError_t launch_fast(const GemmArgs& g, int batch, hipStream_t stream) {
   const int splits = g.splits > 1 ? g.splits : 1;
-  auto kern = fast_gemm_kernel<Cfg, AMC, BMC, OutT, EPI, RSUM>;
+  auto kern = fast_gemm_kernel<Cfg, AMC, BMC, OutT, EPI, RSUM, ANY>;
   // per instantiation, once (thread-safe static initialisation): allow more than 64 KB of dynamic LDS
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS);
@@ -1021,13 +1203,13 @@ inline hipError_t launch_fast(const GemmArgs& g, int batch, hipStream_t stream) 
   return hipGetLastError();
 }
 
-// Launches g1 and g2 (both fast_ok, splits 1, no batch) as one grid of
-// fast_gemm_pair_kernel on the 32x32 configuration of T.
+// Launches g1 and g2 (both fast_ok, or both any_ok with ANY; splits 1, no
+// batch) as one grid of fast_gemm_pair_kernel on the 32x32 configuration of T.
 template <typename T, bool AMC1, bool BMC1, typename OutT1, int EPI1, bool RSUM1, bool AMC2, bool BMC2,
-          typename OutT2, int EPI2, bool RSUM2>
+          typename OutT2, int EPI2, bool RSUM2, bool ANY = false>
 inline hipError_t launch_fast_pair(GemmArgs g1, GemmArgs g2, hipStream_t stream) {
   using Cfg = typename FastCfgs<T>::Small;
-  auto kern = fast_gemm_pair_kernel<Cfg, AMC1, BMC1, OutT1, EPI1, RSUM1, AMC2, BMC2, OutT2, EPI2, RSUM2>;
+  auto kern = fast_gemm_pair_kernel<Cfg, AMC1, BMC1, OutT1, EPI1, RSUM1, AMC2, BMC2, OutT2, EPI2, RSUM2, ANY>;
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS);
   if (attr != hipSuccess) return attr;
@@ -1093,6 +1275,68 @@ inline hipError_t run_fast_gemm(GemmArgs g, int batch, hipStream_t stream, float
   }
   g.rsum = nullptr;
   return launch_planned<T, AMC, BMC, OutT, EPI, false>(g, p.kind, batch, stream);
+}
+
+// Plan of the register-load variant. fp32 takes the direct-load plan. bf16
+// has two tile sizes here: its 256-wide tiles leave no registers for two slabs
+// in flight. The split count never exceeds what the workspace of the problem
+// was sized for (the direct-load or the general kernel's plan).
+template <typename T>
+inline FastPlan plan_any(int M, int N, int K, int kbatch, int batch) {
+  FastPlan p = plan_fast<T>(M, N, K, kbatch, batch);
+  if constexpr (sizeof(T) == 2) {
+    using C = FastCfgs<bf16>;
+    const int gs = plan_gemm<T>(M, N, K, kbatch, batch).splits;
+    const int cap = p.splits > gs ? p.splits : gs;
+    const int64_t kb = kbatch > 0 ? kbatch : 1;
+    auto tiles_of = [&](int b) { return static_cast<int64_t>((M + b - 1) / b) * ((N + b - 1) / b) * batch; };
+    p.kind = tiles_of(C::Big::BM) >= kTargetBlocks / 2 ? FAST_BIG : FAST_SMALL;
+    const int b = p.kind == FAST_BIG ? C::Big::BM : C::Small::BM, bk = p.kind == FAST_BIG ? C::Big::BK : C::Small::BK;
+    p.splits = fast_splits(tiles_of(b), kb * ((K + bk - 1) / bk));
+    if (p.splits > cap) p.splits = cap;
+  }
+  return p;
+}
+
+// Runs a GEMM whose operands are plain strided views (any_ok): on the direct
+// loads where the rows start on 16 bytes (fast_ok), else on register loads.
+template <typename T, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false>
+inline hipError_t run_strided_gemm(GemmArgs g, int batch, hipStream_t stream, float* partial,
+                                   bool* rsum_done = nullptr) {
+  if (fast_ok<AMC, BMC>(g, sizeof(T)))
+    return run_fast_gemm<T, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream, partial, rsum_done);
+  if (rsum_done) *rsum_done = false;
+  if (g.M <= 0 || g.N <= 0 || batch <= 0) return hipSuccess;
+  FastPlan p = plan_any<T>(g.M, g.N, g.K, g.kbatch, batch);
+  const int64_t kb = g.kbatch > 0 ? g.kbatch : 1;
+  if (!partial || kb * (g.K / 32 + 1) * p.splits >= int64_t{1} << 31) p.splits = 1;
+  g.splits = p.splits;
+  g.partial = partial;
+  using C = FastCfgs<T>;
+  const bool rs = RSUM && g.rsum && p.splits == 1;
+  if (!rs) g.rsum = nullptr;
+  if (rsum_done) *rsum_done = rs;
+  auto go = [&](auto cfg) {
+    using Cfg = decltype(cfg);
+    if constexpr (RSUM) {
+      if (rs) return launch_fast<Cfg, AMC, BMC, OutT, EPI, true, true>(g, batch, stream);
+    }
+    return launch_fast<Cfg, AMC, BMC, OutT, EPI, false, true>(g, batch, stream);
+  };
+  if (p.kind == FAST_SMALL) return go(typename C::Small{});
+  if constexpr (sizeof(T) == 4) {
+    if (p.kind == FAST_HUGE) return go(typename C::Huge{});
+    if (p.kind == FAST_NARROW) return go(typename C::Narrow{});
+  }
+  return go(typename C::Big{});
+}
+
+// Whether the pair runs as one launch of the register-load 32x32 tiles.
+template <typename T>
+inline bool any_pair_ok(const GemmArgs& g1, const GemmArgs& g2) {
+  if (g1.M <= 0 || g1.N <= 0 || g2.M <= 0 || g2.N <= 0) return false;
+  const FastPlan p1 = plan_any<T>(g1.M, g1.N, g1.K, 1, 1), p2 = plan_any<T>(g2.M, g2.N, g2.K, 1, 1);
+  return p1.kind == FAST_SMALL && p2.kind == FAST_SMALL && p1.splits == 1 && p2.splits == 1;
 }
 
 }  // namespace ard
