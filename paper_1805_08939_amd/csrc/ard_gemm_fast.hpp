@@ -587,6 +587,21 @@ struct RegSrc {
     }
   }
 
+  // As DmaSrc::init_rows.
+  template <class F>
+  __device__ __forceinline__ void init_rows(int64_t ld, F rowof, int wave) {
+    static_assert(!MC, "row gather of a k-contiguous operand");
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) {
+      const int pos = (wave * PER_WAVE + i) * 64 + lane;
+      const int r = pos / CPR;
+      const int c = (pos % CPR) ^ kc_swz<CPR>(r);
+      off[i] = static_cast<uint32_t>(static_cast<int64_t>(rowof(r)) * ld * ES) + static_cast<uint32_t>(c * 16);
+      k[i] = c * EPC;
+    }
+  }
+
   // The slab whose first element is at base, of which the first kv k (k-rows) are valid.
   __device__ __forceinline__ void load(const char* base, int kv, u32x4 (&v)[PER_WAVE]) const {
 #pragma unroll

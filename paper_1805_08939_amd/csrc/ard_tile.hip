@@ -8,13 +8,16 @@
 // pipeline of the fast GEMM, its base taken from the list. bwd_weight runs one
 // workgroup per group of up to kTdpChunk kept tiles of one tile row, which
 // share their dY rows; the X rows of the group's tiles are gathered through
-// the lanes' load offsets. Dropped tiles are never read or computed.
+// the lanes' load offsets. Dropped tiles are never read or computed. 32 x 32
+// tiles, batches whose rows are no multiple of 16 bytes and grids too small
+// for that pipeline run on the wave kernels of ard_tile_wave.hpp.
 
 #include <hip/hip_runtime.h>
 
 #include "ard_gemm.hpp"
 #include "ard_gemm_fast.hpp"
 #include "ard_internal.hpp"
+#include "ard_tile_wave.hpp"
 
 namespace ard {
 
@@ -824,6 +827,20 @@ __global__ void __launch_bounds__(CfgD::NT) tdp_fast_bwd_kernel(TdpFastArgs d, T
     tdp_dw_walk<CfgW, float>(w, b - nd, nw, smem);
 }
 
+// The same with the wave kernels' bwd_data (ard_tile_wave.hpp), for tile
+// columns and batches whose workgroup tiles would not fill the chip.
+template <class WCD, class CfgW, typename T>
+__global__ void __launch_bounds__(WCD::NT) tile_wave_group_bwd_kernel(TileWaveArgs d, TdpFastArgs w, int32_t nd,
+                                                                      int32_t nw) {
+  static_assert(WCD::NT == CfgW::NT, "one block size");
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int b = static_cast<int>(blockIdx.x);
+  if (b < nd)
+    tile_wave_rows<WCD, T, WAVE_BWD_DATA, false>(d, b, 0, smem);
+  else
+    tdp_dw_walk<CfgW, float>(w, b - nd, nw, smem);
+}
+
 // ZERO mode: clears every dropped tile of dW.
 __global__ void zero_dropped_tiles_kernel(const uint32_t* __restrict__ bits, float* __restrict__ dW,
                                           int32_t K, int32_t tile, int32_t tiles_k) {
@@ -914,8 +931,9 @@ hipError_t launch_with_lds(dim3 grid, const TdpFastArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The fast path takes 64 x 64 tiles, batch rows of whole 16-byte chunks, and
-// operands whose chunk offsets from a slab's first element stay below 2^31.
+// The workgroup pipeline takes 64 x 64 tiles, batch rows of whole 16-byte
+// chunks, and operands whose chunk offsets from a slab's first element stay
+// below 2^31.
 template <typename T>
 bool tdp_fast_ok(const TdpArgs& a) {
   const int64_t es = sizeof(T);
@@ -923,6 +941,55 @@ bool tdp_fast_ok(const TdpArgs& a) {
          static_cast<int64_t>(a.K) * a.B * es < (int64_t{1} << 31) &&
          static_cast<int64_t>(a.N) * a.B * es < (int64_t{1} << 31) &&
          static_cast<int64_t>(kFastTile + 1) * a.K * es < (int64_t{1} << 31);
+}
+
+// Whether fwd / bwd_data of `owners` tile rows (columns) runs on the workgroup
+// pipeline rather than the wave kernels: where its tiles fill the chip, alone
+// (fwd) or together with the weight gradient that shares bwd_data's launch.
+// One workgroup walks a tile row's list alone, so with fewer of them the
+// longest list is the product's time. Measured on MI355X, layers at p = 0.5
+// unless noted (pipeline / wave kernels):
+//   fwd, workgroups 256: bf16 4096 x 4096 batch 512 19 / 25 us, fp32 102 / 108;
+//   128: bf16 2048 x 2048 batch 512 11.8 / 10.5; 64: fp32 2048 -> 1024 batch 512
+//   47 / 19; 55: bf16 256 -> 3520 batch 48 7.3 / 4.7; 32: fp32 2048 x 2048 batch
+//   128 50 / 12
+//   one-launch bwd, bwd_data workgroups 128: fp32 2048 -> 1024 batch 512 42 / 47,
+//   bf16 2048 x 2048 batch 512 19 / 20; 102: fp32 2176 -> 512 batch 304, p = 0.3,
+//   29 / 37; 64: bf16 4096 x 4096 batch 64 21.0 / 21.7, fp32 batch 128 115 / 68;
+//   36: fp32 1152 -> 3712 batch 176, p = 0.7, 71 / 31; 12: bf16 384 -> 3840 batch
+//   160, p = 0.7, 12.8 / 10.0
+template <typename T>
+bool rows_on_pipeline(int pass, const TdpArgs& a, int owners) {
+  using C = TdpFastCfgs<T>;
+  int bn = C::Rows::BN;
+  if constexpr (sizeof(T) == 4) {
+    if (a.B <= C::Narrow::BN) bn = C::Narrow::BN;
+  }
+  const int64_t wgs = static_cast<int64_t>(owners) * ((a.B + bn - 1) / bn);
+  return tdp_fast_ok<T>(a) && wgs >= (pass == TDP_FWD ? kTargetBlocks : kTargetBlocks * 3 / 8);
+}
+
+// Group records of a plan with nnz kept tiles in `rows` tile rows of tiles_k
+// (nnz < 0: known on the device only, every row full).
+int64_t group_bound(int nnz, int rows, int tiles_k) {
+  if (nnz < 0) return static_cast<int64_t>(rows) * ((tiles_k + kTdpChunk - 1) / kTdpChunk);
+  const int64_t r = rows < nnz ? rows : nnz;
+  return (nnz + (kTdpChunk - 1) * r) / kTdpChunk;
+}
+
+// Whether bwd_weight runs on the workgroup pipeline's groups (64 rows x four
+// tiles, up to 256 walkers) rather than the wave kernels' 32-row blocks:
+// always where bwd_data does (they share a launch); bf16, whose four tiles
+// share the dY block through LDS (one-launch bwd with groups / blocks: 2048 x
+// 2048 batch 512 20 / 26 us, 4096 x 4096 batch 64 22 / 35 us); fp32, bound by
+// the matrix cores either way, where the grid of groups runs two full rounds
+// (4096 x 4096 batch 128 68 / 80 us, but 2048 -> 1024 batch 512 54 / 47 us, 1152
+// -> 3712 batch 176 35 / 31 us). The rule counts the groups of a full grid, so
+// it does not depend on where the kept count is known.
+template <typename T>
+bool dw_on_pipeline(const TdpArgs& a) {
+  return tdp_fast_ok<T>(a) && (sizeof(T) == 2 || rows_on_pipeline<T>(TDP_BWD_DATA, a, a.tiles_k) ||
+                               group_bound(-1, a.N / a.tile, a.tiles_k) >= 2 * kTargetBlocks);
 }
 
 // fwd or bwd_data on tile configuration Cfg: batch blocks of Cfg::BN, one
@@ -991,6 +1058,188 @@ hipError_t run_tdp_fast_bwd(const TdpArgs& ad, const TdpArgs& aw, const int32_t*
     if (ad.B <= C::Narrow::BN) return launch_tdp_fast_bwd<typename C::Narrow, T>(ad, aw, chunks, tiles_n, tiles_k, nnz, s);
   }
   return launch_tdp_fast_bwd<typename C::Rows, T>(ad, aw, chunks, tiles_n, tiles_k, nnz, s);
+}
+
+// The wave kernels (ard_tile_wave.hpp) take what the workgroup pipeline does
+// not: 32 x 32 tiles and batch rows of any length. Chunk offsets from a part's
+// first element stay below 2^31 bytes.
+template <typename T>
+bool tdp_wave_ok(const TdpArgs& a) {
+  const int64_t es = sizeof(T);
+  return static_cast<int64_t>(a.K) * a.B * es < (int64_t{1} << 31) &&
+         static_cast<int64_t>(a.N) * a.B * es < (int64_t{1} << 31) &&
+         static_cast<int64_t>(a.tile + 1) * a.K * es < (int64_t{1} << 31);
+}
+
+template <void (*KERN)(TileWaveArgs), int LDS>
+hipError_t launch_wave(dim3 grid, int threads, const TileWaveArgs& a, hipStream_t s) {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(KERN),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if (attr != hipSuccess) return attr;
+  auto kern = KERN;
+  hipLaunchKernelGGL(kern, grid, dim3(threads), LDS, s, a);
+  return hipGetLastError();
+}
+
+template <class WC, typename T, bool ANY>
+hipError_t launch_wave_rows(int pass, TileWaveArgs& w, hipStream_t s) {
+  w.nx = (w.B + WC::BN - 1) / WC::BN;
+  const dim3 grid(static_cast<unsigned>(w.nx * w.ny), static_cast<unsigned>(w.splits > 1 ? w.splits : 1));
+  constexpr int LDS = ANY ? WC::LDS_ANY : WC::LDS;
+  if (pass == TDP_FWD)
+    return launch_wave<tile_wave_rows_kernel<WC, T, WAVE_FWD, ANY>, LDS>(grid, WC::NT, w, s);
+  return launch_wave<tile_wave_rows_kernel<WC, T, WAVE_BWD_DATA, ANY>, LDS>(grid, WC::NT, w, s);
+}
+
+template <typename T>
+struct WaveCfgs;
+template <>
+struct WaveCfgs<float> {
+  using N32 = WaveCfg<float, 32, 4, 4>;    // 128 KB LDS
+  using N64 = WaveCfg<float, 64, 4, 3>;    // 144 KB
+  using N128 = WaveCfg<float, 128, 4, 2>;  // 160 KB
+  using Dw = WaveCfg<float, 128, 4, 1>;    // 80 KB
+};
+template <>
+struct WaveCfgs<bf16> {
+  using N32 = WaveCfg<bf16, 32, 4, 8>;    // 128 KB
+  using N64 = WaveCfg<bf16, 64, 4, 6>;    // 144 KB
+  using N128 = WaveCfg<bf16, 128, 4, 4>;  // 160 KB
+  using Dw = WaveCfg<bf16, 128, 4, 2>;    // 80 KB
+};
+
+// Batch columns per workgroup of ny 32-row blocks: wider ones read each W tile
+// fewer times; taken as long as the grid still gives every compute unit a
+// workgroup.
+inline int wave_bn(int64_t ny, int64_t B) {
+  if (B > 64 && ny * ((B + 127) / 128) >= kTargetBlocks) return 128;
+  if (B > 32 && ny * ((B + 63) / 64) >= kTargetBlocks) return 64;
+  return 32;
+}
+
+template <typename T>
+bool rows_aligned(int64_t B) { return (B * static_cast<int64_t>(sizeof(T))) % 16 == 0; }
+
+// fwd / bwd_data of w.ny 32-row blocks.
+template <typename T>
+hipError_t run_wave_rows(int pass, TileWaveArgs& w, hipStream_t s) {
+  using C = WaveCfgs<T>;
+  const int bn = wave_bn(w.ny, w.B);
+  if (rows_aligned<T>(w.B))
+    return bn == 128  ? launch_wave_rows<typename C::N128, T, false>(pass, w, s)
+           : bn == 64 ? launch_wave_rows<typename C::N64, T, false>(pass, w, s)
+                      : launch_wave_rows<typename C::N32, T, false>(pass, w, s);
+  return bn == 128  ? launch_wave_rows<typename C::N128, T, true>(pass, w, s)
+         : bn == 64 ? launch_wave_rows<typename C::N64, T, true>(pass, w, s)
+                    : launch_wave_rows<typename C::N32, T, true>(pass, w, s);
+}
+
+template <typename T>
+TileWaveArgs wave_rows_args(const TdpArgs& a, int owners) {
+  TileWaveArgs w = {};
+  w.act = a.act;
+  w.W = a.W;
+  w.out = a.out;
+  w.ptr = a.ptr;
+  w.list = a.list;
+  w.B = a.B;
+  w.K = a.K;
+  w.tile = a.tile;
+  w.ny = owners * (a.tile / 32);
+  w.hi = 1 << 30;
+  w.scale = a.scale;
+  w.splits = 1;
+  return w;
+}
+
+// Arguments and workgroup count of the weight gradient over at most `groups` records.
+template <typename T>
+TileWaveDwArgs wave_dw_args(const TdpArgs& a, const int32_t* chunks, int64_t groups, int64_t* wgs) {
+  const int64_t blocks = groups * (a.tile == 32 ? 1 : 4);
+  *wgs = blocks < 2 * kTargetBlocks ? blocks : 2 * kTargetBlocks;  // the kernel strides over the rest
+  return {a.act, a.act2, static_cast<float*>(a.out), chunks, a.B, a.K, a.tile, a.scale};
+}
+
+template <typename T, bool ANY>
+hipError_t launch_wave_dw(const TileWaveDwArgs& w, int64_t wgs, hipStream_t s) {
+  using WC = typename WaveCfgs<T>::Dw;
+  constexpr int LDS = ANY ? WC::LDS_ANY : WC::LDS;
+  auto kern = tile_wave_dw_kernel<WC, T, ANY>;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(wgs)), dim3(WC::NT), LDS, s, w);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t run_tdp_wave(int pass, const TdpArgs& a, const int32_t* chunks, int owners, int nnz, hipStream_t s) {
+  if (pass == TDP_BWD_WEIGHT) {
+    if (nnz == 0) return hipSuccess;
+    int64_t wgs;
+    const TileWaveDwArgs w = wave_dw_args<T>(a, chunks, group_bound(nnz, owners, a.tiles_k), &wgs);
+    return rows_aligned<T>(a.B) ? launch_wave_dw<T, false>(w, wgs, s) : launch_wave_dw<T, true>(w, wgs, s);
+  }
+  TileWaveArgs w = wave_rows_args<T>(a, owners);
+  return run_wave_rows<T>(pass, w, s);
+}
+
+template <class WCD, typename T, bool ANY>
+hipError_t launch_wave_bwd(TileWaveArgs& d, const TileWaveDwArgs& w, int64_t nw, hipStream_t s) {
+  using WCW = typename WaveCfgs<T>::Dw;
+  constexpr int LD = ANY ? WCD::LDS_ANY : WCD::LDS, LW = ANY ? WCW::LDS_ANY : WCW::LDS;
+  constexpr int LDS = LD > LW ? LD : LW;
+  auto kern = tile_wave_bwd_kernel<WCD, WCW, T, ANY>;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if (attr != hipSuccess) return attr;
+  d.nx = (d.B + WCD::BN - 1) / WCD::BN;
+  const int64_t nd = static_cast<int64_t>(d.nx) * d.ny;
+  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(nd + nw)), dim3(WCD::NT), LDS, s, d, w,
+                     static_cast<int32_t>(nd));
+  return hipGetLastError();
+}
+
+// The wave kernels' bwd_data with the pipeline's weight-gradient walkers.
+template <class WCD, typename T>
+hipError_t launch_wave_group_bwd(TileWaveArgs& d, const TdpArgs& aw, const int32_t* chunks, int64_t groups,
+                                 hipStream_t s) {
+  using CfgW = typename TdpFastCfgs<T>::Group;
+  constexpr int LDS = WCD::LDS > CfgW::LDS ? WCD::LDS : CfgW::LDS;
+  auto kern = tile_wave_group_bwd_kernel<WCD, CfgW, T>;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if (attr != hipSuccess) return attr;
+  d.nx = (d.B + WCD::BN - 1) / WCD::BN;
+  const TdpFastArgs w = {aw.act, aw.act2, aw.W, aw.out, aw.B, aw.K, 0, 0, aw.ptr, aw.list, chunks, aw.scale};
+  const int64_t nw = groups < kTargetBlocks ? groups : kTargetBlocks;
+  const int64_t nd = static_cast<int64_t>(d.nx) * d.ny;
+  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(nd + nw)), dim3(WCD::NT), LDS, s, d, w,
+                     static_cast<int32_t>(nd), static_cast<int32_t>(nw));
+  return hipGetLastError();
+}
+
+// bwd_data (tiles_k columns) and bwd_weight as one launch of the wave kernels.
+template <typename T>
+hipError_t run_tdp_wave_bwd(const TdpArgs& ad, const TdpArgs& aw, const int32_t* chunks, int tiles_n, int nnz,
+                            hipStream_t s) {
+  using C = WaveCfgs<T>;
+  TileWaveArgs d = wave_rows_args<T>(ad, ad.tiles_k);
+  const int bn = wave_bn(d.ny, d.B);
+  const int64_t groups = group_bound(nnz, tiles_n, aw.tiles_k);
+  if (dw_on_pipeline<T>(aw))
+    return bn == 128  ? launch_wave_group_bwd<typename C::N128, T>(d, aw, chunks, groups, s)
+           : bn == 64 ? launch_wave_group_bwd<typename C::N64, T>(d, aw, chunks, groups, s)
+                      : launch_wave_group_bwd<typename C::N32, T>(d, aw, chunks, groups, s);
+  int64_t nw = 0;
+  const TileWaveDwArgs w = wave_dw_args<T>(aw, chunks, groups, &nw);
+  if (rows_aligned<T>(d.B))
+    return bn == 128  ? launch_wave_bwd<typename C::N128, T, false>(d, w, nw, s)
+           : bn == 64 ? launch_wave_bwd<typename C::N64, T, false>(d, w, nw, s)
+                      : launch_wave_bwd<typename C::N32, T, false>(d, w, nw, s);
+  return bn == 128  ? launch_wave_bwd<typename C::N128, T, true>(d, w, nw, s)
+         : bn == 64 ? launch_wave_bwd<typename C::N64, T, true>(d, w, nw, s)
+                    : launch_wave_bwd<typename C::N32, T, true>(d, w, nw, s);
 }
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
@@ -1169,13 +1418,17 @@ int ard_tile_fwd(const ard_tile_desc* desc, const ard_tile_plan* plan, const voi
   const int full = plan->tiles_n * plan->tiles_k;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (desc->dtype == ARD_BF16) {
-    if (tdp_fast_ok<bf16>(a))
+    if (rows_on_pipeline<bf16>(TDP_FWD, a, plan->tiles_n))
       ARD_HIP_CHECK(run_tdp_fast<bf16>(TDP_FWD, a, plan->d_chunks, plan->tiles_n, plan->nnz, s));
+    else if (tdp_wave_ok<bf16>(a))
+      ARD_HIP_CHECK(run_tdp_wave<bf16>(TDP_FWD, a, plan->d_chunks, plan->tiles_n, plan->nnz, s));
     else
       ARD_HIP_CHECK(run_tdp<bf16>(TDP_FWD, a, plan->tiles_n, plan->nnz, full, s));
   } else {
-    if (tdp_fast_ok<float>(a))
+    if (rows_on_pipeline<float>(TDP_FWD, a, plan->tiles_n))
       ARD_HIP_CHECK(run_tdp_fast<float>(TDP_FWD, a, plan->d_chunks, plan->tiles_n, plan->nnz, s));
+    else if (tdp_wave_ok<float>(a))
+      ARD_HIP_CHECK(run_tdp_wave<float>(TDP_FWD, a, plan->d_chunks, plan->tiles_n, plan->nnz, s));
     else
       ARD_HIP_CHECK(run_tdp<float>(TDP_FWD, a, plan->tiles_n, plan->nnz, full, s));
   }
@@ -1194,13 +1447,17 @@ int ard_tile_bwd_data(const ard_tile_desc* desc, const ard_tile_plan* plan, cons
   const int full = plan->tiles_n * plan->tiles_k;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (desc->dtype == ARD_BF16) {
-    if (tdp_fast_ok<bf16>(a))
+    if (rows_on_pipeline<bf16>(TDP_BWD_DATA, a, plan->tiles_k))
       ARD_HIP_CHECK(run_tdp_fast<bf16>(TDP_BWD_DATA, a, plan->d_chunks, plan->tiles_k, plan->nnz, s));
+    else if (tdp_wave_ok<bf16>(a))
+      ARD_HIP_CHECK(run_tdp_wave<bf16>(TDP_BWD_DATA, a, plan->d_chunks, plan->tiles_k, plan->nnz, s));
     else
       ARD_HIP_CHECK(run_tdp<bf16>(TDP_BWD_DATA, a, plan->tiles_k, plan->nnz, full, s));
   } else {
-    if (tdp_fast_ok<float>(a))
+    if (rows_on_pipeline<float>(TDP_BWD_DATA, a, plan->tiles_k))
       ARD_HIP_CHECK(run_tdp_fast<float>(TDP_BWD_DATA, a, plan->d_chunks, plan->tiles_k, plan->nnz, s));
+    else if (tdp_wave_ok<float>(a))
+      ARD_HIP_CHECK(run_tdp_wave<float>(TDP_BWD_DATA, a, plan->d_chunks, plan->tiles_k, plan->nnz, s));
     else
       ARD_HIP_CHECK(run_tdp<float>(TDP_BWD_DATA, a, plan->tiles_k, plan->nnz, full, s));
   }
@@ -1220,12 +1477,18 @@ int ard_tile_bwd(const ard_tile_desc* desc, const ard_tile_plan* plan, const voi
   const TdpArgs aw = {Xt, dYt, nullptr, dW, desc->batch, plan->n, plan->k, plan->tile, plan->tiles_k,
                       plan->d_row_ptr, plan->d_row_cols, desc->scale, plan->d_row_ptr + plan->tiles_n};
   const bool bf = desc->dtype == ARD_BF16;
-  if (!(bf ? tdp_fast_ok<bf16>(ad) : tdp_fast_ok<float>(ad))) {  // the two calls one after the other
+  const bool fast = bf ? rows_on_pipeline<bf16>(TDP_BWD_DATA, ad, plan->tiles_k)
+                       : rows_on_pipeline<float>(TDP_BWD_DATA, ad, plan->tiles_k);
+  if (!fast && !(bf ? tdp_wave_ok<bf16>(ad) : tdp_wave_ok<float>(ad))) {  // the two calls one after the other
     if ((st = ard_tile_bwd_data(desc, plan, dYt, W, dXt, stream)) != ARD_OK) return st;
     return ard_tile_bwd_weight(desc, plan, Xt, dYt, dW, stream);
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (bf)
+  if (!fast && bf)
+    ARD_HIP_CHECK(run_tdp_wave_bwd<bf16>(ad, aw, plan->d_chunks, plan->tiles_n, plan->nnz, s));
+  else if (!fast)
+    ARD_HIP_CHECK(run_tdp_wave_bwd<float>(ad, aw, plan->d_chunks, plan->tiles_n, plan->nnz, s));
+  else if (bf)
     ARD_HIP_CHECK(run_tdp_fast_bwd<bf16>(ad, aw, plan->d_chunks, plan->tiles_n, plan->tiles_k, plan->nnz, s));
   else
     ARD_HIP_CHECK(run_tdp_fast_bwd<float>(ad, aw, plan->d_chunks, plan->tiles_n, plan->tiles_k, plan->nnz, s));
@@ -1253,13 +1516,17 @@ int ard_tile_bwd_weight(const ard_tile_desc* desc, const ard_tile_plan* plan, co
   f.list = plan->d_row_cols;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (desc->dtype == ARD_BF16) {
-    if (tdp_fast_ok<bf16>(a))
+    if (dw_on_pipeline<bf16>(a))
       ARD_HIP_CHECK(run_tdp_fast<bf16>(TDP_BWD_WEIGHT, f, plan->d_chunks, plan->tiles_n, plan->nnz, s));
+    else if (tdp_wave_ok<bf16>(a))
+      ARD_HIP_CHECK(run_tdp_wave<bf16>(TDP_BWD_WEIGHT, f, plan->d_chunks, plan->tiles_n, plan->nnz, s));
     else
       ARD_HIP_CHECK(run_tdp<bf16>(TDP_BWD_WEIGHT, a, 0, plan->nnz, full, s));
   } else {
-    if (tdp_fast_ok<float>(a))
+    if (dw_on_pipeline<float>(a))
       ARD_HIP_CHECK(run_tdp_fast<float>(TDP_BWD_WEIGHT, f, plan->d_chunks, plan->tiles_n, plan->nnz, s));
+    else if (tdp_wave_ok<float>(a))
+      ARD_HIP_CHECK(run_tdp_wave<float>(TDP_BWD_WEIGHT, f, plan->d_chunks, plan->tiles_n, plan->nnz, s));
     else
       ARD_HIP_CHECK(run_tdp<float>(TDP_BWD_WEIGHT, a, 0, plan->nnz, full, s));
   }

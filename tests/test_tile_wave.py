@@ -1,0 +1,77 @@
+"""The tile layer on the wave kernels (32 x 32 tiles, batch rows of any length,
+grids that do not fill the chip) against float64 torch: every batch block
+width, remainders of the batch, empty and full tile rows, lists longer than one
+64-entry window, and the one-call backward bit for bit the two calls."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import ard_dtype, device
+from paper_1805_08939_amd import api, synth
+
+pytestmark = pytest.mark.gpu
+
+# largest |error| over |A| |B|: fp32 partial sums, bf16 outputs rounded by 2^-9
+TOL = {"f32": 1e-5, "bf16": 2.0 ** -8}
+
+
+def close(got, a, b, tol):
+    want, norm = a @ b, a.abs() @ b.abs()
+    assert torch.isfinite(got).all()
+    err = (got.double() - want).abs()
+    assert (err <= tol * norm + 1e-30).all(), float((err / (norm + 1e-30)).max())
+
+
+# (tile, tiles_n, tiles_k, batch): one tile; batch blocks of 32, 64 and 128 columns with remainders; lists of
+# more than 64 entries; rows that start at any element; the pipeline's rows and groups beside the wave kernels
+CASES = [(32, 1, 1, 1), (32, 3, 5, 31), (32, 9, 130, 33), (32, 70, 6, 200), (32, 140, 5, 129), (64, 2, 3, 7),
+         (64, 5, 70, 64), (64, 33, 9, 100), (64, 66, 3, 257), (64, 40, 40, 96), (64, 3, 100, 128), (64, 24, 24, 516)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("known", [True, False])
+def test_wave_kernels(dtype, case, known):
+    tile, tn, tk, B = case
+    print(dtype, case, known, flush=True)
+    N, K = tn * tile, tk * tile
+    sdt = synth.storage_dtype(dtype)
+    g = synth.generator(5)
+    X, W, dY = synth.normal(g, (K, B)).to(sdt), synth.normal(g, (N, K)).to(sdt), synth.normal(g, (N, B)).to(sdt)
+    X, W, dY = X.to(device()), W.to(device()), dY.to(device())
+    ws = torch.empty(max(api.ard_tile_plan_workspace_bytes(tn, tk), 16) // 4, dtype=torch.int32, device=device())
+    p = 0.4
+    bits = api.ard_tile_bitmap_bernoulli(tn, tk, p, 11, 0, 3)
+    keep = np.array([(int(bits[t // 32]) >> (t % 32)) & 1 for t in range(tn * tk)]).reshape(tn, tk)
+    if known:  # a full and an empty tile row (and column)
+        if tn > 2 and tk > 2:
+            keep[0], keep[1], keep[:, 1] = 1, 0, 0
+        flat = keep.reshape(-1)
+        words = np.zeros((tn * tk + 31) // 32, dtype=np.uint32)
+        for t in np.nonzero(flat)[0]:
+            words[t // 32] |= np.uint32(1 << (t % 32))
+        dbits = torch.from_numpy(words.view("int32").copy()).to(device())
+        plan = api.ard_plan_tiles(N, K, tile, dbits, int(flat.sum()), ws)
+    else:
+        dbits = torch.zeros((tn * tk + 31) // 32, dtype=torch.int32, device=device())
+        plan = api.ard_plan_tiles_bernoulli(N, K, tile, p, 11, 0, 3, dbits, ws)
+    M = torch.from_numpy(np.kron(keep, np.ones((tile, tile)))).to(device())
+    W = torch.where(M > 0, W, torch.full_like(W, float("nan")))  # dropped tiles are never read
+    desc = api.tile_desc(ard_dtype(dtype), B, K, N, 0.5, api.ARD_DROPPED_SKIP)
+    Y, dX = torch.full((N, B), 7.0, dtype=sdt, device=device()), torch.full((K, B), 7.0, dtype=sdt, device=device())
+    dW = torch.full((N, K), 7.0, device=device())
+    dX2, dW2 = dX.clone(), dW.clone()
+    api.ard_tile_fwd(desc, plan, X, W, Y)
+    api.ard_tile_bwd_data(desc, plan, dY, W, dX)
+    api.ard_tile_bwd_weight(desc, plan, X, dY, dW)
+    api.ard_tile_bwd(desc, plan, X, dY, W, dX2, dW2)
+    torch.cuda.synchronize()
+    Wm = torch.where(M > 0, W.double(), torch.zeros_like(M))
+    close(Y, 0.5 * Wm, X.double(), TOL[dtype])
+    close(dX, 0.5 * Wm.t(), dY.double(), TOL[dtype])
+    kept = M > 0
+    want = 0.5 * (dY.double() @ X.double().t())
+    norm = 0.5 * (dY.double().abs() @ X.double().abs().t())
+    assert ((dW.double() - want).abs()[kept] <= TOL["f32"] * norm[kept] + 1e-30).all()
+    assert (dW[~kept] == 7.0).all()
+    assert torch.equal(dX, dX2) and torch.equal(dW, dW2)
