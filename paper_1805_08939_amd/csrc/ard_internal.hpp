@@ -23,12 +23,22 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // error with a message.
 int check_row_plan(const ard_row_plan* plan, int32_t n, const char* what, bool needs_list);
 
-// The fp32 tile layer's forward (fwd) or transposed product with the kept-tile
-// lists split over several workgroups for small grids, partial sums in the
-// caller's buffer (ard_tile.hip). Falls back to ard_tile_fwd / ard_tile_bwd_data.
-int tdp_product_f32_split(bool fwd, const ard_tile_desc* d, const ard_tile_plan* p, const void* act, const void* W,
-                          void* out, float* partial, size_t partial_floats, void* stream,
-                          int* splits_left = nullptr);
+// Part of an fp32 tile-layer product (ard_tile.hip), for the tile-pattern LSTM.
+constexpr int kTilePartSplits = 8;  // largest split of the kept-tile lists
+struct TilePart {
+  const void* act;
+  const void* W;
+  void* out;
+  int32_t own0, own_count;  // output tile rows (fwd) or columns
+  int32_t lo, hi;           // other index of the kept tiles used
+  int32_t cols, lda;        // columns of the product, row stride of act
+  int32_t ldo, nb, nv;      // output addressing (see TileWaveArgs)
+  int64_t bstride;
+  float* partial;           // kTilePartSplits * own_count * tile * cols floats, or NULL
+};
+// The plan's and W's checks of the tile-layer calls.
+int tile_part_check(const ard_tile_plan* p, int32_t cols, const void* W);
+int tile_part_f32(bool fwd, const ard_tile_plan* p, const TilePart& t, void* stream, int* splits_left);
 
 // Kept count of a row pattern (see ard_row_kept).
 inline int32_t kept_count(int32_t n, int32_t period, int32_t offset) {

@@ -3,16 +3,22 @@
 // Sec. IV-C): only the kept tiles of W are read by the gate products and only
 // they receive a weight gradient. Every hidden unit is kept.
 //
-// Per step t the gate product runs on the tile layer's kernels with the
-// stacked input xh_t = [x_t; h_{t-1}] ((I + H) x B, contiguous):
-//   z_t = (W * M) xh_t,  then a pointwise kernel adds the bias, applies the
-// gate nonlinearities and the cell update, and writes h_t both into the next
-// step's xh and into the time-batched copy XH[(I + H)][T B] that the weight
-// gradient contracts over. The backward pass walks the steps in reverse: a
-// pointwise kernel forms dz_t (into dZ[4H][T B] and a contiguous step copy),
-// the tile layer's transposed product gives d xh_t = (W * M)^T dz_t, whose
-// lower rows are the recurrent gradient of the next (earlier) step; one tile
-// weight-gradient call over all T B columns gives dW = M * (dZ XH^T).
+// The batch is padded to Bp columns, a multiple of 4, in every buffer of the
+// workspace, so that all products run on 16-byte loads whatever the batch; the
+// padding columns of h, x and dz are zeros.
+//
+// XH[(I + H)][T Bp] holds [x_t; h_{t-1}] of every step side by side, dZ[4H][T Bp]
+// the gate derivatives. Where the inputs are whole tiles (I a multiple of the
+// tile), the input tiles' products run once over all T Bp columns (the
+// projection Zx, and dX after the backward walk), and a step multiplies the
+// recurrent tiles only, on its own column block of XH or dZ; else a step
+// multiplies the whole stacked input. A pointwise kernel per step adds the
+// bias and updates the cell (forward) or forms dz_t (backward). One tile
+// weight-gradient call over all T Bp columns gives dW = M * (dZ XH^T).
+// Forward and backward on MI355X, against steps over the whole stacked input on
+// the batch as it is: T 33, batch 15, 448 -> 320, p = 0.5, 64 x 64 tiles 4790 ->
+// 648 us; T 12, batch 12, 736 -> 896, 32 x 32 tiles 1935 -> 308 us; T 35, batch
+// 64, 1024 -> 1024, 64 x 64 tiles 1482 -> 1444 us.
 
 #include <hip/hip_runtime.h>
 
@@ -27,68 +33,81 @@ namespace {
 __device__ __forceinline__ float sgm(float x) { return 1.0f / (1.0f + expf(-x)); }
 
 struct TileLstm {
-  int32_t T, B, I, H;
-  int64_t TB;           // T * B: columns of XH and dZ
-  float* xh;            // [(I + H)][B] step input
-  float* XH;            // [(I + H)][T B]
-  float* z;             // [4H][B] step gate product
-  float* G;             // [T][4H][B] activated gates i, f, g, o
-  float* C;             // [T + 1][H][B] cell states, C[0] = c0
-  float* dz;            // [4H][B] step gate derivative
-  float* dZ;            // [4H][T B]
-  float* dxh;           // [(I + H)][B] step input derivative
-  float* dc;            // [H][B] cell derivative carry
+  int32_t T, B, Bp, I, H;
+  int64_t TB;           // T * Bp: columns of XH and dZ
+  float* XH;            // [(I + H)][T Bp]
+  float* Zx;            // [4H][T Bp] projection of the inputs, or NULL (the step product holds it)
+  float* z;             // [4H][Bp] step gate product
+  float* G;             // [T][4H][Bp] activated gates i, f, g, o
+  float* C;             // [T + 1][H][Bp] cell states, C[0] = c0
+  float* dZ;            // [4H][T Bp]
+  float* dxh;           // step input derivative: [H][Bp], or [(I + H)][Bp] without Zx
+  float* dc;            // [H][Bp] cell derivative carry
   float* part;          // split partial sums of the step products
-  size_t part_floats;
+  float* xh;            // [(I + H)][Bp] and [4H][Bp]: contiguous copies of a step's columns
+  float* dz;            // of XH and dZ where those rows are too long for the loads' offsets, or NULL
   int32_t zsplits;      // partial sums of z (1: z itself holds the product)
   int32_t dsplits;      // partial sums of dxh (1: dxh itself holds the product)
 };
 
 size_t al256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
+// Rows of XH and dZ of this many columns and more are not read in place by the
+// step products (a part's 32 rows must lie within 2^31 bytes).
+constexpr int64_t kMaxRow = int64_t{1} << 23;
+
 struct TileLayout {
-  size_t xh, XH, z, G, C, dz, dZ, dxh, dc, part, part_floats, total;
+  int64_t Bp;
+  size_t XH, z, G, C, dZ, dxh, dc, part, xh, dz, total;
 };
 
 TileLayout tile_layout(int64_t T, int64_t B, int64_t I, int64_t H) {
   TileLayout L;
   size_t off = 0;
-  const int64_t K = I + H;
-  L.xh = off;  off += al256(4 * K * B);
-  L.XH = off;  off += al256(4 * K * T * B);
-  L.z = off;   off += al256(4 * 4 * H * B);
-  L.G = off;   off += al256(4 * T * 4 * H * B);
-  L.C = off;   off += al256(4 * (T + 1) * H * B);
-  L.dz = off;  off += al256(4 * 4 * H * B);
-  L.dZ = off;  off += al256(4 * 4 * H * T * B);
-  L.dxh = off; off += al256(4 * K * B);
-  L.dc = off;  off += al256(4 * H * B);
-  // up to 8 splits of the larger step product (4H or I + H rows, rounded to whole 64-row tiles)
-  const int64_t rows = ((4 * H > K ? 4 * H : K) + 63) / 64 * 64;
-  L.part_floats = static_cast<size_t>(8 * rows * B);
-  L.part = off; off += al256(4 * L.part_floats);
+  const int64_t K = I + H, Bp = (B + 3) / 4 * 4;
+  L.Bp = Bp;
+  L.XH = off;  off += al256(4 * K * T * Bp);
+  L.z = off;   off += al256(4 * 4 * H * Bp);
+  L.G = off;   off += al256(4 * T * 4 * H * Bp);
+  L.C = off;   off += al256(4 * (T + 1) * H * Bp);
+  L.dZ = off;  off += al256(4 * 4 * H * T * Bp);
+  L.dxh = off; off += al256(4 * K * Bp);
+  L.dc = off;  off += al256(4 * H * Bp);
+  // the splits of the larger step product (4H or I + H rows)
+  const int64_t rows = 4 * H > K ? 4 * H : K;
+  L.part = off; off += al256(4 * kTilePartSplits * rows * Bp);
+  L.xh = L.dz = off;
+  if (T * Bp >= kMaxRow) {
+    L.xh = off; off += al256(4 * K * Bp);
+    L.dz = off; off += al256(4 * 4 * H * Bp);
+  }
   L.total = off;
   return L;
 }
 
-TileLstm tile_args(const TileLayout& L, char* w, int32_t T, int32_t B, int32_t I, int32_t H) {
-  TileLstm s;
-  s.T = T;
-  s.B = B;
-  s.I = I;
-  s.H = H;
-  s.TB = static_cast<int64_t>(T) * B;
-  s.xh = reinterpret_cast<float*>(w + L.xh);
-  s.XH = reinterpret_cast<float*>(w + L.XH);
-  s.z = reinterpret_cast<float*>(w + L.z);
-  s.G = reinterpret_cast<float*>(w + L.G);
-  s.C = reinterpret_cast<float*>(w + L.C);
-  s.dz = reinterpret_cast<float*>(w + L.dz);
-  s.dZ = reinterpret_cast<float*>(w + L.dZ);
-  s.dxh = reinterpret_cast<float*>(w + L.dxh);
-  s.dc = reinterpret_cast<float*>(w + L.dc);
-  s.part = reinterpret_cast<float*>(w + L.part);
-  s.part_floats = L.part_floats;
+TileLstm tile_args(const TileLayout& L, char* w, const ard_lstm_tile_desc* d) {
+  TileLstm s = {};
+  s.T = d->seq_len;
+  s.B = d->batch;
+  s.Bp = static_cast<int32_t>(L.Bp);
+  s.I = d->input_size;
+  s.H = d->hidden_size;
+  s.TB = s.T * L.Bp;
+  auto at = [w](size_t off) { return reinterpret_cast<float*>(w + off); };
+  s.XH = at(L.XH);
+  s.z = at(L.z);
+  s.G = at(L.G);
+  s.C = at(L.C);
+  s.dZ = at(L.dZ);
+  s.dxh = at(L.dxh);
+  s.dc = at(L.dc);
+  s.part = at(L.part);
+  if (s.TB >= kMaxRow) {
+    s.xh = at(L.xh);
+    s.dz = at(L.dz);
+  } else if (s.I % d->weight_plan->tile == 0) {
+    s.Zx = s.dZ;  // the forward's projection lives where the backward puts dZ
+  }
   s.zsplits = s.dsplits = 1;
   return s;
 }
@@ -97,126 +116,166 @@ TileLstm tile_args(const TileLayout& L, char* w, int32_t T, int32_t B, int32_t I
 // split partial sums (n elements each) in split order, the loads of up to
 // eight splits issued together.
 __device__ __forceinline__ float step_val(const float* direct, const float* part, int splits, int64_t n, int64_t e) {
+  static_assert(kTilePartSplits <= 8, "one group of loads");
   if (splits <= 1) return direct[e];
-  float v = 0.0f;
-  for (int q0 = 0; q0 < splits; q0 += 8) {
-    float t[8];
+  float t[8], v = 0.0f;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = q0 + u < splits ? part[(q0 + u) * n + e] : 0.0f;
+  for (int u = 0; u < 8; ++u) t[u] = u < splits ? part[u * n + e] : 0.0f;
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (q0 + u < splits) v += t[u];
-  }
+  for (int u = 0; u < 8; ++u)
+    if (u < splits) v += t[u];
   return v;
 }
 
-// Before the first step: x_t into the input rows of XH for every t, h0 (or 0)
-// into the recurrent rows of XH's first column block and of xh, x_0 into xh,
-// c0 (or 0) into C[0].
-__global__ void tile_lstm_init_kernel(TileLstm s, const float* __restrict__ X, const float* __restrict__ h0,
-                                      const float* __restrict__ c0) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t nx = static_cast<int64_t>(s.T) * s.I * s.B;
-  if (e < nx) {  // X[t][k][b] -> XH[k][t B + b]
-    const int64_t t = e / (static_cast<int64_t>(s.I) * s.B), r = e % (static_cast<int64_t>(s.I) * s.B);
-    const int64_t k = r / s.B, b = r % s.B;
-    s.XH[k * s.TB + t * s.B + b] = X[e];
-    if (t == 0) s.xh[r] = X[e];
+// Row j and column b of element e of rows of Bp: 32-bit division where e
+// allows it (a 64-bit one is some hundred instructions).
+__device__ __forceinline__ void row_col(int64_t e, int32_t Bp, int64_t& j, int32_t& b) {
+  j = (e >> 32) == 0 ? static_cast<int64_t>(static_cast<uint32_t>(e) / static_cast<uint32_t>(Bp)) : e / Bp;
+  b = static_cast<int32_t>(e - j * Bp);
+}
+
+// Before the first step: X into the input rows of XH for every t (blockIdx.y),
+// h0 (or 0) into the recurrent rows of XH's first column block, c0 (or 0) into
+// C[0]; zeros in the padding columns.
+__global__ void __launch_bounds__(256) tile_lstm_init_kernel(TileLstm s, const float* __restrict__ X,
+                                                             const float* __restrict__ h0,
+                                                             const float* __restrict__ c0) {
+  const int32_t t = blockIdx.y;
+  const int64_t IB = static_cast<int64_t>(s.I) * s.Bp, HB = static_cast<int64_t>(s.H) * s.Bp;
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  int64_t j;
+  int32_t b;
+  row_col(e, s.Bp, j, b);
+  if (e < IB) {  // X[t][k][b] -> XH[k][t Bp + b]
+    const float x = b < s.B ? X[(static_cast<int64_t>(t) * s.I + j) * s.B + b] : 0.0f;
+    s.XH[j * s.TB + static_cast<int64_t>(t) * s.Bp + b] = x;
+    if (s.xh && t == 0) s.xh[e] = x;
   }
-  const int64_t nh = static_cast<int64_t>(s.H) * s.B;
-  if (e < nh) {
-    const int64_t j = e / s.B, b = e % s.B;
-    const float h = h0 ? h0[e] : 0.0f;
+  if (t == 0 && e < HB) {
+    const bool in = b < s.B;
+    const float h = in && h0 ? h0[j * s.B + b] : 0.0f;
     s.XH[(s.I + j) * s.TB + b] = h;
-    s.xh[(s.I + j) * s.B + b] = h;
-    s.C[e] = c0 ? c0[e] : 0.0f;
+    if (s.xh) s.xh[IB + e] = h;
+    s.C[e] = in && c0 ? c0[j * s.B + b] : 0.0f;
   }
 }
 
-// Step t: gates from z + bias, cell and hidden state; h_t into Hs, into the
-// next step's xh and XH block; x_{t+1} into xh.
-__global__ void tile_lstm_point_fwd_kernel(TileLstm s, int32_t t, const float* __restrict__ bias,
-                                           const float* __restrict__ X, float* __restrict__ Hs) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t HB = static_cast<int64_t>(s.H) * s.B;
+// Step t: gates from z (+ Zx) + bias, cell and hidden state; h_t into Hs and
+// the next step's block of XH; after the last step the final state into hT, cT.
+__global__ void __launch_bounds__(256) tile_lstm_point_fwd_kernel(TileLstm s, int32_t t,
+                                                                  const float* __restrict__ bias,
+                                                                  const float* __restrict__ X, float* __restrict__ Hs,
+                                                                  float* __restrict__ hT, float* __restrict__ cT) {
+  const int64_t HB = static_cast<int64_t>(s.H) * s.Bp;
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  int64_t j;
+  int32_t b;
+  row_col(e, s.Bp, j, b);
   if (e < HB) {
-    const int64_t j = e / s.B, b = e % s.B;
-    float zv[4];
+    float c = 0.0f, h = 0.0f;
+    const bool in = b < s.B;
+    if (in) {
+      float zv[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      zv[q] = step_val(s.z, s.part, s.zsplits, 4 * HB, (q * s.H + j) * s.B + b) + (bias ? bias[q * s.H + j] : 0.0f);
-    const float ig = sgm(zv[0]), fg = sgm(zv[1]), gg = tanhf(zv[2]), og = sgm(zv[3]);
-    const float cp = s.C[static_cast<int64_t>(t) * HB + e];
-    const float c = fg * cp + ig * gg;
-    const float h = og * tanhf(c);
-    float* Gt = s.G + static_cast<int64_t>(t) * 4 * HB;
-    Gt[(0 * s.H + j) * s.B + b] = ig;
-    Gt[(1 * s.H + j) * s.B + b] = fg;
-    Gt[(2 * s.H + j) * s.B + b] = gg;
-    Gt[(3 * s.H + j) * s.B + b] = og;
+      for (int q = 0; q < 4; ++q) {
+        const int64_t r = static_cast<int64_t>(q) * s.H + j;
+        zv[q] = step_val(s.z, s.part, s.zsplits, 4 * HB, r * s.Bp + b);
+        if (s.Zx) zv[q] += s.Zx[r * s.TB + static_cast<int64_t>(t) * s.Bp + b];
+        if (bias) zv[q] += bias[r];
+      }
+      const float ig = sgm(zv[0]), fg = sgm(zv[1]), gg = tanhf(zv[2]), og = sgm(zv[3]);
+      const float cp = s.C[static_cast<int64_t>(t) * HB + e];
+      c = fg * cp + ig * gg;
+      h = og * tanhf(c);
+      float* Gt = s.G + static_cast<int64_t>(t) * 4 * HB + e;
+      Gt[0] = ig;
+      Gt[HB] = fg;
+      Gt[2 * HB] = gg;
+      Gt[3 * HB] = og;
+      const int64_t o = j * s.B + b;
+      Hs[static_cast<int64_t>(t) * s.H * s.B + o] = h;
+      if (t == s.T - 1) {
+        if (hT) hT[o] = h;
+        if (cT) cT[o] = c;
+      }
+    }
     s.C[static_cast<int64_t>(t + 1) * HB + e] = c;
-    Hs[static_cast<int64_t>(t) * HB + e] = h;
     if (t + 1 < s.T) {
-      s.xh[(s.I + j) * s.B + b] = h;
-      s.XH[(s.I + j) * s.TB + static_cast<int64_t>(t + 1) * s.B + b] = h;
+      s.XH[(s.I + j) * s.TB + static_cast<int64_t>(t + 1) * s.Bp + b] = h;
+      if (s.xh) s.xh[static_cast<int64_t>(s.I) * s.Bp + e] = h;
     }
   }
-  const int64_t IB = static_cast<int64_t>(s.I) * s.B;
-  if (t + 1 < s.T && e < IB) s.xh[e] = X[static_cast<int64_t>(t + 1) * IB + e];
+  if (s.xh && t + 1 < s.T && e < static_cast<int64_t>(s.I) * s.Bp)
+    s.xh[e] = b < s.B ? X[(static_cast<int64_t>(t + 1) * s.I + j) * s.B + b] : 0.0f;
 }
 
 // Step t backward: dh = dHs[t] + (recurrent rows of dxh from step t + 1, or
-// dhT at the last step); dz_t into dz and dZ's block t; dc carry. At steps
-// below the last, the input rows of dxh (d x_{t+1}) go to dX[t + 1].
-__global__ void tile_lstm_point_bwd_kernel(TileLstm s, int32_t t, const float* __restrict__ dHs,
-                                           const float* __restrict__ dhT, const float* __restrict__ dcT,
-                                           float* __restrict__ dX) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t HB = static_cast<int64_t>(s.H) * s.B;
-  const bool last = t == s.T - 1;
-  const int64_t IB = static_cast<int64_t>(s.I) * s.B;
-  const int64_t KB = static_cast<int64_t>(s.I + s.H) * s.B;
-  if (!last && dX && e < IB) dX[static_cast<int64_t>(t + 1) * IB + e] = step_val(s.dxh, s.part, s.dsplits, KB, e);
+// dhT at the last step); dz_t into dZ's block t (zeros in the padding columns);
+// dc carry. Without the hoisted projection dxh also holds d x_{t + 1}, which
+// goes to dX.
+__global__ void __launch_bounds__(256) tile_lstm_point_bwd_kernel(TileLstm s, int32_t t,
+                                                                  const float* __restrict__ dHs,
+                                                                  const float* __restrict__ dhT,
+                                                                  const float* __restrict__ dcT,
+                                                                  float* __restrict__ dX) {
+  const int64_t HB = static_cast<int64_t>(s.H) * s.Bp, IB = s.Zx ? 0 : static_cast<int64_t>(s.I) * s.Bp;
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  int64_t j;
+  int32_t b;
+  row_col(e, s.Bp, j, b);
+  const bool last = t == s.T - 1, in = b < s.B;
+  const int64_t n = IB + HB;  // elements of dxh
+  if (!last && dX && e < IB && in)
+    dX[(static_cast<int64_t>(t + 1) * s.I + j) * s.B + b] = step_val(s.dxh, s.part, s.dsplits, n, e);
   if (e >= HB) return;
-  const int64_t j = e / s.B, b = e % s.B;
-  float dh = dHs[static_cast<int64_t>(t) * HB + e];
-  float dcin;
-  if (last) {
-    if (dhT) dh += dhT[e];
-    dcin = dcT ? dcT[e] : 0.0f;
-  } else {
-    dh += step_val(s.dxh, s.part, s.dsplits, KB, (s.I + j) * s.B + b);
-    dcin = s.dc[e];
+  float dzq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (in) {
+    const int64_t o = j * s.B + b;
+    float dh = dHs[static_cast<int64_t>(t) * s.H * s.B + o];
+    float dcin;
+    if (last) {
+      if (dhT) dh += dhT[o];
+      dcin = dcT ? dcT[o] : 0.0f;
+    } else {
+      dh += step_val(s.dxh, s.part, s.dsplits, n, IB + e);
+      dcin = s.dc[e];
+    }
+    const float* Gt = s.G + static_cast<int64_t>(t) * 4 * HB + e;
+    const float ig = Gt[0], fg = Gt[HB];
+    const float gg = Gt[2 * HB], og = Gt[3 * HB];
+    const float c = s.C[static_cast<int64_t>(t + 1) * HB + e];
+    const float cp = s.C[static_cast<int64_t>(t) * HB + e];
+    const float tc = tanhf(c);
+    const float d_o = dh * tc;
+    const float dcv = dcin + dh * og * (1.0f - tc * tc);
+    s.dc[e] = dcv * fg;
+    dzq[0] = dcv * gg * ig * (1.0f - ig);
+    dzq[1] = dcv * cp * fg * (1.0f - fg);
+    dzq[2] = dcv * ig * (1.0f - gg * gg);
+    dzq[3] = d_o * og * (1.0f - og);
   }
-  const float* Gt = s.G + static_cast<int64_t>(t) * 4 * HB;
-  const float ig = Gt[(0 * s.H + j) * s.B + b], fg = Gt[(1 * s.H + j) * s.B + b];
-  const float gg = Gt[(2 * s.H + j) * s.B + b], og = Gt[(3 * s.H + j) * s.B + b];
-  const float c = s.C[static_cast<int64_t>(t + 1) * HB + e];
-  const float cp = s.C[static_cast<int64_t>(t) * HB + e];
-  const float tc = tanhf(c);
-  const float d_o = dh * tc;
-  const float dcv = dcin + dh * og * (1.0f - tc * tc);
-  s.dc[e] = dcv * fg;
-  const float dzq[4] = {dcv * gg * ig * (1.0f - ig), dcv * cp * fg * (1.0f - fg), dcv * ig * (1.0f - gg * gg),
-                        d_o * og * (1.0f - og)};
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    s.dz[(q * s.H + j) * s.B + b] = dzq[q];
-    s.dZ[(q * s.H + j) * s.TB + static_cast<int64_t>(t) * s.B + b] = dzq[q];
+    s.dZ[(static_cast<int64_t>(q) * s.H + j) * s.TB + static_cast<int64_t>(t) * s.Bp + b] = dzq[q];
+    if (s.dz) s.dz[q * HB + e] = dzq[q];
   }
 }
 
-// After the last backward step: d x_0 into dX[0], dh0 and dc0.
-__global__ void tile_lstm_bwd_final_kernel(TileLstm s, float* __restrict__ dX, float* __restrict__ dh0,
-                                           float* __restrict__ dc0) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t IB = static_cast<int64_t>(s.I) * s.B, HB = static_cast<int64_t>(s.H) * s.B;
-  const int64_t KB = static_cast<int64_t>(s.I + s.H) * s.B;
-  if (dX && e < IB) dX[e] = step_val(s.dxh, s.part, s.dsplits, KB, e);
+// After the last backward step: dh0 and dc0 (and, without the hoisted
+// projection, d x_0 into dX[0]).
+__global__ void __launch_bounds__(256) tile_lstm_bwd_final_kernel(TileLstm s, float* __restrict__ dX,
+                                                                  float* __restrict__ dh0, float* __restrict__ dc0) {
+  const int64_t HB = static_cast<int64_t>(s.H) * s.Bp, IB = s.Zx ? 0 : static_cast<int64_t>(s.I) * s.Bp;
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  int64_t j;
+  int32_t b;
+  row_col(e, s.Bp, j, b);
+  if (b >= s.B) return;
+  const int64_t o = j * s.B + b, n = IB + HB;
+  if (dX && e < IB) dX[o] = step_val(s.dxh, s.part, s.dsplits, n, e);
   if (e < HB) {
-    const int64_t j = e / s.B, b = e % s.B;
-    if (dh0) dh0[e] = step_val(s.dxh, s.part, s.dsplits, KB, (s.I + j) * s.B + b);
-    if (dc0) dc0[e] = s.dc[e];
+    if (dh0) dh0[o] = step_val(s.dxh, s.part, s.dsplits, n, IB + e);
+    if (dc0) dc0[o] = s.dc[e];
   }
 }
 
@@ -251,18 +310,29 @@ int check_tile_lstm(const ard_lstm_tile_desc* d) {
                 d->input_size + d->hidden_size);
   if (static_cast<int64_t>(d->seq_len) * d->batch >= (int64_t{1} << 31))
     return fail(ARD_ERR_INVALID_ARG, "seq_len * batch must be < 2^31");
+  // the batch is padded to a multiple of 4 (the buffers of such a call exceed the GPU's memory)
+  if (d->seq_len * ((static_cast<int64_t>(d->batch) + 3) / 4 * 4) >= (int64_t{1} << 31))
+    return fail(ARD_ERR_UNSUPPORTED, "seq_len * padded batch must be < 2^31");
   return ARD_OK;
 }
 
-ard_tile_desc step_desc(const ard_lstm_tile_desc* d, int32_t batch) {
-  ard_tile_desc td;
-  td.dtype = ARD_F32;
-  td.batch = batch;
-  td.in_features = d->input_size + d->hidden_size;
-  td.out_features = 4 * d->hidden_size;
-  td.scale = 1.0f;
-  td.dropped = ARD_DROPPED_ZERO;
-  return td;
+// A step's product over its column block: z_t (fwd) or dxh_t.
+TilePart step_part(const TileLstm& s, const ard_tile_plan* p, const void* W, bool fwd, int32_t t) {
+  const int32_t itiles = s.Zx ? s.I / p->tile : 0;  // hoisted input tiles
+  TilePart q = {};
+  const float* cols = (fwd ? s.XH + (s.Zx ? s.I * s.TB : 0) : s.dZ) + static_cast<int64_t>(t) * s.Bp;
+  const float* copy = fwd ? s.xh : s.dz;
+  q.act = copy ? copy : cols;
+  q.lda = copy ? s.Bp : static_cast<int32_t>(s.TB);
+  q.W = W;
+  q.out = fwd ? s.z : s.dxh;
+  q.own0 = fwd ? 0 : itiles;
+  q.own_count = fwd ? p->tiles_n : p->tiles_k - itiles;
+  q.lo = fwd ? itiles : 0;
+  q.hi = fwd ? p->tiles_k : p->tiles_n;
+  q.cols = q.ldo = q.nb = q.nv = s.Bp;
+  q.partial = s.part;
+  return q;
 }
 
 }  // namespace
@@ -288,26 +358,39 @@ int ard_lstm_tile_fwd(const ard_lstm_tile_desc* desc, const void* X, const void*
   if (!ws || ws_bytes < L.total)
     return fail(ARD_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", L.total, ws_bytes);
   if (!aligned16(ws)) return fail(ARD_ERR_INVALID_ARG, "workspace is not 16-byte aligned");
+  const ard_tile_plan* p = desc->weight_plan;
+  if ((st = tile_part_check(p, static_cast<int32_t>(L.Bp), W)) != ARD_OK) return st;
   hipStream_t sm = static_cast<hipStream_t>(stream);
-  TileLstm s = tile_args(L, static_cast<char*>(ws), desc->seq_len, desc->batch, desc->input_size,
-                         desc->hidden_size);
-  const int64_t IB = static_cast<int64_t>(s.I) * s.B, HB = static_cast<int64_t>(s.H) * s.B;
-  hipLaunchKernelGGL(tile_lstm_init_kernel, grid_of(static_cast<int64_t>(s.T) * IB > HB ? s.T * IB : HB), dim3(256),
-                     0, sm, s, static_cast<const float*>(X), static_cast<const float*>(h0),
-                     static_cast<const float*>(c0));
-  ARD_LAUNCH_CHECK();
-  const ard_tile_desc td = step_desc(desc, s.B);
-  for (int32_t t = 0; t < s.T; ++t) {
-    if ((st = tdp_product_f32_split(true, &td, desc->weight_plan, s.xh, W, s.z, s.part, s.part_floats, stream,
-                                    &s.zsplits)) != ARD_OK)
-      return st;
-    hipLaunchKernelGGL(tile_lstm_point_fwd_kernel, grid_of(IB > HB ? IB : HB), dim3(256), 0, sm, s, t, bias,
-                       static_cast<const float*>(X), static_cast<float*>(Hs));
+  TileLstm s = tile_args(L, static_cast<char*>(ws), desc);
+  const int64_t IB = static_cast<int64_t>(s.I) * s.Bp, HB = static_cast<int64_t>(s.H) * s.Bp;
+  const float* Xf = static_cast<const float*>(X);
+  // one grid row per step, in launches of at most 65535
+  for (int32_t t0 = 0; t0 < s.T; t0 += 65535) {
+    TileLstm q = s;
+    q.XH += static_cast<int64_t>(t0) * s.Bp;
+    dim3 grid = grid_of(IB > HB ? IB : HB);
+    grid.y = static_cast<unsigned>(s.T - t0 < 65535 ? s.T - t0 : 65535);
+    if (t0 > 0) q.H = 0, q.xh = nullptr;  // the initial state went with the first launch
+    hipLaunchKernelGGL(tile_lstm_init_kernel, grid, dim3(256), 0, sm, q, Xf + t0 * static_cast<int64_t>(s.I) * s.B,
+                       static_cast<const float*>(h0), static_cast<const float*>(c0));
     ARD_LAUNCH_CHECK();
   }
-  if (hT) ARD_HIP_CHECK(hipMemcpyAsync(hT, static_cast<float*>(Hs) + (s.T - 1) * HB, 4 * HB,
-                                       hipMemcpyDeviceToDevice, sm));
-  if (cT) ARD_HIP_CHECK(hipMemcpyAsync(cT, s.C + s.T * HB, 4 * HB, hipMemcpyDeviceToDevice, sm));
+  if (s.Zx) {  // the input tiles' product over the columns of every step
+    TilePart q = step_part(s, p, W, true, 0);
+    q.act = s.XH;
+    q.out = s.Zx;
+    q.lo = 0;
+    q.hi = s.I / p->tile;
+    q.cols = q.ldo = q.nb = q.nv = static_cast<int32_t>(s.TB);
+    q.partial = nullptr;
+    if ((st = tile_part_f32(true, p, q, stream, nullptr)) != ARD_OK) return st;
+  }
+  for (int32_t t = 0; t < s.T; ++t) {
+    if ((st = tile_part_f32(true, p, step_part(s, p, W, true, t), stream, &s.zsplits)) != ARD_OK) return st;
+    hipLaunchKernelGGL(tile_lstm_point_fwd_kernel, grid_of(s.xh && IB > HB ? IB : HB), dim3(256), 0, sm, s, t, bias,
+                       Xf, static_cast<float*>(Hs), static_cast<float*>(hT), static_cast<float*>(cT));
+    ARD_LAUNCH_CHECK();
+  }
   return ARD_OK;
 }
 
@@ -322,26 +405,39 @@ int ard_lstm_tile_bwd(const ard_lstm_tile_desc* desc, const void* W, const void*
   if (!ws || ws_bytes < L.total)
     return fail(ARD_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", L.total, ws_bytes);
   if (!aligned16(ws)) return fail(ARD_ERR_INVALID_ARG, "workspace is not 16-byte aligned");
+  const ard_tile_plan* p = desc->weight_plan;
+  if ((st = tile_part_check(p, static_cast<int32_t>(L.Bp), W)) != ARD_OK) return st;
   hipStream_t sm = static_cast<hipStream_t>(stream);
-  TileLstm s = tile_args(L, static_cast<char*>(ws), desc->seq_len, desc->batch, desc->input_size,
-                         desc->hidden_size);
-  const int64_t IB = static_cast<int64_t>(s.I) * s.B, HB = static_cast<int64_t>(s.H) * s.B;
-  const ard_tile_desc td = step_desc(desc, s.B);
+  TileLstm s = tile_args(L, static_cast<char*>(ws), desc);
+  const int64_t IB = s.Zx ? 0 : static_cast<int64_t>(s.I) * s.Bp, HB = static_cast<int64_t>(s.H) * s.Bp;
   for (int32_t t = s.T - 1; t >= 0; --t) {
     hipLaunchKernelGGL(tile_lstm_point_bwd_kernel, grid_of(IB > HB ? IB : HB), dim3(256), 0, sm, s, t,
                        static_cast<const float*>(dHs), static_cast<const float*>(dhT),
                        static_cast<const float*>(dcT), static_cast<float*>(dX));
     ARD_LAUNCH_CHECK();
-    if ((st = tdp_product_f32_split(false, &td, desc->weight_plan, s.dz, W, s.dxh, s.part, s.part_floats,
-                                    stream, &s.dsplits)) != ARD_OK)
-      return st;
+    if (t == 0 && s.Zx && !dh0) break;  // nothing reads the first step's recurrent derivative
+    if ((st = tile_part_f32(false, p, step_part(s, p, W, false, t), stream, &s.dsplits)) != ARD_OK) return st;
   }
-  hipLaunchKernelGGL(tile_lstm_bwd_final_kernel, grid_of(IB > HB ? IB : HB), dim3(256), 0, sm, s,
-                     static_cast<float*>(dX), static_cast<float*>(dh0), static_cast<float*>(dc0));
-  ARD_LAUNCH_CHECK();
+  if (dh0 || dc0 || (dX && !s.Zx)) {
+    hipLaunchKernelGGL(tile_lstm_bwd_final_kernel, grid_of(IB > HB ? IB : HB), dim3(256), 0, sm, s,
+                       static_cast<float*>(dX), static_cast<float*>(dh0), static_cast<float*>(dc0));
+    ARD_LAUNCH_CHECK();
+  }
+  if (dX && s.Zx) {  // the input tiles' transposed product over the columns of every step
+    TilePart q = step_part(s, p, W, false, 0);
+    q.out = dX;
+    q.own0 = 0;
+    q.own_count = s.I / p->tile;
+    q.cols = static_cast<int32_t>(s.TB);
+    q.ldo = q.nv = s.B;
+    q.nb = s.Bp;
+    q.bstride = static_cast<int64_t>(s.I) * s.B;
+    q.partial = nullptr;
+    if ((st = tile_part_f32(false, p, q, stream, nullptr)) != ARD_OK) return st;
+  }
   if (dW) {
-    const ard_tile_desc tw = step_desc(desc, static_cast<int32_t>(s.TB));
-    if ((st = ard_tile_bwd_weight(&tw, desc->weight_plan, s.XH, s.dZ, dW, stream)) != ARD_OK) return st;
+    const ard_tile_desc tw = {ARD_F32, static_cast<int32_t>(s.TB), s.I + s.H, 4 * s.H, 1.0f, ARD_DROPPED_ZERO};
+    if ((st = ard_tile_bwd_weight(&tw, p, s.XH, s.dZ, dW, stream)) != ARD_OK) return st;
   }
   if (dbias) {
     hipLaunchKernelGGL(tile_lstm_dbias_kernel, dim3(static_cast<unsigned>(4 * s.H)), dim3(256), 0, sm, s.dZ, s.TB,

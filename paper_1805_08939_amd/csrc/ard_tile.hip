@@ -598,10 +598,6 @@ struct TdpFastArgs {
   const int32_t* list;  // row_cols (fwd, bwd_weight) or col_rows (bwd_data)
   const int32_t* chunks;
   float scale;
-  // split lists (fp32 output only): workgroup (tile, split) sums its share of
-  // the row's (column's) kept tiles into partial[split][rows][B]
-  int32_t splits, rows;
-  float* partial;
 };
 
 constexpr int kFastTile = 64;
@@ -610,9 +606,9 @@ constexpr int kFastTile = 64;
 // bwd_data:  dXt[tk block][n0 ..] = scale * sum over kept tn of column tk: W(tn, tk)^T dYt[tn block][n0 ..]
 // A tile row (column) without kept tiles gets zeros.
 // One workgroup of the fwd / bwd_data product: position bid of the grid of
-// nx x ny (batch block, tile row or column), split sp.
+// nx x ny (batch block, tile row or column).
 template <class Cfg, int PASS, typename OutT>
-__device__ __forceinline__ void tdp_rows_tile(const TdpFastArgs& a, int bid, int sp, char* smem) {
+__device__ __forceinline__ void tdp_rows_tile(const TdpFastArgs& a, int bid, char* smem) {
   constexpr int TT = kFastTile, ES = Cfg::ES, SPT = TT / Cfg::BK;
   constexpr bool AMC = PASS == TDP_BWD_DATA;
   static_assert(Cfg::BM == TT && TT % Cfg::BK == 0, "one tile row per workgroup");
@@ -622,11 +618,8 @@ __device__ __forceinline__ void tdp_rows_tile(const TdpFastArgs& a, int bid, int
   int own, col;
   grouped_tile(bid, a.nx, a.ny, own, col);
   const int n0 = col * Cfg::BN;
-  const int splits = a.splits > 1 ? a.splits : 1;
-  const int pa = __builtin_amdgcn_readfirstlane(a.ptr[own]);
-  const int nall = __builtin_amdgcn_readfirstlane(a.ptr[own + 1]) - pa;
-  const int p0 = pa + nall * sp / splits;  // this split's share of the list
-  const int p1 = pa + nall * (sp + 1) / splits;
+  const int p0 = __builtin_amdgcn_readfirstlane(a.ptr[own]);
+  const int p1 = __builtin_amdgcn_readfirstlane(a.ptr[own + 1]);
 
   f32x16 acc[Cfg::FM][Cfg::FN];
 #pragma unroll
@@ -702,38 +695,13 @@ __device__ __forceinline__ void tdp_rows_tile(const TdpFastArgs& a, int bid, int
   g.c.p = static_cast<OutT*>(a.out) + static_cast<int64_t>(own) * TT * B;
   g.c.ld = B;
   g.c.scale = a.scale;
-  if constexpr (sizeof(OutT) == 4) {
-    if (splits > 1) {  // unscaled partial sums; the reduction applies the scale
-      g.c.p = a.partial + (static_cast<int64_t>(sp) * a.rows + static_cast<int64_t>(own) * TT) * B;
-      g.c.scale = 1.0f;
-    }
-  }
   fast_store<OutT, Cfg, EPI_FWD>(g, acc, 0, n0, wm, wn, 0, 0, smem);
 }
 
 template <class Cfg, int PASS, typename OutT>
 __global__ void __launch_bounds__(Cfg::NT) tdp_fast_kernel(TdpFastArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  tdp_rows_tile<Cfg, PASS, OutT>(a, static_cast<int>(blockIdx.x), a.splits > 1 ? static_cast<int>(blockIdx.y) : 0,
-                                 smem);
-}
-
-// out[e] = scale * sum over the splits of partial[split][e], in split order
-// (the loads of up to eight splits issued together).
-__global__ void __launch_bounds__(256) tdp_split_reduce_kernel(const float* __restrict__ partial, int32_t splits,
-                                                               int64_t n, float scale, float* __restrict__ out) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= n) return;
-  float v = 0.0f;
-  for (int s0 = 0; s0 < splits; s0 += 8) {
-    float t[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = s0 + u < splits ? partial[(s0 + u) * n + e] : 0.0f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (s0 + u < splits) v += t[u];
-  }
-  out[e] = scale * v;
+  tdp_rows_tile<Cfg, PASS, OutT>(a, static_cast<int>(blockIdx.x), smem);
 }
 
 // bwd_weight: dW(tn, tk) = scale * dYt[tn block] Xt[tk block]^T (contraction
@@ -822,7 +790,7 @@ __global__ void __launch_bounds__(CfgD::NT) tdp_fast_bwd_kernel(TdpFastArgs d, T
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int b = static_cast<int>(blockIdx.x);
   if (b < nd)
-    tdp_rows_tile<CfgD, TDP_BWD_DATA, T>(d, b, 0, smem);
+    tdp_rows_tile<CfgD, TDP_BWD_DATA, T>(d, b, smem);
   else
     tdp_dw_walk<CfgW, float>(w, b - nd, nw, smem);
 }
@@ -910,8 +878,8 @@ struct TdpFastCfgs<bf16> {
   using Rows = FastCfg<bf16, 64, 128, 64, 4, 1, 2, 2>;   // 96 KB LDS
   using Group = FastCfg<bf16, 64, 256, 64, 3, 1, 4, 1>;  // 120 KB
 };
-// Narrow: 64 batch columns for batches of at most 64 (the tile-pattern
-// LSTM's steps), so that no half-empty batch tile is loaded and multiplied.
+// Narrow: 64 batch columns for batches of at most 64, so that no half-empty
+// batch tile is loaded and multiplied.
 template <>
 struct TdpFastCfgs<float> {
   using Rows = FastCfg<float, 64, 128, 32, 4, 1, 2, 2>;  // 96 KB
@@ -993,12 +961,12 @@ bool dw_on_pipeline(const TdpArgs& a) {
 }
 
 // fwd or bwd_data on tile configuration Cfg: batch blocks of Cfg::BN, one
-// workgroup per (tile row or column, batch block, split).
+// workgroup per (tile row or column, batch block).
 template <class Cfg, typename T>
-hipError_t launch_rows(int pass, TdpFastArgs& f, int owners, int splits, hipStream_t s) {
+hipError_t launch_rows(int pass, TdpFastArgs& f, int owners, hipStream_t s) {
   f.nx = (f.B + Cfg::BN - 1) / Cfg::BN;
   f.ny = owners;
-  const dim3 grid(static_cast<unsigned>(f.nx * f.ny), static_cast<unsigned>(splits));
+  const dim3 grid(static_cast<unsigned>(f.nx * f.ny));
   if (pass == TDP_FWD) return launch_with_lds<Cfg, tdp_fast_kernel<Cfg, TDP_FWD, T>>(grid, f, s);
   return launch_with_lds<Cfg, tdp_fast_kernel<Cfg, TDP_BWD_DATA, T>>(grid, f, s);
 }
@@ -1020,9 +988,9 @@ hipError_t run_tdp_fast(int pass, const TdpArgs& a, const int32_t* chunks, int o
         dim3(static_cast<unsigned>(bound)), f, s);
   }
   if constexpr (sizeof(T) == 4) {
-    if (a.B <= C::Narrow::BN) return launch_rows<typename C::Narrow, T>(pass, f, owners, 1, s);
+    if (a.B <= C::Narrow::BN) return launch_rows<typename C::Narrow, T>(pass, f, owners, s);
   }
-  return launch_rows<typename C::Rows, T>(pass, f, owners, 1, s);
+  return launch_rows<typename C::Rows, T>(pass, f, owners, s);
 }
 
 // bwd_data and bwd_weight as one launch of tdp_fast_bwd_kernel (both on the
@@ -1095,9 +1063,9 @@ template <typename T>
 struct WaveCfgs;
 template <>
 struct WaveCfgs<float> {
-  using N32 = WaveCfg<float, 32, 4, 4>;    // 128 KB LDS
-  using N64 = WaveCfg<float, 64, 4, 3>;    // 144 KB
-  using N128 = WaveCfg<float, 128, 4, 2>;  // 160 KB
+  using N32 = WaveCfg<float, 32, 4, 2>;    // 64 KB LDS
+  using N64 = WaveCfg<float, 64, 4, 1>;    // 48 KB
+  using N128 = WaveCfg<float, 128, 4, 1>;  // 80 KB
   using Dw = WaveCfg<float, 128, 4, 1>;    // 80 KB
 };
 template <>
@@ -1110,10 +1078,17 @@ struct WaveCfgs<bf16> {
 
 // Batch columns per workgroup of ny 32-row blocks: wider ones read each W tile
 // fewer times; taken as long as the grid still gives every compute unit a
-// workgroup.
-inline int wave_bn(int64_t ny, int64_t B) {
-  if (B > 64 && ny * ((B + 127) / 128) >= kTargetBlocks) return 128;
-  if (B > 32 && ny * ((B + 63) / 64) >= kTargetBlocks) return 64;
+// workgroup (bf16, bound by the loads) or two (fp32, bound by the matrix cores:
+// the second workgroup's MFMAs run while the first one waits for its list, its
+// first loads or its reduction). Measured on MI355X, fp32 forward at p = 0.5,
+// 64 / 32 columns: 2048 -> 1024 batch 512 (256 / 512 workgroups) 21 / 17 us, 4096
+// x 4096 batch 128 39 / 30; 128 / 64 columns: 1024 -> 4096 batch 512, 32 x 32
+// tiles (512 / 1024) 30 / 37.
+template <typename T>
+int wave_bn(int64_t ny, int64_t B) {
+  const int64_t want = sizeof(T) == 4 ? 2 * kTargetBlocks : kTargetBlocks;
+  if (B > 64 && ny * ((B + 127) / 128) >= want) return 128;
+  if (B > 32 && ny * ((B + 63) / 64) >= want) return 64;
   return 32;
 }
 
@@ -1124,8 +1099,8 @@ bool rows_aligned(int64_t B) { return (B * static_cast<int64_t>(sizeof(T))) % 16
 template <typename T>
 hipError_t run_wave_rows(int pass, TileWaveArgs& w, hipStream_t s) {
   using C = WaveCfgs<T>;
-  const int bn = wave_bn(w.ny, w.B);
-  if (rows_aligned<T>(w.B))
+  const int bn = wave_bn<T>(static_cast<int64_t>(w.ny) * (w.splits > 1 ? w.splits : 1), w.B);
+  if (rows_aligned<T>(w.lda))
     return bn == 128  ? launch_wave_rows<typename C::N128, T, false>(pass, w, s)
            : bn == 64 ? launch_wave_rows<typename C::N64, T, false>(pass, w, s)
                       : launch_wave_rows<typename C::N32, T, false>(pass, w, s);
@@ -1142,11 +1117,11 @@ TileWaveArgs wave_rows_args(const TdpArgs& a, int owners) {
   w.out = a.out;
   w.ptr = a.ptr;
   w.list = a.list;
-  w.B = a.B;
+  w.B = w.lda = w.ldo = w.nb = w.nv = a.B;
   w.K = a.K;
   w.tile = a.tile;
   w.ny = owners * (a.tile / 32);
-  w.hi = 1 << 30;
+  w.hi = kAllTiles;
   w.scale = a.scale;
   w.splits = 1;
   return w;
@@ -1225,7 +1200,7 @@ hipError_t run_tdp_wave_bwd(const TdpArgs& ad, const TdpArgs& aw, const int32_t*
                             hipStream_t s) {
   using C = WaveCfgs<T>;
   TileWaveArgs d = wave_rows_args<T>(ad, ad.tiles_k);
-  const int bn = wave_bn(d.ny, d.B);
+  const int bn = wave_bn<T>(d.ny, d.B);
   const int64_t groups = group_bound(nnz, tiles_n, aw.tiles_k);
   if (dw_on_pipeline<T>(aw))
     return bn == 128  ? launch_wave_group_bwd<typename C::N128, T>(d, aw, chunks, groups, s)
@@ -1324,53 +1299,51 @@ int plan_tiles(int32_t n, int32_t k, int32_t tile, uint32_t* d_bits, int32_t nnz
 
 }  // namespace
 
-// The fp32 tile layer's forward (fwd) or transposed product with each tile
-// row's (column's) kept-tile list split over up to 8 workgroups when the tile
-// rows (columns) alone would leave most of the chip idle, as for a recurrent
-// step at a small batch: partial sums in `partial` (partial_floats floats),
-// then a fixed-order reduction that applies the scale. Runs the single-pass
-// call when no split applies (another dtype, the register-staged path, too
-// many workgroups already, or too small a partial buffer).
-int tdp_product_f32_split(bool fwd, const ard_tile_desc* d, const ard_tile_plan* p, const void* act, const void* W,
-                          void* out, float* partial, size_t partial_floats, void* stream, int* splits_left) {
+// Part of an fp32 tile product for the tile-pattern LSTM: output tile rows
+// (fwd) or columns from own0 on, own_count of them, over the kept tiles whose
+// other index lies in [lo, hi); act row 0 belongs to index lo. Columns and
+// output addressing as in TileWaveArgs. With a partial buffer, and where the
+// grid would leave most of the chip idle, the lists are split over workgroups:
+// *splits_left > 1 then says that partial holds that many sums of
+// own_count * tile x cols, to be added in order (out is not written).
+int tile_part_check(const ard_tile_plan* p, int32_t cols, const void* W) {
+  const ard_tile_desc d = {ARD_F32, cols, p->k, p->n, 1.0f, ARD_DROPPED_ZERO};
+  const int st = check_tile_call(&d, p);
+  return st != ARD_OK ? st : check_dev_ptr(W, "W");
+}
+
+int tile_part_f32(bool fwd, const ard_tile_plan* p, const TilePart& t, void* stream, int* splits_left) {
   if (splits_left) *splits_left = 1;
-  int st = check_tile_call(d, p);
-  if (st != ARD_OK) return st;
-  auto single = [&]() {
-    return fwd ? ard_tile_fwd(d, p, act, W, out, stream) : ard_tile_bwd_data(d, p, act, W, out, stream);
-  };
-  if (d->dtype != ARD_F32 || !partial || !aligned16(partial)) return single();
-  if ((st = check_dev_ptr(act, "act")) || (st = check_dev_ptr(W, "W")) || (st = check_dev_ptr(out, "out")))
-    return st;
-  TdpArgs a = {act, nullptr, W, out, d->batch, p->n, p->k, p->tile, p->tiles_k,
-               fwd ? p->d_row_ptr : p->d_col_ptr, fwd ? p->d_row_cols : p->d_col_rows, d->scale,
-               p->d_row_ptr + p->tiles_n};
-  if (!tdp_fast_ok<float>(a)) return single();
-  using C = TdpFastCfgs<float>;
-  const int owners = fwd ? p->tiles_n : p->tiles_k;
-  const bool narrow = a.B <= C::Narrow::BN;
-  const int bn = narrow ? C::Narrow::BN : C::Rows::BN;
-  const int nx = (a.B + bn - 1) / bn;
-  int splits = 1;
-  while (splits < 8 && static_cast<int64_t>(nx) * owners * splits * 2 <= kTargetBlocks) splits *= 2;
-  const int64_t rows = static_cast<int64_t>(owners) * kFastTile;
-  if (splits == 1 || static_cast<size_t>(splits) * rows * a.B > partial_floats) return single();
-  TdpFastArgs f = {a.act, nullptr, a.W, a.out, a.B, a.K, nx, owners, a.ptr, a.list, p->d_chunks, a.scale,
-                   splits, static_cast<int32_t>(rows), partial};
-  hipStream_t sm = static_cast<hipStream_t>(stream);
-  const int pass = fwd ? TDP_FWD : TDP_BWD_DATA;
-  if (narrow)
-    ARD_HIP_CHECK((launch_rows<C::Narrow, float>(pass, f, owners, splits, sm)));
-  else
-    ARD_HIP_CHECK((launch_rows<C::Rows, float>(pass, f, owners, splits, sm)));
-  if (splits_left) {  // the caller adds the partial sums itself (scale 1 only)
-    *splits_left = splits;
-    return ARD_OK;
+  if (t.own_count <= 0 || t.cols <= 0) return ARD_OK;
+  TileWaveArgs w = {};
+  w.act = t.act;
+  w.W = t.W;
+  w.out = t.out;
+  w.ptr = fwd ? p->d_row_ptr : p->d_col_ptr;
+  w.list = fwd ? p->d_row_cols : p->d_col_rows;
+  w.B = t.cols;
+  w.lda = t.lda;
+  w.ldo = t.ldo;
+  w.nb = t.nb;
+  w.nv = t.nv;
+  w.bstride = t.bstride;
+  w.K = p->k;
+  w.tile = p->tile;
+  w.ny = t.own_count * (p->tile / 32);
+  w.own0 = t.own0;
+  w.lo = t.lo;
+  w.hi = t.lo == 0 && t.hi >= (fwd ? p->tiles_k : p->tiles_n) ? kAllTiles : t.hi;
+  w.scale = 1.0f;
+  w.splits = 1;
+  w.partial = t.partial;
+  if (t.partial && splits_left) {
+    // a split keeps at least two parts per wave of a full list
+    const int64_t wgs = static_cast<int64_t>(w.ny) * ((t.cols + 31) / 32);
+    const int64_t units = static_cast<int64_t>(t.hi - t.lo) * (p->tile / 32);
+    while (w.splits < kTilePartSplits && wgs * w.splits * 2 <= 2 * kTargetBlocks && units / (w.splits * 2) >= 8) w.splits *= 2;
+    *splits_left = w.splits;
   }
-  const int64_t n = rows * a.B;
-  hipLaunchKernelGGL(tdp_split_reduce_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, sm,
-                     partial, splits, n, a.scale, static_cast<float*>(out));
-  ARD_LAUNCH_CHECK();
+  ARD_HIP_CHECK(run_wave_rows<float>(fwd ? TDP_FWD : TDP_BWD_DATA, w, static_cast<hipStream_t>(stream)));
   return ARD_OK;
 }
 

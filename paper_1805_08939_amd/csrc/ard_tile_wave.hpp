@@ -32,8 +32,14 @@ struct TileWaveArgs {
   void* out;            // Yt or dXt
   const int32_t* ptr;   // row_ptr (fwd) or col_ptr (bwd_data)
   const int32_t* list;  // row_cols (fwd) or col_rows (bwd_data), ascending per row
-  int32_t B, K, tile;
-  int32_t nx, ny;       // grid: batch blocks x 32-row blocks of the output
+  int32_t B, K, tile;   // columns of the product; row stride of W
+  int32_t lda;          // row stride of act
+  // output element (m, n): out[m * ldo + (n / nb) * bstride + n % nb], written
+  // where n % nb < nv (a product over the columns of several steps at once;
+  // nb is a multiple of 4, or B)
+  int32_t ldo, nb, nv;
+  int64_t bstride;
+  int32_t nx, ny;       // grid: column blocks x 32-row blocks of the output
   int32_t own0;         // first output tile row (fwd) or column (bwd_data)
   int32_t lo, hi;       // list entries in [lo, hi) only; act row 0 belongs to entry lo
   float scale;
@@ -44,6 +50,7 @@ struct TileWaveArgs {
 };
 
 enum { WAVE_FWD = 0, WAVE_BWD_DATA = 1 };
+constexpr int kAllTiles = 1 << 30;  // hi of an unrestricted list
 
 template <typename T, int BN_, int NWV_, int STAGES_>
 struct WaveCfg {
@@ -67,7 +74,7 @@ struct PartWalk {
   const char* b0;
   int64_t a_tile, a_part, b_tile, b_part;
   const int32_t* list;
-  int32_t n, parts, u, last, step, wbase, win, base;
+  int32_t n, parts, u, last, step, wbase, win, base;  // win: list[wbase + lane]
 
   __device__ __forceinline__ void refill() {
     const int lane = threadIdx.x & 63;
@@ -248,20 +255,23 @@ __device__ __forceinline__ void tile_wave_rows(const TileWaveArgs& a, int bid, i
   const int n0 = col * WC::BN;
   const int parts = a.tile / 32;
   const int own = a.own0 + blk / parts, sub = blk % parts;
-  int pa = __builtin_amdgcn_readfirstlane(a.ptr[own]);
-  int pb = __builtin_amdgcn_readfirstlane(a.ptr[own + 1]);
-  // the entries in [lo, hi) of an ascending list are a run of it
-  if (a.lo > 0 || a.hi < (1 << 30)) {
-    int below = 0, inside = 0;
-    for (int i = pa; i < pb; i += 64) {
-      const int t = i + lane < pb ? a.list[i + lane] : (1 << 30);
-      below += __popcll(__ballot(t < a.lo));
-      inside += __popcll(__ballot(t >= a.lo && t < a.hi));
+  const int pa = __builtin_amdgcn_readfirstlane(a.ptr[own]);
+  const int len = __builtin_amdgcn_readfirstlane(a.ptr[own + 1]) - pa;
+  // the list's first window, and where the entries in [lo, hi) of the
+  // ascending list begin and end in it
+  const int first = len > 0 ? a.list[pa + (lane < len ? lane : len - 1)] : 0;
+  int e0 = 0, e1 = len;
+  if (a.lo > 0 || a.hi < kAllTiles) {
+    int t = lane < len ? first : kAllTiles;
+    e0 = __popcll(__ballot(t < a.lo));
+    e1 = __popcll(__ballot(t < a.hi));
+    for (int i = 64; i < len; i += 64) {
+      t = i + lane < len ? a.list[pa + i + lane] : kAllTiles;
+      e0 += __popcll(__ballot(t < a.lo));
+      e1 += __popcll(__ballot(t < a.hi));
     }
-    pa = __builtin_amdgcn_readfirstlane(pa + below);
-    pb = __builtin_amdgcn_readfirstlane(pa + inside);
   }
-  const int units = (pb - pa) * parts;
+  const int units = (e1 - e0) * parts;
   const int u0 = units * sp / splits, u1 = units * (sp + 1) / splits;  // this split's parts
   const int nu = u1 - u0 > wave ? (u1 - u0 - wave + WC::NWV - 1) / WC::NWV : 0;
 
@@ -286,17 +296,18 @@ __device__ __forceinline__ void tile_wave_rows(const TileWaveArgs& a, int bid, i
       pw.a_part = 32 * K * ES;
     }
     pw.b0 = static_cast<const char*>(a.act);
-    pw.b_tile = TT * B * ES;
-    pw.b_part = 32 * B * ES;
+    pw.b_tile = TT * a.lda * ES;
+    pw.b_part = static_cast<int64_t>(32) * a.lda * ES;
     pw.list = a.list + pa;
-    pw.n = pb - pa;
+    pw.n = len;
     pw.parts = parts;
-    pw.u = u0 + wave;
-    pw.last = u1 - 1;
+    pw.u = e0 * parts + u0 + wave;
+    pw.last = e0 * parts + u1 - 1;
     pw.step = WC::NWV;
     pw.base = a.lo;
     pw.wbase = (pw.u / parts) / 64 * 64;
-    pw.refill();
+    pw.win = first;
+    if (pw.wbase > 0) pw.refill();
     auto next = [&](const char*& pA, const char*& pB) {
       pw.next(pA, pB);
       return static_cast<int>(Cfg::BK);
@@ -305,26 +316,30 @@ __device__ __forceinline__ void tile_wave_rows(const TileWaveArgs& a, int bid, i
       RegSrc<Cfg, 32, AMC> da;
       RegSrc<Cfg, WC::BN, true> db;
       da.init(K, 0, 32, 0);
-      db.init(B, n0, a.B, 0);
+      db.init(a.lda, n0, a.B, 0);
       wave_walk_any<Cfg, AMC, true>(da, db, next, nu, acc, smem + wave * Cfg::STAGE);
     } else {
       DmaSrc<Cfg, 32, AMC> da;
       DmaSrc<Cfg, WC::BN, true> db;
       da.init(K, 0, 32, 0);
-      db.init(B, n0, a.B, 0);
+      db.init(a.lda, n0, a.B, 0);
       wave_walk_dma<Cfg, AMC, true>(da, db, next, nu, acc, smem + wave * Cfg::LDS);
     }
   }
-  const bool vec = a.B % 4 == 0;  // rows of whole 4-element pieces
   if (splits > 1) {
     float* part = a.partial + (static_cast<int64_t>(sp) * a.ny + blk) * 32 * B;
     wave_reduce<WC>(acc, smem, [&](int row, int c, const f32x4& v) {
-      if (n0 + c < a.B) put4<float>(part + row * B + n0 + c, v, 1.0f, a.B - n0 - c, vec);
+      if (n0 + c < a.B) put4<float>(part + row * B + n0 + c, v, 1.0f, a.B - n0 - c, a.B % 4 == 0);
     });
   } else {
-    T* out = static_cast<T*>(a.out) + static_cast<int64_t>(blk) * 32 * B;
+    // pieces of 4 aligned elements: rows and blocks of whole pieces
+    const bool vec = a.ldo % 4 == 0 && a.bstride % 4 == 0 && a.nb % 4 == 0 &&
+                     reinterpret_cast<uintptr_t>(a.out) % (4 * sizeof(T)) == 0;
+    T* out = static_cast<T*>(a.out) + static_cast<int64_t>(blk) * 32 * a.ldo;
     wave_reduce<WC>(acc, smem, [&](int row, int c, const f32x4& v) {
-      if (n0 + c < a.B) put4<T>(out + row * B + n0 + c, v, a.scale, a.B - n0 - c, vec);
+      if (n0 + c >= a.B) return;
+      const int t = (n0 + c) / a.nb, b = n0 + c - t * a.nb;
+      put4<T>(out + static_cast<int64_t>(row) * a.ldo + t * a.bstride + b, v, a.scale, a.nv - b, vec);
     });
   }
 }

@@ -75,3 +75,55 @@ def test_wave_kernels(dtype, case, known):
     assert ((dW.double() - want).abs()[kept] <= TOL["f32"] * norm[kept] + 1e-30).all()
     assert (dW[~kept] == 7.0).all()
     assert torch.equal(dX, dX2) and torch.equal(dW, dW2)
+
+
+@pytest.mark.parametrize("T,B,I,H,tile", [(3, 5, 64, 32, 32), (2, 1, 40, 24, 32), (4, 66, 128, 192, 64),
+                                          (2, 64, 96, 160, 64), (1, 7, 32, 32, 32), (3, 16, 1024, 128, 32)])
+@pytest.mark.parametrize("outs", ["all", "some"])
+def test_lstm_tile_padded_batch(T, B, I, H, tile, outs):
+    """The tile-pattern LSTM with a batch that is padded inside, with the input
+    tiles' products hoisted out of the steps (I a multiple of the tile) and not."""
+    from oracle import lstm as olstm
+    print(T, B, I, H, tile, outs, flush=True)
+    tn, tk = 4 * H // tile, (I + H) // tile
+    g = synth.generator(9)
+    X, W = synth.uniform(g, (T, B, I), 0.5), synth.uniform(g, (4 * H, I + H), 0.2)
+    b, dHs = synth.uniform(g, (4 * H,), 0.1), synth.normal(g, (T, B, H))
+    h0, c0, dhT, dcT = (synth.normal(g, (B, H), 0.3) for _ in range(4))
+    bits = api.ard_tile_bitmap_bernoulli(tn, tk, 0.5, 3, 0, 1)
+    keep = np.array([(int(bits[t // 32]) >> (t % 32)) & 1 for t in range(tn * tk)]).reshape(tn, tk)
+    M = np.kron(keep, np.ones((tile, tile)))
+    ws = torch.empty(max(api.ard_tile_plan_workspace_bytes(tn, tk), 16) // 4, dtype=torch.int32, device=device())
+    plan = api.ard_plan_tiles(4 * H, I + H, tile, torch.from_numpy(bits.view("int32").copy()).to(device()),
+                              int(keep.sum()), ws)
+    desc = api.lstm_tile_desc(api.ARD_F32, T, B, I, H, plan)
+
+    def dev(t):
+        return t.permute(*range(t.dim() - 2), -1, -2).contiguous().to(device())
+
+    Wd = torch.where(torch.from_numpy(M).bool(), W, torch.full_like(W, float("nan"))).to(device())
+    lw = torch.full((api.ard_lstm_tile_workspace_bytes(desc) // 4 + 4,), float("nan"), device=device())
+    Hs = torch.full((T, H, B), 7.0, device=device())
+    hT, cT = torch.empty(H, B, device=device()), torch.empty(H, B, device=device())
+    full = outs == "all"
+    api.ard_lstm_tile_fwd(desc, dev(X), Wd, b.to(device()), dev(h0) if full else None, dev(c0) if full else None, Hs,
+                          hT if full else None, cT if full else None, lw)
+    dX, dW = torch.full((T, I, B), 7.0, device=device()), torch.full((4 * H, I + H), 7.0, device=device())
+    db, dh0, dc0 = torch.empty(4 * H, device=device()), hT.clone(), cT.clone()
+    for _ in range(2):  # the forward's workspace serves a second backward too
+        api.ard_lstm_tile_bwd(desc, Wd, dev(dHs), dev(dhT) if full else None, dev(dcT) if full else None, lw,
+                              dX, dW, db, dh0 if full else None, dc0 if full else None)
+    torch.cuda.synchronize()
+    ones, Wm = np.ones(H), W.double().numpy() * M
+    n = (lambda t: t.double().numpy()) if full else (lambda t: None)
+    Hs64, hT64, cT64, cache = olstm.lstm_forward(X.double().numpy(), Wm, b.double().numpy(), ones, n(h0), n(c0))
+    dX64, dW64, db64, dh64, dc64 = olstm.lstm_backward(X.double().numpy(), Wm, ones, cache, dHs.double().numpy(),
+                                                       n(dhT), n(dcT))
+    want = [(Hs, Hs64.transpose(0, 2, 1)), (dX, dX64.transpose(0, 2, 1)), (dW, dW64 * M), (db, db64)]
+    if full:
+        want += [(hT, hT64.T), (cT, cT64.T), (dh0, dh64.T), (dc0, dc64.T)]
+    for got, w in want:
+        got = got.double().cpu().numpy()
+        assert np.isfinite(got).all()
+        # fp32 gates and sums over a few steps: some tens of roundings of 2^-24 of the largest value
+        assert np.abs(got - w).max() <= 1e-5 * max(np.abs(w).max(), 1e-3)
