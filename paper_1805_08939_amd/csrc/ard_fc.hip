@@ -258,30 +258,44 @@ int check_desc(const ard_fc_desc* d, FcShape* s) {
 
 size_t al256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
+constexpr size_t kNoAllocScratchBytes = size_t{32} << 20;  // scratch of ard_fc_fwd_noalloc
+
 size_t compact_bytes(const FcShape& s) { return static_cast<size_t>(s.kout) * s.ldc * s.esize; }
 
 // Split-K partial floats of one problem under whichever kernel may run it.
 template <typename T>
-size_t problem_partials(int M, int N, int K) {
+size_t problem_partials(int M, int N, int K, bool required) {
   size_t f = gemm_partial_floats<T>(M, N, K, 1, 1);
-  const size_t h = fast_partial_floats<T>(M, N, K, 1, 1);
+  const size_t h = fast_partial_floats<T>(M, N, K, required);
   return f > h ? f : h;
 }
 
 template <typename T>
-size_t partial_bytes(const FcShape& s) {
-  size_t f = problem_partials<T>(s.kout, s.B, s.kin);                 // fwd
-  const size_t d = problem_partials<T>(s.kin, s.B, s.kout);           // bwd_data
-  const size_t w = problem_partials<T>(s.kout, s.kin, s.B);           // bwd_weight
+size_t partial_bytes(const FcShape& s, bool required) {
+  size_t f = problem_partials<T>(s.kout, s.B, s.kin, required);                 // fwd
+  const size_t d = problem_partials<T>(s.kin, s.B, s.kout, required);           // bwd_data
+  const size_t w = problem_partials<T>(s.kout, s.kin, s.B, required);           // bwd_weight
   f = f > d ? f : d;
   f = f > w ? f : w;
   return 4 * f;
 }
 
-size_t workspace_bytes(const FcShape& s, int dtype) {
-  const size_t part = dtype == ARD_BF16 ? partial_bytes<bf16>(s) : partial_bytes<float>(s);
+// Workspace that the calls make use of, or the least they accept (required:
+// contractions are then split less).
+size_t workspace_bytes(const FcShape& s, int dtype, bool required) {
+  size_t part = dtype == ARD_BF16 ? partial_bytes<bf16>(s, required) : partial_bytes<float>(s, required);
+  if (!required) {
+    const size_t least = dtype == ARD_BF16 ? partial_bytes<bf16>(s, true) : partial_bytes<float>(s, true);
+    part = part > least ? part : least;
+  }
   return (s.needs_compact ? al256(compact_bytes(s)) : 0) + al256(part);
 }
+
+// A call's workspace: its address and what fits behind the compact weight copy.
+struct Workspace {
+  void* p;
+  size_t bytes;
+};
 
 int check_ptr(const void* p, const char* name) {
   if (!p) return fail(ARD_ERR_INVALID_ARG, "%s is NULL", name);
@@ -289,9 +303,14 @@ int check_ptr(const void* p, const char* name) {
   return ARD_OK;
 }
 
-int check_ws(const FcShape& s, int dtype, void* ws, size_t ws_bytes) {
-  const size_t need = workspace_bytes(s, dtype);
-  if (need == 0) return ARD_OK;
+int check_ws(const FcShape& s, int dtype, void* ws, size_t ws_bytes, Workspace* use) {
+  const size_t need = workspace_bytes(s, dtype, true);
+  if (need == 0) {  // nothing is needed: one that cannot be used is not used
+    if (!ws || !aligned16(ws)) *use = {nullptr, 0};
+    else *use = {ws, ws_bytes};
+    return ARD_OK;
+  }
+  *use = {ws, ws_bytes};
   if (!ws || ws_bytes < need)
     return fail(ARD_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, ws_bytes);
   if (!aligned16(ws)) return fail(ARD_ERR_INVALID_ARG, "workspace is not 16-byte aligned");
@@ -376,11 +395,12 @@ GemmOutput strided_out(void* p, int64_t ld, size_t esize, int32_t period, int32_
 struct WeightView {
   GemmOperand op;
   float* partial;  // split-K partial sums in ws, or NULL
+  int64_t cap;     // floats that fit there
 };
 
 template <typename T>
-int weight_view(const FcShape& s, const void* W, void* ws, hipStream_t stream, WeightView* v) {
-  char* w = static_cast<char*>(ws);
+int weight_view(const FcShape& s, const void* W, Workspace ws, hipStream_t stream, WeightView* v) {
+  char* w = static_cast<char*>(ws.p);
   if (s.compact_given) {
     v->op = kept_rows(W, nullptr, s.ldc, 1, 0, sizeof(T), 0);
   } else if (s.input_major) {  // the kept input rows of W^T[K][N]
@@ -392,16 +412,23 @@ int weight_view(const FcShape& s, const void* W, void* ws, hipStream_t stream, W
   } else {
     v->op = kept_rows(W, nullptr, s.K, s.out_period, s.out_offset, sizeof(T), 0);
   }
-  v->partial = ws ? reinterpret_cast<float*>(w) : nullptr;
+  v->partial = ws.p ? reinterpret_cast<float*>(w) : nullptr;
+  v->cap = ws.p ? static_cast<int64_t>(ws.bytes - (w - static_cast<char*>(ws.p))) / 4 : 0;
   return ARD_OK;
 }
 
 template <typename T>
 int fc_fwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const void* W,
-                const float* bias, void* Yt, void* ws, hipStream_t stream) {
+                const float* bias, void* Yt, Workspace ws, hipStream_t stream) {
   WeightView wv;
   int st = weight_view<T>(s, W, ws, stream, &wv);
   if (st != ARD_OK) return st;
+  // no more room than ard_fc_fwd_noalloc has, so that its results are these bit for bit
+  const size_t skip = s.needs_compact ? al256(compact_bytes(s)) : 0;
+  if (skip < kNoAllocScratchBytes) {
+    const int64_t most = static_cast<int64_t>(kNoAllocScratchBytes - skip) / 4;
+    if (wv.cap > most) wv.cap = most;
+  }
   GemmArgs g = {};
   g.M = s.kout;
   g.N = s.B;
@@ -414,13 +441,13 @@ int fc_fwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const vo
   const bool b_vec = vec_rows(s.B, sizeof(T));
   if (s.input_major) {  // A(m, k) = W^T[in(k)][m]: m-contiguous
     if (any_ok<true, true>(g, sizeof(T))) {
-      ARD_HIP_CHECK((run_strided_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, wv.partial)));
+      ARD_HIP_CHECK((run_strided_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, wv.partial, wv.cap)));
     } else {
       ARD_HIP_CHECK((run_gemm<T, T, MC_VEC, MC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
           g, 1, a_vec, b_vec, stream, wv.partial)));
     }
   } else if (any_ok<false, true>(g, sizeof(T))) {
-    ARD_HIP_CHECK((run_strided_gemm<T, false, true, T, EPI_FWD>(g, 1, stream, wv.partial)));
+    ARD_HIP_CHECK((run_strided_gemm<T, false, true, T, EPI_FWD>(g, 1, stream, wv.partial, wv.cap)));
   } else {
     ARD_HIP_CHECK((run_gemm<T, T, KC_VEC, KC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
         g, 1, a_vec, b_vec, stream, wv.partial)));
@@ -532,13 +559,13 @@ int finish_bwd_weight(const ard_fc_desc* d, const FcShape& s, const void* dYt, c
 
 template <typename T>
 int run_bwd_data(const ard_fc_desc* d, const FcShape& s, const GemmArgs& g, const void* Yt, void* dXt,
-                 float* partial, hipStream_t stream) {
+                 float* partial, int64_t cap, hipStream_t stream) {
   const bool gated = d->act == ARD_ACT_RELU && Yt != nullptr;
   const bool a_vec = vec_rows(g.a.ld, sizeof(T));
   const bool b_vec = vec_rows(s.B, sizeof(T));
   if (s.input_major) {  // A(m, t) = W^T[in(m)][t]: k-contiguous rows
     if (any_ok<false, true>(g, sizeof(T))) {
-      ARD_HIP_CHECK((run_strided_gemm<T, false, true, T, EPI_FWD>(g, 1, stream, partial)));
+      ARD_HIP_CHECK((run_strided_gemm<T, false, true, T, EPI_FWD>(g, 1, stream, partial, cap)));
     } else if (gated) {
       ARD_HIP_CHECK((run_gemm<T, T, KC_VEC, KC_ELEM, MC_VEC, MC_ELEM, false, true, EPI_FWD>(
           g, 1, a_vec, b_vec, stream, partial)));
@@ -547,7 +574,7 @@ int run_bwd_data(const ard_fc_desc* d, const FcShape& s, const GemmArgs& g, cons
           g, 1, a_vec, b_vec, stream, partial)));
     }
   } else if (any_ok<true, true>(g, sizeof(T))) {
-    ARD_HIP_CHECK((run_strided_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, partial)));
+    ARD_HIP_CHECK((run_strided_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, partial, cap)));
   } else if (gated) {
     ARD_HIP_CHECK((run_gemm<T, T, MC_VEC, MC_ELEM, MC_VEC, MC_ELEM, false, true, EPI_FWD>(
         g, 1, a_vec, b_vec, stream, partial)));
@@ -560,26 +587,26 @@ int run_bwd_data(const ard_fc_desc* d, const FcShape& s, const GemmArgs& g, cons
 
 template <typename T>
 int fc_bwd_data_impl(const ard_fc_desc* d, const FcShape& s, const void* dYt, const void* Yt,
-                     const void* W, void* dXt, const void* Xgate, void* ws, hipStream_t stream) {
+                     const void* W, void* dXt, const void* Xgate, Workspace ws, hipStream_t stream) {
   WeightView wv;
   int st = weight_view<T>(s, W, ws, stream, &wv);
   if (st != ARD_OK) return st;
-  return run_bwd_data<T>(d, s, bwd_data_args<T>(d, s, dYt, Yt, wv.op, dXt, Xgate), Yt, dXt, wv.partial, stream);
+  return run_bwd_data<T>(d, s, bwd_data_args<T>(d, s, dYt, Yt, wv.op, dXt, Xgate), Yt, dXt, wv.partial, wv.cap, stream);
 }
 
 template <typename T>
 int fc_bwd_weight_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const void* dYt,
-                       const void* Yt, float* dW, float* dbias, void* ws, hipStream_t stream) {
+                       const void* Yt, float* dW, float* dbias, Workspace ws, hipStream_t stream) {
   GemmArgs g = bwd_weight_args<T>(d, s, Xt, dYt, Yt, dW);
   const bool gated = d->act == ARD_ACT_RELU && Yt != nullptr;
   const bool v = vec_rows(s.B, sizeof(T));
-  float* partial = ws ? reinterpret_cast<float*>(static_cast<char*>(ws) +
-                                                 (s.needs_compact ? al256(compact_bytes(s)) : 0))
-                      : nullptr;
+  const size_t skip = s.needs_compact ? al256(compact_bytes(s)) : 0;
+  float* partial = ws.p ? reinterpret_cast<float*>(static_cast<char*>(ws.p) + skip) : nullptr;
+  const int64_t cap = ws.p && ws.bytes > skip ? static_cast<int64_t>(ws.bytes - skip) / 4 : 0;
   bool dbias_done = false;
   if (s.input_major) {  // the bias gradient from dbias_kernel (G is the B operand here)
     if (any_ok<false, false>(g, sizeof(T))) {
-      ARD_HIP_CHECK((run_strided_gemm<T, false, false, float, EPI_FWD>(g, 1, stream, partial)));
+      ARD_HIP_CHECK((run_strided_gemm<T, false, false, float, EPI_FWD>(g, 1, stream, partial, cap)));
     } else if (gated) {
       ARD_HIP_CHECK((run_gemm<T, float, KC_VEC, KC_ELEM, KC_VEC, KC_ELEM, false, true, EPI_FWD>(
           g, 1, v, v, stream, partial)));
@@ -593,7 +620,7 @@ int fc_bwd_weight_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, c
       g.rsum = dbias + s.out_offset;
       g.rsum_ld = s.out_period;
     }
-    ARD_HIP_CHECK((run_strided_gemm<T, false, false, float, EPI_FWD, true>(g, 1, stream, partial, &dbias_done)));
+    ARD_HIP_CHECK((run_strided_gemm<T, false, false, float, EPI_FWD, true>(g, 1, stream, partial, cap, &dbias_done)));
   } else if (gated) {
     ARD_HIP_CHECK((run_gemm<T, float, KC_VEC, KC_ELEM, KC_VEC, KC_ELEM, true, false, EPI_FWD>(
         g, 1, v, v, stream, partial)));
@@ -611,7 +638,7 @@ int fc_bwd_weight_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, c
 // output tile is computed by the same code on the same operands.
 template <typename T>
 int fc_bwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const void* dYt, const void* Yt,
-                const void* W, void* dXt, const void* Xgate, float* dW, float* dbias, void* ws,
+                const void* W, void* dXt, const void* Xgate, float* dW, float* dbias, Workspace ws,
                 hipStream_t stream) {
   WeightView wv;
   int st = weight_view<T>(s, W, ws, stream, &wv);
@@ -622,7 +649,7 @@ int fc_bwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const vo
   // both on register loads: neither is split off to the direct loads of a call of its own
   const bool any = !fast && !fast_ok<true, true>(gd, sizeof(T)) && !fast_ok<false, false>(gw, sizeof(T)) &&
                    any_ok<true, true>(gd, sizeof(T)) && any_ok<false, false>(gw, sizeof(T));
-  if (!s.input_major && ((fast && fast_pair_ok<T>(gd, gw)) || (any && any_pair_ok<T>(gd, gw)))) {
+  if (!s.input_major && ((fast && fast_pair_ok<T>(gd, gw, wv.cap)) || (any && any_pair_ok<T>(gd, gw, wv.cap)))) {
     if (dbias) {
       gw.rsum = dbias + s.out_offset;
       gw.rsum_ld = s.out_period;
@@ -634,17 +661,17 @@ int fc_bwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const vo
       ARD_HIP_CHECK((launch_fast_pair<T, true, true, T, EPI_FWD, false, false, false, float, EPI_FWD, false>(
           gd, gw, stream)));
     else if (dbias)
-      ARD_HIP_CHECK((launch_fast_pair<T, true, true, T, EPI_FWD, false, false, false, float, EPI_FWD, true, true>(
+      ARD_HIP_CHECK((launch_fast_pair<T, true, true, T, EPI_FWD, false, false, false, float, EPI_FWD, true, LOAD_ANY>(
           gd, gw, stream)));
     else
-      ARD_HIP_CHECK((launch_fast_pair<T, true, true, T, EPI_FWD, false, false, false, float, EPI_FWD, false, true>(
+      ARD_HIP_CHECK((launch_fast_pair<T, true, true, T, EPI_FWD, false, false, false, float, EPI_FWD, false, LOAD_ANY>(
           gd, gw, stream)));
     if ((st = zero_dropped_inputs<T>(d, s, dXt, stream)) != ARD_OK) return st;
     return finish_bwd_weight<T>(d, s, dYt, Yt, dW, dbias, dbias != nullptr, stream);
   }
   // the compact weights (if built into ws) are not needed past bwd_data,
   // whose partial sums lie behind them: bwd_weight's own call layout
-  if ((st = run_bwd_data<T>(d, s, gd, Yt, dXt, wv.partial, stream)) != ARD_OK) return st;
+  if ((st = run_bwd_data<T>(d, s, gd, Yt, dXt, wv.partial, wv.cap, stream)) != ARD_OK) return st;
   return fc_bwd_weight_impl<T>(d, s, Xt, dYt, Yt, dW, dbias, ws, stream);
 }
 
@@ -655,8 +682,7 @@ int fc_bwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const vo
 // GPU the library runs on, held until the process ends. Its host-side name is
 // only a stand-in for the symbol: host code uses the per-device address that
 // hipGetSymbolAddress returns, never the name.
-constexpr size_t kNoAllocScratchBytes = size_t{32} << 20;
-static __device__ __align__(256) char scratch[kNoAllocScratchBytes];
+static __device__ __align__(256) char scratch[ard::kNoAllocScratchBytes];
 
 namespace ard {
 namespace {
@@ -697,13 +723,16 @@ int ard_fc_fwd_noalloc(const ard_fc_desc* desc, const void* Xt, const void* W, c
   if ((st = check_ptr(Xt, "Xt")) || (st = check_ptr(W, "W")) || (st = check_ptr(Yt, "Yt")))
     return st;
   if (bias && !aligned16(bias)) return fail(ARD_ERR_INVALID_ARG, "bias is not 16-byte aligned");
-  const size_t need = workspace_bytes(s, desc->dtype);
+  const size_t need = workspace_bytes(s, desc->dtype, true);
   if (need > kNoAllocScratchBytes)
     return fail(ARD_ERR_WORKSPACE,
                 "the layer needs %zu bytes of scratch, the static scratch holds %zu (use ard_fc_fwd with a workspace)",
                 need, kNoAllocScratchBytes);
-  void* ws = nullptr;
-  if (need > 0 && (st = device_scratch(&ws)) != ARD_OK) return st;
+  Workspace ws = {nullptr, 0};
+  if (workspace_bytes(s, desc->dtype, false) > 0) {
+    if ((st = device_scratch(&ws.p)) != ARD_OK) return st;
+    ws.bytes = kNoAllocScratchBytes;
+  }
   hipStream_t sm = static_cast<hipStream_t>(stream);
   if (desc->dtype == ARD_BF16) return fc_fwd_impl<bf16>(desc, s, Xt, W, bias, Yt, ws, sm);
   return fc_fwd_impl<float>(desc, s, Xt, W, bias, Yt, ws, sm);
@@ -839,7 +868,7 @@ int ard_fc_sgd_momentum(const ard_fc_desc* desc, void* W, float* V, const float*
 size_t ard_fc_workspace_bytes(const ard_fc_desc* desc) {
   FcShape s;
   if (check_desc(desc, &s) != ARD_OK) return 0;
-  return workspace_bytes(s, desc->dtype);
+  return workspace_bytes(s, desc->dtype, false);
 }
 
 int ard_fc_fwd(const ard_fc_desc* desc, const void* Xt, const void* W, const float* bias, void* Yt,
@@ -851,10 +880,11 @@ int ard_fc_fwd(const ard_fc_desc* desc, const void* Xt, const void* W, const flo
   if ((st = check_ptr(Xt, "Xt")) || (st = check_ptr(W, "W")) || (st = check_ptr(Yt, "Yt")))
     return st;
   if (bias && !aligned16(bias)) return fail(ARD_ERR_INVALID_ARG, "bias is not 16-byte aligned");
-  if ((st = check_ws(s, desc->dtype, ws, ws_bytes))) return st;
+  Workspace use;
+  if ((st = check_ws(s, desc->dtype, ws, ws_bytes, &use))) return st;
   hipStream_t sm = static_cast<hipStream_t>(stream);
-  if (desc->dtype == ARD_BF16) return fc_fwd_impl<bf16>(desc, s, Xt, W, bias, Yt, ws, sm);
-  return fc_fwd_impl<float>(desc, s, Xt, W, bias, Yt, ws, sm);
+  if (desc->dtype == ARD_BF16) return fc_fwd_impl<bf16>(desc, s, Xt, W, bias, Yt, use, sm);
+  return fc_fwd_impl<float>(desc, s, Xt, W, bias, Yt, use, sm);
 }
 
 int ard_fc_bwd_data(const ard_fc_desc* desc, const void* dYt, const void* Yt, const void* W,
@@ -867,10 +897,11 @@ int ard_fc_bwd_data(const ard_fc_desc* desc, const void* dYt, const void* Yt, co
     return st;
   if (Yt && !aligned16(Yt)) return fail(ARD_ERR_INVALID_ARG, "Yt is not 16-byte aligned");
   if (Xgate && !aligned16(Xgate)) return fail(ARD_ERR_INVALID_ARG, "Xgate is not 16-byte aligned");
-  if ((st = check_ws(s, desc->dtype, ws, ws_bytes))) return st;
+  Workspace use;
+  if ((st = check_ws(s, desc->dtype, ws, ws_bytes, &use))) return st;
   hipStream_t sm = static_cast<hipStream_t>(stream);
-  if (desc->dtype == ARD_BF16) return fc_bwd_data_impl<bf16>(desc, s, dYt, Yt, W, dXt, Xgate, ws, sm);
-  return fc_bwd_data_impl<float>(desc, s, dYt, Yt, W, dXt, Xgate, ws, sm);
+  if (desc->dtype == ARD_BF16) return fc_bwd_data_impl<bf16>(desc, s, dYt, Yt, W, dXt, Xgate, use, sm);
+  return fc_bwd_data_impl<float>(desc, s, dYt, Yt, W, dXt, Xgate, use, sm);
 }
 
 int ard_fc_bwd(const ard_fc_desc* desc, const void* Xt, const void* dYt, const void* Yt, const void* W,
@@ -885,10 +916,11 @@ int ard_fc_bwd(const ard_fc_desc* desc, const void* Xt, const void* dYt, const v
   if (Yt && !aligned16(Yt)) return fail(ARD_ERR_INVALID_ARG, "Yt is not 16-byte aligned");
   if (Xgate && !aligned16(Xgate)) return fail(ARD_ERR_INVALID_ARG, "Xgate is not 16-byte aligned");
   if (dbias && !aligned16(dbias)) return fail(ARD_ERR_INVALID_ARG, "dbias is not 16-byte aligned");
-  if ((st = check_ws(s, desc->dtype, ws, ws_bytes))) return st;
+  Workspace use;
+  if ((st = check_ws(s, desc->dtype, ws, ws_bytes, &use))) return st;
   hipStream_t sm = static_cast<hipStream_t>(stream);
-  if (desc->dtype == ARD_BF16) return fc_bwd_impl<bf16>(desc, s, Xt, dYt, Yt, W, dXt, Xgate, dW, dbias, ws, sm);
-  return fc_bwd_impl<float>(desc, s, Xt, dYt, Yt, W, dXt, Xgate, dW, dbias, ws, sm);
+  if (desc->dtype == ARD_BF16) return fc_bwd_impl<bf16>(desc, s, Xt, dYt, Yt, W, dXt, Xgate, dW, dbias, use, sm);
+  return fc_bwd_impl<float>(desc, s, Xt, dYt, Yt, W, dXt, Xgate, dW, dbias, use, sm);
 }
 
 int ard_fc_bwd_weight(const ard_fc_desc* desc, const void* Xt, const void* dYt, const void* Yt,
@@ -901,11 +933,12 @@ int ard_fc_bwd_weight(const ard_fc_desc* desc, const void* Xt, const void* dYt, 
     return st;
   if (Yt && !aligned16(Yt)) return fail(ARD_ERR_INVALID_ARG, "Yt is not 16-byte aligned");
   if (dbias && !aligned16(dbias)) return fail(ARD_ERR_INVALID_ARG, "dbias is not 16-byte aligned");
-  if ((st = check_ws(s, desc->dtype, ws, ws_bytes))) return st;
+  Workspace use;
+  if ((st = check_ws(s, desc->dtype, ws, ws_bytes, &use))) return st;
   hipStream_t sm = static_cast<hipStream_t>(stream);
   if (desc->dtype == ARD_BF16)
-    return fc_bwd_weight_impl<bf16>(desc, s, Xt, dYt, Yt, dW, dbias, ws, sm);
-  return fc_bwd_weight_impl<float>(desc, s, Xt, dYt, Yt, dW, dbias, ws, sm);
+    return fc_bwd_weight_impl<bf16>(desc, s, Xt, dYt, Yt, dW, dbias, use, sm);
+  return fc_bwd_weight_impl<float>(desc, s, Xt, dYt, Yt, dW, dbias, use, sm);
 }
 
 }  // extern "C"

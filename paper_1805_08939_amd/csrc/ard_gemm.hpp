@@ -46,7 +46,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 enum LoadMode { KC_VEC = 0, KC_ELEM = 1, MC_VEC = 2, MC_ELEM = 3 };
-enum Epilogue { EPI_STORE = 0, EPI_FWD = 1 };
+// EPI_COLS: EPI_FWD with blocked output columns (GemmOutput::nblk).
+enum Epilogue { EPI_STORE = 0, EPI_FWD = 1, EPI_COLS = 2 };
 
 struct GemmOperand {
   const void* p;         // view base
@@ -58,6 +59,11 @@ struct GemmOperand {
   int32_t relu;          // gated operand: multiply by [Y > 0]
   float scale;           // unused by the loaders (kept for layout stability)
   int64_t kbstride;      // elements between K batches (see GemmArgs::kbatch)
+  // n-contiguous B operand of an EPI_COLS problem: column n lies at
+  // (n / nblk) * nstride + n % nblk of a row (the samples of several steps side
+  // by side); nblk a whole number of 16-byte chunks
+  int32_t nblk;
+  int64_t nstride;
 };
 
 struct GemmOutput {
@@ -74,10 +80,24 @@ struct GemmOutput {
                          // position (the ReLU derivative of the layer below)
   int64_t col_stride;    // elements between consecutive output columns when cidx is NULL (0 = 1)
   int64_t bias_stride;   // elements between the bias entries of consecutive rows when ridx is NULL (0 = 1)
+  // EPI_COLS: column n lies at (n / nblk) * nstride + n % nblk of a row and is
+  // written where n % nblk < nvalid; nblk a multiple of 4
+  int32_t nblk, nvalid;
+  int64_t nstride;
 };
 
-// Output column offset of compact column n, and bias index of compact row m.
+// Output column offset of compact column n (EPI_COLS: and whether it is
+// written), and bias index of compact row m.
+template <int EPI>
+__device__ __forceinline__ bool col_in(const GemmOutput& c, int n) {
+  return EPI != EPI_COLS || n % c.nblk < c.nvalid;
+}
+template <int EPI = EPI_FWD>
 __device__ __forceinline__ int64_t out_col(const GemmOutput& c, int64_t n) {
+  if constexpr (EPI == EPI_COLS) {
+    const int32_t t = static_cast<int32_t>(n) / c.nblk;
+    return t * c.nstride + (static_cast<int32_t>(n) - t * c.nblk);
+  }
   return c.cidx ? static_cast<int64_t>(c.cidx[n]) : n * (c.col_stride > 1 ? c.col_stride : 1);
 }
 __device__ __forceinline__ int64_t bias_row(const GemmOutput& c, int64_t m) {
@@ -93,6 +113,9 @@ __device__ __forceinline__ int64_t bias_row(const GemmOutput& c, int64_t m) {
 // receives c.scale times the sum of row m of A over the whole contraction at
 // rsum[bz * rsum_bstride + m * rsum_ld]: a bias gradient taken from the A
 // operand of the weight-gradient product that reads it anyway.
+// LOAD_FLAT (direct-load kernel, both operands k-contiguous): the kbatch runs of
+// K, a whole number of 16-byte chunks, form one contraction of length kbatch * K
+// with no partial slab between them.
 struct GemmArgs {
   int32_t M, N, K;
   GemmOperand a, b;
@@ -328,7 +351,7 @@ __device__ __forceinline__ void mma_slab(const T* As, const T* Bs, f32x16 (&acc)
 // Applies the epilogue to one accumulator value of compact element (m, n).
 template <int EPI>
 __device__ __forceinline__ float epilogue(const GemmOutput& c, float v, float bias) {
-  if constexpr (EPI == EPI_FWD) {
+  if constexpr (EPI != EPI_STORE) {
     v += bias;
     if (c.relu) v = v > 0.0f ? v : 0.0f;
     v *= c.scale;
@@ -368,14 +391,14 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, f32x16 (&acc)[Cfg:
       const int m = m0 + wm * Cfg::TM + 32 * i + 8 * (r >> 2) + 4 * lh + (r & 3);
       if (m >= g.M) continue;
       const int64_t orow = gather(g.c.ridx, m);
-      const float bias = (EPI == EPI_FWD && g.c.bias) ? g.c.bias[bias_row(g.c, m)] : 0.0f;
+      const float bias = (EPI != EPI_STORE && g.c.bias) ? g.c.bias[bias_row(g.c, m)] : 0.0f;
 #pragma unroll
       for (int j = 0; j < Cfg::FN; ++j) {
         const int n = n0 + wn * Cfg::TN + 32 * j + lr;
-        if (n >= g.N) continue;
-        const int64_t o = orow * g.c.ld + out_col(g.c, n);
+        if (n >= g.N || !col_in<EPI>(g.c, n)) continue;
+        const int64_t o = orow * g.c.ld + out_col<EPI>(g.c, n);
         float v = epilogue<EPI>(g.c, acc[i][j][r], bias);
-        if (EPI == EPI_FWD && g.c.gate && !(to_f32(static_cast<const OutT*>(g.c.gate)[bz * g.c.bstride + o]) > 0.0f))
+        if (EPI != EPI_STORE && g.c.gate && !(to_f32(static_cast<const OutT*>(g.c.gate)[bz * g.c.bstride + o]) > 0.0f))
           v = 0.0f;
         out[o] = from_f32<OutT>(v);
       }

@@ -169,7 +169,8 @@ struct DmaSrc {
   uint32_t off0[PER_WAVE];  // the same chunk at k (KC) or k-row (MC) 0 of the slab
   int k[PER_WAVE];          // the chunk's k (KC) or k-row (MC) within the slab
 
-  __device__ __forceinline__ void init(int64_t ld, int r0, int rext, int wave) {
+  // nblk > 0: m/n-contiguous with blocked columns (GemmOperand::nblk)
+  __device__ __forceinline__ void init(int64_t ld, int r0, int rext, int wave, int nblk = 0, int64_t nstride = 0) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int i = 0; i < PER_WAVE; ++i) {
@@ -184,7 +185,11 @@ struct DmaSrc {
       } else {
         const int kk = pos / CPR;
         const int c = (pos % CPR) ^ mc_swz<CPR, ES>(kk);
-        const int col = r0 + c * EPC < rext ? r0 + c * EPC : 0;
+        int64_t col = r0 + c * EPC < rext ? r0 + c * EPC : 0;
+        if (nblk > 0) {
+          const int t = static_cast<int>(col) / nblk;
+          col = t * nstride + (static_cast<int>(col) - t * nblk);
+        }
         off0[i] = static_cast<uint32_t>(col * ES);
         off[i] = off0[i] + static_cast<uint32_t>(kk * ld * ES);
         k[i] = kk;
@@ -399,6 +404,70 @@ struct SlabLoader {
       ik += Cfg::BK;
       if (ik >= K) ik = 0, na += a_wrap, nb += b_wrap;
     }
+  }
+  __device__ __forceinline__ void issue() {
+    issue_a();
+    issue_b();
+  }
+};
+
+// The direct loads of a flat contraction (LOAD_FLAT): k = q * kb + r of a
+// row lies at q * kbs + r, so a chunk's place in its row follows from k by one
+// division (a multiply by 2^32 / kb, exact while k * kb < 2^32). Without it an
+// LSTM's weight gradient, a sum over steps of products only a batch deep, runs
+// every step's samples as a slab of its own, 20 of 32 or 64 k filled.
+template <class Cfg, int R>
+struct FlatSrc {
+  static constexpr int ES = Cfg::ES, EPC = 16 / ES, CPR = Cfg::BK * ES / 16;
+  static constexpr int PER_WAVE = R * Cfg::BK * ES / 1024 / Cfg::NW;
+  uint32_t off[PER_WAVE];  // byte offset of the lane's row
+  int k[PER_WAVE];         // the chunk's first k within the slab
+
+  __device__ __forceinline__ void init(int64_t ld, int r0, int rext, int wave) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) {
+      const int pos = (wave * PER_WAVE + i) * 64 + lane;
+      const int r = pos / CPR;
+      off[i] = static_cast<uint32_t>((r0 + r < rext ? r0 + r : rext - 1) * ld * ES);
+      k[i] = ((pos % CPR) ^ kc_swz<CPR>(r)) * EPC;
+    }
+  }
+  // The chunks of the slab at k0 (past the contraction length: k 0, zeroed in LDS before use).
+  __device__ __forceinline__ void issue(const char* base, int k0, int K, uint32_t kb, uint32_t magic, uint32_t kbs,
+                                        uint32_t region, int wave) const {
+    const char* b = uniform_ptr(base);
+    const uint32_t r0 = region + static_cast<uint32_t>(wave * PER_WAVE * 1024);
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) {
+      const uint32_t kg = k0 + k[i] < K ? static_cast<uint32_t>(k0 + k[i]) : 0u;
+      const uint32_t q = __umulhi(kg, magic);
+      const uint32_t o = off[i] + (q * kbs + (kg - q * kb)) * ES;
+      if (i == 0)
+        dma16<true>(b, o, r0);
+      else
+        dma16<false>(b, o, r0 + static_cast<uint32_t>(i * 1024));
+    }
+  }
+};
+
+template <class Cfg>
+struct FlatLoader {
+  FlatSrc<Cfg, Cfg::BM> da;
+  FlatSrc<Cfg, Cfg::BN> db;
+  const char* na;
+  const char* nb;
+  uint32_t kb, magic, a_kbs, b_kbs;
+  int K, ik, is, left, wv;
+  uint32_t lds0;
+
+  __device__ __forceinline__ void issue_a() {
+    da.issue(na, ik, K, kb, magic, a_kbs, lds0 + static_cast<uint32_t>(is * Cfg::STAGE), wv);
+  }
+  __device__ __forceinline__ void issue_b() {
+    db.issue(nb, ik, K, kb, magic, b_kbs, lds0 + static_cast<uint32_t>(is * Cfg::STAGE) + Cfg::ABYTES, wv);
+    is = is + 1 == Cfg::STAGES ? 0 : is + 1;
+    if (left > 0) --left, ik += Cfg::BK;
   }
   __device__ __forceinline__ void issue() {
     issue_a();
@@ -702,12 +771,12 @@ __device__ __forceinline__ void fast_store(const GemmArgs& g, f32x16 (&acc)[Cfg:
   const int64_t ld = part ? g.N : g.c.ld;
   char* base = part ? reinterpret_cast<char*>(g.partial + (bz * g.splits + split) * static_cast<int64_t>(g.M) * g.N)
                     : reinterpret_cast<char*>(static_cast<OutT*>(g.c.p) + bz * g.c.bstride);
-  const char* gate = (!part && EPI == EPI_FWD && g.c.gate)
+  const char* gate = (!part && EPI != EPI_STORE && g.c.gate)
                          ? reinterpret_cast<const char*>(static_cast<const OutT*>(g.c.gate) + bz * g.c.bstride)
                          : nullptr;
   const int64_t piece = 4 * es;
   const bool vec = (part || (g.c.cidx == nullptr && g.c.col_stride <= 1 && g.c.ridx == nullptr)) &&
-                   (ld * es) % piece == 0 && reinterpret_cast<uintptr_t>(base) % piece == 0 &&
+                   (EPI != EPI_COLS || (g.c.nstride % 4 == 0 && g.c.nvalid % 4 == 0)) && (ld * es) % piece == 0 && reinterpret_cast<uintptr_t>(base) % piece == 0 &&
                    reinterpret_cast<uintptr_t>(gate) % piece == 0;
   if (!vec) {
     store_tile<OutT, Cfg, EPI>(g, acc, m0, n0, wm, wn, bz, split);
@@ -729,7 +798,7 @@ __device__ __forceinline__ void fast_store(const GemmArgs& g, f32x16 (&acc)[Cfg:
   // flight together (a load per accumulator row, each waited for before its
   // row's values are staged, cost ~4 us per call of a small product), then
   // read from LDS: the wave reads only what it wrote itself.
-  const bool has_bias = !part && EPI == EPI_FWD && g.c.bias;
+  const bool has_bias = !part && EPI != EPI_STORE && g.c.bias;
   float* bias_lds = reinterpret_cast<float*>(smem + Cfg::NW * 32 * ROW) + wave * Cfg::TM;
   if (has_bias) {
     float bv[(Cfg::TM + 63) / 64];
@@ -776,7 +845,8 @@ __device__ __forceinline__ void fast_store(const GemmArgs& g, f32x16 (&acc)[Cfg:
       const f32x4 v = *reinterpret_cast<const f32x4*>(region + rl * ROW + ch * 16);
       const int m = m0w + 32 * i + rl, n = n0w + 4 * ch;
       if (m >= g.M) continue;
-      const int64_t o = static_cast<int64_t>(m) * ld + n;
+      if (EPI == EPI_COLS && !part && !col_in<EPI>(g.c, n)) continue;
+      const int64_t o = static_cast<int64_t>(m) * ld + (EPI == EPI_COLS && !part ? out_col<EPI>(g.c, n) : n);
       if (part) {
         float* out = reinterpret_cast<float*>(base) + o;
         if (n + 3 < g.N) {
@@ -821,8 +891,13 @@ __device__ __forceinline__ void fast_store(const GemmArgs& g, f32x16 (&acc)[Cfg:
 // row 32 i + l % 32, the waves of a k split are added in LDS in split order.
 // One workgroup's output tile: position bid of an nx x ny tile grid in the
 // grouped order, batch-and-split index bzs.
-// ANY: the operands' rows start at any element (register loads).
-template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false, bool ANY = false>
+// LD: how the operands are loaded.
+enum FastLoad {
+  LOAD_DMA = 0,   // direct loads
+  LOAD_ANY = 1,   // rows starting at any element (register loads)
+  LOAD_FLAT = 2   // direct loads of a flat contraction (LOAD_FLAT)
+};
+template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false, int LD = LOAD_DMA>
 __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, int tile_col, int bzs, char* smem) {
   using T = typename Cfg::T;
   const int n0 = tile_col * Cfg::BN;
@@ -846,9 +921,10 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  const int nks = (g.K + Cfg::BK - 1) / Cfg::BK;
   const int kbatch = g.kbatch > 0 ? g.kbatch : 1;
-  const int nslab = kbatch * nks;
+  const int klen = LD == LOAD_FLAT ? kbatch * g.K : g.K;  // length of one run of slabs
+  const int nks = (klen + Cfg::BK - 1) / Cfg::BK;
+  const int nslab = LD == LOAD_FLAT ? nks : kbatch * nks;
   // slabs of this split (32-bit divisions: nslab * splits < 2^31; none without a split)
   int q0 = 0, q1 = nslab;
   if (splits > 1) {
@@ -857,34 +933,60 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
   }
 
   // slabs q0 .. q1 - 1 of this split
-  using Loader = typename std::conditional<ANY, RegLoader<Cfg, AMC, BMC>, SlabLoader<Cfg, AMC, BMC>>::type;
-  Loader ld;
-  ld.wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   static_assert(DmaSrc<Cfg, Cfg::BM, AMC>::PER_WAVE + DmaSrc<Cfg, Cfg::BN, BMC>::PER_WAVE == Cfg::LPW, "load count");
-  if (q0 < q1) {
-    ld.da.init(g.a.ld, m0, g.M, ld.wv);
-    ld.db.init(g.b.ld, n0, g.N, ld.wv);
-  }
   constexpr int ES = Cfg::ES;
-  ld.K = g.K;
-  ld.a_step = (AMC ? g.a.ld : 1) * Cfg::BK * ES;
-  ld.b_step = (BMC ? g.b.ld : 1) * Cfg::BK * ES;
-  ld.a_wrap = g.a.kbstride * ES - nks * ld.a_step;
-  ld.b_wrap = g.b.kbstride * ES - nks * ld.b_step;
-  const int ib = q0 == 0 ? 0 : q0 / (nks > 0 ? nks : 1);
-  ld.ik = (q0 - ib * nks) * Cfg::BK;
-  ld.na = uniform_ptr(reinterpret_cast<const char*>(abase) + (ib * g.a.kbstride) * ES + ld.ik / Cfg::BK * ld.a_step);
-  ld.nb = uniform_ptr(reinterpret_cast<const char*>(bbase) + (ib * g.b.kbstride) * ES + ld.ik / Cfg::BK * ld.b_step);
   float rs[Cfg::FM];
 #pragma unroll
   for (int i = 0; i < Cfg::FM; ++i) rs[i] = 0.0f;
-  if constexpr (ANY) {
-    run_slabs_reg<Cfg, AMC, BMC, RSUM>(ld, q1 - q0, acc, wm, wn, ks * Cfg::KW, smem, rs);
-  } else {
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (LD == LOAD_FLAT) {
+    static_assert(!AMC && !BMC, "k-contiguous operands");
+    FlatLoader<Cfg> ld;
+    ld.wv = wv;
     ld.lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
+    if (q0 < q1) {
+      ld.da.init(g.a.ld, m0, g.M, wv);
+      ld.db.init(g.b.ld, n0, g.N, wv);
+    }
+    ld.kb = static_cast<uint32_t>(g.K);
+    ld.magic = static_cast<uint32_t>(((uint64_t{1} << 32) + ld.kb - 1) / ld.kb);
+    ld.a_kbs = static_cast<uint32_t>(g.a.kbstride);
+    ld.b_kbs = static_cast<uint32_t>(g.b.kbstride);
+    ld.na = uniform_ptr(reinterpret_cast<const char*>(abase));
+    ld.nb = uniform_ptr(reinterpret_cast<const char*>(bbase));
+    ld.K = klen;
+    ld.ik = q0 * Cfg::BK;
     ld.is = 0;
     ld.left = q1 - q0 - 1;
-    run_slabs<Cfg, AMC, BMC, true, RSUM>(ld, q1 - q0, g.K, ld.ik, acc, wm, wn, ks * Cfg::KW, smem, rs);
+    run_slabs<Cfg, AMC, BMC, true, RSUM>(ld, q1 - q0, klen, ld.ik, acc, wm, wn, ks * Cfg::KW, smem, rs);
+  } else {
+    using Loader = typename std::conditional<LD == LOAD_ANY, RegLoader<Cfg, AMC, BMC>, SlabLoader<Cfg, AMC, BMC>>::type;
+    Loader ld;
+    ld.wv = wv;
+    if (q0 < q1) {
+      ld.da.init(g.a.ld, m0, g.M, ld.wv);
+      if constexpr (EPI == EPI_COLS && LD == LOAD_DMA)
+        ld.db.init(g.b.ld, n0, g.N, ld.wv, g.b.nblk, g.b.nstride);
+      else
+        ld.db.init(g.b.ld, n0, g.N, ld.wv);
+    }
+    ld.K = g.K;
+    ld.a_step = (AMC ? g.a.ld : 1) * Cfg::BK * ES;
+    ld.b_step = (BMC ? g.b.ld : 1) * Cfg::BK * ES;
+    ld.a_wrap = g.a.kbstride * ES - nks * ld.a_step;
+    ld.b_wrap = g.b.kbstride * ES - nks * ld.b_step;
+    const int ib = q0 == 0 ? 0 : q0 / (nks > 0 ? nks : 1);
+    ld.ik = (q0 - ib * nks) * Cfg::BK;
+    ld.na = uniform_ptr(reinterpret_cast<const char*>(abase) + (ib * g.a.kbstride) * ES + ld.ik / Cfg::BK * ld.a_step);
+    ld.nb = uniform_ptr(reinterpret_cast<const char*>(bbase) + (ib * g.b.kbstride) * ES + ld.ik / Cfg::BK * ld.b_step);
+    if constexpr (LD == LOAD_ANY) {
+      run_slabs_reg<Cfg, AMC, BMC, RSUM>(ld, q1 - q0, acc, wm, wn, ks * Cfg::KW, smem, rs);
+    } else {
+      ld.lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
+      ld.is = 0;
+      ld.left = q1 - q0 - 1;
+      run_slabs<Cfg, AMC, BMC, true, RSUM>(ld, q1 - q0, g.K, ld.ik, acc, wm, wn, ks * Cfg::KW, smem, rs);
+    }
   }
   const int rlane = threadIdx.x & 63;
   if constexpr (RSUM) {
@@ -947,16 +1049,16 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
       for (int u = 0; u < Cfg::KSPLIT; ++u) v += red[((u * Cfg::WGM * Cfg::WGN + wmn) * NREG + t) * 64 + lane];
       const int m = m0 + wm * Cfg::TM + 32 * i + 8 * (r >> 2) + 4 * lh + (r & 3);
       const int n = n0 + wn * Cfg::TN + 32 * j + lr;
-      if (m >= g.M || n >= g.N) continue;
+      if (m >= g.M || n >= g.N || !col_in<EPI>(g.c, n)) continue;
       if (splits > 1) {
         g.partial[(bz * splits + split) * static_cast<int64_t>(g.M) * g.N + static_cast<int64_t>(m) * g.N + n] = v;
         continue;
       }
       const int64_t orow = gather(g.c.ridx, m);
-      const float bias = (EPI == EPI_FWD && g.c.bias) ? g.c.bias[bias_row(g.c, m)] : 0.0f;
-      const int64_t o = orow * g.c.ld + out_col(g.c, n);
+      const float bias = (EPI != EPI_STORE && g.c.bias) ? g.c.bias[bias_row(g.c, m)] : 0.0f;
+      const int64_t o = orow * g.c.ld + out_col<EPI>(g.c, n);
       v = epilogue<EPI>(g.c, v, bias);
-      if (EPI == EPI_FWD && g.c.gate && !(to_f32(static_cast<const OutT*>(g.c.gate)[bz * g.c.bstride + o]) > 0.0f))
+      if (EPI != EPI_STORE && g.c.gate && !(to_f32(static_cast<const OutT*>(g.c.gate)[bz * g.c.bstride + o]) > 0.0f))
         v = 0.0f;
       (static_cast<OutT*>(g.c.p) + bz * g.c.bstride)[o] = from_f32<OutT>(v);
     }
@@ -972,7 +1074,7 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
 // holding a few tiles of every slice. When an operand is shared by the batch
 // entries (batch stride 0), positions run within each slice: XCD x then holds
 // the same tiles of every entry and the shared panels stay in its L2.
-template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false, bool ANY = false>
+template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false, int LD = LOAD_DMA>
 __global__ void __launch_bounds__(Cfg::NT) fast_gemm_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nx = gridDim.x, ny = gridDim.y, nxy = nx * ny;
@@ -986,7 +1088,7 @@ __global__ void __launch_bounds__(Cfg::NT) fast_gemm_kernel(GemmArgs g) {
     grouped_order(t % nxy, nx, ny, tile_row, tile_col);
     z = t / nxy;
   }
-  fast_gemm_tile<Cfg, AMC, BMC, OutT, EPI, RSUM, ANY>(g, tile_row, tile_col, z, smem);
+  fast_gemm_tile<Cfg, AMC, BMC, OutT, EPI, RSUM, LD>(g, tile_row, tile_col, z, smem);
 }
 
 // Two independent GEMMs of one configuration in one launch (no batch, no k
@@ -994,7 +1096,7 @@ __global__ void __launch_bounds__(Cfg::NT) fast_gemm_kernel(GemmArgs g) {
 // One launch instead of two saves a kernel's fixed start and drain time, and
 // two problems too small to fill the chip alone run side by side.
 template <class Cfg, bool AMC1, bool BMC1, typename OutT1, int EPI1, bool RSUM1, bool AMC2, bool BMC2,
-          typename OutT2, int EPI2, bool RSUM2, bool ANY = false>
+          typename OutT2, int EPI2, bool RSUM2, int LD = LOAD_DMA>
 __global__ void __launch_bounds__(Cfg::NT) fast_gemm_pair_kernel(GemmArgs g1, GemmArgs g2) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nx1 = (g1.N + Cfg::BN - 1) / Cfg::BN, ny1 = (g1.M + Cfg::BM - 1) / Cfg::BM;
@@ -1002,11 +1104,11 @@ __global__ void __launch_bounds__(Cfg::NT) fast_gemm_pair_kernel(GemmArgs g1, Ge
   int row, col;
   if (b < nx1 * ny1) {
     grouped_tile(b, nx1, ny1, row, col);
-    fast_gemm_tile<Cfg, AMC1, BMC1, OutT1, EPI1, RSUM1, ANY>(g1, row, col, 0, smem);
+    fast_gemm_tile<Cfg, AMC1, BMC1, OutT1, EPI1, RSUM1, LD>(g1, row, col, 0, smem);
   } else {
     const int nx2 = (g2.N + Cfg::BN - 1) / Cfg::BN, ny2 = (g2.M + Cfg::BM - 1) / Cfg::BM;
     grouped_tile(b - nx1 * ny1, nx2, ny2, row, col);
-    fast_gemm_tile<Cfg, AMC2, BMC2, OutT2, EPI2, RSUM2, ANY>(g2, row, col, 0, smem);
+    fast_gemm_tile<Cfg, AMC2, BMC2, OutT2, EPI2, RSUM2, LD>(g2, row, col, 0, smem);
   }
 }
 
@@ -1059,15 +1161,21 @@ struct FastCfgs<bf16> {
 };
 template <>
 struct FastCfgs<float> {
-  using Huge = FastCfg<float, 128, 128, 32, 4, 2, 4, 1>;  // 128 KB, 8 waves
+  // The larger tiles leave room for two or three workgroups on a compute unit:
+  // one's MFMAs run while another waits for its first slabs or stores. Measured
+  // on MI355X, 2048 x 2240 x 1024: 128 x 128 tiles with 4 stages (one workgroup)
+  // 147 us, 2 stages 136; 64 x 64 x 64 with 3 stages 119, 2 stages 94; 64 x 64 x
+  // 32 with 3 stages 93. 8800 x 700 x 750: 107, 99, 104, 87, 84 us.
+  using Huge = FastCfg<float, 128, 128, 32, 2, 2, 4, 1>;  // 64 KB, 8 waves
   using Wide = Huge;
   using Tall = Huge;
-  using Big = FastCfg<float, 64, 64, 64, 3, 2, 2, 2>;     // 96 KB, 8 waves on 32-deep k shares
+  using Big = FastCfg<float, 64, 64, 64, 2, 2, 2, 2>;     // 64 KB, 8 waves on 32-deep k shares
+  using Mid = FastCfg<float, 64, 64, 32, 3, 2, 2, 1>;     // 48 KB, 4 waves
   using Narrow = FastCfg<float, 128, 32, 32, 4, 2, 1, 2>; // 80 KB, 4 waves on 16-deep k shares
   using Small = FastCfg<float, 32, 32, 128, 4, 1, 1, 8>;  // 128 KB, 8 waves on 16-deep k shares
 };
 
-enum FastKind { FAST_HUGE, FAST_WIDE, FAST_TALL, FAST_BIG, FAST_SMALL, FAST_NARROW };
+enum FastKind { FAST_HUGE, FAST_WIDE, FAST_TALL, FAST_BIG, FAST_SMALL, FAST_NARROW, FAST_MID };
 
 struct FastPlan {
   int kind;    // FastKind
@@ -1082,60 +1190,79 @@ inline int fast_splits(int64_t tiles, int64_t slabs) {
   return s;
 }
 
-// fp32: the largest tile that the output fills along both sides and whose
-// grid still covers 5/8 of the chip, then split-K.
-inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch) {
+// fp32 partial sums that a call must be given room for: those of the plan that
+// sized workspaces before the cost model below (the largest tile whose grid
+// covers 5/8 of the chip, splits on long contractions only). A call with more
+// room may split further, one with this much is never refused.
+inline int64_t required_splits_f32(int M, int N, int K) {
+  auto tiles_of = [&](int bm, int bn) { return static_cast<int64_t>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  constexpr int64_t kFill = kTargetBlocks * 5 / 8;
+  if (N <= 32 && tiles_of(128, 32) >= kFill) return K >= 8192 ? fast_splits(tiles_of(128, 32), (K + 31) / 32) : 1;
+  if (M > 64 && N > 64 && tiles_of(128, 128) >= kFill)
+    return K >= 8192 ? fast_splits(tiles_of(128, 128), (K + 31) / 32) : 1;
+  if (tiles_of(64, 64) >= kFill) return K >= 8192 ? fast_splits(tiles_of(64, 64), (K + 63) / 64) : 1;
+  const int64_t slabs = (K + 127) / 128;
+  double best_t = 0.9 * static_cast<double>(slabs);
+  int64_t best = 1;
+  for (int s = 2; s <= kMaxSplits && tiles_of(32, 32) * s <= kTargetBlocks && slabs >= s; s *= 2) {
+    const double t = 0.9 * static_cast<double>((slabs + s - 1) / s) + 3.0;
+    if (t < best_t) best_t = t, best = s;
+  }
+  return best;
+}
+
+// fp32: the (configuration, split) pair with the smallest modelled time, in us.
+// The workgroups of a compute unit share its matrix cores (614 GFLOP/s), so a
+// grid takes the MFMA time of the most tiles on one unit, times a factor for
+// what their waits leave idle (larger when a unit holds one workgroup only),
+// plus the fixed time of a launch, its first slabs and its stores; the 32 x 32
+// tiles take 0.9 us per 128-deep slab (measured on MI355X; the model is within
+// 7% of the eleven shapes that it was fitted on). A split adds the partial-sum
+// round trip and the reduction launch; its sums must fit cap floats.
+inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_t cap) {
   using C = FastCfgs<float>;
+  struct Cand {
+    int kind, bm, bn, bk;
+    double one, two, many, fixed;  // idle factor with one, two or more tiles on a compute unit; fixed us
+  };
+  static const Cand cands[] = {
+      {FAST_HUGE, C::Huge::BM, C::Huge::BN, C::Huge::BK, 1.14, 1.14, 1.14, 7.0},
+      {FAST_MID, C::Mid::BM, C::Mid::BN, C::Mid::BK, 1.5, 1.25, 1.17, 6.0},
+      {FAST_BIG, C::Big::BM, C::Big::BN, C::Big::BK, 1.33, 1.17, 1.2, 6.0},
+      {FAST_SMALL, C::Small::BM, C::Small::BN, C::Small::BK, 2.11, 2.11, 2.11, 5.0},
+  };
+  const int64_t kb = kbatch > 0 ? kbatch : 1;
   auto tiles_of = [&](int bm, int bn) {
     return static_cast<int64_t>((M + bm - 1) / bm) * ((N + bn - 1) / bn) * batch;
   };
-  FastPlan p;
-  int bk;
-  int64_t tiles;
-  const int64_t kb = kbatch > 0 ? kbatch : 1;
   // at most 32 columns (an LSTM's per-step products at a small batch): 128 x
   // 32 tiles, so that most of each tile is not zero padding of the columns
   if (N <= C::Narrow::BN && tiles_of(C::Narrow::BM, C::Narrow::BN) >= kTargetBlocks * 5 / 8) {
-    p.kind = FAST_NARROW;
-    tiles = tiles_of(C::Narrow::BM, C::Narrow::BN);
-    p.splits = kb * K >= 8192 ? fast_splits(tiles, kb * ((K + C::Narrow::BK - 1) / C::Narrow::BK)) : 1;
-    return p;
+    const int64_t tiles = tiles_of(C::Narrow::BM, C::Narrow::BN);
+    int64_t s = kb * K >= 8192 ? fast_splits(tiles, kb * ((K + C::Narrow::BK - 1) / C::Narrow::BK)) : 1;
+    while (s > 1 && s * M * N * batch > cap) s /= 2;
+    return {FAST_NARROW, static_cast<int>(s)};
   }
-  if (M > C::Big::BM && N > C::Big::BN && tiles_of(C::Huge::BM, C::Huge::BN) >= kTargetBlocks * 5 / 8) {
-    p.kind = FAST_HUGE;
-    bk = C::Huge::BK;
-    tiles = tiles_of(C::Huge::BM, C::Huge::BN);
-  } else if (tiles_of(C::Big::BM, C::Big::BN) >= kTargetBlocks * 5 / 8) {
-    p.kind = FAST_BIG;
-    bk = C::Big::BK;
-    tiles = tiles_of(C::Big::BM, C::Big::BN);
-  } else {
-    p.kind = FAST_SMALL;
-    bk = C::Small::BK;
-    tiles = tiles_of(C::Small::BM, C::Small::BN);
-  }
-  const int64_t slabs = kb * ((K + bk - 1) / bk);
-  if (p.kind == FAST_SMALL) {
-    // A 32x32 workgroup takes about 0.9 us per 128-deep slab however many run
-    // beside it (measured on MI355X), so a long contraction over few tiles is
-    // a serial chain: split it over more workgroups (up to one round of the
-    // chip) when that saves more than the partial-sum round trip and the
-    // reduction launch cost (about 3 us).
-    double best_t = 0.9 * static_cast<double>(slabs);
-    p.splits = 1;
-    for (int s = 2; s <= kMaxSplits && tiles * s <= kTargetBlocks && slabs >= s; s *= 2) {
-      const double t = 0.9 * static_cast<double>((slabs + s - 1) / s) + 3.0;
+  FastPlan best = {FAST_SMALL, 1};
+  double best_t = 1e300;
+  for (const Cand& c : cands) {
+    const int64_t tiles = tiles_of(c.bm, c.bn);
+    const int64_t slabs = kb * ((K + c.bk - 1) / c.bk);
+    for (int s = 1; s <= kMaxSplits; s *= 2) {
+      if (s > 1 && (slabs < s || tiles * s > 4 * kTargetBlocks ||
+                    static_cast<int64_t>(s) * M * N * batch > cap))
+        break;
+      const int64_t n = (tiles * s + kTargetBlocks - 1) / kTargetBlocks;
+      const double work = 2.0 * c.bm * c.bn * c.bk * ((slabs + s - 1) / s) / 614e3;
+      double t = n * work * (n > 2 ? c.many : n > 1 ? c.two : c.one) + c.fixed;
+      if (s > 1) t += 4.0 * M * N * batch * (s + 1) / 5e6 + 3.0;
       if (t < best_t) {
         best_t = t;
-        p.splits = s;
+        best = {c.kind, s};
       }
     }
-    return p;
   }
-  // larger tiles: split-K pays for its partial-sum round trip and reduction
-  // launch only on long contractions (measured on MI355X: never below K = 2048)
-  p.splits = kb * K >= 8192 ? fast_splits(tiles, slabs) : 1;
-  return p;
+  return best;
 }
 
 // bf16: the (configuration, split) pair with the smallest modelled time. A
@@ -1181,24 +1308,34 @@ inline FastPlan plan_fast_bf16(int M, int N, int K, int kbatch, int batch) {
   return best;
 }
 
+// cap: floats of partial sums that the caller has room for (fp32; the bf16 plan
+// is the one that sizes them).
 template <typename T>
-inline FastPlan plan_fast(int M, int N, int K, int kbatch, int batch) {
+inline FastPlan plan_fast(int M, int N, int K, int kbatch, int batch, int64_t cap) {
   if constexpr (sizeof(T) == 2)
     return plan_fast_bf16(M, N, K, kbatch, batch);
   else
-    return plan_fast_f32(M, N, K, kbatch, batch);
+    return plan_fast_f32(M, N, K, kbatch, batch, cap);
 }
 
+constexpr int64_t kAnyRoom = int64_t{1} << 60;
+
+// Floats of split-K partials of a product: what a call must be given room for
+// (required), and what it makes use of.
 template <typename T>
-inline size_t fast_partial_floats(int M, int N, int K, int kbatch, int batch) {
-  const FastPlan p = plan_fast<T>(M, N, K, kbatch, batch);
-  return p.splits > 1 ? static_cast<size_t>(p.splits) * batch * M * N : 0;
+inline size_t fast_partial_floats(int M, int N, int K, bool required) {
+  int64_t s;
+  if constexpr (sizeof(T) == 4)
+    s = required ? required_splits_f32(M, N, K) : plan_fast_f32(M, N, K, 1, 1, kAnyRoom).splits;
+  else
+    s = plan_fast_bf16(M, N, K, 1, 1).splits;
+  return s > 1 ? static_cast<size_t>(s) * M * N : 0;
 }
 
-template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false, bool ANY = false>
+template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false, int LD = LOAD_DMA>
 inline hipError_t launch_fast(const GemmArgs& g, int batch, hipStream_t stream) {
   const int splits = g.splits > 1 ? g.splits : 1;
-  auto kern = fast_gemm_kernel<Cfg, AMC, BMC, OutT, EPI, RSUM, ANY>;
+  auto kern = fast_gemm_kernel<Cfg, AMC, BMC, OutT, EPI, RSUM, LD>;
   // per instantiation, once (thread-safe static initialisation): allow more than 64 KB of dynamic LDS
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS);
@@ -1218,13 +1355,13 @@ inline hipError_t launch_fast(const GemmArgs& g, int batch, hipStream_t stream) 
   return hipGetLastError();
 }
 
-// Launches g1 and g2 (both fast_ok, or both any_ok with ANY; splits 1, no
+// Launches g1 and g2 (both fast_ok, or both any_ok with LOAD_ANY; splits 1, no
 // batch) as one grid of fast_gemm_pair_kernel on the 32x32 configuration of T.
 template <typename T, bool AMC1, bool BMC1, typename OutT1, int EPI1, bool RSUM1, bool AMC2, bool BMC2,
-          typename OutT2, int EPI2, bool RSUM2, bool ANY = false>
+          typename OutT2, int EPI2, bool RSUM2, int LD = LOAD_DMA>
 inline hipError_t launch_fast_pair(GemmArgs g1, GemmArgs g2, hipStream_t stream) {
   using Cfg = typename FastCfgs<T>::Small;
-  auto kern = fast_gemm_pair_kernel<Cfg, AMC1, BMC1, OutT1, EPI1, RSUM1, AMC2, BMC2, OutT2, EPI2, RSUM2, ANY>;
+  auto kern = fast_gemm_pair_kernel<Cfg, AMC1, BMC1, OutT1, EPI1, RSUM1, AMC2, BMC2, OutT2, EPI2, RSUM2, LD>;
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS);
   if (attr != hipSuccess) return attr;
@@ -1241,31 +1378,34 @@ inline hipError_t launch_fast_pair(GemmArgs g1, GemmArgs g2, hipStream_t stream)
 // Whether two problems run as one fast_gemm_pair_kernel launch: both take the
 // 32x32 configuration without a k split on their own, and each has a tile.
 template <typename T>
-inline bool fast_pair_ok(const GemmArgs& g1, const GemmArgs& g2) {
+inline bool fast_pair_ok(const GemmArgs& g1, const GemmArgs& g2, int64_t cap) {
   if (g1.M <= 0 || g1.N <= 0 || g2.M <= 0 || g2.N <= 0) return false;
-  const FastPlan p1 = plan_fast<T>(g1.M, g1.N, g1.K, 1, 1), p2 = plan_fast<T>(g2.M, g2.N, g2.K, 1, 1);
+  const FastPlan p1 = plan_fast<T>(g1.M, g1.N, g1.K, 1, 1, cap), p2 = plan_fast<T>(g2.M, g2.N, g2.K, 1, 1, cap);
   return p1.kind == FAST_SMALL && p2.kind == FAST_SMALL && p1.splits == 1 && p2.splits == 1;
 }
 
-template <typename T, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM>
+template <typename T, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM, int LD = LOAD_DMA>
 inline hipError_t launch_planned(const GemmArgs& g, int kind, int batch, hipStream_t stream) {
   using C = FastCfgs<T>;
   switch (kind) {
     case FAST_HUGE:
       // the bf16 256x256 tile has no registers left for row sums (it spills)
       if constexpr (RSUM && sizeof(T) == 2) return hipErrorNotSupported;
-      else return launch_fast<typename C::Huge, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream);
+      else return launch_fast<typename C::Huge, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
     case FAST_WIDE:
-      return launch_fast<typename C::Wide, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream);
+      return launch_fast<typename C::Wide, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
     case FAST_TALL:
-      return launch_fast<typename C::Tall, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream);
+      return launch_fast<typename C::Tall, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
     case FAST_BIG:
-      return launch_fast<typename C::Big, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream);
+      return launch_fast<typename C::Big, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
+    case FAST_MID:  // fp32 only
+      if constexpr (sizeof(T) == 4) return launch_fast<typename C::Mid, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
+      else return hipErrorNotSupported;
     case FAST_NARROW:  // fp32 only
-      if constexpr (sizeof(T) == 4) return launch_fast<typename C::Narrow, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream);
+      if constexpr (sizeof(T) == 4) return launch_fast<typename C::Narrow, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
       else return hipErrorNotSupported;
     default:
-      return launch_fast<typename C::Small, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream);
+      return launch_fast<typename C::Small, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
   }
 }
 
@@ -1274,11 +1414,11 @@ inline hipError_t launch_planned(const GemmArgs& g, int kind, int batch, hipStre
 // not the bf16 256x256 tile, and *rsum_done says whether it did (else the
 // caller computes them itself).
 template <typename T, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false>
-inline hipError_t run_fast_gemm(GemmArgs g, int batch, hipStream_t stream, float* partial,
+inline hipError_t run_fast_gemm(GemmArgs g, int batch, hipStream_t stream, float* partial, int64_t cap,
                                 bool* rsum_done = nullptr) {
   if (rsum_done) *rsum_done = false;
   if (g.M <= 0 || g.N <= 0 || batch <= 0) return hipSuccess;
-  FastPlan p = plan_fast<T>(g.M, g.N, g.K, g.kbatch, batch);
+  FastPlan p = plan_fast<T>(g.M, g.N, g.K, g.kbatch, batch, partial ? cap : 0);
   // the kernel splits the slabs with 32-bit arithmetic
   const int64_t kb = g.kbatch > 0 ? g.kbatch : 1;
   if (!partial || kb * (g.K / 32 + 1) * p.splits >= int64_t{1} << 31) p.splits = 1;
@@ -1297,18 +1437,18 @@ inline hipError_t run_fast_gemm(GemmArgs g, int batch, hipStream_t stream, float
 // in flight. The split count never exceeds what the workspace of the problem
 // was sized for (the direct-load or the general kernel's plan).
 template <typename T>
-inline FastPlan plan_any(int M, int N, int K, int kbatch, int batch) {
-  FastPlan p = plan_fast<T>(M, N, K, kbatch, batch);
+inline FastPlan plan_any(int M, int N, int K, int kbatch, int batch, int64_t cap) {
+  FastPlan p = plan_fast<T>(M, N, K, kbatch, batch, cap);
   if constexpr (sizeof(T) == 2) {
     using C = FastCfgs<bf16>;
     const int gs = plan_gemm<T>(M, N, K, kbatch, batch).splits;
-    const int cap = p.splits > gs ? p.splits : gs;
+    const int most = p.splits > gs ? p.splits : gs;
     const int64_t kb = kbatch > 0 ? kbatch : 1;
     auto tiles_of = [&](int b) { return static_cast<int64_t>((M + b - 1) / b) * ((N + b - 1) / b) * batch; };
     p.kind = tiles_of(C::Big::BM) >= kTargetBlocks / 2 ? FAST_BIG : FAST_SMALL;
     const int b = p.kind == FAST_BIG ? C::Big::BM : C::Small::BM, bk = p.kind == FAST_BIG ? C::Big::BK : C::Small::BK;
     p.splits = fast_splits(tiles_of(b), kb * ((K + bk - 1) / bk));
-    if (p.splits > cap) p.splits = cap;
+    if (p.splits > most) p.splits = most;
   }
   return p;
 }
@@ -1316,13 +1456,13 @@ inline FastPlan plan_any(int M, int N, int K, int kbatch, int batch) {
 // Runs a GEMM whose operands are plain strided views (any_ok): on the direct
 // loads where the rows start on 16 bytes (fast_ok), else on register loads.
 template <typename T, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false>
-inline hipError_t run_strided_gemm(GemmArgs g, int batch, hipStream_t stream, float* partial,
+inline hipError_t run_strided_gemm(GemmArgs g, int batch, hipStream_t stream, float* partial, int64_t cap,
                                    bool* rsum_done = nullptr) {
   if (fast_ok<AMC, BMC>(g, sizeof(T)))
-    return run_fast_gemm<T, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream, partial, rsum_done);
+    return run_fast_gemm<T, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream, partial, cap, rsum_done);
   if (rsum_done) *rsum_done = false;
   if (g.M <= 0 || g.N <= 0 || batch <= 0) return hipSuccess;
-  FastPlan p = plan_any<T>(g.M, g.N, g.K, g.kbatch, batch);
+  FastPlan p = plan_any<T>(g.M, g.N, g.K, g.kbatch, batch, partial ? cap : 0);
   const int64_t kb = g.kbatch > 0 ? g.kbatch : 1;
   if (!partial || kb * (g.K / 32 + 1) * p.splits >= int64_t{1} << 31) p.splits = 1;
   g.splits = p.splits;
@@ -1334,24 +1474,62 @@ inline hipError_t run_strided_gemm(GemmArgs g, int batch, hipStream_t stream, fl
   auto go = [&](auto cfg) {
     using Cfg = decltype(cfg);
     if constexpr (RSUM) {
-      if (rs) return launch_fast<Cfg, AMC, BMC, OutT, EPI, true, true>(g, batch, stream);
+      if (rs) return launch_fast<Cfg, AMC, BMC, OutT, EPI, true, LOAD_ANY>(g, batch, stream);
     }
-    return launch_fast<Cfg, AMC, BMC, OutT, EPI, false, true>(g, batch, stream);
+    return launch_fast<Cfg, AMC, BMC, OutT, EPI, false, LOAD_ANY>(g, batch, stream);
   };
   if (p.kind == FAST_SMALL) return go(typename C::Small{});
   if constexpr (sizeof(T) == 4) {
     if (p.kind == FAST_HUGE) return go(typename C::Huge{});
     if (p.kind == FAST_NARROW) return go(typename C::Narrow{});
+    if (p.kind == FAST_MID) return go(typename C::Mid{});
   }
   return go(typename C::Big{});
 }
 
 // Whether the pair runs as one launch of the register-load 32x32 tiles.
 template <typename T>
-inline bool any_pair_ok(const GemmArgs& g1, const GemmArgs& g2) {
+inline bool any_pair_ok(const GemmArgs& g1, const GemmArgs& g2, int64_t cap) {
   if (g1.M <= 0 || g1.N <= 0 || g2.M <= 0 || g2.N <= 0) return false;
-  const FastPlan p1 = plan_any<T>(g1.M, g1.N, g1.K, 1, 1), p2 = plan_any<T>(g2.M, g2.N, g2.K, 1, 1);
+  const FastPlan p1 = plan_any<T>(g1.M, g1.N, g1.K, 1, 1, cap), p2 = plan_any<T>(g2.M, g2.N, g2.K, 1, 1, cap);
   return p1.kind == FAST_SMALL && p2.kind == FAST_SMALL && p1.splits == 1 && p2.splits == 1;
+}
+
+// A fp32 product over the columns of several steps at once (EPI_COLS): B's and
+// C's columns in blocks. cols_ok: fast_ok, blocks of whole chunks, and a slab's
+// span below 2^31 bytes with the blocks' strides.
+template <bool AMC>
+inline bool cols_ok(const GemmArgs& g) {
+  if (!fast_ok<AMC, true>(g, 4) || g.b.nblk <= 0 || g.b.nblk % 4 || g.b.nstride % 4 || g.c.nblk % 4) return false;
+  return ((static_cast<int64_t>(g.N) / g.b.nblk + 1) * g.b.nstride + 256 * g.b.ld) * 4 < (int64_t{1} << 31);
+}
+template <bool AMC>
+inline hipError_t run_cols_gemm(GemmArgs g, hipStream_t stream) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  const FastPlan p = plan_fast_f32(g.M, g.N, g.K, 1, 1, 0);
+  g.splits = 1;
+  g.partial = nullptr;
+  g.rsum = nullptr;
+  return launch_planned<float, AMC, true, float, EPI_COLS, false>(g, p.kind, 1, stream);
+}
+
+// A fp32 product with both operands k-contiguous over a flat contraction
+// (LOAD_FLAT); see FlatLoader. rsum is always taken when set.
+inline bool flat_ok(const GemmArgs& g) {
+  const int64_t kb = g.kbatch > 0 ? g.kbatch : 1, k = kb * g.K;
+  auto span = [&](const GemmOperand& o, int ext) {
+    return (static_cast<int64_t>(ext - 1) * o.ld + (kb - 1) * o.kbstride + g.K) * 4 < (int64_t{1} << 31);
+  };
+  return fast_ok<false, false>(g, 4) && g.K % 4 == 0 && k * g.K < (int64_t{1} << 32) && k < (int64_t{1} << 30) &&
+         g.M > 0 && g.N > 0 && span(g.a, g.M) && span(g.b, g.N);
+}
+template <bool RSUM>
+inline hipError_t run_flat_gemm(GemmArgs g, int batch, hipStream_t stream) {
+  const FastPlan p = plan_fast_f32(g.M, g.N, (g.kbatch > 0 ? g.kbatch : 1) * g.K, 1, batch, 0);
+  g.splits = 1;
+  g.partial = nullptr;
+  if (!RSUM) g.rsum = nullptr;
+  return launch_planned<float, false, false, float, EPI_FWD, RSUM, LOAD_FLAT>(g, p.kind, batch, stream);
 }
 
 }  // namespace ard

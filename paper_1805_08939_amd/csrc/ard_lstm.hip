@@ -12,7 +12,14 @@
 // accumulator layout each lane holds the four gates of one unit in four
 // consecutive registers, and the cell update runs in registers.
 //
-// fwd: one batched GEMM for the input projection of all steps (bias folded
+// Every buffer of the workspace has the batch padded to Bp columns, a multiple
+// of 4, so that all products run on 16-byte loads whatever the batch (an X of
+// another batch is copied once, kept rows only). The padding columns of h and
+// dA are zeros. The products over all steps (input projection, dX, weight
+// gradients) take the T Bp columns of all steps as one dimension: one GEMM with
+// full tiles instead of T products a batch wide, or T slabs a batch deep.
+//
+// fwd: one GEMM for the input projection of all steps (bias folded
 // in), then per step a kernel computing Wc_h h_{t-1} for a 32-row x 32-column
 // tile (four waves split the contraction and reduce through LDS; 16 x 16
 // tiles for small kept sets) fused with the gate nonlinearities and the state
@@ -22,8 +29,8 @@
 // small product still fills the chip), then the pointwise backward of step t,
 // which adds the partial sums in a fixed order; for small kept sets instead
 // one kernel per step that runs the whole contraction on 16 x 16 output tiles
-// and the pointwise backward on its outputs. Then K-batched GEMMs over all
-// steps for the weight gradients and one batched GEMM for dX.
+// and the pointwise backward on its outputs. Then the GEMMs over all steps for
+// the weight gradients and dX.
 
 #include <hip/hip_runtime.h>
 
@@ -43,9 +50,10 @@ using RecWideCfg = FastCfg<float, 32, 64, 128, 3, 1, 2, 4>;
 
 struct Layout {
   int64_t T, B, I, H, ns, G4, KW, S;
+  int64_t Bp;          // columns of the buffers: the batch padded to a multiple of 4
   int64_t Ic, ip, io;  // kept inputs (compact input width) and their pattern
   int64_t R;           // first recurrent column of a compact row: Ic rounded up to 16 bytes
-  size_t wc, bc, rowmap, z, cc, hc, da, dc, part, total;
+  size_t wc, bc, rowmap, z, cc, hc, da, dc, part, xp, total;
 };
 
 // Splits of the backward recurrent contraction (length 4 ns): enough
@@ -78,41 +86,55 @@ Layout make_layout(const ard_lstm_desc* d, int32_t ns) {
   // keeps, so the step kernels' direct loads can read it
   L.R = (L.Ic + 3) / 4 * 4;
   L.KW = (L.R + ns + 3) / 4 * 4;
-  L.S = bwd_splits(ns, L.B);
+  L.Bp = (L.B + 3) / 4 * 4;
+  L.S = bwd_splits(ns, L.Bp);
   size_t off = 0;
   L.wc = off;     off += al256(4 * L.G4 * L.KW);
   L.bc = off;     off += al256(4 * L.G4 + 4);
   L.rowmap = off; off += al256(4 * L.G4 + 4);
-  L.z = off;      off += al256(4 * L.T * L.G4 * L.B);
-  L.cc = off;     off += al256(4 * (L.T + 1) * ns * L.B);
-  L.hc = off;     off += al256(4 * (L.T + 1) * ns * L.B);
-  L.da = off;     off += al256(4 * L.T * L.G4 * L.B);
-  L.dc = off;     off += al256(4 * static_cast<int64_t>(ns) * L.B + 4);
-  L.part = off;   off += al256(4 * L.S * ns * L.B + 4);
+  L.z = off;      off += al256(4 * L.T * L.G4 * L.Bp);
+  L.cc = off;     off += al256(4 * (L.T + 1) * ns * L.Bp);
+  L.hc = off;     off += al256(4 * (L.T + 1) * ns * L.Bp);
+  L.da = off;     off += al256(4 * L.T * L.G4 * L.Bp);
+  L.dc = off;     off += al256(4 * static_cast<int64_t>(ns) * L.Bp + 4);
+  L.part = off;   off += al256(4 * L.S * ns * L.Bp + 4);
+  L.xp = off;     off += L.Bp != L.B ? al256(4 * L.T * L.Ic * L.Bp) : 0;  // the kept input rows, padded
   L.total = off;
   return L;
 }
 
 }  // namespace
 
-__device__ __forceinline__ int64_t unit_row(const int32_t* idx, int64_t u) { return idx ? idx[u] : u; }
+// The kept units of a row pattern, by arithmetic rather than from the plan's
+// list: a load of the list would put one memory latency in front of every
+// access that depends on it.
+struct Units {
+  int32_t period, offset;
+  __device__ __forceinline__ int64_t row(int64_t u) const { return offset + period * u; }
+};
 __device__ __forceinline__ float sigm(float x) { return 1.0f / (1.0f + expf(-x)); }
+// Row j and column b of element e of rows of cols : 32-bit
+// division where e allows it (a 64-bit one is some hundred instructions).
+__device__ __forceinline__ void row_col(int64_t e, int32_t cols, int64_t& j, int32_t& b) {
+  j = (e >> 32) == 0 ? static_cast<int64_t>(static_cast<uint32_t>(e) / static_cast<uint32_t>(cols)) : e / cols;
+  b = static_cast<int32_t>(e - j * cols);
+}
 
 // Compact weights (rows of KW entries: the Ic kept inputs, zeros up to R,
 // the |S| kept recurrent columns from R on, zeros after), bias and row map;
 // one block per compact row 4u + g.
 __global__ void lstm_prepare_kernel(const float* __restrict__ W, const float* __restrict__ bias,
-                                    const int32_t* __restrict__ idx, int32_t I, int32_t Ic, int32_t R, int32_t ip,
+                                    Units S, int32_t I, int32_t Ic, int32_t R, int32_t ip,
                                     int32_t io, int32_t H, int32_t ns, int32_t KW, float* __restrict__ Wc,
                                     float* __restrict__ bc, int32_t* __restrict__ rowmap) {
   const int r = blockIdx.x;
   const int u = r >> 2, g = r & 3;
-  const int64_t src = static_cast<int64_t>(g) * H + unit_row(idx, u);
+  const int64_t src = static_cast<int64_t>(g) * H + S.row(u);
   const float* wrow = W + src * (I + H);
   float* crow = Wc + static_cast<int64_t>(r) * KW;
   for (int c = threadIdx.x; c < KW; c += blockDim.x)
     crow[c] = c < Ic                  ? wrow[io + static_cast<int64_t>(ip) * c]
-              : c >= R && c < R + ns ? wrow[I + unit_row(idx, c - R)]
+              : c >= R && c < R + ns ? wrow[I + S.row(c - R)]
                                      : 0.0f;
   if (threadIdx.x == 0) {
     bc[r] = bias ? bias[src] : 0.0f;
@@ -120,30 +142,70 @@ __global__ void lstm_prepare_kernel(const float* __restrict__ W, const float* __
   }
 }
 
-// Compact initial state: dst[u][b] = src ? src[S(u)][b] : 0.
-__global__ void lstm_gather_state_kernel(const float* __restrict__ src, const int32_t* __restrict__ idx,
-                                         int32_t ns, int32_t B, float* __restrict__ dst) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= static_cast<int64_t>(ns) * B) return;
-  const int64_t u = e / B, b = e % B;
-  dst[e] = src ? src[unit_row(idx, u) * B + b] : 0.0f;
+// Compact initial state of h (blockIdx.y 0) and c (1): dst[u][b] = src ?
+// src[S(u)][b] : 0, zeros in the padding columns.
+__global__ void __launch_bounds__(256) lstm_gather_state_kernel(const float* __restrict__ h0,
+                                                                const float* __restrict__ c0,
+                                                                Units S, int64_t n, int32_t B, int32_t Bp, float* __restrict__ hc,
+                                                                float* __restrict__ cc) {
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (e >= n) return;
+  const float* src = blockIdx.y == 0 ? h0 : c0;
+  int64_t u;
+  int32_t b;
+  row_col(e, Bp, u, b);
+  (blockIdx.y == 0 ? hc : cc)[e] = src && b < B ? src[S.row(u) * B + b] : 0.0f;
 }
 
-// Full state from compact: dst[j][b] = kept(j) ? src[u(j)][b] : 0 over H rows.
-__global__ void lstm_scatter_state_kernel(const float* __restrict__ src, int32_t H, int32_t B,
-                                          int32_t period, int32_t offset, float* __restrict__ dst) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= static_cast<int64_t>(H) * B) return;
-  const int64_t j = e / B, b = e % B;
-  dst[e] = (j % period == offset) ? src[((j - offset) / period) * B + b] : 0.0f;
+// Full states from compact ones (blockIdx.y picks the pair; dst NULL = none):
+// dst[j][b] = kept(j) ? src[u(j)][b] : 0 over H rows.
+struct StatePair {
+  const float* src[2];
+  float* dst[2];
+};
+__global__ void __launch_bounds__(256) lstm_scatter_state_kernel(StatePair p, int64_t n, int32_t B, int32_t Bp,
+                                                                 int32_t period, int32_t offset) {
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  float* dst = p.dst[blockIdx.y];
+  if (e >= n || !dst) return;
+  int64_t j;
+  int32_t b;
+  row_col(e, B, j, b);
+  const int64_t u = (j - offset) / period;
+  dst[e] = j >= offset && u * period + offset == j ? p.src[blockIdx.y][u * Bp + b] : 0.0f;
 }
 
-// Zeroes rows r of out[rows][cols] whose unit (r % H) is dropped.
-__global__ void lstm_zero_dropped_rows_kernel(float* __restrict__ out, int64_t rows, int32_t cols,
-                                              int32_t H, int32_t period, int32_t offset) {
-  const int64_t r = blockIdx.x;
-  if (r >= rows || ((r % H) % period) == offset) return;
-  for (int c = threadIdx.x; c < cols; c += blockDim.x) out[r * cols + c] = 0.0f;
+// The kept input rows of X with the batch padded: dst[t][k][b] = X[t][io + ip
+// k][b], zeros in the padding columns. blockIdx.y: steps t0 ..
+__global__ void __launch_bounds__(256) lstm_pad_input_kernel(const float* __restrict__ X, int64_t n, int32_t I,
+                                                             int32_t ip, int32_t io, int32_t B, int32_t Bp, int32_t t0,
+                                                             float* __restrict__ dst) {
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (e >= n) return;
+  const int64_t t = t0 + static_cast<int64_t>(blockIdx.y);
+  int64_t k;
+  int32_t b;
+  row_col(e, Bp, k, b);
+  dst[t * n + e] = b < B ? X[(t * I + io + ip * k) * B + b] : 0.0f;
+}
+
+// Zeroes rows r of out[rows][cols] whose unit (r % H) is dropped: a thread per
+// V consecutive columns (cols a multiple of V).
+template <int V>
+__global__ void __launch_bounds__(256) lstm_zero_dropped_rows_kernel(float* __restrict__ out, int64_t n, int32_t cols,
+                                                                     int32_t H, int32_t period, int32_t offset) {
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (e >= n) return;
+  int64_t r;
+  int32_t c;
+  row_col(e, cols / V, r, c);
+  const int32_t j = (r >> 31) == 0 ? static_cast<int32_t>(static_cast<uint32_t>(r) % static_cast<uint32_t>(H))
+                                   : static_cast<int32_t>(r % H);
+  if (j % period == offset) return;
+  if constexpr (V == 4)
+    *reinterpret_cast<f32x4*>(out + 4 * e) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  else
+    out[e] = 0.0f;
 }
 
 // dW[4H][I+H]: zero the rows of dropped units, the recurrent columns of
@@ -166,22 +228,24 @@ __global__ void fill_kernel(float* __restrict__ p, int64_t n, float v) {
 
 // rowmap[4u + g] = g H + idx[u]: the W row of compact gate row r, from the
 // plan (the backward rebuilds it rather than trust the forward's workspace).
-__global__ void lstm_rowmap_kernel(const int32_t* __restrict__ idx, int32_t H, int32_t rows,
+__global__ void lstm_rowmap_kernel(Units S, int32_t H, int32_t rows,
                                    int32_t* __restrict__ rowmap) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < rows) rowmap[r] = static_cast<int32_t>(static_cast<int64_t>(r & 3) * H + unit_row(idx, r >> 2));
+  if (r < rows) rowmap[r] = static_cast<int32_t>(static_cast<int64_t>(r & 3) * H + S.row(r >> 2));
 }
 
 // dbias[rowmap[r]] = sum over t, b of dA[t][r][b]; one block per row r.
 __global__ void __launch_bounds__(256) lstm_dbias_kernel(const float* __restrict__ dA,
                                                          const int32_t* __restrict__ rowmap, int32_t T,
-                                                         int32_t G4, int32_t B, float* __restrict__ dbias) {
+                                                         int32_t G4, int32_t Bp, float* __restrict__ dbias) {
   __shared__ float part[256];
   const int r = blockIdx.x;
   float s = 0.0f;
-  for (int64_t e = threadIdx.x; e < static_cast<int64_t>(T) * B; e += 256) {
-    const int64_t t = e / B, b = e % B;
-    s += dA[(t * G4 + r) * B + b];
+  for (int64_t e = threadIdx.x; e < static_cast<int64_t>(T) * Bp; e += 256) {
+    int64_t t;
+    int32_t b;
+    row_col(e, Bp, t, b);
+    s += dA[(t * G4 + r) * Bp + b];  // the padding columns are zeros
   }
   part[threadIdx.x] = s;
   __syncthreads();
@@ -194,18 +258,61 @@ __global__ void __launch_bounds__(256) lstm_dbias_kernel(const float* __restrict
 
 struct LstmStep {
   const float* Wc;      // compact weights [G4][KW]
-  const int32_t* idx;   // S list or NULL
-  float* Z;             // [T][G4][B]: input projection + bias, then activated gates
-  float* Cc;            // [T+1][ns][B]
-  float* Hc;            // [T+1][ns][B]
+  Units S;              // the kept units
+  float* Z;             // [T][G4][Bp]: input projection + bias, then activated gates
+  float* Cc;            // [T+1][ns][Bp]
+  float* Hc;            // [T+1][ns][Bp]
   float* Hs;            // [T][H][B] output
-  float* dA;            // [T][G4][B]
-  float* dc;            // [ns][B] carry
+  float* dA;            // [T][G4][Bp]
+  float* dc;            // [ns][Bp] carry
   const float* dHs;     // [T][H][B]
   float* dh0;           // [H][B] or NULL (final backward step)
-  int32_t t, B, I, H, ns, G4, KW;
+  int32_t t, B, Bp, I, H, ns, G4, KW;
   int32_t R;            // first recurrent column of a Wc row (16-byte aligned)
 };
+
+// What the cell update of unit u, column col of step t adds to the recurrent
+// product. The step kernels load it before their first slab, so that its
+// latency passes under the product's (at the end it stood alone: 0.5 us of a
+// 6.6 us step).
+struct CellIn {
+  float z[4], cp;
+};
+__device__ __forceinline__ CellIn lstm_cell_load(const LstmStep& s, int64_t u, int64_t col) {
+  CellIn in = {};
+  if (u < s.ns && col < s.B) {
+    const float* Zt = s.Z + (static_cast<int64_t>(s.t) * s.G4 + 4 * u) * s.Bp + col;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) in.z[q] = Zt[q * s.Bp];
+    in.cp = s.Cc[(static_cast<int64_t>(s.t) * s.ns + u) * s.Bp + col];
+  }
+  return in;
+}
+
+// The cell update from the product's gate sums z: the activated gates into Z, c
+// and h into the state buffers and Hs. Columns past the batch are padding:
+// their h is 0.
+__device__ __forceinline__ void lstm_cell(const LstmStep& s, int64_t u, int64_t col, const float (&z)[4],
+                                          const CellIn& in) {
+  if (u >= s.ns || col >= s.Bp) return;
+  const int64_t o = (static_cast<int64_t>(s.t + 1) * s.ns + u) * s.Bp + col;
+  if (col >= s.B) {
+    s.Hc[o] = 0.0f;
+    return;
+  }
+  float* Zt = s.Z + (static_cast<int64_t>(s.t) * s.G4 + 4 * u) * s.Bp + col;
+  const float ig = sigm(z[0] + in.z[0]), fg = sigm(z[1] + in.z[1]);
+  const float gg = tanhf(z[2] + in.z[2]), og = sigm(z[3] + in.z[3]);
+  const float c = fg * in.cp + ig * gg;
+  const float h = og * tanhf(c);
+  s.Hc[o] = h;
+  Zt[0] = ig;
+  Zt[s.Bp] = fg;
+  Zt[2 * s.Bp] = gg;
+  Zt[3 * s.Bp] = og;
+  s.Cc[o] = c;
+  s.Hs[(static_cast<int64_t>(s.t) * s.H + s.S.row(u)) * s.B + col] = h;
+}
 
 constexpr int kStepBK = 64;
 constexpr int kStepLDK = kStepBK + 4;
@@ -252,42 +359,27 @@ __device__ __forceinline__ void splitk_32x32(const GemmOperand& a, const float* 
   }
 }
 
-// Forward step t: gates of 8 units x 32 samples.
-template <bool AVEC, bool BVEC>
+// Forward step t: gates of 8 units x 32 samples, for operands that the direct
+// loads' offsets do not reach.
 __global__ void __launch_bounds__(256) lstm_fwd_step_kernel(LstmStep s) {
   const int r0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   GemmOperand a = {}, b = {};
   a.ld = s.KW;
-  b.ld = s.B;
-  const float* hprev = s.Hc + static_cast<int64_t>(s.t) * s.ns * s.B;
-  float z[4];
-  splitk_32x32<AVEC ? KC_VEC : KC_ELEM, BVEC ? MC_VEC : MC_ELEM>(a, s.Wc + s.R, b, hprev, r0, n0, s.G4, s.B,
-                                                                  s.ns, z);
+  b.ld = s.Bp;
+  const float* hprev = s.Hc + static_cast<int64_t>(s.t) * s.ns * s.Bp;
   const int64_t u = r0 / 4 + 2 * w + (lane >> 5);
   const int64_t col = n0 + (lane & 31);
-  if (u >= s.ns || col >= s.B) return;
-  float* Zt = s.Z + static_cast<int64_t>(s.t) * s.G4 * s.B;
-  float gate[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) gate[q] = z[q] + Zt[(4 * u + q) * s.B + col];
-  const float ig = sigm(gate[0]), fg = sigm(gate[1]), gg = tanhf(gate[2]), og = sigm(gate[3]);
-  const float cp = s.Cc[(static_cast<int64_t>(s.t) * s.ns + u) * s.B + col];
-  const float c = fg * cp + ig * gg;
-  const float h = og * tanhf(c);
-  Zt[(4 * u + 0) * s.B + col] = ig;
-  Zt[(4 * u + 1) * s.B + col] = fg;
-  Zt[(4 * u + 2) * s.B + col] = gg;
-  Zt[(4 * u + 3) * s.B + col] = og;
-  s.Cc[(static_cast<int64_t>(s.t + 1) * s.ns + u) * s.B + col] = c;
-  s.Hc[(static_cast<int64_t>(s.t + 1) * s.ns + u) * s.B + col] = h;
-  s.Hs[(static_cast<int64_t>(s.t) * s.H + unit_row(s.idx, u)) * s.B + col] = h;
+  const CellIn in = lstm_cell_load(s, u, col);
+  float z[4];
+  splitk_32x32<KC_VEC, MC_VEC>(a, s.Wc + s.R, b, hprev, r0, n0, s.G4, s.Bp, s.ns, z);
+  lstm_cell(s, u, col, z, in);
 }
 
 // The same forward step on the direct-load pipeline: 32 gate rows x 32
 // samples, the four waves splitting each slab's k; after the LDS reduction
 // wave w holds the four gates of units r0 / 4 + 2 w + lane / 32. Needs
-// 16-byte aligned rows (I, KW and B multiples of 4).
+// 16-byte aligned rows.
 using StepCfg = FastCfg<float, 32, 32, 64, 4, 1, 1, 4>;  // 64 KB LDS
 
 __global__ void __launch_bounds__(StepCfg::NT) lstm_fwd_step_fast_kernel(LstmStep s) {
@@ -295,6 +387,9 @@ __global__ void __launch_bounds__(StepCfg::NT) lstm_fwd_step_fast_kernel(LstmSte
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int r0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t u = r0 / 4 + 2 * w + (lane >> 5);
+  const int64_t col = n0 + (lane & 31);
+  const CellIn in = lstm_cell_load(s, u, col);
   f32x16 acc[1][1];
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.0f;
@@ -303,17 +398,17 @@ __global__ void __launch_bounds__(StepCfg::NT) lstm_fwd_step_fast_kernel(LstmSte
   ld.wv = __builtin_amdgcn_readfirstlane(w);
   ld.lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
   ld.da.init(s.KW, r0, s.G4, ld.wv);
-  ld.db.init(s.B, n0, s.B, ld.wv);
+  ld.db.init(s.Bp, n0, s.Bp, ld.wv);
   ld.K = s.ns;
   ld.ik = 0;
   ld.is = 0;
   ld.left = nslab - 1;
   ld.a_step = Cfg::BK * 4;
-  ld.b_step = static_cast<int64_t>(s.B) * Cfg::BK * 4;
+  ld.b_step = static_cast<int64_t>(s.Bp) * Cfg::BK * 4;
   ld.a_wrap = 0;
   ld.b_wrap = 0;
   ld.na = uniform_ptr(reinterpret_cast<const char*>(s.Wc + s.R));
-  ld.nb = uniform_ptr(reinterpret_cast<const char*>(s.Hc + static_cast<int64_t>(s.t) * s.ns * s.B));
+  ld.nb = uniform_ptr(reinterpret_cast<const char*>(s.Hc + static_cast<int64_t>(s.t) * s.ns * s.Bp));
   run_slabs<Cfg, false, true, true>(ld, nslab, s.ns, 0, acc, 0, 0, w * Cfg::KW, smem);
   // wave v's registers 4 w' .. 4 w' + 3 (rows 8 w' + 4 (lane / 32) + q) go to wave w'
   float* red = reinterpret_cast<float*>(smem);
@@ -329,24 +424,7 @@ __global__ void __launch_bounds__(StepCfg::NT) lstm_fwd_step_fast_kernel(LstmSte
     for (int u = 0; u < Cfg::KSPLIT; ++u) v += red[(u * 16 + 4 * w + q) * 64 + lane];
     z[q] = v;
   }
-  const int64_t u = r0 / 4 + 2 * w + (lane >> 5);
-  const int64_t col = n0 + (lane & 31);
-  if (u >= s.ns || col >= s.B) return;
-  float* Zt = s.Z + static_cast<int64_t>(s.t) * s.G4 * s.B;
-  float gate[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) gate[q] = z[q] + Zt[(4 * u + q) * s.B + col];
-  const float ig = sigm(gate[0]), fg = sigm(gate[1]), gg = tanhf(gate[2]), og = sigm(gate[3]);
-  const float cp = s.Cc[(static_cast<int64_t>(s.t) * s.ns + u) * s.B + col];
-  const float c = fg * cp + ig * gg;
-  const float h = og * tanhf(c);
-  Zt[(4 * u + 0) * s.B + col] = ig;
-  Zt[(4 * u + 1) * s.B + col] = fg;
-  Zt[(4 * u + 2) * s.B + col] = gg;
-  Zt[(4 * u + 3) * s.B + col] = og;
-  s.Cc[(static_cast<int64_t>(s.t + 1) * s.ns + u) * s.B + col] = c;
-  s.Hc[(static_cast<int64_t>(s.t + 1) * s.ns + u) * s.B + col] = h;
-  s.Hs[(static_cast<int64_t>(s.t) * s.H + unit_row(s.idx, u)) * s.B + col] = h;
+  lstm_cell(s, u, col, z, in);
 }
 
 // The same step on 16 x 16 tiles (four units x 16 samples), for kept sets
@@ -365,22 +443,26 @@ __global__ void __launch_bounds__(StepCfg16::NT) lstm_fwd_step16_kernel(LstmStep
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int r0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t u = r0 / 4 + (lane >> 4);
+  const int64_t col = n0 + (lane & 15);
+  CellIn in = {};
+  if (w == 0) in = lstm_cell_load(s, u, col);  // the wave that updates the cells
   const int nslab = (s.ns + Cfg::BK - 1) / Cfg::BK;
   SlabLoader<Cfg, false, true> ld;
   ld.wv = __builtin_amdgcn_readfirstlane(w);
   ld.lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
   ld.da.init(s.KW, r0, s.G4, ld.wv);
-  ld.db.init(s.B, n0, s.B, ld.wv);
+  ld.db.init(s.Bp, n0, s.Bp, ld.wv);
   ld.K = s.ns;
   ld.ik = 0;
   ld.is = 0;
   ld.left = nslab - 1;
   ld.a_step = Cfg::BK * 4;
-  ld.b_step = static_cast<int64_t>(s.B) * Cfg::BK * 4;
+  ld.b_step = static_cast<int64_t>(s.Bp) * Cfg::BK * 4;
   ld.a_wrap = 0;
   ld.b_wrap = 0;
   ld.na = uniform_ptr(reinterpret_cast<const char*>(s.Wc + s.R));
-  ld.nb = uniform_ptr(reinterpret_cast<const char*>(s.Hc + static_cast<int64_t>(s.t) * s.ns * s.B));
+  ld.nb = uniform_ptr(reinterpret_cast<const char*>(s.Hc + static_cast<int64_t>(s.t) * s.ns * s.Bp));
   f32x4 acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int q = 0; q < Cfg::STAGES - 1; ++q) ld.issue();
@@ -426,59 +508,67 @@ __global__ void __launch_bounds__(StepCfg16::NT) lstm_fwd_step16_kernel(LstmStep
     for (int ww = 0; ww < 4; ++ww) v += red[(ww * 4 + q) * 64 + lane];
     z[q] = v;
   }
-  const int64_t u = r0 / 4 + (lane >> 4);
-  const int64_t col = n0 + (lane & 15);
-  if (u >= s.ns || col >= s.B) return;
-  float* Zt = s.Z + static_cast<int64_t>(s.t) * s.G4 * s.B;
-  float gate[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) gate[q] = z[q] + Zt[(4 * u + q) * s.B + col];
-  const float ig = sigm(gate[0]), fg = sigm(gate[1]), gg = tanhf(gate[2]), og = sigm(gate[3]);
-  const float cp = s.Cc[(static_cast<int64_t>(s.t) * s.ns + u) * s.B + col];
-  const float c = fg * cp + ig * gg;
-  const float h = og * tanhf(c);
-  Zt[(4 * u + 0) * s.B + col] = ig;
-  Zt[(4 * u + 1) * s.B + col] = fg;
-  Zt[(4 * u + 2) * s.B + col] = gg;
-  Zt[(4 * u + 3) * s.B + col] = og;
-  s.Cc[(static_cast<int64_t>(s.t + 1) * s.ns + u) * s.B + col] = c;
-  s.Hc[(static_cast<int64_t>(s.t + 1) * s.ns + u) * s.B + col] = h;
-  s.Hs[(static_cast<int64_t>(s.t) * s.H + unit_row(s.idx, u)) * s.B + col] = h;
+  lstm_cell(s, u, col, z, in);
 }
 
-// Pointwise backward of step t for unit u, sample b, given dL/dh_t.
-__device__ __forceinline__ void lstm_point_bwd(const LstmStep& s, int t, int64_t u, int64_t b, float dh) {
-  const float* Zt = s.Z + static_cast<int64_t>(t) * s.G4 * s.B;
-  const float ig = Zt[(4 * u + 0) * s.B + b], fg = Zt[(4 * u + 1) * s.B + b];
-  const float gg = Zt[(4 * u + 2) * s.B + b], og = Zt[(4 * u + 3) * s.B + b];
-  const float c = s.Cc[(static_cast<int64_t>(t + 1) * s.ns + u) * s.B + b];
-  const float cp = s.Cc[(static_cast<int64_t>(t) * s.ns + u) * s.B + b];
-  const float tc = tanhf(c);
+// What the pointwise backward of step t reads for unit u, column b (see
+// CellIn: loaded before the product where one runs in the same kernel).
+struct PointIn {
+  float dh, ig, fg, gg, og, c, cp;
+};
+__device__ __forceinline__ PointIn lstm_point_load(const LstmStep& s, int t, int64_t u, int64_t b) {
+  PointIn in = {};
+  if (u < s.ns && b < s.B) {
+    in.dh = s.dHs[(static_cast<int64_t>(t) * s.H + s.S.row(u)) * s.B + b];
+    const float* Zt = s.Z + (static_cast<int64_t>(t) * s.G4 + 4 * u) * s.Bp + b;
+    in.ig = Zt[0];
+    in.fg = Zt[s.Bp];
+    in.gg = Zt[2 * s.Bp];
+    in.og = Zt[3 * s.Bp];
+    const int64_t o = (static_cast<int64_t>(t) * s.ns + u) * s.Bp + b;
+    in.c = s.Cc[o + static_cast<int64_t>(s.ns) * s.Bp];
+    in.cp = s.Cc[o];
+  }
+  return in;
+}
+
+// Pointwise backward of step t for unit u, column b, given what the recurrence
+// adds to dL/dh_t (dHs[t]) and the carry dc; padding columns get dA = 0.
+__device__ __forceinline__ void lstm_point_bwd(const LstmStep& s, int t, int64_t u, int64_t b, float dh_rec,
+                                               float dcin, const PointIn& in) {
+  float* dAt = s.dA + (static_cast<int64_t>(t) * s.G4 + 4 * u) * s.Bp + b;
+  if (b >= s.B) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) dAt[q * s.Bp] = 0.0f;
+    return;
+  }
+  const float dh = in.dh + dh_rec;
+  const float tc = tanhf(in.c);
   const float d_o = dh * tc;
-  const float dcv = s.dc[u * s.B + b] + dh * og * (1.0f - tc * tc);
-  s.dc[u * s.B + b] = dcv * fg;
-  float* dAt = s.dA + static_cast<int64_t>(t) * s.G4 * s.B;
-  dAt[(4 * u + 0) * s.B + b] = dcv * gg * ig * (1.0f - ig);
-  dAt[(4 * u + 1) * s.B + b] = dcv * cp * fg * (1.0f - fg);
-  dAt[(4 * u + 2) * s.B + b] = dcv * ig * (1.0f - gg * gg);
-  dAt[(4 * u + 3) * s.B + b] = d_o * og * (1.0f - og);
+  const float dcv = dcin + dh * in.og * (1.0f - tc * tc);
+  s.dc[u * s.Bp + b] = dcv * in.fg;
+  dAt[0] = dcv * in.gg * in.ig * (1.0f - in.ig);
+  dAt[s.Bp] = dcv * in.cp * in.fg * (1.0f - in.fg);
+  dAt[2 * s.Bp] = dcv * in.ig * (1.0f - in.gg * in.gg);
+  dAt[3 * s.Bp] = d_o * in.og * (1.0f - in.og);
 }
 
 // Last step: dh = dHs[T-1] + dhT, dc carry starts at dcT.
-__global__ void lstm_bwd_last_kernel(LstmStep s, const float* __restrict__ dhT, const float* __restrict__ dcT) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= static_cast<int64_t>(s.ns) * s.B) return;
-  const int64_t u = e / s.B, b = e % s.B;
-  const int64_t j = unit_row(s.idx, u);
-  s.dc[e] = dcT ? dcT[j * s.B + b] : 0.0f;
-  float dh = s.dHs[(static_cast<int64_t>(s.t) * s.H + j) * s.B + b];
-  if (dhT) dh += dhT[j * s.B + b];
-  lstm_point_bwd(s, s.t, u, b, dh);
+__global__ void __launch_bounds__(256) lstm_bwd_last_kernel(LstmStep s, const float* __restrict__ dhT,
+                                                            const float* __restrict__ dcT) {
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (e >= static_cast<int64_t>(s.ns) * s.Bp) return;
+  int64_t u;
+  int32_t b;
+  row_col(e, s.Bp, u, b);
+  const int64_t o = s.S.row(u) * s.B + b;
+  const bool in = b < s.B;
+  lstm_point_bwd(s, s.t, u, b, in && dhT ? dhT[o] : 0.0f, in && dcT ? dcT[o] : 0.0f,
+                 lstm_point_load(s, s.t, u, b));
 }
 
 // Partial sums of dh_rec = Wc_h^T dA[t]: workgroup (x, y, z) computes 32
 // units x 32 samples over gate rows [z * ks, (z + 1) * ks) into part[z].
-template <bool AVEC, bool BVEC>
 __global__ void __launch_bounds__(256) lstm_bwd_rec_kernel(LstmStep s, float* __restrict__ part, int32_t ks) {
   const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -486,22 +576,21 @@ __global__ void __launch_bounds__(256) lstm_bwd_rec_kernel(LstmStep s, float* __
   const int klen = static_cast<int>(s.G4 - k0 < ks ? s.G4 - k0 : ks);
   GemmOperand a = {}, b = {};
   a.ld = s.KW;
-  b.ld = s.B;
-  const float* dAt = s.dA + static_cast<int64_t>(s.t) * s.G4 * s.B;
+  b.ld = s.Bp;
+  const float* dAt = s.dA + static_cast<int64_t>(s.t) * s.G4 * s.Bp;
   float z[4];
-  splitk_32x32<AVEC ? MC_VEC : MC_ELEM, BVEC ? MC_VEC : MC_ELEM>(a, s.Wc + s.R + k0 * s.KW, b, dAt + k0 * s.B, m0,
-                                                                  n0, s.ns, s.B, klen, z);
+  splitk_32x32<MC_VEC, MC_VEC>(a, s.Wc + s.R + k0 * s.KW, b, dAt + k0 * s.Bp, m0, n0, s.ns, s.Bp, klen, z);
   const int64_t col = n0 + (lane & 31);
-  if (col >= s.B) return;
-  float* out = part + static_cast<int64_t>(blockIdx.z) * s.ns * s.B;
+  if (col >= s.Bp) return;
+  float* out = part + static_cast<int64_t>(blockIdx.z) * s.ns * s.Bp;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int64_t u = m0 + 8 * w + 4 * (lane >> 5) + q;
-    if (u < s.ns) out[u * s.B + col] = z[q];
+    if (u < s.ns) out[u * s.Bp + col] = z[q];
   }
 }
 
-// dh_rec of unit u, sample b: the splits' partial sums added in split order.
+// dh_rec of element e: the splits' partial sums added in split order.
 // The loads of up to eight splits are issued together, then added in order.
 __device__ __forceinline__ float rec_sum(const float* __restrict__ part, int32_t splits, int64_t nsB, int64_t e) {
   float v = 0.0f;
@@ -521,16 +610,23 @@ __device__ __forceinline__ float rec_sum(const float* __restrict__ part, int32_t
 template <bool FINAL>
 __global__ void __launch_bounds__(256) lstm_bwd_point_kernel(LstmStep s, const float* __restrict__ part,
                                                              int32_t splits) {
-  const int64_t nsB = static_cast<int64_t>(s.ns) * s.B;
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t nsB = static_cast<int64_t>(s.ns) * s.Bp;
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (e >= nsB) return;
-  const int64_t u = e / s.B, b = e % s.B;
-  const int64_t j = unit_row(s.idx, u);
-  const float r = rec_sum(part, splits, nsB, e);
+  int64_t u;
+  int32_t b;
+  row_col(e, s.Bp, u, b);
+  PointIn in = {};
+  float dc = 0.0f;
+  if (!FINAL) {  // every load of the step in flight before the first use
+    in = lstm_point_load(s, s.t - 1, u, b);
+    dc = s.dc[e];
+  }
+  const float r = b < s.B ? rec_sum(part, splits, nsB, e) : 0.0f;
   if (FINAL) {
-    if (s.dh0) s.dh0[j * s.B + b] = r;
+    if (s.dh0 && b < s.B) s.dh0[s.S.row(u) * s.B + b] = r;
   } else {
-    lstm_point_bwd(s, s.t - 1, u, b, s.dHs[(static_cast<int64_t>(s.t - 1) * s.H + j) * s.B + b] + r);
+    lstm_point_bwd(s, s.t - 1, u, b, r, dc, in);
   }
 }
 
@@ -543,8 +639,7 @@ __global__ void __launch_bounds__(256) lstm_bwd_point_kernel(LstmStep s, const f
 // dh0 = dh_rec). Small output tiles give the grid its width in place of a
 // split contraction, so no partial sums leave the workgroup and no second
 // kernel is needed per step. A (m-contiguous): column I + u of Wc's gate rows;
-// B (n-contiguous): dA[t]. Needs 16-byte aligned rows (I, KW and B multiples
-// of 4). 128 gate rows per slab, 4 stages: the deeper 256-row slabs and 3 to
+// B (n-contiguous): dA[t]. Needs 16-byte aligned rows. 128 gate rows per slab, 4 stages: the deeper 256-row slabs and 3 to
 // 8 stages measured the same or slower.
 using RecStepCfg = FastCfg<float, 16, 16, 128, 4, 1, 1, 4>;  // 64 KB LDS
 
@@ -556,22 +651,30 @@ __global__ void __launch_bounds__(RecStepCfg::NT) lstm_bwd_step_fused_kernel(Lst
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int u0 = blockIdx.y * 16, b0 = blockIdx.x * 16;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int tm = threadIdx.x >> 4, tn = threadIdx.x & 15;
+  const int64_t u = u0 + tm, b = b0 + tn;
+  PointIn in = {};
+  float dc = 0.0f;
+  if (!FINAL) {
+    in = lstm_point_load(s, s.t - 1, u, b);
+    if (u < s.ns && b < s.B) dc = s.dc[u * s.Bp + b];
+  }
   const int nslab = (s.G4 + Cfg::BK - 1) / Cfg::BK;
   SlabLoader<Cfg, true, true> ld;
   ld.wv = __builtin_amdgcn_readfirstlane(w);
   ld.lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
   ld.da.init(s.KW, u0, s.ns, ld.wv);
-  ld.db.init(s.B, b0, s.B, ld.wv);
+  ld.db.init(s.Bp, b0, s.Bp, ld.wv);
   ld.K = s.G4;
   ld.ik = 0;
   ld.is = 0;
   ld.left = nslab - 1;
   ld.a_step = static_cast<int64_t>(Cfg::BK) * s.KW * 4;
-  ld.b_step = static_cast<int64_t>(Cfg::BK) * s.B * 4;
+  ld.b_step = static_cast<int64_t>(Cfg::BK) * s.Bp * 4;
   ld.a_wrap = 0;
   ld.b_wrap = 0;
   ld.na = uniform_ptr(reinterpret_cast<const char*>(s.Wc + s.R));
-  ld.nb = uniform_ptr(reinterpret_cast<const char*>(s.dA + static_cast<int64_t>(s.t) * s.G4 * s.B));
+  ld.nb = uniform_ptr(reinterpret_cast<const char*>(s.dA + static_cast<int64_t>(s.t) * s.G4 * s.Bp));
   // two accumulators on alternate k steps, so that consecutive MFMAs do not
   // wait for each other's result
   f32x4 acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -614,18 +717,15 @@ __global__ void __launch_bounds__(RecStepCfg::NT) lstm_bwd_step_fused_kernel(Lst
 #pragma unroll
   for (int i = 0; i < 4; ++i) red[(w * 4 + i) * 64 + lane] = acc0[i] + acc1[i];
   lds_barrier();
-  const int tm = threadIdx.x >> 4, tn = threadIdx.x & 15;
   const int src = (tm >> 2) * 16 + tn, reg = tm & 3;
   float v = 0.0f;
 #pragma unroll
   for (int ww = 0; ww < 4; ++ww) v += red[(ww * 4 + reg) * 64 + src];
-  const int64_t u = u0 + tm, b = b0 + tn;
-  if (u >= s.ns || b >= s.B) return;
-  const int64_t j = unit_row(s.idx, u);
+  if (u >= s.ns || b >= s.Bp) return;
   if (FINAL) {
-    if (s.dh0) s.dh0[j * s.B + b] = v;
+    if (s.dh0 && b < s.B) s.dh0[s.S.row(u) * s.B + b] = v;
   } else {
-    lstm_point_bwd(s, s.t - 1, u, b, s.dHs[(static_cast<int64_t>(s.t - 1) * s.H + j) * s.B + b] + v);
+    lstm_point_bwd(s, s.t - 1, u, b, v, dc, in);
   }
 }
 
@@ -662,16 +762,17 @@ int check_opt(const void* p, const char* name) {
 
 inline dim3 grid1d(int64_t n, int threads) { return dim3(static_cast<unsigned>((n + threads - 1) / threads)); }
 
-LstmStep step_args(const Layout& L, char* w, const int32_t* idx) {
+LstmStep step_args(const Layout& L, char* w, int32_t period, int32_t offset) {
   LstmStep s = {};
   s.Wc = reinterpret_cast<const float*>(w + L.wc);
-  s.idx = idx;
+  s.S = {period, offset};
   s.Z = reinterpret_cast<float*>(w + L.z);
   s.Cc = reinterpret_cast<float*>(w + L.cc);
   s.Hc = reinterpret_cast<float*>(w + L.hc);
   s.dA = reinterpret_cast<float*>(w + L.da);
   s.dc = reinterpret_cast<float*>(w + L.dc);
   s.B = static_cast<int32_t>(L.B);
+  s.Bp = static_cast<int32_t>(L.Bp);
   s.I = static_cast<int32_t>(L.Ic);  // compact input width
   s.R = static_cast<int32_t>(L.R);   // the recurrent columns of Wc start here
   s.H = static_cast<int32_t>(L.H);
@@ -679,6 +780,41 @@ LstmStep step_args(const Layout& L, char* w, const int32_t* idx) {
   s.G4 = static_cast<int32_t>(L.G4);
   s.KW = static_cast<int32_t>(L.KW);
   return s;
+}
+
+// Zeroes the rows of out[rows][cols] whose unit is dropped.
+hipError_t zero_rows(float* out, int64_t rows, int32_t cols, int32_t H, int32_t period, int32_t offset, hipStream_t s) {
+  if (cols % 4 == 0)
+    hipLaunchKernelGGL(lstm_zero_dropped_rows_kernel<4>, grid1d(rows * cols / 4, 256), dim3(256), 0, s, out,
+                       rows * cols / 4, cols, H, period, offset);
+  else
+    hipLaunchKernelGGL(lstm_zero_dropped_rows_kernel<1>, grid1d(rows * cols, 256), dim3(256), 0, s, out, rows * cols,
+                       cols, H, period, offset);
+  return hipGetLastError();
+}
+
+// A batch of products over the steps (batch strides of B and C, a shared A) as
+// one product over the T Bp columns of all steps; nvalid of each Bp columns are
+// written. N = 0 where their number does not fit.
+GemmArgs all_steps(GemmArgs g, const Layout& L, int32_t nvalid) {
+  g.b.nblk = g.c.nblk = static_cast<int32_t>(L.Bp);
+  g.b.nstride = g.b.bstride;
+  g.c.nstride = g.c.bstride;
+  g.b.bstride = g.c.bstride = 0;
+  g.c.nvalid = nvalid;
+  g.N = L.T * L.Bp < (int64_t{1} << 30) ? static_cast<int32_t>(L.T * L.Bp) : 0;
+  return g;
+}
+
+// The layer's input as the products read it: element (t, k, b) of the kept
+// inputs at p[t * tstride + k * ld + b]; X itself, or its padded copy.
+struct InputView {
+  const float* p;
+  int64_t ld, tstride;
+};
+InputView input_view(const Layout& L, const void* X, const char* w) {
+  if (L.Bp != L.B) return {reinterpret_cast<const float*>(w + L.xp), L.Bp, L.Ic * L.Bp};
+  return {static_cast<const float*>(X) + L.io * L.B, L.ip * L.B, L.I * L.B};
 }
 
 }  // namespace
@@ -711,7 +847,7 @@ int ard_lstm_fwd(const ard_lstm_desc* desc, const void* X, const void* W, const 
   if ((st = check_ws(L, ws, ws_bytes))) return st;
   hipStream_t sm = static_cast<hipStream_t>(stream);
   char* w = static_cast<char*>(ws);
-  LstmStep s = step_args(L, w, idx);
+  LstmStep s = step_args(L, w, period, offset);
   float* Hsf = static_cast<float*>(Hs);
   s.Hs = Hsf;
   const int64_t HB = L.H * L.B;
@@ -725,45 +861,56 @@ int ard_lstm_fwd(const ard_lstm_desc* desc, const void* X, const void* W, const 
   }
 
   hipLaunchKernelGGL(lstm_prepare_kernel, dim3(static_cast<unsigned>(L.G4)), dim3(256), 0, sm,
-                     static_cast<const float*>(W), bias, idx, static_cast<int32_t>(L.I), s.I, s.R,
+                     static_cast<const float*>(W), bias, s.S, static_cast<int32_t>(L.I), s.I, s.R,
                      static_cast<int32_t>(L.ip), static_cast<int32_t>(L.io), s.H, ns, s.KW, const_cast<float*>(s.Wc),
                      reinterpret_cast<float*>(w + L.bc), reinterpret_cast<int32_t*>(w + L.rowmap));
   ARD_LAUNCH_CHECK();
-  const int64_t nsB = static_cast<int64_t>(ns) * L.B;
-  hipLaunchKernelGGL(lstm_gather_state_kernel, grid1d(nsB, 256), dim3(256), 0, sm,
-                     static_cast<const float*>(h0), idx, ns, s.B, s.Hc);
-  hipLaunchKernelGGL(lstm_gather_state_kernel, grid1d(nsB, 256), dim3(256), 0, sm,
-                     static_cast<const float*>(c0), idx, ns, s.B, s.Cc);
+  const int64_t nsB = static_cast<int64_t>(ns) * L.Bp;
+  dim3 ggrid = grid1d(nsB, 256);
+  ggrid.y = 2;
+  hipLaunchKernelGGL(lstm_gather_state_kernel, ggrid, dim3(256), 0, sm, static_cast<const float*>(h0),
+                     static_cast<const float*>(c0), s.S, nsB, s.B, s.Bp, s.Hc, s.Cc);
   ARD_LAUNCH_CHECK();
-
-  // input projection of every step, bias folded in: Z[t] = Wc_x X[t] + bc
-  GemmArgs g = {};
-  g.M = static_cast<int32_t>(L.G4);
-  g.N = s.B;
-  g.K = s.I;
-  g.a = {s.Wc, nullptr, L.KW, nullptr, nullptr, 0, 0, 1.0f, 0};
-  // the kept input rows io + ip * k of X[t]: a strided view
-  g.b = {static_cast<const float*>(X) + L.io * L.B, nullptr, L.ip * L.B, nullptr, nullptr, L.I * L.B, 0, 1.0f, 0};
-  g.c = {s.Z, L.B, nullptr, nullptr, L.G4 * L.B, reinterpret_cast<const float*>(w + L.bc), 0, 1.0f};
-  const bool kw_vec = L.KW % 4 == 0;
-  const bool b_vec = L.B % 4 == 0 && L.I % 4 == 0;
-  if (fast_ok<false, true>(g, sizeof(float))) {
-    ARD_HIP_CHECK((run_fast_gemm<float, false, true, float, EPI_FWD>(g, static_cast<int>(L.T), sm, nullptr)));
-  } else {
-    ARD_HIP_CHECK((run_gemm<float, float, KC_VEC, KC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
-        g, static_cast<int>(L.T), kw_vec, b_vec, sm)));
+  if (L.Bp != L.B) {
+    for (int64_t t0 = 0; t0 < L.T; t0 += 65535) {
+      dim3 pgrid = grid1d(L.Ic * L.Bp, 256);
+      pgrid.y = static_cast<unsigned>(L.T - t0 < 65535 ? L.T - t0 : 65535);
+      hipLaunchKernelGGL(lstm_pad_input_kernel, pgrid, dim3(256), 0, sm, static_cast<const float*>(X), L.Ic * L.Bp,
+                         static_cast<int32_t>(L.I), static_cast<int32_t>(L.ip), static_cast<int32_t>(L.io), s.B, s.Bp,
+                         static_cast<int32_t>(t0), reinterpret_cast<float*>(w + L.xp));
+      ARD_LAUNCH_CHECK();
+    }
   }
 
-  const dim3 sgrid(static_cast<unsigned>((L.B + 31) / 32), static_cast<unsigned>((L.G4 + 31) / 32));
-  const bool avec = kw_vec, bvec = L.B % 4 == 0;  // the recurrent columns start aligned (R)
-  // direct loads: aligned rows, and every chunk offset of a slab below 2^31 bytes
-  const bool step_fast = avec && bvec && aligned16(s.Wc) &&
-                         (L.G4 + 1) * L.KW * 4 < (int64_t{1} << 31) && (L.ns + 64) * L.B * 4 < (int64_t{1} << 31);
+  // input projection of every step, bias folded in: Z[t] = Wc_x X[t] + bc, the
+  // columns of all steps as one dimension
+  const InputView xv = input_view(L, X, w);
+  GemmArgs g = {};
+  g.M = static_cast<int32_t>(L.G4);
+  g.N = s.Bp;
+  g.K = s.I;
+  g.a = {s.Wc, nullptr, L.KW, nullptr, nullptr, 0, 0, 1.0f, 0};
+  g.b = {xv.p, nullptr, xv.ld, nullptr, nullptr, xv.tstride, 0, 1.0f, 0};
+  g.c = {s.Z, L.Bp, nullptr, nullptr, L.G4 * L.Bp, reinterpret_cast<const float*>(w + L.bc), 0, 1.0f};
+  GemmArgs gc = all_steps(g, L, s.Bp);
+  if (gc.N > 0 && cols_ok<false>(gc)) {
+    ARD_HIP_CHECK(run_cols_gemm<false>(gc, sm));
+  } else if (fast_ok<false, true>(g, sizeof(float))) {
+    ARD_HIP_CHECK((run_fast_gemm<float, false, true, float, EPI_FWD>(g, static_cast<int>(L.T), sm, nullptr, 0)));
+  } else {
+    ARD_HIP_CHECK((run_gemm<float, float, KC_VEC, KC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
+        g, static_cast<int>(L.T), true, xv.ld % 4 == 0 && xv.tstride % 4 == 0, sm)));
+  }
+
+  const dim3 sgrid(static_cast<unsigned>((L.Bp + 31) / 32), static_cast<unsigned>((L.G4 + 31) / 32));
+  // direct loads: every chunk offset of a slab below 2^31 bytes (the rows start aligned)
+  const bool step_fast = aligned16(s.Wc) && (L.G4 + 1) * L.KW * 4 < (int64_t{1} << 31) &&
+                         (L.ns + 64) * L.Bp * 4 < (int64_t{1} << 31);
   // 16 x 16 tiles where the 32 x 32 grid holds fewer than 128 workgroups
   // (measured on MI355X, T 35, batch 64, H 1024: 255-269 against 288-290 us per
   // forward at |S| = 256, 210-218 against 237-244 us at 128, equal at 342 and
   // 64, slower at 512 and 1024)
-  const bool step16 = step_fast && ((L.G4 + 31) / 32) * ((L.B + 31) / 32) < 128;
+  const bool step16 = step_fast && ((L.G4 + 31) / 32) * ((L.Bp + 31) / 32) < 128;
   if (step_fast) {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(lstm_fwd_step_fast_kernel),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, StepCfg::LDS);
@@ -772,31 +919,25 @@ int ard_lstm_fwd(const ard_lstm_desc* desc, const void* X, const void* W, const 
     ARD_HIP_CHECK(attr);
     ARD_HIP_CHECK(attr16);
   }
-  const dim3 sgrid16(static_cast<unsigned>((L.B + 15) / 16), static_cast<unsigned>((L.G4 + 15) / 16));
+  const dim3 sgrid16(static_cast<unsigned>((L.Bp + 15) / 16), static_cast<unsigned>((L.G4 + 15) / 16));
   for (int t = 0; t < L.T; ++t) {
     s.t = t;
     if (step16)
       hipLaunchKernelGGL(lstm_fwd_step16_kernel, sgrid16, dim3(StepCfg16::NT), StepCfg16::LDS, sm, s);
     else if (step_fast)
       hipLaunchKernelGGL(lstm_fwd_step_fast_kernel, sgrid, dim3(StepCfg::NT), StepCfg::LDS, sm, s);
-    else if (avec && bvec)
-      hipLaunchKernelGGL((lstm_fwd_step_kernel<true, true>), sgrid, dim3(256), 0, sm, s);
     else
-      hipLaunchKernelGGL((lstm_fwd_step_kernel<false, false>), sgrid, dim3(256), 0, sm, s);
+      hipLaunchKernelGGL(lstm_fwd_step_kernel, sgrid, dim3(256), 0, sm, s);
     ARD_LAUNCH_CHECK();
   }
-  if (period > 1) {
-    hipLaunchKernelGGL(lstm_zero_dropped_rows_kernel, dim3(static_cast<unsigned>(L.T * L.H)), dim3(256), 0, sm,
-                       Hsf, L.T * L.H, s.B, s.H, period, offset);
+  if (period > 1) ARD_HIP_CHECK(zero_rows(Hsf, L.T * L.H, s.B, s.H, period, offset, sm));
+  if (hT || cT) {
+    const StatePair p = {{s.Hc + L.T * nsB, s.Cc + L.T * nsB}, {static_cast<float*>(hT), static_cast<float*>(cT)}};
+    dim3 grid = grid1d(HB, 256);
+    grid.y = 2;
+    hipLaunchKernelGGL(lstm_scatter_state_kernel, grid, dim3(256), 0, sm, p, HB, s.B, s.Bp, period, offset);
     ARD_LAUNCH_CHECK();
   }
-  if (hT)
-    hipLaunchKernelGGL(lstm_scatter_state_kernel, grid1d(HB, 256), dim3(256), 0, sm,
-                       s.Hc + L.T * nsB, s.H, s.B, period, offset, static_cast<float*>(hT));
-  if (cT)
-    hipLaunchKernelGGL(lstm_scatter_state_kernel, grid1d(HB, 256), dim3(256), 0, sm,
-                       s.Cc + L.T * nsB, s.H, s.B, period, offset, static_cast<float*>(cT));
-  ARD_LAUNCH_CHECK();
   return ARD_OK;
 }
 
@@ -817,7 +958,7 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
   if ((st = check_ws(L, ws, ws_bytes))) return st;
   hipStream_t sm = static_cast<hipStream_t>(stream);
   char* w = static_cast<char*>(ws);
-  LstmStep s = step_args(L, w, idx);
+  LstmStep s = step_args(L, w, period, offset);
   s.dHs = static_cast<const float*>(dHs);
   const int64_t HB = L.H * L.B;
   const int64_t rowsW = 4 * L.H, colsW = L.I + L.H;
@@ -832,7 +973,8 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
     return ARD_OK;
   }
 
-  const int64_t nsB = static_cast<int64_t>(ns) * L.B;
+  const int64_t nsB = static_cast<int64_t>(ns) * L.Bp;
+  const InputView xv = input_view(L, X, w);
   s.t = static_cast<int32_t>(L.T - 1);
   hipLaunchKernelGGL(lstm_bwd_last_kernel, grid1d(nsB, 256), dim3(256), 0, sm, s,
                      static_cast<const float*>(dhT), static_cast<const float*>(dcT));
@@ -847,7 +989,7 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
   // exact split count for the direct-load GEMM (0 = none): its 32 x 32 tiles
   // run one workgroup per compute unit, so the splits stop at one round of
   // 256 workgroups (a second, partial round costs more than longer splits)
-  const int64_t rtiles = ((ns + 31) / 32) * ((L.B + 31) / 32);
+  const int64_t rtiles = ((ns + 31) / 32) * ((L.Bp + 31) / 32);
   int32_t fs = 0;
   for (int32_t d = static_cast<int32_t>(L.S); d >= 1; --d)
     if (L.G4 % d == 0 && L.G4 / d >= 256 && (d == 1 || rtiles * d <= 256)) {
@@ -857,9 +999,9 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
   // A batch of 64 is one column of 32 x 64 tiles: each block of the recurrent
   // weights is then read by one workgroup per step instead of two. Taken when
   // those tiles alone fill one round of 256 workgroups.
-  const int64_t wtiles = ((ns + 31) / 32) * ((L.B + 63) / 64);
+  const int64_t wtiles = ((ns + 31) / 32) * ((L.Bp + 63) / 64);
   bool rec_wide = false;
-  if (L.B > 32 && L.B <= 64) {
+  if (L.Bp > 32 && L.Bp <= 64) {
     for (int32_t d = static_cast<int32_t>(L.S); d >= 1; --d)
       if (L.G4 % d == 0 && L.G4 / d >= 256 && wtiles * d == 256) {
         fs = d;
@@ -871,20 +1013,19 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
   bool rec_fast = false;
   if (fs > 0) {
     gr.M = ns;
-    gr.N = s.B;
+    gr.N = s.Bp;
     gr.K = static_cast<int32_t>(L.G4 / fs);
     gr.a = {s.Wc + L.R, nullptr, L.KW, nullptr, nullptr, gr.K * L.KW, 0, 1.0f, 0};
-    gr.b = {s.dA, nullptr, L.B, nullptr, nullptr, gr.K * L.B, 0, 1.0f, 0};
-    gr.c = {part, L.B, nullptr, nullptr, nsB, nullptr, 0, 1.0f};
+    gr.b = {s.dA, nullptr, L.Bp, nullptr, nullptr, gr.K * L.Bp, 0, 1.0f, 0};
+    gr.c = {part, L.Bp, nullptr, nullptr, nsB, nullptr, 0, 1.0f};
     rec_fast = fast_ok<true, true>(gr, sizeof(float));
     if (rec_fast) {
       ks = gr.K;
       splits = fs;
     }
   }
-  const dim3 rgrid(static_cast<unsigned>((L.B + 31) / 32), static_cast<unsigned>((ns + 31) / 32),
+  const dim3 rgrid(static_cast<unsigned>((L.Bp + 31) / 32), static_cast<unsigned>((ns + 31) / 32),
                    static_cast<unsigned>(splits));
-  const bool vec = L.KW % 4 == 0 && L.B % 4 == 0;
   // One fused launch per step where the direct loads can take the operands
   // (aligned rows; chunk offsets of a slab below 2^31 bytes) and the operand
   // stream stays small: 16-wide tiles read each operand twice as often as the
@@ -892,10 +1033,10 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
   // on MI355X (T 35, batch 64, H 1024, backward per sequence): fused 262 / 329
   // / 373 / 514 us at |S| = 64 / 128 / 256 / 342 against 408 / 460 / 463 / 600
   // us split; 650 against 586 us at |S| = 512, where the stream is 32 MB.
-  const bool rec_fused = vec && aligned16(s.Wc) && aligned16(s.dA) &&
+  const bool rec_fused = aligned16(s.Wc) && aligned16(s.dA) &&
                          int64_t{RecStepCfg::BK} * L.KW * 4 < (int64_t{1} << 31) &&
-                         int64_t{RecStepCfg::BK} * L.B * 4 < (int64_t{1} << 31) &&
-                         static_cast<int64_t>(ns) * L.G4 * L.B / 2 <= (int64_t{16} << 20);
+                         int64_t{RecStepCfg::BK} * L.Bp * 4 < (int64_t{1} << 31) &&
+                         static_cast<int64_t>(ns) * L.G4 * L.Bp / 2 <= (int64_t{16} << 20);
   if (rec_fused) {
     static const hipError_t a0 = hipFuncSetAttribute(
         reinterpret_cast<const void*>(lstm_bwd_step_fused_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -906,7 +1047,7 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
     ARD_HIP_CHECK(a0);
     ARD_HIP_CHECK(a1);
   }
-  const dim3 fgrid(static_cast<unsigned>((L.B + 15) / 16), static_cast<unsigned>((ns + 15) / 16));
+  const dim3 fgrid(static_cast<unsigned>((L.Bp + 15) / 16), static_cast<unsigned>((ns + 15) / 16));
   for (int t = static_cast<int>(L.T) - 1; t >= 0; --t) {
     if (t == 0 && !dh0) break;
     s.t = t;
@@ -921,15 +1062,13 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
       continue;
     }
     if (rec_fast) {
-      gr.b.p = s.dA + static_cast<int64_t>(t) * L.G4 * L.B;
+      gr.b.p = s.dA + static_cast<int64_t>(t) * L.G4 * L.Bp;
       if (rec_wide)
         ARD_HIP_CHECK((launch_fast<RecWideCfg, true, true, float, EPI_FWD>(gr, splits, sm)));
       else
-        ARD_HIP_CHECK((run_fast_gemm<float, true, true, float, EPI_FWD>(gr, splits, sm, nullptr)));
-    } else if (vec) {
-      hipLaunchKernelGGL((lstm_bwd_rec_kernel<true, true>), rgrid, dim3(256), 0, sm, s, part, ks);
+        ARD_HIP_CHECK((run_fast_gemm<float, true, true, float, EPI_FWD>(gr, splits, sm, nullptr, 0)));
     } else {
-      hipLaunchKernelGGL((lstm_bwd_rec_kernel<false, false>), rgrid, dim3(256), 0, sm, s, part, ks);
+      hipLaunchKernelGGL(lstm_bwd_rec_kernel, rgrid, dim3(256), 0, sm, s, part, ks);
     }
     ARD_LAUNCH_CHECK();
     if (t > 0) {
@@ -940,14 +1079,10 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
     }
     ARD_LAUNCH_CHECK();
   }
-  if (dh0 && period > 1) {
-    hipLaunchKernelGGL(lstm_zero_dropped_rows_kernel, dim3(static_cast<unsigned>(L.H)), dim3(256), 0, sm,
-                       static_cast<float*>(dh0), L.H, s.B, s.H, period, offset);
-    ARD_LAUNCH_CHECK();
-  }
+  if (dh0 && period > 1) ARD_HIP_CHECK(zero_rows(static_cast<float*>(dh0), L.H, s.B, s.H, period, offset, sm));
   if (dc0) {
-    hipLaunchKernelGGL(lstm_scatter_state_kernel, grid1d(HB, 256), dim3(256), 0, sm, s.dc, s.H, s.B, period,
-                       offset, static_cast<float*>(dc0));
+    const StatePair p = {{s.dc, nullptr}, {static_cast<float*>(dc0), nullptr}};
+    hipLaunchKernelGGL(lstm_scatter_state_kernel, grid1d(HB, 256), dim3(256), 0, sm, p, HB, s.B, s.Bp, period, offset);
     ARD_LAUNCH_CHECK();
   }
 
@@ -955,12 +1090,11 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
   int32_t* rowmap = reinterpret_cast<int32_t*>(w + L.rowmap);
   auto build_rowmap = [&]() -> hipError_t {
     if (L.G4 <= 0) return hipSuccess;
-    hipLaunchKernelGGL(lstm_rowmap_kernel, grid1d(L.G4, 256), dim3(256), 0, sm, idx, static_cast<int32_t>(L.H),
+    hipLaunchKernelGGL(lstm_rowmap_kernel, grid1d(L.G4, 256), dim3(256), 0, sm, s.S, static_cast<int32_t>(L.H),
                        static_cast<int32_t>(L.G4), rowmap);
     return hipGetLastError();
   };
   bool rowmap_built = false;
-  const bool bv = L.B % 4 == 0;
   // Per gate q the compact rows 4u + q of dA are every fourth row, and the
   // output rows q H + S(u) and recurrent columns I + S(v) of a row pattern are
   // strided views of dW: the weight gradient runs as four plain strided
@@ -970,27 +1104,36 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
     GemmArgs g = {};
     g.M = ns;
     g.N = s.I;
-    g.K = s.B;
+    g.K = s.Bp;
     g.kbatch = static_cast<int32_t>(L.T);
-    g.a = {s.dA, nullptr, 4 * L.B, nullptr, nullptr, L.B, 0, 1.0f, L.G4 * L.B};
-    g.b = {static_cast<const float*>(X) + L.io * L.B, nullptr, L.ip * L.B, nullptr, nullptr, 0, 0, 1.0f, L.I * L.B};
+    g.a = {s.dA, nullptr, 4 * L.Bp, nullptr, nullptr, L.Bp, 0, 1.0f, L.G4 * L.Bp};
+    g.b = {xv.p, nullptr, xv.ld, nullptr, nullptr, 0, 0, 1.0f, xv.tstride};
     g.c = {dW + static_cast<int64_t>(offset) * colsW + L.io, period * colsW, nullptr, nullptr, L.H * colsW, nullptr,
            0, 1.0f};
     g.c.col_stride = L.ip;
     GemmArgs gr = g;  // recurrent columns
     gr.N = ns;
-    gr.b = {s.Hc, nullptr, L.B, nullptr, nullptr, 0, 0, 1.0f, nsB};
+    gr.b = {s.Hc, nullptr, L.Bp, nullptr, nullptr, 0, 0, 1.0f, nsB};
     gr.c.p = dW + static_cast<int64_t>(offset) * colsW + L.I + offset;
     gr.c.col_stride = period;
-    if (fast_ok<false, false>(g, sizeof(float)) && fast_ok<false, false>(gr, sizeof(float))) {
-      // dbias[q H + S(u)] = sum over t, b of dA: the row sums of the first product's A
-      if (dbias) {
-        g.rsum = dbias + offset;
-        g.rsum_ld = period;
-        g.rsum_bstride = L.H;
-      }
-      ARD_HIP_CHECK((run_fast_gemm<float, false, false, float, EPI_FWD, true>(g, 4, sm, nullptr, &dbias_done)));
-      ARD_HIP_CHECK((run_fast_gemm<float, false, false, float, EPI_FWD>(gr, 4, sm, nullptr)));
+    // dbias[q H + S(u)] = sum over t, b of dA: the row sums of the first product's A
+    if (dbias) {
+      g.rsum = dbias + offset;
+      g.rsum_ld = period;
+      g.rsum_bstride = L.H;
+    }
+    if (flat_ok(g) && flat_ok(gr)) {
+      // the T Bp samples of all steps as one contraction
+      if (dbias)
+        ARD_HIP_CHECK(run_flat_gemm<true>(g, 4, sm));
+      else
+        ARD_HIP_CHECK(run_flat_gemm<false>(g, 4, sm));
+      ARD_HIP_CHECK(run_flat_gemm<false>(gr, 4, sm));
+      dw_done = true;
+      dbias_done = dbias != nullptr;
+    } else if (fast_ok<false, false>(g, sizeof(float)) && fast_ok<false, false>(gr, sizeof(float))) {
+      ARD_HIP_CHECK((run_fast_gemm<float, false, false, float, EPI_FWD, true>(g, 4, sm, nullptr, 0, &dbias_done)));
+      ARD_HIP_CHECK((run_fast_gemm<float, false, false, float, EPI_FWD>(gr, 4, sm, nullptr, 0)));
       dw_done = true;
     }
   }
@@ -1001,24 +1144,24 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
     GemmArgs g = {};
     g.M = static_cast<int32_t>(L.G4);
     g.N = s.I;
-    g.K = s.B;
+    g.K = s.Bp;
     g.kbatch = static_cast<int32_t>(L.T);
-    g.a = {s.dA, nullptr, L.B, nullptr, nullptr, 0, 0, 1.0f, L.G4 * L.B};
-    g.b = {static_cast<const float*>(X) + L.io * L.B, nullptr, L.ip * L.B, nullptr, nullptr, 0, 0, 1.0f, L.I * L.B};
+    g.a = {s.dA, nullptr, L.Bp, nullptr, nullptr, 0, 0, 1.0f, L.G4 * L.Bp};
+    g.b = {xv.p, nullptr, xv.ld, nullptr, nullptr, 0, 0, 1.0f, xv.tstride};
     g.c = {dW + L.io, colsW, rowmap, nullptr, 0, nullptr, 0, 1.0f};
     g.c.col_stride = L.ip;
     ARD_HIP_CHECK((run_gemm<float, float, KC_VEC, KC_ELEM, KC_VEC, KC_ELEM, false, false, EPI_FWD>(
-        g, 1, bv, bv && L.I % 4 == 0, sm)));
+        g, 1, true, xv.ld % 4 == 0 && xv.tstride % 4 == 0, sm)));
     g.N = ns;
-    g.b = {s.Hc, nullptr, L.B, nullptr, nullptr, 0, 0, 1.0f, nsB};
+    g.b = {s.Hc, nullptr, L.Bp, nullptr, nullptr, 0, 0, 1.0f, nsB};
     g.c = {dW + L.I, colsW, rowmap, idx, 0, nullptr, 0, 1.0f};
     ARD_HIP_CHECK((run_gemm<float, float, KC_VEC, KC_ELEM, KC_VEC, KC_ELEM, false, false, EPI_FWD>(
-        g, 1, bv, bv, sm)));
+        g, 1, true, true, sm)));
   }
   if (dbias && !dbias_done) {
     if (!rowmap_built) ARD_HIP_CHECK(build_rowmap());
     hipLaunchKernelGGL(lstm_dbias_kernel, dim3(static_cast<unsigned>(L.G4)), dim3(256), 0, sm, s.dA, rowmap,
-                       static_cast<int32_t>(L.T), static_cast<int32_t>(L.G4), s.B, dbias);
+                       static_cast<int32_t>(L.T), static_cast<int32_t>(L.G4), s.Bp, dbias);
     ARD_LAUNCH_CHECK();
   }
   if ((period > 1 && (dW || dbias)) || (L.ip > 1 && dW)) {
@@ -1027,33 +1170,32 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
                          dbias, static_cast<int32_t>(L.I), s.H, period, offset, static_cast<int32_t>(L.ip),
                          static_cast<int32_t>(L.io));
     } else {
-      hipLaunchKernelGGL(lstm_zero_dropped_rows_kernel, dim3(static_cast<unsigned>(rowsW)), dim3(64), 0, sm,
-                         dbias, rowsW, 1, s.H, period, offset);
+      ARD_HIP_CHECK(zero_rows(dbias, rowsW, 1, s.H, period, offset, sm));
     }
     ARD_LAUNCH_CHECK();
   }
   if (dX) {
-    // dX[t] = Wc_x^T dA[t] for every step
+    // dX[t] = Wc_x^T dA[t] for every step, the columns of all steps as one dimension
     GemmArgs g = {};
     g.M = s.I;
     g.N = s.B;
     g.K = static_cast<int32_t>(L.G4);
     g.a = {s.Wc, nullptr, L.KW, nullptr, nullptr, 0, 0, 1.0f, 0};
-    g.b = {s.dA, nullptr, L.B, nullptr, nullptr, L.G4 * L.B, 0, 1.0f, 0};
+    g.b = {s.dA, nullptr, L.Bp, nullptr, nullptr, L.G4 * L.Bp, 0, 1.0f, 0};
     // rows io + ip * k of dX[t]; the rows of dropped inputs are written 0
     g.c = {static_cast<float*>(dX) + L.io * L.B, L.ip * L.B, nullptr, nullptr, L.I * L.B, nullptr, 0, 1.0f};
-    if (fast_ok<true, true>(g, sizeof(float))) {
-      ARD_HIP_CHECK((run_fast_gemm<float, true, true, float, EPI_FWD>(g, static_cast<int>(L.T), sm, nullptr)));
+    const GemmArgs gc = all_steps(g, L, s.B);
+    if (gc.N > 0 && cols_ok<true>(gc)) {
+      ARD_HIP_CHECK(run_cols_gemm<true>(gc, sm));
+    } else if (fast_ok<true, true>(g, sizeof(float))) {
+      ARD_HIP_CHECK((run_fast_gemm<float, true, true, float, EPI_FWD>(g, static_cast<int>(L.T), sm, nullptr, 0)));
     } else {
       ARD_HIP_CHECK((run_gemm<float, float, MC_VEC, MC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
-          g, static_cast<int>(L.T), L.KW % 4 == 0 && L.Ic % 4 == 0, bv, sm)));
+          g, static_cast<int>(L.T), true, true, sm)));
     }
-    if (L.ip > 1) {
-      hipLaunchKernelGGL(lstm_zero_dropped_rows_kernel, dim3(static_cast<unsigned>(L.T * L.I)), dim3(256), 0, sm,
-                         static_cast<float*>(dX), L.T * L.I, s.B, static_cast<int32_t>(L.I),
-                         static_cast<int32_t>(L.ip), static_cast<int32_t>(L.io));
-      ARD_LAUNCH_CHECK();
-    }
+    if (L.ip > 1)
+      ARD_HIP_CHECK(zero_rows(static_cast<float*>(dX), L.T * L.I, s.B, static_cast<int32_t>(L.I),
+                              static_cast<int32_t>(L.ip), static_cast<int32_t>(L.io), sm));
   }
   return ARD_OK;
 }
