@@ -46,7 +46,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 enum LoadMode { KC_VEC = 0, KC_ELEM = 1, MC_VEC = 2, MC_ELEM = 3 };
-// EPI_COLS: EPI_FWD with blocked output columns (GemmOutput::nblk).
+// EPI_COLS: EPI_FWD with blocked columns (GemmArgs::nblk).
 enum Epilogue { EPI_STORE = 0, EPI_FWD = 1, EPI_COLS = 2 };
 
 struct GemmOperand {
@@ -59,11 +59,6 @@ struct GemmOperand {
   int32_t relu;          // gated operand: multiply by [Y > 0]
   float scale;           // unused by the loaders (kept for layout stability)
   int64_t kbstride;      // elements between K batches (see GemmArgs::kbatch)
-  // n-contiguous B operand of an EPI_COLS problem: column n lies at
-  // (n / nblk) * nstride + n % nblk of a row (the samples of several steps side
-  // by side); nblk a whole number of 16-byte chunks
-  int32_t nblk;
-  int64_t nstride;
 };
 
 struct GemmOutput {
@@ -80,24 +75,10 @@ struct GemmOutput {
                          // position (the ReLU derivative of the layer below)
   int64_t col_stride;    // elements between consecutive output columns when cidx is NULL (0 = 1)
   int64_t bias_stride;   // elements between the bias entries of consecutive rows when ridx is NULL (0 = 1)
-  // EPI_COLS: column n lies at (n / nblk) * nstride + n % nblk of a row and is
-  // written where n % nblk < nvalid; nblk a multiple of 4
-  int32_t nblk, nvalid;
-  int64_t nstride;
 };
 
-// Output column offset of compact column n (EPI_COLS: and whether it is
-// written), and bias index of compact row m.
-template <int EPI>
-__device__ __forceinline__ bool col_in(const GemmOutput& c, int n) {
-  return EPI != EPI_COLS || n % c.nblk < c.nvalid;
-}
-template <int EPI = EPI_FWD>
+// Output column offset of compact column n, and bias index of compact row m.
 __device__ __forceinline__ int64_t out_col(const GemmOutput& c, int64_t n) {
-  if constexpr (EPI == EPI_COLS) {
-    const int32_t t = static_cast<int32_t>(n) / c.nblk;
-    return t * c.nstride + (static_cast<int32_t>(n) - t * c.nblk);
-  }
   return c.cidx ? static_cast<int64_t>(c.cidx[n]) : n * (c.col_stride > 1 ? c.col_stride : 1);
 }
 __device__ __forceinline__ int64_t bias_row(const GemmOutput& c, int64_t m) {
@@ -125,7 +106,27 @@ struct GemmArgs {
   float* partial;
   float* rsum;
   int64_t rsum_ld, rsum_bstride;
+  // EPI_COLS: column n of B (n-contiguous) and of C lies at (n / nblk) * nstride
+  // + n % nblk of a row (the samples of several steps side by side), and C's is
+  // written where n % nblk < nvalid; nblk a multiple of 4. Last, so that the
+  // other kernels' argument layout does not depend on them.
+  int32_t nblk, nvalid;
+  int64_t b_nstride, c_nstride;
 };
+
+// EPI_COLS: whether compact column n is written, and where it lies.
+template <int EPI>
+__device__ __forceinline__ bool col_in(const GemmArgs& g, int n) {
+  return EPI != EPI_COLS || n % g.nblk < g.nvalid;
+}
+template <int EPI>
+__device__ __forceinline__ int64_t out_col(const GemmArgs& g, int64_t n) {
+  if constexpr (EPI == EPI_COLS) {
+    const int32_t t = static_cast<int32_t>(n) / g.nblk;
+    return t * g.c_nstride + (static_cast<int32_t>(n) - t * g.nblk);
+  }
+  return out_col(g.c, n);
+}
 
 template <typename T>
 struct TypeTraits;
@@ -395,8 +396,8 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, f32x16 (&acc)[Cfg:
 #pragma unroll
       for (int j = 0; j < Cfg::FN; ++j) {
         const int n = n0 + wn * Cfg::TN + 32 * j + lr;
-        if (n >= g.N || !col_in<EPI>(g.c, n)) continue;
-        const int64_t o = orow * g.c.ld + out_col<EPI>(g.c, n);
+        if (n >= g.N || !col_in<EPI>(g, n)) continue;
+        const int64_t o = orow * g.c.ld + out_col<EPI>(g, n);
         float v = epilogue<EPI>(g.c, acc[i][j][r], bias);
         if (EPI != EPI_STORE && g.c.gate && !(to_f32(static_cast<const OutT*>(g.c.gate)[bz * g.c.bstride + o]) > 0.0f))
           v = 0.0f;

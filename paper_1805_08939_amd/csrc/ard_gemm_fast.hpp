@@ -169,7 +169,7 @@ struct DmaSrc {
   uint32_t off0[PER_WAVE];  // the same chunk at k (KC) or k-row (MC) 0 of the slab
   int k[PER_WAVE];          // the chunk's k (KC) or k-row (MC) within the slab
 
-  // nblk > 0: m/n-contiguous with blocked columns (GemmOperand::nblk)
+  // nblk > 0: m/n-contiguous with blocked columns (GemmArgs::nblk)
   __device__ __forceinline__ void init(int64_t ld, int r0, int rext, int wave, int nblk = 0, int64_t nstride = 0) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -776,7 +776,8 @@ __device__ __forceinline__ void fast_store(const GemmArgs& g, f32x16 (&acc)[Cfg:
                          : nullptr;
   const int64_t piece = 4 * es;
   const bool vec = (part || (g.c.cidx == nullptr && g.c.col_stride <= 1 && g.c.ridx == nullptr)) &&
-                   (EPI != EPI_COLS || (g.c.nstride % 4 == 0 && g.c.nvalid % 4 == 0)) && (ld * es) % piece == 0 && reinterpret_cast<uintptr_t>(base) % piece == 0 &&
+                   (EPI != EPI_COLS || (g.c_nstride % 4 == 0 && g.nvalid % 4 == 0)) && (ld * es) % piece == 0 &&
+                   reinterpret_cast<uintptr_t>(base) % piece == 0 &&
                    reinterpret_cast<uintptr_t>(gate) % piece == 0;
   if (!vec) {
     store_tile<OutT, Cfg, EPI>(g, acc, m0, n0, wm, wn, bz, split);
@@ -845,8 +846,8 @@ __device__ __forceinline__ void fast_store(const GemmArgs& g, f32x16 (&acc)[Cfg:
       const f32x4 v = *reinterpret_cast<const f32x4*>(region + rl * ROW + ch * 16);
       const int m = m0w + 32 * i + rl, n = n0w + 4 * ch;
       if (m >= g.M) continue;
-      if (EPI == EPI_COLS && !part && !col_in<EPI>(g.c, n)) continue;
-      const int64_t o = static_cast<int64_t>(m) * ld + (EPI == EPI_COLS && !part ? out_col<EPI>(g.c, n) : n);
+      if (EPI == EPI_COLS && !part && !col_in<EPI>(g, n)) continue;
+      const int64_t o = static_cast<int64_t>(m) * ld + (EPI == EPI_COLS && !part ? out_col<EPI>(g, n) : n);
       if (part) {
         float* out = reinterpret_cast<float*>(base) + o;
         if (n + 3 < g.N) {
@@ -966,7 +967,7 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
     if (q0 < q1) {
       ld.da.init(g.a.ld, m0, g.M, ld.wv);
       if constexpr (EPI == EPI_COLS && LD == LOAD_DMA)
-        ld.db.init(g.b.ld, n0, g.N, ld.wv, g.b.nblk, g.b.nstride);
+        ld.db.init(g.b.ld, n0, g.N, ld.wv, g.nblk, g.b_nstride);
       else
         ld.db.init(g.b.ld, n0, g.N, ld.wv);
     }
@@ -1049,14 +1050,14 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
       for (int u = 0; u < Cfg::KSPLIT; ++u) v += red[((u * Cfg::WGM * Cfg::WGN + wmn) * NREG + t) * 64 + lane];
       const int m = m0 + wm * Cfg::TM + 32 * i + 8 * (r >> 2) + 4 * lh + (r & 3);
       const int n = n0 + wn * Cfg::TN + 32 * j + lr;
-      if (m >= g.M || n >= g.N || !col_in<EPI>(g.c, n)) continue;
+      if (m >= g.M || n >= g.N || !col_in<EPI>(g, n)) continue;
       if (splits > 1) {
         g.partial[(bz * splits + split) * static_cast<int64_t>(g.M) * g.N + static_cast<int64_t>(m) * g.N + n] = v;
         continue;
       }
       const int64_t orow = gather(g.c.ridx, m);
       const float bias = (EPI != EPI_STORE && g.c.bias) ? g.c.bias[bias_row(g.c, m)] : 0.0f;
-      const int64_t o = orow * g.c.ld + out_col<EPI>(g.c, n);
+      const int64_t o = orow * g.c.ld + out_col<EPI>(g, n);
       v = epilogue<EPI>(g.c, v, bias);
       if (EPI != EPI_STORE && g.c.gate && !(to_f32(static_cast<const OutT*>(g.c.gate)[bz * g.c.bstride + o]) > 0.0f))
         v = 0.0f;
@@ -1500,8 +1501,8 @@ inline bool any_pair_ok(const GemmArgs& g1, const GemmArgs& g2, int64_t cap) {
 // span below 2^31 bytes with the blocks' strides.
 template <bool AMC>
 inline bool cols_ok(const GemmArgs& g) {
-  if (!fast_ok<AMC, true>(g, 4) || g.b.nblk <= 0 || g.b.nblk % 4 || g.b.nstride % 4 || g.c.nblk % 4) return false;
-  return ((static_cast<int64_t>(g.N) / g.b.nblk + 1) * g.b.nstride + 256 * g.b.ld) * 4 < (int64_t{1} << 31);
+  if (!fast_ok<AMC, true>(g, 4) || g.nblk <= 0 || g.nblk % 4 || g.b_nstride % 4) return false;
+  return ((static_cast<int64_t>(g.N) / g.nblk + 1) * g.b_nstride + 256 * g.b.ld) * 4 < (int64_t{1} << 31);
 }
 template <bool AMC>
 inline hipError_t run_cols_gemm(GemmArgs g, hipStream_t stream) {

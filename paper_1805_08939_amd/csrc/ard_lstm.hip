@@ -797,11 +797,11 @@ hipError_t zero_rows(float* out, int64_t rows, int32_t cols, int32_t H, int32_t 
 // one product over the T Bp columns of all steps; nvalid of each Bp columns are
 // written. N = 0 where their number does not fit.
 GemmArgs all_steps(GemmArgs g, const Layout& L, int32_t nvalid) {
-  g.b.nblk = g.c.nblk = static_cast<int32_t>(L.Bp);
-  g.b.nstride = g.b.bstride;
-  g.c.nstride = g.c.bstride;
+  g.nblk = static_cast<int32_t>(L.Bp);
+  g.b_nstride = g.b.bstride;
+  g.c_nstride = g.c.bstride;
   g.b.bstride = g.c.bstride = 0;
-  g.c.nvalid = nvalid;
+  g.nvalid = nvalid;
   g.N = L.T * L.Bp < (int64_t{1} << 30) ? static_cast<int32_t>(L.T * L.Bp) : 0;
   return g;
 }
