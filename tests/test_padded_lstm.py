@@ -1,0 +1,70 @@
+"""The LSTM's products over all steps at once at batches that are padded inside
+(no multiple of 4), and the fp32 tile configurations and splits of the FC
+products, with the reported workspace and the smallest accepted one."""
+import pytest
+import torch
+
+from gpu_util import device
+from paper_1805_08939_amd import api, synth
+from test_lstm_parity import run_lstm
+
+pytestmark = pytest.mark.gpu
+
+
+# (T, B, I, H), hidden pattern, input pattern: padded batches of one sample to
+# more than one tile; 32-, 64- and 128-wide tiles of T * Bp columns that end
+# inside a step; flat contractions over T * Bp with remainders of a slab, in the
+# gathered and the identity layout; rows of X that are no multiple of 16 bytes
+LSTM = [((1, 1, 3, 5), (1, 0), (1, 0)), ((7, 1, 40, 64), (2, 1), (1, 0)), ((35, 5, 96, 130), (2, 0), (3, 1)),
+        ((9, 10, 300, 512), (2, 1), (1, 0)), ((5, 20, 256, 1024), (2, 1), (2, 0)), ((3, 66, 130, 96), (3, 2), (1, 0)),
+        ((2, 129, 512, 256), (1, 0), (4, 1)), ((20, 64, 768, 640), (2, 0), (1, 0))]
+
+
+@pytest.mark.parametrize("shape,pattern,in_pattern", LSTM)
+@pytest.mark.parametrize("states", [True, False])
+def test_products_over_all_steps(shape, pattern, in_pattern, states):
+    print(shape, pattern, in_pattern, states, flush=True)
+    run_lstm(*shape, pattern, seed=sum(shape), with_state=states, with_final_grads=states, in_pattern=in_pattern)
+
+
+# (batch, inputs, outputs): 128x128, 64x64 (two depths) and 32x32 tiles of the
+# three products, with and without a split contraction, remainders of each
+FC = [(2048, 1536, 2240), (1028, 2052, 1028), (260, 4100, 516), (20, 9000, 1500), (700, 3004, 1500), (64, 8200, 68)]
+
+
+@pytest.mark.parametrize("shape", FC)
+def test_f32_tiles_and_workspaces(shape):
+    B, K, N = shape
+    g = synth.generator(41)
+    X, W = synth.normal(g, (K, B)).to(device()), synth.normal(g, (N, K)).to(device())
+    dY, b = synth.normal(g, (N, B)).to(device()), synth.normal(g, (N,)).to(device())
+    plan = [api.ard_plan_rows(n, 1, 0, None) for n in (K, N)]
+    desc = api.fc_desc(api.ARD_F32, B, K, N, plan[0], plan[1], 1.0, api.ARD_ACT_NONE, api.ARD_DROPPED_SKIP,
+                       api.ARD_WEIGHTS_FULL)
+    full = api.ard_fc_workspace_bytes(desc)
+    sizes = [full] + [s for s in (full * 3 // 4, full // 2, full // 4, full // 8, 0) if s < full]
+    x, w, dy = X.double(), W.double(), dY.double()
+    want = [(w @ x + b.double()[:, None], w.abs() @ x.abs()), (w.t() @ dy, w.abs().t() @ dy.abs()),
+            (dy @ x.t(), dy.abs() @ x.abs().t()), (dy.sum(1), dy.abs().sum(1))]
+    ran = 0
+    for size in sizes:
+        print(shape, size, flush=True)
+        ws = torch.full((size // 16 * 4 + 64,), float("nan"), device=device())  # 256 bytes more than are named
+        use = ws[:size // 16 * 4] if size >= 16 else None
+        Y, dX = torch.full((N, B), 7.0, device=device()), torch.full((K, B), 7.0, device=device())
+        dW, db = torch.full((N, K), 7.0, device=device()), torch.full((N,), 7.0, device=device())
+        try:
+            api.ard_fc_fwd(desc, X, W, b, Y, use)
+            api.ard_fc_bwd(desc, X, dY, None, W, dX, dW, db, use)
+        except api.ArdError:
+            assert size < full  # a smaller one may be refused, but never overrun
+            continue
+        finally:
+            torch.cuda.synchronize()
+            assert torch.isnan(ws[size // 16 * 4:]).all()
+        ran += 1
+        for got, (v, norm) in zip((Y, dX, dW, db), want):
+            # fp32 sums of up to 9000 terms in at least 8 chains: (9000 / 8) 2^-24 = 7e-5 at the most, typically its
+            # square root's worth (2e-6); the bias is one term more
+            assert ((got.double() - v).abs() <= 1e-5 * norm + 1e-6).all()
+    assert ran > 0
