@@ -43,7 +43,7 @@ namespace ard {
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
-template <typename T_, int BM_, int BN_, int BK_, int STAGES_, int WGM_, int WGN_, int KSPLIT_>
+template <typename T_, int BM_, int BN_, int BK_, int STAGES_, int WGM_, int WGN_, int KSPLIT_, int CHAINS_ = 1>
 struct FastCfg {
   using T = T_;
   static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_;
@@ -52,6 +52,7 @@ struct FastCfg {
   static constexpr int TM = BM / WGM, TN = BN / WGN;  // wave tile
   static constexpr int FM = TM / 32, FN = TN / 32;    // 32x32 MFMA blocks per wave
   static constexpr int KW = BK / KSPLIT;              // k per wave per slab
+  static constexpr int CHAINS = CHAINS_;              // accumulators per output (AccChains)
   static constexpr int ES = sizeof(T);
   static constexpr int ABYTES = BM * BK * ES, BBYTES = BN * BK * ES;
   static constexpr int STAGE = ABYTES + BBYTES;
@@ -374,6 +375,47 @@ struct StepFrags {
   }
 };
 
+// The accumulators of a wave. With CHAINS > 1 the k steps of a slab go to CHAINS
+// sums in turn, added at the end: a fp32 sum's rounding error grows with the
+// length of its chain of additions, and a tile that does not split its slab's
+// k over waves would run one chain as long as the contraction.
+template <class Cfg>
+struct AccChains {
+  using Acc = f32x16[Cfg::FM][Cfg::FN];
+  Acc& first;
+  f32x16 more[Cfg::CHAINS > 1 ? Cfg::CHAINS - 1 : 1][Cfg::FM][Cfg::FN];
+
+  __device__ __forceinline__ explicit AccChains(Acc& acc) : first(acc) {
+#pragma unroll
+    for (int c = 0; c < Cfg::CHAINS - 1; ++c)
+#pragma unroll
+      for (int i = 0; i < Cfg::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < Cfg::FN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) more[c][i][j][r] = 0.0f;
+  }
+  __device__ __forceinline__ Acc& of(int s) {  // k step s, a constant where it is used
+    return s % Cfg::CHAINS == 0 ? first : more[s % Cfg::CHAINS - 1];
+  }
+  __device__ __forceinline__ void sum() {
+    auto add = [](Acc& a, const Acc& b) {
+#pragma unroll
+      for (int i = 0; i < Cfg::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < Cfg::FN; ++j) a[i][j] += b[i][j];
+    };
+    static_assert(Cfg::CHAINS == 1 || Cfg::CHAINS == 2 || Cfg::CHAINS == 4, "pairwise sum");
+    if constexpr (Cfg::CHAINS == 4) {
+      add(first, more[0]);
+      add(more[1], more[2]);
+      add(first, more[1]);
+    } else if constexpr (Cfg::CHAINS == 2) {
+      add(first, more[0]);
+    }
+  }
+};
+
 // The direct loads of one operand pair, slab after slab: wave-uniform
 // pointers to the next slab's first element, its first k, its stage, and how
 // many slabs of the split are still to come after it. Past the last slab the
@@ -523,6 +565,8 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
   using Frags = StepFrags<Cfg, AMC, BMC>;
   constexpr int STEPS = Cfg::KW / Frags::KSTEP;
   static_assert(STEPS % 2 == 0, "a slab holds an even number of k steps");
+  static_assert(STEPS % Cfg::CHAINS == 0, "every chain takes the same k steps of a slab");
+  AccChains<Cfg> ch(acc);
   int cs = 0;  // stage of the slab being computed
   Frags fr[2];
   char* st = smem;
@@ -562,7 +606,7 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
         ld.issue_a();  // into the stage of slab q; B half after the next slab's first k step
         fr[(s + 1) & 1].load(st, wm, wn, kw0);
       }
-      fr[s & 1].mma(acc);
+      fr[s & 1].mma(ch.of(s));
       if constexpr (RSUM) fr[s & 1].rowsum(*reinterpret_cast<float(*)[Cfg::FM]>(rs));
       if (s == 0) ld.issue_b();
     }
@@ -571,11 +615,12 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
       if (s + 1 < STEPS) fr[(s + 1) & 1].load(st, wm, wn, kw0 + (s + 1) * Frags::KSTEP);
-      fr[s & 1].mma(acc);
+      fr[s & 1].mma(ch.of(s));
       if constexpr (RSUM) fr[s & 1].rowsum(*reinterpret_cast<float(*)[Cfg::FM]>(rs));
       if (s == 0) ld.issue_b();
     }
   }
+  ch.sum();
   wait_vm<0>();  // no direct load may still write LDS past this point
 }
 
@@ -729,7 +774,9 @@ __device__ __forceinline__ void run_slabs_reg(RegLoader<Cfg, AMC, BMC>& ld, int 
   using Frags = StepFrags<Cfg, AMC, BMC>;
   constexpr int STEPS = Cfg::KW / Frags::KSTEP;
   static_assert(Cfg::STAGES >= 2, "two LDS stages");
+  static_assert(STEPS % Cfg::CHAINS == 0, "every chain takes the same k steps of a slab");
   if (nslab <= 0) return;
+  AccChains<Cfg> ch(acc);
   typename RegLoader<Cfg, AMC, BMC>::Regs buf[2];
   ld.load(buf[0]);
   if (nslab > 1) ld.load(buf[1]);
@@ -743,7 +790,7 @@ __device__ __forceinline__ void run_slabs_reg(RegLoader<Cfg, AMC, BMC>& ld, int 
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
       if (s + 1 < STEPS) fr[(s + 1) & 1].load(st, wm, wn, kw0 + (s + 1) * Frags::KSTEP);
-      fr[s & 1].mma(acc);
+      fr[s & 1].mma(ch.of(s));
       if constexpr (RSUM) fr[s & 1].rowsum(*reinterpret_cast<float(*)[Cfg::FM]>(rs));
     }
     if (q + 1 < nslab) ld.store(smem + (par ^ 1) * Cfg::STAGE, buf[par ^ 1]);
@@ -754,6 +801,7 @@ __device__ __forceinline__ void run_slabs_reg(RegLoader<Cfg, AMC, BMC>& ld, int 
     slab(q, 0);
     if (q + 1 < nslab) slab(q + 1, 1);
   }
+  ch.sum();
 }
 
 // Output of one wave's accumulator tile. Each block row of 32 rows passes
@@ -1167,11 +1215,15 @@ struct FastCfgs<float> {
   // on MI355X, 2048 x 2240 x 1024: 128 x 128 tiles with 4 stages (one workgroup)
   // 147 us, 2 stages 136; 64 x 64 x 64 with 3 stages 119, 2 stages 94; 64 x 64 x
   // 32 with 3 stages 93. 8800 x 700 x 750: 107, 99, 104, 87, 84 us.
-  using Huge = FastCfg<float, 128, 128, 32, 2, 2, 4, 1>;  // 64 KB, 8 waves
+  // Their last parameter is the number of accumulators per output (AccChains):
+  // with one, the 1500 -> 8800 layer at batch 700 (forward and backward) is
+  // 8.4e-7 off the 64-bit result and takes 301 us, with these 4.2e-7 and 302 us;
+  // an LSTM 1024 -> 1024, T 35, batch 64: 8.2e-7, 916 us and 4.7e-7, 916 us.
+  using Huge = FastCfg<float, 128, 128, 32, 2, 2, 4, 1, 2>;  // 64 KB, 8 waves
   using Wide = Huge;
   using Tall = Huge;
-  using Big = FastCfg<float, 64, 64, 64, 2, 2, 2, 2>;     // 64 KB, 8 waves on 32-deep k shares
-  using Mid = FastCfg<float, 64, 64, 32, 3, 2, 2, 1>;     // 48 KB, 4 waves
+  using Big = FastCfg<float, 64, 64, 64, 2, 2, 2, 2, 2>;     // 64 KB, 8 waves on 32-deep k shares
+  using Mid = FastCfg<float, 64, 64, 32, 3, 2, 2, 1, 4>;     // 48 KB, 4 waves
   using Narrow = FastCfg<float, 128, 32, 32, 4, 2, 1, 2>; // 80 KB, 4 waves on 16-deep k shares
   using Small = FastCfg<float, 32, 32, 128, 4, 1, 1, 8>;  // 128 KB, 8 waves on 16-deep k shares
 };
