@@ -1315,6 +1315,22 @@ int tile_part_check(const ard_tile_plan* p, int32_t cols, const void* W) {
 int tile_part_f32(bool fwd, const ard_tile_plan* p, const TilePart& t, void* stream, int* splits_left) {
   if (splits_left) *splits_left = 1;
   if (t.own_count <= 0 || t.cols <= 0) return ARD_OK;
+  const int owners = fwd ? p->tiles_n : p->tiles_k, others = fwd ? p->tiles_k : p->tiles_n;
+  // The wave kernels' chunk offsets from a part's first element: 32 rows of act
+  // (tile + 1 of W) below 2^31 bytes. Longer rows are those of a step's
+  // contiguous copies, whose product is the whole one: the register-staged
+  // kernel with 64-bit addresses takes it.
+  if (int64_t{32} * t.lda * 4 >= int64_t{1} << 31 || static_cast<int64_t>(p->tile + 1) * p->k * 4 >= int64_t{1} << 31) {
+    if (t.own0 != 0 || t.own_count != owners || t.lo != 0 || t.hi != others || t.lda != t.cols || t.ldo != t.cols ||
+        t.nb != t.cols || t.nv != t.cols)
+      return fail(ARD_ERR_UNSUPPORTED, "part of a tile product with rows of %d columns", t.lda);
+    const TdpArgs a = {t.act, nullptr, t.W, t.out, t.cols, p->n, p->k, p->tile, p->tiles_k,
+                       fwd ? p->d_row_ptr : p->d_col_ptr, fwd ? p->d_row_cols : p->d_col_rows, 1.0f,
+                       p->d_row_ptr + p->tiles_n};
+    ARD_HIP_CHECK(run_tdp<float>(fwd ? TDP_FWD : TDP_BWD_DATA, a, owners, p->nnz, owners * others,
+                                 static_cast<hipStream_t>(stream)));
+    return ARD_OK;
+  }
   TileWaveArgs w = {};
   w.act = t.act;
   w.W = t.W;
@@ -1332,7 +1348,7 @@ int tile_part_f32(bool fwd, const ard_tile_plan* p, const TilePart& t, void* str
   w.ny = t.own_count * (p->tile / 32);
   w.own0 = t.own0;
   w.lo = t.lo;
-  w.hi = t.lo == 0 && t.hi >= (fwd ? p->tiles_k : p->tiles_n) ? kAllTiles : t.hi;
+  w.hi = t.lo == 0 && t.hi >= others ? kAllTiles : t.hi;
   w.scale = 1.0f;
   w.splits = 1;
   w.partial = t.partial;
