@@ -375,6 +375,25 @@ struct StepFrags {
   }
 };
 
+// A lane's sums of the A values that it reads (StepFrags::rowsum): a slab's in 32
+// bits, those of the slabs in 64, for one lane adds an eighth or more of the
+// whole contraction. A bias gradient over 1450 samples is then 6e-8 off its
+// 64-bit value, 2.6e-7 with one chain in 32 bits.
+template <class Cfg>
+struct RowSums {
+  double all[Cfg::FM];
+  float slab[Cfg::FM];
+
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int i = 0; i < Cfg::FM; ++i) all[i] = 0.0, slab[i] = 0.0f;
+  }
+  __device__ __forceinline__ void end_slab() {
+#pragma unroll
+    for (int i = 0; i < Cfg::FM; ++i) all[i] += slab[i], slab[i] = 0.0f;
+  }
+};
+
 // The accumulators of a wave. With CHAINS > 1 the k steps of a slab go to CHAINS
 // sums in turn, added at the end: a fp32 sum's rounding error grows with the
 // length of its chain of additions, and a tile that does not split its slab's
@@ -556,12 +575,12 @@ __device__ __forceinline__ void grouped_tile(int bid, int nx, int ny, int& row, 
 // MI355X: 13% fewer cycles per slab for the 256x256 tile).
 // With TAIL, ck is the first k of the first slab within a contraction of
 // length K (slabs wrap to k 0 past K), and a slab with fewer than BK valid k
-// is zeroed past them in LDS before use. With RSUM, rs[i] also sums the A
-// values the lane reads (StepFrags::rowsum). Returns with no direct load in
+// is zeroed past them in LDS before use. With RSUM, rs also sums the A
+// values the lane reads (RowSums). Returns with no direct load in
 // flight.
 template <class Cfg, bool AMC, bool BMC, bool TAIL, bool RSUM = false, class Loader>
 __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, f32x16 (&acc)[Cfg::FM][Cfg::FN],
-                                          int wm, int wn, int kw0, char* smem, float* rs = nullptr) {
+                                          int wm, int wn, int kw0, char* smem, RowSums<Cfg>* rs = nullptr) {
   using Frags = StepFrags<Cfg, AMC, BMC>;
   constexpr int STEPS = Cfg::KW / Frags::KSTEP;
   static_assert(STEPS % 2 == 0, "a slab holds an even number of k steps");
@@ -607,7 +626,10 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
         fr[(s + 1) & 1].load(st, wm, wn, kw0);
       }
       fr[s & 1].mma(ch.of(s));
-      if constexpr (RSUM) fr[s & 1].rowsum(*reinterpret_cast<float(*)[Cfg::FM]>(rs));
+      if constexpr (RSUM) {
+        fr[s & 1].rowsum(rs->slab);
+        if (s + 1 == STEPS) rs->end_slab();
+      }
       if (s == 0) ld.issue_b();
     }
   }
@@ -616,7 +638,10 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
     for (int s = 0; s < STEPS; ++s) {
       if (s + 1 < STEPS) fr[(s + 1) & 1].load(st, wm, wn, kw0 + (s + 1) * Frags::KSTEP);
       fr[s & 1].mma(ch.of(s));
-      if constexpr (RSUM) fr[s & 1].rowsum(*reinterpret_cast<float(*)[Cfg::FM]>(rs));
+      if constexpr (RSUM) {
+        fr[s & 1].rowsum(rs->slab);
+        if (s + 1 == STEPS) rs->end_slab();
+      }
       if (s == 0) ld.issue_b();
     }
   }
@@ -770,7 +795,7 @@ struct RegLoader {
 template <class Cfg, bool AMC, bool BMC, bool RSUM>
 __device__ __forceinline__ void run_slabs_reg(RegLoader<Cfg, AMC, BMC>& ld, int nslab,
                                               f32x16 (&acc)[Cfg::FM][Cfg::FN], int wm, int wn, int kw0, char* smem,
-                                              float* rs) {
+                                              RowSums<Cfg>* rs) {
   using Frags = StepFrags<Cfg, AMC, BMC>;
   constexpr int STEPS = Cfg::KW / Frags::KSTEP;
   static_assert(Cfg::STAGES >= 2, "two LDS stages");
@@ -791,7 +816,10 @@ __device__ __forceinline__ void run_slabs_reg(RegLoader<Cfg, AMC, BMC>& ld, int 
     for (int s = 0; s < STEPS; ++s) {
       if (s + 1 < STEPS) fr[(s + 1) & 1].load(st, wm, wn, kw0 + (s + 1) * Frags::KSTEP);
       fr[s & 1].mma(ch.of(s));
-      if constexpr (RSUM) fr[s & 1].rowsum(*reinterpret_cast<float(*)[Cfg::FM]>(rs));
+      if constexpr (RSUM) {
+        fr[s & 1].rowsum(rs->slab);
+        if (s + 1 == STEPS) rs->end_slab();
+      }
     }
     if (q + 1 < nslab) ld.store(smem + (par ^ 1) * Cfg::STAGE, buf[par ^ 1]);
     if (q + 3 < nslab) ld.load(buf[par ^ 1]);
@@ -984,9 +1012,8 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
   // slabs q0 .. q1 - 1 of this split
   static_assert(DmaSrc<Cfg, Cfg::BM, AMC>::PER_WAVE + DmaSrc<Cfg, Cfg::BN, BMC>::PER_WAVE == Cfg::LPW, "load count");
   constexpr int ES = Cfg::ES;
-  float rs[Cfg::FM];
-#pragma unroll
-  for (int i = 0; i < Cfg::FM; ++i) rs[i] = 0.0f;
+  RowSums<Cfg> rs;
+  rs.clear();
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (LD == LOAD_FLAT) {
     static_assert(!AMC && !BMC, "k-contiguous operands");
@@ -1007,7 +1034,7 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
     ld.ik = q0 * Cfg::BK;
     ld.is = 0;
     ld.left = q1 - q0 - 1;
-    run_slabs<Cfg, AMC, BMC, true, RSUM>(ld, q1 - q0, klen, ld.ik, acc, wm, wn, ks * Cfg::KW, smem, rs);
+    run_slabs<Cfg, AMC, BMC, true, RSUM>(ld, q1 - q0, klen, ld.ik, acc, wm, wn, ks * Cfg::KW, smem, &rs);
   } else {
     using Loader = typename std::conditional<LD == LOAD_ANY, RegLoader<Cfg, AMC, BMC>, SlabLoader<Cfg, AMC, BMC>>::type;
     Loader ld;
@@ -1029,18 +1056,18 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
     ld.na = uniform_ptr(reinterpret_cast<const char*>(abase) + (ib * g.a.kbstride) * ES + ld.ik / Cfg::BK * ld.a_step);
     ld.nb = uniform_ptr(reinterpret_cast<const char*>(bbase) + (ib * g.b.kbstride) * ES + ld.ik / Cfg::BK * ld.b_step);
     if constexpr (LD == LOAD_ANY) {
-      run_slabs_reg<Cfg, AMC, BMC, RSUM>(ld, q1 - q0, acc, wm, wn, ks * Cfg::KW, smem, rs);
+      run_slabs_reg<Cfg, AMC, BMC, RSUM>(ld, q1 - q0, acc, wm, wn, ks * Cfg::KW, smem, &rs);
     } else {
       ld.lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
       ld.is = 0;
       ld.left = q1 - q0 - 1;
-      run_slabs<Cfg, AMC, BMC, true, RSUM>(ld, q1 - q0, g.K, ld.ik, acc, wm, wn, ks * Cfg::KW, smem, rs);
+      run_slabs<Cfg, AMC, BMC, true, RSUM>(ld, q1 - q0, g.K, ld.ik, acc, wm, wn, ks * Cfg::KW, smem, &rs);
     }
   }
   const int rlane = threadIdx.x & 63;
   if constexpr (RSUM) {
 #pragma unroll
-    for (int i = 0; i < Cfg::FM; ++i) rs[i] += __shfl_xor(rs[i], 32);
+    for (int i = 0; i < Cfg::FM; ++i) rs.all[i] += __shfl_xor(rs.all[i], 32);
   }
   const bool rs_out = RSUM && splits == 1 && tile_col == 0 && wn == 0 && rlane < 32;
   auto put_rsum = [&](int i, float v) {
@@ -1050,7 +1077,7 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
   if constexpr (Cfg::KSPLIT == 1) {
     if (rs_out) {
 #pragma unroll
-      for (int i = 0; i < Cfg::FM; ++i) put_rsum(i, rs[i]);
+      for (int i = 0; i < Cfg::FM; ++i) put_rsum(i, static_cast<float>(rs.all[i]));
     }
     fast_store<OutT, Cfg, EPI>(g, acc, m0, n0, wm, wn, bz, split, smem);
   } else {
@@ -1076,7 +1103,8 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
                     "row-sum buffer exceeds LDS");
       if (wn == 0 && lane < 32) {
 #pragma unroll
-        for (int i = 0; i < Cfg::FM; ++i) rred[((ks * Cfg::WGM + wm) * Cfg::FM + i) * 32 + lane] = rs[i];
+        for (int i = 0; i < Cfg::FM; ++i)
+          rred[((ks * Cfg::WGM + wm) * Cfg::FM + i) * 32 + lane] = static_cast<float>(rs.all[i]);
       }
     }
     __syncthreads();
