@@ -356,13 +356,15 @@ struct StepFrags {
     }
   }
 
-  __device__ __forceinline__ void mma(f32x16 (&acc)[Cfg::FM][Cfg::FN]) const {
+  // acc(m): the accumulators of MFMA m of this k step (one of 16 bf16 k, four of 2 fp32 k).
+  template <class Accs>
+  __device__ __forceinline__ void mma_to(Accs acc) const {
     if constexpr (Cfg::ES == 2) {
 #pragma unroll
       for (int i = 0; i < Cfg::FM; ++i)
 #pragma unroll
         for (int j = 0; j < Cfg::FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+          acc(0)[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc(0)[i][j], 0, 0, 0);
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -370,8 +372,11 @@ struct StepFrags {
         for (int i = 0; i < Cfg::FM; ++i)
 #pragma unroll
           for (int j = 0; j < Cfg::FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+            acc(e)[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc(e)[i][j], 0, 0, 0);
     }
+  }
+  __device__ __forceinline__ void mma(f32x16 (&acc)[Cfg::FM][Cfg::FN]) const {
+    mma_to([&](int) -> f32x16(&)[Cfg::FM][Cfg::FN] { return acc; });
   }
 };
 
@@ -394,7 +399,7 @@ struct RowSums {
   }
 };
 
-// The accumulators of a wave. With CHAINS > 1 the k steps of a slab go to CHAINS
+// The accumulators of a wave. With CHAINS > 1 the MFMAs of a slab go to CHAINS
 // sums in turn, added at the end: a fp32 sum's rounding error grows with the
 // length of its chain of additions, and a tile that does not split its slab's
 // k over waves would run one chain as long as the contraction.
@@ -414,8 +419,13 @@ struct AccChains {
 #pragma unroll
           for (int r = 0; r < 16; ++r) more[c][i][j][r] = 0.0f;
   }
-  __device__ __forceinline__ Acc& of(int s) {  // k step s, a constant where it is used
-    return s % Cfg::CHAINS == 0 ? first : more[s % Cfg::CHAINS - 1];
+  __device__ __forceinline__ Acc& of(int m) {  // MFMA m of the slab, a constant where it is used
+    return m % Cfg::CHAINS == 0 ? first : more[m % Cfg::CHAINS - 1];
+  }
+  template <class Frags>
+  __device__ __forceinline__ void mma(const Frags& fr, int s) {  // k step s of the slab
+    constexpr int PER = Cfg::ES == 2 ? 1 : 4;                    // MFMAs of a k step per output block
+    fr.mma_to([&](int e) -> Acc& { return of(PER * s + e); });
   }
   __device__ __forceinline__ void sum() {
     auto add = [](Acc& a, const Acc& b) {
@@ -424,14 +434,11 @@ struct AccChains {
 #pragma unroll
         for (int j = 0; j < Cfg::FN; ++j) a[i][j] += b[i][j];
     };
-    static_assert(Cfg::CHAINS == 1 || Cfg::CHAINS == 2 || Cfg::CHAINS == 4, "pairwise sum");
-    if constexpr (Cfg::CHAINS == 4) {
-      add(first, more[0]);
-      add(more[1], more[2]);
-      add(first, more[1]);
-    } else if constexpr (Cfg::CHAINS == 2) {
-      add(first, more[0]);
-    }
+    static_assert((Cfg::CHAINS & (Cfg::CHAINS - 1)) == 0, "pairwise sum");
+#pragma unroll
+    for (int w = 1; w < Cfg::CHAINS; w *= 2)
+#pragma unroll
+      for (int c = 0; c < Cfg::CHAINS; c += 2 * w) add(of(c), of(c + w));
   }
 };
 
@@ -584,7 +591,7 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
   using Frags = StepFrags<Cfg, AMC, BMC>;
   constexpr int STEPS = Cfg::KW / Frags::KSTEP;
   static_assert(STEPS % 2 == 0, "a slab holds an even number of k steps");
-  static_assert(STEPS % Cfg::CHAINS == 0, "every chain takes the same k steps of a slab");
+  static_assert((Cfg::ES == 2 ? STEPS : 4 * STEPS) % Cfg::CHAINS == 0, "every chain takes as many MFMAs of a slab");
   AccChains<Cfg> ch(acc);
   int cs = 0;  // stage of the slab being computed
   Frags fr[2];
@@ -625,7 +632,7 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
         ld.issue_a();  // into the stage of slab q; B half after the next slab's first k step
         fr[(s + 1) & 1].load(st, wm, wn, kw0);
       }
-      fr[s & 1].mma(ch.of(s));
+      ch.mma(fr[s & 1], s);
       if constexpr (RSUM) {
         fr[s & 1].rowsum(rs->slab);
         if (s + 1 == STEPS) rs->end_slab();
@@ -637,7 +644,7 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
       if (s + 1 < STEPS) fr[(s + 1) & 1].load(st, wm, wn, kw0 + (s + 1) * Frags::KSTEP);
-      fr[s & 1].mma(ch.of(s));
+      ch.mma(fr[s & 1], s);
       if constexpr (RSUM) {
         fr[s & 1].rowsum(rs->slab);
         if (s + 1 == STEPS) rs->end_slab();
@@ -799,7 +806,7 @@ __device__ __forceinline__ void run_slabs_reg(RegLoader<Cfg, AMC, BMC>& ld, int 
   using Frags = StepFrags<Cfg, AMC, BMC>;
   constexpr int STEPS = Cfg::KW / Frags::KSTEP;
   static_assert(Cfg::STAGES >= 2, "two LDS stages");
-  static_assert(STEPS % Cfg::CHAINS == 0, "every chain takes the same k steps of a slab");
+  static_assert((Cfg::ES == 2 ? STEPS : 4 * STEPS) % Cfg::CHAINS == 0, "every chain takes as many MFMAs of a slab");
   if (nslab <= 0) return;
   AccChains<Cfg> ch(acc);
   typename RegLoader<Cfg, AMC, BMC>::Regs buf[2];
@@ -815,7 +822,7 @@ __device__ __forceinline__ void run_slabs_reg(RegLoader<Cfg, AMC, BMC>& ld, int 
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
       if (s + 1 < STEPS) fr[(s + 1) & 1].load(st, wm, wn, kw0 + (s + 1) * Frags::KSTEP);
-      fr[s & 1].mma(ch.of(s));
+      ch.mma(fr[s & 1], s);
       if constexpr (RSUM) {
         fr[s & 1].rowsum(rs->slab);
         if (s + 1 == STEPS) rs->end_slab();
@@ -1246,11 +1253,12 @@ struct FastCfgs<float> {
   // Their last parameter is the number of accumulators per output (AccChains):
   // with one, the 1500 -> 8800 layer at batch 700 (forward and backward) is
   // 8.4e-7 off the 64-bit result and takes 301 us, with these 4.2e-7 and 302 us;
-  // an LSTM 1024 -> 1024, T 35, batch 64: 8.2e-7, 916 us and 4.7e-7, 916 us.
+  // an LSTM 1024 -> 1024, T 35, batch 64: 8.2e-7, 916 us and 4.7e-7, 916 us. Big
+  // has as many chains per output as the 32 x 32 tile (8).
   using Huge = FastCfg<float, 128, 128, 32, 2, 2, 4, 1, 2>;  // 64 KB, 8 waves
   using Wide = Huge;
   using Tall = Huge;
-  using Big = FastCfg<float, 64, 64, 64, 2, 2, 2, 2, 2>;     // 64 KB, 8 waves on 32-deep k shares
+  using Big = FastCfg<float, 64, 64, 64, 2, 2, 2, 2, 4>;     // 64 KB, 8 waves on 32-deep k shares
   using Mid = FastCfg<float, 64, 64, 32, 3, 2, 2, 1, 4>;     // 48 KB, 4 waves
   using Narrow = FastCfg<float, 128, 32, 32, 4, 2, 1, 2>; // 80 KB, 4 waves on 16-deep k shares
   using Small = FastCfg<float, 32, 32, 128, 4, 1, 1, 8>;  // 128 KB, 8 waves on 16-deep k shares
@@ -1271,25 +1279,67 @@ inline int fast_splits(int64_t tiles, int64_t slabs) {
   return s;
 }
 
-// fp32 partial sums that a call must be given room for: those of the plan that
-// sized workspaces before the cost model below (the largest tile whose grid
-// covers 5/8 of the chip, splits on long contractions only). A call with more
-// room may split further, one with this much is never refused.
-inline int64_t required_splits_f32(int M, int N, int K) {
-  auto tiles_of = [&](int bm, int bn) { return static_cast<int64_t>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+// The plan that sized workspaces before the cost model below: the largest tile
+// whose grid covers 5/8 of the chip, splits on long contractions only, in at
+// most cap floats. It gives the room that a call must be given (a call with
+// more room may split further, one with this much is never refused), and the
+// precision that a plan must keep: its tiles had no further accumulators.
+inline FastPlan least_plan_f32(int M, int N, int K, int kbatch, int batch, int64_t cap) {
+  using C = FastCfgs<float>;
+  auto tiles_of = [&](int bm, int bn) {
+    return static_cast<int64_t>((M + bm - 1) / bm) * ((N + bn - 1) / bn) * batch;
+  };
+  const int64_t kb = kbatch > 0 ? kbatch : 1;
+  auto slabs_of = [&](int bk) { return kb * ((K + bk - 1) / bk); };
   constexpr int64_t kFill = kTargetBlocks * 5 / 8;
-  if (N <= 32 && tiles_of(128, 32) >= kFill) return K >= 8192 ? fast_splits(tiles_of(128, 32), (K + 31) / 32) : 1;
-  if (M > 64 && N > 64 && tiles_of(128, 128) >= kFill)
-    return K >= 8192 ? fast_splits(tiles_of(128, 128), (K + 31) / 32) : 1;
-  if (tiles_of(64, 64) >= kFill) return K >= 8192 ? fast_splits(tiles_of(64, 64), (K + 63) / 64) : 1;
-  const int64_t slabs = (K + 127) / 128;
-  double best_t = 0.9 * static_cast<double>(slabs);
-  int64_t best = 1;
-  for (int s = 2; s <= kMaxSplits && tiles_of(32, 32) * s <= kTargetBlocks && slabs >= s; s *= 2) {
-    const double t = 0.9 * static_cast<double>((slabs + s - 1) / s) + 3.0;
-    if (t < best_t) best_t = t, best = s;
+  FastPlan p;
+  int64_t tiles;
+  int bk;
+  if (N <= C::Narrow::BN && tiles_of(C::Narrow::BM, C::Narrow::BN) >= kFill) {
+    p.kind = FAST_NARROW, tiles = tiles_of(C::Narrow::BM, C::Narrow::BN), bk = C::Narrow::BK;
+  } else if (M > 64 && N > 64 && tiles_of(128, 128) >= kFill) {
+    p.kind = FAST_HUGE, tiles = tiles_of(128, 128), bk = C::Huge::BK;
+  } else if (tiles_of(64, 64) >= kFill) {
+    p.kind = FAST_BIG, tiles = tiles_of(64, 64), bk = C::Big::BK;
+  } else {
+    p.kind = FAST_SMALL, tiles = tiles_of(32, 32), bk = C::Small::BK;
   }
-  return best;
+  const int64_t slabs = slabs_of(bk);
+  p.splits = 1;
+  if (p.kind == FAST_SMALL) {
+    double best_t = 0.9 * static_cast<double>(slabs);
+    for (int s = 2; s <= kMaxSplits && tiles * s <= kTargetBlocks && slabs >= s; s *= 2) {
+      const double t = 0.9 * static_cast<double>((slabs + s - 1) / s) + 3.0;
+      if (t < best_t) best_t = t, p.splits = s;
+    }
+  } else if (kb * K >= 8192) {
+    p.splits = fast_splits(tiles, slabs);
+  }
+  while (p.splits > 1 && static_cast<int64_t>(p.splits) * M * N * batch > cap) p.splits /= 2;
+  return p;
+}
+
+// MFMAs (of 2 k each) in the longest chain of additions behind one output: its
+// rounding error grows with it. Measured over 120 products of 1 to 3 M outputs, a
+// plan whose chains are no longer than another's is at most 5% (splits by 16)
+// and on average less far from the 64-bit result.
+inline int64_t chain_f32(int bk, int ksplit, int chains, int K, int64_t kb, int splits) {
+  const int64_t slabs = kb * ((K + bk - 1) / bk), q = (slabs + splits - 1) / splits;
+  const int64_t share = bk / ksplit;
+  int64_t last = share;  // k of the first wave in the last slab
+  if (kb == 1 && splits == 1 && K - (slabs - 1) * bk < share) last = K - (slabs - 1) * bk;
+  return ((q - 1) * share + last + 2 * chains - 1) / (2 * chains);
+}
+template <class Cfg>
+inline int64_t chain_f32(int chains, int K, int64_t kb, int splits) {
+  return chain_f32(Cfg::BK, Cfg::KSPLIT, chains, K, kb, splits);
+}
+inline int64_t least_chain_f32(const FastPlan& p, int K, int64_t kb) {
+  using C = FastCfgs<float>;
+  return p.kind == FAST_HUGE     ? chain_f32<C::Huge>(1, K, kb, p.splits)
+         : p.kind == FAST_NARROW ? chain_f32<C::Narrow>(1, K, kb, p.splits)
+         : p.kind == FAST_BIG    ? chain_f32<C::Big>(1, K, kb, p.splits)
+                                 : chain_f32<C::Small>(1, K, kb, p.splits);
 }
 
 // fp32: the (configuration, split) pair with the smallest modelled time, in us.
@@ -1299,18 +1349,21 @@ inline int64_t required_splits_f32(int M, int N, int K) {
 // plus the fixed time of a launch, its first slabs and its stores; the 32 x 32
 // tiles take 0.9 us per 128-deep slab (measured on MI355X; the model is within
 // 7% of the eleven shapes that it was fitted on). A split adds the partial-sum
-// round trip and the reduction launch; its sums must fit cap floats.
+// round trip and the reduction launch; its sums must fit cap floats. A plan with
+// longer chains of additions than least_plan_f32's is not taken: without that
+// line one product in fifty (all with K below 1100) was up to 1.4 times further
+// off its 64-bit value.
 inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_t cap) {
   using C = FastCfgs<float>;
   struct Cand {
-    int kind, bm, bn, bk;
+    int kind, bm, bn, bk, ksplit, chains;
     double one, two, many, fixed;  // idle factor with one, two or more tiles on a compute unit; fixed us
   };
   static const Cand cands[] = {
-      {FAST_HUGE, C::Huge::BM, C::Huge::BN, C::Huge::BK, 1.14, 1.14, 1.14, 7.0},
-      {FAST_MID, C::Mid::BM, C::Mid::BN, C::Mid::BK, 1.5, 1.25, 1.17, 6.0},
-      {FAST_BIG, C::Big::BM, C::Big::BN, C::Big::BK, 1.33, 1.17, 1.2, 6.0},
-      {FAST_SMALL, C::Small::BM, C::Small::BN, C::Small::BK, 2.11, 2.11, 2.11, 5.0},
+      {FAST_HUGE, C::Huge::BM, C::Huge::BN, C::Huge::BK, C::Huge::KSPLIT, C::Huge::CHAINS, 1.14, 1.14, 1.14, 7.0},
+      {FAST_MID, C::Mid::BM, C::Mid::BN, C::Mid::BK, C::Mid::KSPLIT, C::Mid::CHAINS, 1.5, 1.25, 1.17, 6.0},
+      {FAST_BIG, C::Big::BM, C::Big::BN, C::Big::BK, C::Big::KSPLIT, C::Big::CHAINS, 1.33, 1.17, 1.2, 6.0},
+      {FAST_SMALL, C::Small::BM, C::Small::BN, C::Small::BK, C::Small::KSPLIT, C::Small::CHAINS, 2.11, 2.11, 2.11, 5.0},
   };
   const int64_t kb = kbatch > 0 ? kbatch : 1;
   auto tiles_of = [&](int bm, int bn) {
@@ -1324,6 +1377,7 @@ inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_
     while (s > 1 && s * M * N * batch > cap) s /= 2;
     return {FAST_NARROW, static_cast<int>(s)};
   }
+  const int64_t longest = least_chain_f32(least_plan_f32(M, N, K, kbatch, batch, cap), K, kb);
   FastPlan best = {FAST_SMALL, 1};
   double best_t = 1e300;
   for (const Cand& c : cands) {
@@ -1333,6 +1387,7 @@ inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_
       if (s > 1 && (slabs < s || tiles * s > 4 * kTargetBlocks ||
                     static_cast<int64_t>(s) * M * N * batch > cap))
         break;
+      if (chain_f32(c.bk, c.ksplit, c.chains, K, kb, s) > longest) continue;
       const int64_t n = (tiles * s + kTargetBlocks - 1) / kTargetBlocks;
       const double work = 2.0 * c.bm * c.bn * c.bk * ((slabs + s - 1) / s) / 614e3;
       double t = n * work * (n > 2 ? c.many : n > 1 ? c.two : c.one) + c.fixed;
@@ -1407,7 +1462,7 @@ template <typename T>
 inline size_t fast_partial_floats(int M, int N, int K, bool required) {
   int64_t s;
   if constexpr (sizeof(T) == 4)
-    s = required ? required_splits_f32(M, N, K) : plan_fast_f32(M, N, K, 1, 1, kAnyRoom).splits;
+    s = required ? least_plan_f32(M, N, K, 1, 1, kAnyRoom).splits : plan_fast_f32(M, N, K, 1, 1, kAnyRoom).splits;
   else
     s = plan_fast_bf16(M, N, K, 1, 1).splits;
   return s > 1 ? static_cast<size_t>(s) * M * N : 0;
