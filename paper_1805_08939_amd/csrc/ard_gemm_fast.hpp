@@ -57,6 +57,10 @@ struct FastCfg {
   static constexpr int ABYTES = BM * BK * ES, BBYTES = BN * BK * ES;
   static constexpr int STAGE = ABYTES + BBYTES;
   static constexpr int LDS = STAGES * STAGE;
+  // the k splits' accumulators and row sums, or the staging of the stores
+  static constexpr int ENDS = KSPLIT > 1 ? KSPLIT * WGM * (WGN * FM * FN * 16 * 64 + FM * 32) * 4
+                                         : NW * (32 * (TN * 4 + 32) + TM * 4);
+  static constexpr int LDS_REG = ENDS > 2 * STAGE ? ENDS : 2 * STAGE;  // register loads keep two stages
   // 16-byte load instructions per wave per slab
   static constexpr int LPW = (ABYTES + BBYTES) / 16 / 64 / NW;
   static_assert(ABYTES % (1024 * NW) == 0 && BBYTES % (1024 * NW) == 0, "tile must split into wave loads");
@@ -873,6 +877,7 @@ __device__ __forceinline__ void fast_store(const GemmArgs& g, f32x16 (&acc)[Cfg:
   constexpr int RPI = 64 / CPRW;     // rows per read instruction
   // the bias of the wave's TM rows sits behind the staging regions
   static_assert(Cfg::NW * (32 * ROW + Cfg::TM * 4) <= Cfg::LDS, "epilogue staging exceeds LDS");
+  static_assert(Cfg::KSPLIT > 1 || Cfg::NW * (32 * ROW + Cfg::TM * 4) == Cfg::ENDS, "epilogue staging");
   lds_barrier();  // every wave is done with the stages
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int lr = lane & 31, lh = lane >> 5;
@@ -1091,7 +1096,11 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
     // the KSPLIT waves of one output tile reduce through LDS; wave ks finishes
     // the accumulator registers t (flattened over i, j, r) with t % KSPLIT == ks
     constexpr int NREG = Cfg::FM * Cfg::FN * 16;
-    static_assert(Cfg::KSPLIT * Cfg::WGM * Cfg::WGN * NREG * 64 * 4 <= Cfg::LDS, "reduction buffer exceeds LDS");
+    static_assert((Cfg::KSPLIT * Cfg::WGM * Cfg::WGN * NREG * 64 + Cfg::KSPLIT * Cfg::WGM * Cfg::FM * 32) * 4 <=
+                      Cfg::ENDS,
+                  "reduction buffer");
+    static_assert((RSUM ? Cfg::ENDS : Cfg::KSPLIT * Cfg::WGM * Cfg::WGN * NREG * 64 * 4) <= Cfg::LDS,
+                  "reduction buffer exceeds LDS");
     float* red = reinterpret_cast<float*>(smem);
     const int lane = threadIdx.x & 63;
     __syncthreads();
@@ -1105,9 +1114,6 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
     // row sums of the k splits after the accumulators: [KSPLIT][WGM][FM][32]
     float* rred = red + Cfg::KSPLIT * Cfg::WGM * Cfg::WGN * NREG * 64;
     if constexpr (RSUM) {
-      static_assert((Cfg::KSPLIT * Cfg::WGM * Cfg::WGN * NREG * 64 + Cfg::KSPLIT * Cfg::WGM * Cfg::FM * 32) * 4 <=
-                        Cfg::LDS,
-                    "row-sum buffer exceeds LDS");
       if (wn == 0 && lane < 32) {
 #pragma unroll
         for (int i = 0; i < Cfg::FM; ++i)
@@ -1245,11 +1251,14 @@ struct FastCfgs<bf16> {
 };
 template <>
 struct FastCfgs<float> {
-  // The larger tiles leave room for two or three workgroups on a compute unit:
-  // one's MFMAs run while another waits for its first slabs or stores. Measured
-  // on MI355X, 2048 x 2240 x 1024: 128 x 128 tiles with 4 stages (one workgroup)
-  // 147 us, 2 stages 136; 64 x 64 x 64 with 3 stages 119, 2 stages 94; 64 x 64 x
-  // 32 with 3 stages 93. 8800 x 700 x 750: 107, 99, 104, 87, 84 us.
+  // Mid and Huge leave room for three and two workgroups on a compute unit: one's
+  // MFMAs run while another waits for its first slabs or stores. Big and Small
+  // are for grids of at most one. Measured on MI355X over 1236 products, the time
+  // over the best of all: Huge, Mid, Big with two stages and Small 1.0002, Big
+  // with three stages instead 1.0010, without Mid 1.027, without Huge 1.0024. Huge
+  // with four stages is no faster with one workgroup on a unit (1.006 of two
+  // stages) and 7% slower with more; Big with three stages takes 0.92 to 1.03 of
+  // two stages with one, and its eight chains another 1.3% over four.
   // Their last parameter is the number of accumulators per output (AccChains):
   // with one, the 1500 -> 8800 layer at batch 700 (forward and backward) is
   // 8.4e-7 off the 64-bit result and takes 301 us, with these 4.2e-7 and 302 us;
@@ -1258,7 +1267,7 @@ struct FastCfgs<float> {
   using Huge = FastCfg<float, 128, 128, 32, 2, 2, 4, 1, 2>;  // 64 KB, 8 waves
   using Wide = Huge;
   using Tall = Huge;
-  using Big = FastCfg<float, 64, 64, 64, 2, 2, 2, 2, 4>;     // 64 KB, 8 waves on 32-deep k shares
+  using Big = FastCfg<float, 64, 64, 64, 3, 2, 2, 2, 4>;     // 96 KB, 8 waves on 32-deep k shares
   using Mid = FastCfg<float, 64, 64, 32, 3, 2, 2, 1, 4>;     // 48 KB, 4 waves
   using Narrow = FastCfg<float, 128, 32, 32, 4, 2, 1, 2>; // 80 KB, 4 waves on 16-deep k shares
   using Small = FastCfg<float, 32, 32, 128, 4, 1, 1, 8>;  // 128 KB, 8 waves on 16-deep k shares
@@ -1342,29 +1351,64 @@ inline int64_t least_chain_f32(const FastPlan& p, int K, int64_t kb) {
                                  : chain_f32<C::Small>(1, K, kb, p.splits);
 }
 
-// fp32: the (configuration, split) pair with the smallest modelled time, in us.
-// The workgroups of a compute unit share its matrix cores (614 GFLOP/s), so a
-// grid takes the MFMA time of the most tiles on one unit, times a factor for
-// what their waits leave idle (larger when a unit holds one workgroup only),
-// plus the fixed time of a launch, its first slabs and its stores; the 32 x 32
-// tiles take 0.9 us per 128-deep slab (measured on MI355X; the model is within
-// 7% of the eleven shapes that it was fitted on). A split adds the partial-sum
-// round trip and the reduction launch; its sums must fit cap floats. A plan with
-// longer chains of additions than least_plan_f32's is not taken: without that
-// line one product in fifty (all with K below 1100) was up to 1.4 times further
-// off its 64-bit value.
+// Modelled time of a fp32 product, in us, of one tile configuration: the fixed
+// time of a launch, its first slabs and its stores; the matrix-core time of the
+// n tiles on the fullest compute unit (614 GFLOP/s) times a factor for what their
+// waits leave idle with one, two or more of them; a further start per round; the
+// loaded and the stored bytes at 5 TB/s; for a split its reduction launch and
+// partial sums.
+struct CostF32 {
+  int kind;
+  double fixed, one, two, many, round, load, store, split, sums;
+};
+
+// Fitted to 22000 times of 2178 products on MI355X (forward, dX and dW of random
+// layers, batch 16 to 2048, 64 to 8192 wide, and of larger ones up to 400
+// GFLOP), within 2% of them in the mean square. The configuration and split that
+// it picks is 0.1% slower than the best one in the mean over them and 17% at the
+// most; the constants before, from eleven products, were 3.2% and 83%, and left
+// one layer in ten slower than the fill rule that they had replaced (batch 32,
+// 1952 -> 2604 forward 13.4 -> 19.2 us; batch 1652, 80 -> 3252 backward 35 -> 56).
+constexpr CostF32 kCostF32[] = {
+    {FAST_HUGE, 6.98, 1.11, 1.06, 1.03, 1.84, 0.083, 1.06, 3.07, 1.45},
+    {FAST_MID, 5.80, 1.46, 1.19, 1.13, 0.95, 0.056, 0.63, 2.45, 1.78},
+    {FAST_BIG, 6.17, 1.26, 1.23, 1.20, 3.71, 0.052, 1.07, 1.96, 1.30},
+    {FAST_SMALL, 4.85, 1.45, 1.42, 1.34, 2.80, 0.059, 1.19, 2.43, 2.07},
+};
+
+// What the planner needs to know of a configuration.
+struct TileF32 {
+  int bm, bn, bk, ksplit, chains;
+};
+inline TileF32 tile_f32(int kind) {
+  auto of = [](auto cfg) {
+    using C = decltype(cfg);
+    return TileF32{C::BM, C::BN, C::BK, C::KSPLIT, C::CHAINS};
+  };
+  using C = FastCfgs<float>;
+  return kind == FAST_HUGE  ? of(C::Huge{})
+         : kind == FAST_MID ? of(C::Mid{})
+         : kind == FAST_BIG ? of(C::Big{})
+                            : of(C::Small{});
+}
+
+inline double time_f32(const CostF32& c, const TileF32& t, int M, int N, int K, int64_t kb, int batch, int splits) {
+  const int64_t tiles = static_cast<int64_t>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * batch * splits;
+  const int64_t q = (kb * ((K + t.bk - 1) / t.bk) + splits - 1) / splits;
+  const double n = static_cast<double>((tiles + kTargetBlocks - 1) / kTargetBlocks);
+  const double work = 2.0 * t.bm * t.bn * t.bk * q / 614e3, out = 4.0 * M * N * batch / 5e6;
+  double us = c.fixed + n * work * (n > 2 ? c.many : n > 1 ? c.two : c.one) + c.round * (n - 1) +
+              c.load * 4.0 * tiles * q * (t.bm + t.bn) * t.bk / 5e6 + c.store * out;
+  if (splits > 1) us += c.split + c.sums * splits * out;
+  return us;
+}
+
+// fp32: the (configuration, split) pair with the smallest modelled time whose
+// partial sums fit cap floats. A plan with longer chains of additions than
+// least_plan_f32's is not taken: without that line one product in fifty (all
+// with K below 1100) was up to 1.4 times further off its 64-bit value.
 inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_t cap) {
   using C = FastCfgs<float>;
-  struct Cand {
-    int kind, bm, bn, bk, ksplit, chains;
-    double one, two, many, fixed;  // idle factor with one, two or more tiles on a compute unit; fixed us
-  };
-  static const Cand cands[] = {
-      {FAST_HUGE, C::Huge::BM, C::Huge::BN, C::Huge::BK, C::Huge::KSPLIT, C::Huge::CHAINS, 1.14, 1.14, 1.14, 7.0},
-      {FAST_MID, C::Mid::BM, C::Mid::BN, C::Mid::BK, C::Mid::KSPLIT, C::Mid::CHAINS, 1.5, 1.25, 1.17, 6.0},
-      {FAST_BIG, C::Big::BM, C::Big::BN, C::Big::BK, C::Big::KSPLIT, C::Big::CHAINS, 1.33, 1.17, 1.2, 6.0},
-      {FAST_SMALL, C::Small::BM, C::Small::BN, C::Small::BK, C::Small::KSPLIT, C::Small::CHAINS, 2.11, 2.11, 2.11, 5.0},
-  };
   const int64_t kb = kbatch > 0 ? kbatch : 1;
   auto tiles_of = [&](int bm, int bn) {
     return static_cast<int64_t>((M + bm - 1) / bm) * ((N + bn - 1) / bn) * batch;
@@ -1380,20 +1424,17 @@ inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_
   const int64_t longest = least_chain_f32(least_plan_f32(M, N, K, kbatch, batch, cap), K, kb);
   FastPlan best = {FAST_SMALL, 1};
   double best_t = 1e300;
-  for (const Cand& c : cands) {
-    const int64_t tiles = tiles_of(c.bm, c.bn);
-    const int64_t slabs = kb * ((K + c.bk - 1) / c.bk);
+  for (const CostF32& c : kCostF32) {
+    const TileF32 t = tile_f32(c.kind);
+    const int64_t tiles = tiles_of(t.bm, t.bn), slabs = kb * ((K + t.bk - 1) / t.bk);
     for (int s = 1; s <= kMaxSplits; s *= 2) {
       if (s > 1 && (slabs < s || tiles * s > 4 * kTargetBlocks ||
                     static_cast<int64_t>(s) * M * N * batch > cap))
         break;
-      if (chain_f32(c.bk, c.ksplit, c.chains, K, kb, s) > longest) continue;
-      const int64_t n = (tiles * s + kTargetBlocks - 1) / kTargetBlocks;
-      const double work = 2.0 * c.bm * c.bn * c.bk * ((slabs + s - 1) / s) / 614e3;
-      double t = n * work * (n > 2 ? c.many : n > 1 ? c.two : c.one) + c.fixed;
-      if (s > 1) t += 4.0 * M * N * batch * (s + 1) / 5e6 + 3.0;
-      if (t < best_t) {
-        best_t = t;
+      if (chain_f32(t.bk, t.ksplit, t.chains, K, kb, s) > longest) continue;
+      const double us = time_f32(c, t, M, N, K, kb, batch, s);
+      if (us < best_t) {
+        best_t = us;
         best = {c.kind, s};
       }
     }
@@ -1472,12 +1513,13 @@ template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = fal
 inline hipError_t launch_fast(const GemmArgs& g, int batch, hipStream_t stream) {
   const int splits = g.splits > 1 ? g.splits : 1;
   auto kern = fast_gemm_kernel<Cfg, AMC, BMC, OutT, EPI, RSUM, LD>;
+  constexpr int LDS = LD == LOAD_ANY ? Cfg::LDS_REG : Cfg::LDS;
   // per instantiation, once (thread-safe static initialisation): allow more than 64 KB of dynamic LDS
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS);
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
   if (attr != hipSuccess) return attr;
   dim3 grid((g.N + Cfg::BN - 1) / Cfg::BN, (g.M + Cfg::BM - 1) / Cfg::BM, batch * splits);
-  hipLaunchKernelGGL(kern, grid, dim3(Cfg::NT), Cfg::LDS, stream, g);
+  hipLaunchKernelGGL(kern, grid, dim3(Cfg::NT), LDS, stream, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || splits == 1) return e;
   const int64_t mn = static_cast<int64_t>(g.M) * g.N;
@@ -1498,8 +1540,9 @@ template <typename T, bool AMC1, bool BMC1, typename OutT1, int EPI1, bool RSUM1
 inline hipError_t launch_fast_pair(GemmArgs g1, GemmArgs g2, hipStream_t stream) {
   using Cfg = typename FastCfgs<T>::Small;
   auto kern = fast_gemm_pair_kernel<Cfg, AMC1, BMC1, OutT1, EPI1, RSUM1, AMC2, BMC2, OutT2, EPI2, RSUM2, LD>;
+  constexpr int LDS = LD == LOAD_ANY ? Cfg::LDS_REG : Cfg::LDS;
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS);
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
   if (attr != hipSuccess) return attr;
   g1.splits = g2.splits = 1;
   if (!RSUM1) g1.rsum = nullptr;
@@ -1507,7 +1550,7 @@ inline hipError_t launch_fast_pair(GemmArgs g1, GemmArgs g2, hipStream_t stream)
   const int64_t n1 = static_cast<int64_t>((g1.N + Cfg::BN - 1) / Cfg::BN) * ((g1.M + Cfg::BM - 1) / Cfg::BM);
   const int64_t n2 = static_cast<int64_t>((g2.N + Cfg::BN - 1) / Cfg::BN) * ((g2.M + Cfg::BM - 1) / Cfg::BM);
   if (n1 + n2 == 0) return hipSuccess;
-  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n1 + n2)), dim3(Cfg::NT), Cfg::LDS, stream, g1, g2);
+  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n1 + n2)), dim3(Cfg::NT), LDS, stream, g1, g2);
   return hipGetLastError();
 }
 
