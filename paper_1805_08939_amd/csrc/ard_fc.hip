@@ -264,9 +264,9 @@ size_t compact_bytes(const FcShape& s) { return static_cast<size_t>(s.kout) * s.
 
 // Split-K partial floats of one problem under whichever kernel may run it.
 template <typename T>
-size_t problem_partials(int M, int N, int K, bool required) {
+size_t problem_partials(int M, int N, int K, bool required, bool rowsums = false) {
   size_t f = gemm_partial_floats<T>(M, N, K, 1, 1);
-  const size_t h = fast_partial_floats<T>(M, N, K, required);
+  const size_t h = fast_partial_floats<T>(M, N, K, required, rowsums);
   return f > h ? f : h;
 }
 
@@ -274,7 +274,7 @@ template <typename T>
 size_t partial_bytes(const FcShape& s, bool required) {
   size_t f = problem_partials<T>(s.kout, s.B, s.kin, required);                 // fwd
   const size_t d = problem_partials<T>(s.kin, s.B, s.kout, required);           // bwd_data
-  const size_t w = problem_partials<T>(s.kout, s.kin, s.B, required);           // bwd_weight
+  const size_t w = problem_partials<T>(s.kout, s.kin, s.B, required, !s.input_major);  // bwd_weight
   f = f > d ? f : d;
   f = f > w ? f : w;
   return 4 * f;
@@ -398,19 +398,23 @@ struct WeightView {
   int64_t cap;     // floats that fit there
 };
 
+// The operand that fwd and bwd_data read: W in place, or (needs_compact) the
+// compact copy at wc.
+GemmOperand weight_operand(const FcShape& s, const void* W, const void* wc) {
+  if (s.compact_given) return kept_rows(W, nullptr, s.ldc, 1, 0, s.esize, 0);
+  if (s.input_major)  // the kept input rows of W^T[K][N]
+    return kept_rows(W, nullptr, s.N, s.in_period, s.in_offset, s.esize, 0);
+  if (s.needs_compact) return kept_rows(wc, nullptr, s.ldc, 1, 0, s.esize, 0);
+  return kept_rows(W, nullptr, s.K, s.out_period, s.out_offset, s.esize, 0);
+}
+
 template <typename T>
 int weight_view(const FcShape& s, const void* W, Workspace ws, hipStream_t stream, WeightView* v) {
   char* w = static_cast<char*>(ws.p);
-  if (s.compact_given) {
-    v->op = kept_rows(W, nullptr, s.ldc, 1, 0, sizeof(T), 0);
-  } else if (s.input_major) {  // the kept input rows of W^T[K][N]
-    v->op = kept_rows(W, nullptr, s.N, s.in_period, s.in_offset, sizeof(T), 0);
-  } else if (s.needs_compact) {
+  v->op = weight_operand(s, W, w);
+  if (s.needs_compact) {
     ARD_HIP_CHECK(launch_compact<T>(s, W, w, stream));
-    v->op = kept_rows(w, nullptr, s.ldc, 1, 0, sizeof(T), 0);
     w += al256(compact_bytes(s));
-  } else {
-    v->op = kept_rows(W, nullptr, s.K, s.out_period, s.out_offset, sizeof(T), 0);
   }
   v->partial = ws.p ? reinterpret_cast<float*>(w) : nullptr;
   v->cap = ws.p ? static_cast<int64_t>(ws.bytes - (w - static_cast<char*>(ws.p))) / 4 : 0;
@@ -557,6 +561,28 @@ int finish_bwd_weight(const ard_fc_desc* d, const FcShape& s, const void* dYt, c
   return ARD_OK;
 }
 
+// How a layer's two backward products run: as one launch (on which loads), or
+// as two. By the descriptor and the gate alone (every pointer is 16-byte aligned),
+// so that a call for one of the products runs it on the tiles of the pair, and its
+// results are the one-call backward's bit for bit.
+enum PairLoad { PAIR_NONE, PAIR_DMA, PAIR_REG };
+
+template <typename T>
+PairLoad backward_pair(const ard_fc_desc* d, const FcShape& s, const void* Yt, int64_t cap) {
+  if (s.input_major) return PAIR_NONE;
+  float* p = reinterpret_cast<float*>(uintptr_t{4096});  // aligned as the operands are; never read
+  const void* y = Yt ? p : nullptr;
+  const GemmArgs gd = bwd_data_args<T>(d, s, p, y, weight_operand(s, p, p), p, nullptr);
+  const GemmArgs gw = bwd_weight_args<T>(d, s, p, p, y, p);
+  const bool fd = fast_ok<true, true>(gd, sizeof(T)), fw = fast_ok<false, false>(gw, sizeof(T));
+  if (fd && fw) return fast_pair_ok<T>(gd, gw, cap) ? PAIR_DMA : PAIR_NONE;
+  // both on register loads: neither is split off to the direct loads of a call of its own
+  if (!fd && !fw && any_ok<true, true>(gd, sizeof(T)) && any_ok<false, false>(gw, sizeof(T)) &&
+      any_pair_ok<T>(gd, gw, cap))
+    return PAIR_REG;
+  return PAIR_NONE;
+}
+
 template <typename T>
 int run_bwd_data(const ard_fc_desc* d, const FcShape& s, const GemmArgs& g, const void* Yt, void* dXt,
                  float* partial, int64_t cap, hipStream_t stream) {
@@ -574,7 +600,8 @@ int run_bwd_data(const ard_fc_desc* d, const FcShape& s, const GemmArgs& g, cons
           g, 1, a_vec, b_vec, stream, partial)));
     }
   } else if (any_ok<true, true>(g, sizeof(T))) {
-    ARD_HIP_CHECK((run_strided_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, partial, cap)));
+    const bool pair = backward_pair<T>(d, s, Yt, partial ? cap : 0) != PAIR_NONE;
+    ARD_HIP_CHECK((run_strided_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, partial, cap, nullptr, pair)));
   } else if (gated) {
     ARD_HIP_CHECK((run_gemm<T, T, MC_VEC, MC_ELEM, MC_VEC, MC_ELEM, false, true, EPI_FWD>(
         g, 1, a_vec, b_vec, stream, partial)));
@@ -620,7 +647,9 @@ int fc_bwd_weight_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, c
       g.rsum = dbias + s.out_offset;
       g.rsum_ld = s.out_period;
     }
-    ARD_HIP_CHECK((run_strided_gemm<T, false, false, float, EPI_FWD, true>(g, 1, stream, partial, cap, &dbias_done)));
+    const bool pair = backward_pair<T>(d, s, Yt, cap) != PAIR_NONE;
+    ARD_HIP_CHECK((run_strided_gemm<T, false, false, float, EPI_FWD, true>(g, 1, stream, partial, cap, &dbias_done,
+                                                                           pair)));
   } else if (gated) {
     ARD_HIP_CHECK((run_gemm<T, float, KC_VEC, KC_ELEM, KC_VEC, KC_ELEM, true, false, EPI_FWD>(
         g, 1, v, v, stream, partial)));
@@ -645,11 +674,9 @@ int fc_bwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const vo
   if (st != ARD_OK) return st;
   const GemmArgs gd = bwd_data_args<T>(d, s, dYt, Yt, wv.op, dXt, Xgate);
   GemmArgs gw = bwd_weight_args<T>(d, s, Xt, dYt, Yt, dW);
-  const bool fast = fast_ok<true, true>(gd, sizeof(T)) && fast_ok<false, false>(gw, sizeof(T));
-  // both on register loads: neither is split off to the direct loads of a call of its own
-  const bool any = !fast && !fast_ok<true, true>(gd, sizeof(T)) && !fast_ok<false, false>(gw, sizeof(T)) &&
-                   any_ok<true, true>(gd, sizeof(T)) && any_ok<false, false>(gw, sizeof(T));
-  if (!s.input_major && ((fast && fast_pair_ok<T>(gd, gw, wv.cap)) || (any && any_pair_ok<T>(gd, gw, wv.cap)))) {
+  const PairLoad pair = backward_pair<T>(d, s, Yt, wv.partial ? wv.cap : 0);
+  if (pair != PAIR_NONE) {
+    const bool fast = pair == PAIR_DMA;
     if (dbias) {
       gw.rsum = dbias + s.out_offset;
       gw.rsum_ld = s.out_period;

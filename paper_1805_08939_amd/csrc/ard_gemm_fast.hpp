@@ -1278,6 +1278,7 @@ enum FastKind { FAST_HUGE, FAST_WIDE, FAST_TALL, FAST_BIG, FAST_SMALL, FAST_NARR
 struct FastPlan {
   int kind;    // FastKind
   int splits;  // workgroups per output tile along K (partials reduced by a second kernel)
+  double us;   // modelled time (fp32)
 };
 
 // Split count s for a tile count: the largest power of two that keeps the grid
@@ -1301,7 +1302,7 @@ inline FastPlan least_plan_f32(int M, int N, int K, int kbatch, int batch, int64
   const int64_t kb = kbatch > 0 ? kbatch : 1;
   auto slabs_of = [&](int bk) { return kb * ((K + bk - 1) / bk); };
   constexpr int64_t kFill = kTargetBlocks * 5 / 8;
-  FastPlan p;
+  FastPlan p = {};
   int64_t tiles;
   int bk;
   if (N <= C::Narrow::BN && tiles_of(C::Narrow::BM, C::Narrow::BN) >= kFill) {
@@ -1403,11 +1404,16 @@ inline double time_f32(const CostF32& c, const TileF32& t, int M, int N, int K, 
   return us;
 }
 
+// What a split weight gradient adds: the bias gradient, which an unsplit one
+// takes from the rows that it reads, is then a launch of its own over the M x K
+// operand (measured: 4 us and 1 us per 5 MB).
+inline double rowsums_us(int M, int K) { return 4.0 + 4.0 * M * K / 5e6; }
+
 // fp32: the (configuration, split) pair with the smallest modelled time whose
-// partial sums fit cap floats. A plan with longer chains of additions than
+// partial sums fit cap floats. rowsums: see rowsums_us. A plan with longer chains of additions than
 // least_plan_f32's is not taken: without that line one product in fifty (all
 // with K below 1100) was up to 1.4 times further off its 64-bit value.
-inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_t cap) {
+inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_t cap, bool rowsums = false) {
   using C = FastCfgs<float>;
   const int64_t kb = kbatch > 0 ? kbatch : 1;
   auto tiles_of = [&](int bm, int bn) {
@@ -1419,11 +1425,10 @@ inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_
     const int64_t tiles = tiles_of(C::Narrow::BM, C::Narrow::BN);
     int64_t s = kb * K >= 8192 ? fast_splits(tiles, kb * ((K + C::Narrow::BK - 1) / C::Narrow::BK)) : 1;
     while (s > 1 && s * M * N * batch > cap) s /= 2;
-    return {FAST_NARROW, static_cast<int>(s)};
+    return {FAST_NARROW, static_cast<int>(s), 0.0};
   }
   const int64_t longest = least_chain_f32(least_plan_f32(M, N, K, kbatch, batch, cap), K, kb);
-  FastPlan best = {FAST_SMALL, 1};
-  double best_t = 1e300;
+  FastPlan best = {FAST_SMALL, 1, 1e300};
   for (const CostF32& c : kCostF32) {
     const TileF32 t = tile_f32(c.kind);
     const int64_t tiles = tiles_of(t.bm, t.bn), slabs = kb * ((K + t.bk - 1) / t.bk);
@@ -1432,11 +1437,9 @@ inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_
                     static_cast<int64_t>(s) * M * N * batch > cap))
         break;
       if (chain_f32(t.bk, t.ksplit, t.chains, K, kb, s) > longest) continue;
-      const double us = time_f32(c, t, M, N, K, kb, batch, s);
-      if (us < best_t) {
-        best_t = us;
-        best = {c.kind, s};
-      }
+      double us = time_f32(c, t, M, N, K, kb, batch, s);
+      if (s > 1 && rowsums) us += rowsums_us(M, K);
+      if (us < best.us) best = {c.kind, s, us};
     }
   }
   return best;
@@ -1488,11 +1491,11 @@ inline FastPlan plan_fast_bf16(int M, int N, int K, int kbatch, int batch) {
 // cap: floats of partial sums that the caller has room for (fp32; the bf16 plan
 // is the one that sizes them).
 template <typename T>
-inline FastPlan plan_fast(int M, int N, int K, int kbatch, int batch, int64_t cap) {
+inline FastPlan plan_fast(int M, int N, int K, int kbatch, int batch, int64_t cap, bool rowsums = false) {
   if constexpr (sizeof(T) == 2)
     return plan_fast_bf16(M, N, K, kbatch, batch);
   else
-    return plan_fast_f32(M, N, K, kbatch, batch, cap);
+    return plan_fast_f32(M, N, K, kbatch, batch, cap, rowsums);
 }
 
 constexpr int64_t kAnyRoom = int64_t{1} << 60;
@@ -1500,10 +1503,11 @@ constexpr int64_t kAnyRoom = int64_t{1} << 60;
 // Floats of split-K partials of a product: what a call must be given room for
 // (required), and what it makes use of.
 template <typename T>
-inline size_t fast_partial_floats(int M, int N, int K, bool required) {
+inline size_t fast_partial_floats(int M, int N, int K, bool required, bool rowsums) {
   int64_t s;
   if constexpr (sizeof(T) == 4)
-    s = required ? least_plan_f32(M, N, K, 1, 1, kAnyRoom).splits : plan_fast_f32(M, N, K, 1, 1, kAnyRoom).splits;
+    s = required ? least_plan_f32(M, N, K, 1, 1, kAnyRoom).splits
+                 : plan_fast_f32(M, N, K, 1, 1, kAnyRoom, rowsums).splits;
   else
     s = plan_fast_bf16(M, N, K, 1, 1).splits;
   return s > 1 ? static_cast<size_t>(s) * M * N : 0;
@@ -1554,13 +1558,48 @@ inline hipError_t launch_fast_pair(GemmArgs g1, GemmArgs g2, hipStream_t stream)
   return hipGetLastError();
 }
 
-// Whether two problems run as one fast_gemm_pair_kernel launch: both take the
-// 32x32 configuration without a k split on their own, and each has a tile.
+// Modelled time of fast_gemm_pair_kernel on fp32 operands, in us: its fixed
+// time, the longest tile or the tiles shared out over the chip, further rounds,
+// the loaded and the stored bytes (fitted to 152 layers on MI355X, within 8%).
+inline double pair_us_f32(const GemmArgs& g1, const GemmArgs& g2) {
+  using C = FastCfgs<float>::Small;
+  auto tiles = [](const GemmArgs& g) {
+    return static_cast<double>((g.M + C::BM - 1) / C::BM) * ((g.N + C::BN - 1) / C::BN);
+  };
+  auto slabs = [](const GemmArgs& g) { return static_cast<double>((g.K + C::BK - 1) / C::BK); };
+  const double t1 = tiles(g1), t2 = tiles(g2), q1 = slabs(g1), q2 = slabs(g2);
+  const double work = 2.0 * C::BM * C::BN * C::BK / 614e3, longest = q1 > q2 ? q1 : q2;
+  const double share = (t1 * q1 + t2 * q2) / kTargetBlocks;
+  const double rounds = static_cast<double>((static_cast<int64_t>(t1 + t2) + kTargetBlocks - 1) / kTargetBlocks);
+  return 4.9 + 1.14 * (longest > share ? longest : share) * work + 2.4 * (rounds - 1) +
+         0.22 * 4.0 * (t1 * q1 + t2 * q2) * (C::BM + C::BN) * C::BK / 5e6;
+}
+
+// Whether bwd_data (g1) and bwd_weight (g2, with row sums) run as one
+// fast_gemm_pair_kernel launch of 32x32 tiles without a k split. bf16: where both
+// plans take those. fp32: also where those tiles are least_plan_f32's of both and
+// one launch is modelled faster than the two planned ones. Without that line the
+// cost model, which plans each product alone, sent one in fourteen of the layers
+// that had run as one launch to two (batch 184, 364 -> 832: 10.5 -> 18.1 us; batch
+// 704, 512 -> 688: 22.7 -> 32.2).
+template <typename T>
+inline bool pair_ok(const GemmArgs& g1, const FastPlan& p1, const GemmArgs& g2, const FastPlan& p2, int64_t cap) {
+  if (g1.M <= 0 || g1.N <= 0 || g2.M <= 0 || g2.N <= 0) return false;
+  if (p1.kind == FAST_SMALL && p2.kind == FAST_SMALL && p1.splits == 1 && p2.splits == 1) return true;
+  if constexpr (sizeof(T) == 2) {
+    return false;
+  } else {
+    auto small = [cap](const GemmArgs& g) {
+      const FastPlan l = least_plan_f32(g.M, g.N, g.K, 1, 1, cap);
+      return l.kind == FAST_SMALL && l.splits == 1;
+    };
+    return p1.us > 0.0 && p2.us > 0.0 && small(g1) && small(g2) && pair_us_f32(g1, g2) < p1.us + p2.us;
+  }
+}
 template <typename T>
 inline bool fast_pair_ok(const GemmArgs& g1, const GemmArgs& g2, int64_t cap) {
-  if (g1.M <= 0 || g1.N <= 0 || g2.M <= 0 || g2.N <= 0) return false;
-  const FastPlan p1 = plan_fast<T>(g1.M, g1.N, g1.K, 1, 1, cap), p2 = plan_fast<T>(g2.M, g2.N, g2.K, 1, 1, cap);
-  return p1.kind == FAST_SMALL && p2.kind == FAST_SMALL && p1.splits == 1 && p2.splits == 1;
+  return pair_ok<T>(g1, plan_fast<T>(g1.M, g1.N, g1.K, 1, 1, cap), g2,
+                    plan_fast<T>(g2.M, g2.N, g2.K, 1, 1, cap, true), cap);
 }
 
 template <typename T, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM, int LD = LOAD_DMA>
@@ -1591,13 +1630,15 @@ inline hipError_t launch_planned(const GemmArgs& g, int kind, int batch, hipStre
 // Runs a GEMM on the fast kernel; the caller has checked fast_ok(). With
 // RSUM, g.rsum receives the row sums of A when the plan has no k split and is
 // not the bf16 256x256 tile, and *rsum_done says whether it did (else the
-// caller computes them itself).
+// caller computes them itself). smallest: 32x32 tiles without a split (one half
+// of a pair run on its own).
 template <typename T, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false>
 inline hipError_t run_fast_gemm(GemmArgs g, int batch, hipStream_t stream, float* partial, int64_t cap,
-                                bool* rsum_done = nullptr) {
+                                bool* rsum_done = nullptr, bool smallest = false) {
   if (rsum_done) *rsum_done = false;
   if (g.M <= 0 || g.N <= 0 || batch <= 0) return hipSuccess;
-  FastPlan p = plan_fast<T>(g.M, g.N, g.K, g.kbatch, batch, partial ? cap : 0);
+  FastPlan p = {FAST_SMALL, 1, 0.0};
+  if (!smallest) p = plan_fast<T>(g.M, g.N, g.K, g.kbatch, batch, partial ? cap : 0, RSUM);
   // the kernel splits the slabs with 32-bit arithmetic
   const int64_t kb = g.kbatch > 0 ? g.kbatch : 1;
   if (!partial || kb * (g.K / 32 + 1) * p.splits >= int64_t{1} << 31) p.splits = 1;
@@ -1616,8 +1657,8 @@ inline hipError_t run_fast_gemm(GemmArgs g, int batch, hipStream_t stream, float
 // in flight. The split count never exceeds what the workspace of the problem
 // was sized for (the direct-load or the general kernel's plan).
 template <typename T>
-inline FastPlan plan_any(int M, int N, int K, int kbatch, int batch, int64_t cap) {
-  FastPlan p = plan_fast<T>(M, N, K, kbatch, batch, cap);
+inline FastPlan plan_any(int M, int N, int K, int kbatch, int batch, int64_t cap, bool rowsums = false) {
+  FastPlan p = plan_fast<T>(M, N, K, kbatch, batch, cap, rowsums);
   if constexpr (sizeof(T) == 2) {
     using C = FastCfgs<bf16>;
     const int gs = plan_gemm<T>(M, N, K, kbatch, batch).splits;
@@ -1636,12 +1677,13 @@ inline FastPlan plan_any(int M, int N, int K, int kbatch, int batch, int64_t cap
 // loads where the rows start on 16 bytes (fast_ok), else on register loads.
 template <typename T, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false>
 inline hipError_t run_strided_gemm(GemmArgs g, int batch, hipStream_t stream, float* partial, int64_t cap,
-                                   bool* rsum_done = nullptr) {
+                                   bool* rsum_done = nullptr, bool smallest = false) {
   if (fast_ok<AMC, BMC>(g, sizeof(T)))
-    return run_fast_gemm<T, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream, partial, cap, rsum_done);
+    return run_fast_gemm<T, AMC, BMC, OutT, EPI, RSUM>(g, batch, stream, partial, cap, rsum_done, smallest);
   if (rsum_done) *rsum_done = false;
   if (g.M <= 0 || g.N <= 0 || batch <= 0) return hipSuccess;
-  FastPlan p = plan_any<T>(g.M, g.N, g.K, g.kbatch, batch, partial ? cap : 0);
+  FastPlan p = {FAST_SMALL, 1, 0.0};
+  if (!smallest) p = plan_any<T>(g.M, g.N, g.K, g.kbatch, batch, partial ? cap : 0, RSUM);
   const int64_t kb = g.kbatch > 0 ? g.kbatch : 1;
   if (!partial || kb * (g.K / 32 + 1) * p.splits >= int64_t{1} << 31) p.splits = 1;
   g.splits = p.splits;
@@ -1669,9 +1711,8 @@ inline hipError_t run_strided_gemm(GemmArgs g, int batch, hipStream_t stream, fl
 // Whether the pair runs as one launch of the register-load 32x32 tiles.
 template <typename T>
 inline bool any_pair_ok(const GemmArgs& g1, const GemmArgs& g2, int64_t cap) {
-  if (g1.M <= 0 || g1.N <= 0 || g2.M <= 0 || g2.N <= 0) return false;
-  const FastPlan p1 = plan_any<T>(g1.M, g1.N, g1.K, 1, 1, cap), p2 = plan_any<T>(g2.M, g2.N, g2.K, 1, 1, cap);
-  return p1.kind == FAST_SMALL && p2.kind == FAST_SMALL && p1.splits == 1 && p2.splits == 1;
+  return pair_ok<T>(g1, plan_any<T>(g1.M, g1.N, g1.K, 1, 1, cap), g2,
+                    plan_any<T>(g2.M, g2.N, g2.K, 1, 1, cap, true), cap);
 }
 
 // A fp32 product over the columns of several steps at once (EPI_COLS): B's and

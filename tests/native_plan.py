@@ -25,6 +25,14 @@ void plan_reg(int bf, int M, int N, int K, long cap, int* out) {
   const FastPlan p = bf ? plan_any<bf16>(M, N, K, 1, 1, cap) : plan_any<float>(M, N, K, 1, 1, cap);
   out[0] = p.kind, out[1] = p.splits;
 }
+static GemmArgs product(int M, int N, int K) {
+  GemmArgs g = {};
+  g.M = M, g.N = N, g.K = K;
+  return g;
+}
+int pair_f32(int B, int kin, int kout, long cap) {
+  return fast_pair_ok<float>(product(kin, B, kout), product(kout, kin, B), cap);
+}
 }
 """
 
@@ -47,6 +55,7 @@ class Planner:
     def __init__(self, lib):
         lib.plan_f32.argtypes = [ctypes.c_int] * 5 + [ctypes.c_long, ctypes.c_void_p]
         lib.plan_reg.argtypes = [ctypes.c_int] * 4 + [ctypes.c_long, ctypes.c_void_p]
+        lib.pair_f32.argtypes = [ctypes.c_int] * 3 + [ctypes.c_long]
         self.lib = lib
 
     def f32(self, M, N, K, kb=1, batch=1, cap=ROOM):
@@ -60,3 +69,7 @@ class Planner:
         out = (ctypes.c_int * 2)()
         self.lib.plan_reg(int(dtype == "bf16"), M, N, K, cap, out)
         return KINDS[out[0]], out[1]
+
+    def pair(self, B, kin, kout, cap=ROOM):
+        """Whether an aligned fp32 layer's backward runs as one launch."""
+        return bool(self.lib.pair_f32(B, kin, kout, cap))
