@@ -444,13 +444,13 @@ int fc_fwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const vo
   const bool a_vec = vec_rows(g.a.ld, sizeof(T));
   const bool b_vec = vec_rows(s.B, sizeof(T));
   if (s.input_major) {  // A(m, k) = W^T[in(k)][m]: m-contiguous
-    if (any_ok<true, true>(g, sizeof(T))) {
+    if (strided_ok<T, true, true>(g)) {
       ARD_HIP_CHECK((run_strided_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, wv.partial, wv.cap)));
     } else {
       ARD_HIP_CHECK((run_gemm<T, T, MC_VEC, MC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
           g, 1, a_vec, b_vec, stream, wv.partial)));
     }
-  } else if (any_ok<false, true>(g, sizeof(T))) {
+  } else if (strided_ok<T, false, true>(g)) {
     ARD_HIP_CHECK((run_strided_gemm<T, false, true, T, EPI_FWD>(g, 1, stream, wv.partial, wv.cap)));
   } else {
     ARD_HIP_CHECK((run_gemm<T, T, KC_VEC, KC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
@@ -587,10 +587,11 @@ template <typename T>
 int run_bwd_data(const ard_fc_desc* d, const FcShape& s, const GemmArgs& g, const void* Yt, void* dXt,
                  float* partial, int64_t cap, hipStream_t stream) {
   const bool gated = d->act == ARD_ACT_RELU && Yt != nullptr;
+  const bool pair = backward_pair<T>(d, s, Yt, partial ? cap : 0) != PAIR_NONE;
   const bool a_vec = vec_rows(g.a.ld, sizeof(T));
   const bool b_vec = vec_rows(s.B, sizeof(T));
   if (s.input_major) {  // A(m, t) = W^T[in(m)][t]: k-contiguous rows
-    if (any_ok<false, true>(g, sizeof(T))) {
+    if (strided_ok<T, false, true>(g)) {
       ARD_HIP_CHECK((run_strided_gemm<T, false, true, T, EPI_FWD>(g, 1, stream, partial, cap)));
     } else if (gated) {
       ARD_HIP_CHECK((run_gemm<T, T, KC_VEC, KC_ELEM, MC_VEC, MC_ELEM, false, true, EPI_FWD>(
@@ -599,8 +600,7 @@ int run_bwd_data(const ard_fc_desc* d, const FcShape& s, const GemmArgs& g, cons
       ARD_HIP_CHECK((run_gemm<T, T, KC_VEC, KC_ELEM, MC_VEC, MC_ELEM, false, false, EPI_FWD>(
           g, 1, a_vec, b_vec, stream, partial)));
     }
-  } else if (any_ok<true, true>(g, sizeof(T))) {
-    const bool pair = backward_pair<T>(d, s, Yt, partial ? cap : 0) != PAIR_NONE;
+  } else if (pair || strided_ok<T, true, true>(g)) {
     ARD_HIP_CHECK((run_strided_gemm<T, true, true, T, EPI_FWD>(g, 1, stream, partial, cap, nullptr, pair)));
   } else if (gated) {
     ARD_HIP_CHECK((run_gemm<T, T, MC_VEC, MC_ELEM, MC_VEC, MC_ELEM, false, true, EPI_FWD>(
@@ -632,7 +632,7 @@ int fc_bwd_weight_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, c
   const int64_t cap = ws.p && ws.bytes > skip ? static_cast<int64_t>(ws.bytes - skip) / 4 : 0;
   bool dbias_done = false;
   if (s.input_major) {  // the bias gradient from dbias_kernel (G is the B operand here)
-    if (any_ok<false, false>(g, sizeof(T))) {
+    if (strided_ok<T, false, false>(g)) {
       ARD_HIP_CHECK((run_strided_gemm<T, false, false, float, EPI_FWD>(g, 1, stream, partial, cap)));
     } else if (gated) {
       ARD_HIP_CHECK((run_gemm<T, float, KC_VEC, KC_ELEM, KC_VEC, KC_ELEM, false, true, EPI_FWD>(
@@ -641,7 +641,7 @@ int fc_bwd_weight_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, c
       ARD_HIP_CHECK((run_gemm<T, float, KC_VEC, KC_ELEM, KC_VEC, KC_ELEM, false, false, EPI_FWD>(
           g, 1, v, v, stream, partial)));
     }
-  } else if (any_ok<false, false>(g, sizeof(T))) {
+  } else if (strided_ok<T, false, false>(g, true)) {
     // dbias = scale * G 1: the row sums of A, taken by the same kernel
     if (dbias) {
       g.rsum = dbias + s.out_offset;

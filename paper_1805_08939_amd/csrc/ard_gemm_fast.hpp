@@ -1251,14 +1251,14 @@ struct FastCfgs<bf16> {
 };
 template <>
 struct FastCfgs<float> {
-  // Mid and Huge leave room for three and two workgroups on a compute unit: one's
-  // MFMAs run while another waits for its first slabs or stores. Big and Small
-  // are for grids of at most one. Measured on MI355X over 1236 products, the time
-  // over the best of all: Huge, Mid, Big with two stages and Small 1.0002, Big
-  // with three stages instead 1.0010, without Mid 1.027, without Huge 1.0024. Huge
-  // with four stages is no faster with one workgroup on a unit (1.006 of two
-  // stages) and 7% slower with more; Big with three stages takes 0.92 to 1.03 of
-  // two stages with one, and its eight chains another 1.3% over four.
+  // Mid, Duo and Huge leave room for two or three workgroups on a compute unit:
+  // one's MFMAs run while another waits for its first slabs or stores. Big and
+  // Small are for grids of at most one. Measured on MI355X over 1236 products, the
+  // time over the best of all: without Big 1.0002 (but up to 1.07), without Duo
+  // 1.0010, without Mid 1.027, without Huge 1.0024. Huge with four stages is no
+  // faster with one workgroup on a unit (1.006 of two stages) and 7% slower with
+  // more; Big takes 0.92 to 1.04 of Duo with one, and its eight chains per output
+  // are what products off the Small tile must keep (least_plan_f32).
   // Their last parameter is the number of accumulators per output (AccChains):
   // with one, the 1500 -> 8800 layer at batch 700 (forward and backward) is
   // 8.4e-7 off the 64-bit result and takes 301 us, with these 4.2e-7 and 302 us;
@@ -1268,12 +1268,13 @@ struct FastCfgs<float> {
   using Wide = Huge;
   using Tall = Huge;
   using Big = FastCfg<float, 64, 64, 64, 3, 2, 2, 2, 4>;     // 96 KB, 8 waves on 32-deep k shares
+  using Duo = FastCfg<float, 64, 64, 64, 2, 2, 2, 2, 2>;     // 64 KB, as Big with half the accumulators
   using Mid = FastCfg<float, 64, 64, 32, 3, 2, 2, 1, 4>;     // 48 KB, 4 waves
   using Narrow = FastCfg<float, 128, 32, 32, 4, 2, 1, 2>; // 80 KB, 4 waves on 16-deep k shares
   using Small = FastCfg<float, 32, 32, 128, 4, 1, 1, 8>;  // 128 KB, 8 waves on 16-deep k shares
 };
 
-enum FastKind { FAST_HUGE, FAST_WIDE, FAST_TALL, FAST_BIG, FAST_SMALL, FAST_NARROW, FAST_MID };
+enum FastKind { FAST_HUGE, FAST_WIDE, FAST_TALL, FAST_BIG, FAST_SMALL, FAST_NARROW, FAST_MID, FAST_DUO };
 
 struct FastPlan {
   int kind;    // FastKind
@@ -1370,12 +1371,37 @@ struct CostF32 {
 // most; the constants before, from eleven products, were 3.2% and 83%, and left
 // one layer in ten slower than the fill rule that they had replaced (batch 32,
 // 1952 -> 2604 forward 13.4 -> 19.2 us; batch 1652, 80 -> 3252 backward 35 -> 56).
-constexpr CostF32 kCostF32[] = {
+constexpr CostF32 kCostF32[5] = {
     {FAST_HUGE, 6.98, 1.11, 1.06, 1.03, 1.84, 0.083, 1.06, 3.07, 1.45},
     {FAST_MID, 5.80, 1.46, 1.19, 1.13, 0.95, 0.056, 0.63, 2.45, 1.78},
     {FAST_BIG, 6.17, 1.26, 1.23, 1.20, 3.71, 0.052, 1.07, 1.96, 1.30},
+    {FAST_DUO, 5.96, 1.29, 1.10, 1.09, 1.78, 0.051, 0.89, 1.88, 1.55},
     {FAST_SMALL, 4.85, 1.45, 1.42, 1.34, 2.80, 0.059, 1.19, 2.43, 2.07},
 };
+
+// The same with register loads (LOAD_ANY) by the operands' contiguous sides: A
+// along k and B along n (forward), both across k (dX), both along k (dW). Fitted
+// to 13000 times of 1152 products with rows off 16 bytes on MI355X, within 5%;
+// the picks are 0.7% slower than the best ones in the mean and 20% at the most
+// (one table for all three forms: 1.3% and 27%).
+constexpr CostF32 kCostRegF32[3][5] = {
+    {{FAST_HUGE, 6.78, 1.52, 1.52, 1.44, 1.88, 0.229, 1.49, 0.92, 1.70},
+     {FAST_MID, 5.70, 2.73, 1.92, 1.68, 0.50, 0.169, 0.61, 1.21, 1.80},
+     {FAST_BIG, 5.59, 1.89, 1.93, 1.95, 2.37, 0.268, 0.17, 2.02, 0.76},
+     {FAST_DUO, 5.42, 1.90, 1.47, 1.55, 1.34, 0.205, 0.47, 2.03, 1.32},
+     {FAST_SMALL, 4.22, 2.74, 1.97, 1.98, 0.92, 0.112, 0.54, 2.52, 2.66}},
+    {{FAST_HUGE, 7.23, 1.60, 1.30, 1.27, 0.22, 0.163, 1.44, 0.41, 1.92},
+     {FAST_MID, 5.00, 3.34, 2.13, 1.83, 1.04, 0.141, 0.40, 1.50, 1.65},
+     {FAST_BIG, 5.08, 2.21, 2.11, 2.13, 2.23, 0.187, 0.51, 2.20, 0.82},
+     {FAST_DUO, 5.14, 2.18, 1.68, 1.76, 0.89, 0.165, 0.48, 2.13, 1.25},
+     {FAST_SMALL, 3.93, 3.15, 2.26, 2.30, 0.78, 0.054, 0.95, 2.67, 3.23}},
+    {{FAST_HUGE, 7.11, 1.41, 1.45, 1.42, 1.33, 0.345, 1.46, 1.01, 1.60},
+     {FAST_MID, 6.06, 2.32, 1.78, 1.68, 0.23, 0.100, 1.23, 1.09, 2.11},
+     {FAST_BIG, 6.22, 1.61, 1.77, 1.83, 2.93, 0.277, 0.54, 1.74, 0.31},
+     {FAST_DUO, 6.07, 1.67, 1.40, 1.62, 1.46, 0.125, 0.70, 1.74, 1.28},
+     {FAST_SMALL, 4.80, 2.33, 1.79, 2.10, 1.08, 0.050, 1.06, 2.33, 1.56}},
+};
+constexpr int reg_form(bool amc, bool bmc) { return amc ? 1 : bmc ? 0 : 2; }
 
 // What the planner needs to know of a configuration.
 struct TileF32 {
@@ -1389,6 +1415,7 @@ inline TileF32 tile_f32(int kind) {
   using C = FastCfgs<float>;
   return kind == FAST_HUGE  ? of(C::Huge{})
          : kind == FAST_MID ? of(C::Mid{})
+         : kind == FAST_DUO ? of(C::Duo{})
          : kind == FAST_BIG ? of(C::Big{})
                             : of(C::Small{});
 }
@@ -1410,10 +1437,12 @@ inline double time_f32(const CostF32& c, const TileF32& t, int M, int N, int K, 
 inline double rowsums_us(int M, int K) { return 4.0 + 4.0 * M * K / 5e6; }
 
 // fp32: the (configuration, split) pair with the smallest modelled time whose
-// partial sums fit cap floats. rowsums: see rowsums_us. A plan with longer chains of additions than
+// partial sums fit cap floats. rowsums: see rowsums_us; costs: of the loads that
+// will run. A plan with longer chains of additions than
 // least_plan_f32's is not taken: without that line one product in fifty (all
 // with K below 1100) was up to 1.4 times further off its 64-bit value.
-inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_t cap, bool rowsums = false) {
+inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_t cap, bool rowsums = false,
+                              const CostF32 (&costs)[5] = kCostF32) {
   using C = FastCfgs<float>;
   const int64_t kb = kbatch > 0 ? kbatch : 1;
   auto tiles_of = [&](int bm, int bn) {
@@ -1429,7 +1458,7 @@ inline FastPlan plan_fast_f32(int M, int N, int K, int kbatch, int batch, int64_
   }
   const int64_t longest = least_chain_f32(least_plan_f32(M, N, K, kbatch, batch, cap), K, kb);
   FastPlan best = {FAST_SMALL, 1, 1e300};
-  for (const CostF32& c : kCostF32) {
+  for (const CostF32& c : costs) {
     const TileF32 t = tile_f32(c.kind);
     const int64_t tiles = tiles_of(t.bm, t.bn), slabs = kb * ((K + t.bk - 1) / t.bk);
     for (int s = 1; s <= kMaxSplits; s *= 2) {
@@ -1505,10 +1534,17 @@ constexpr int64_t kAnyRoom = int64_t{1} << 60;
 template <typename T>
 inline size_t fast_partial_floats(int M, int N, int K, bool required, bool rowsums) {
   int64_t s;
-  if constexpr (sizeof(T) == 4)
-    s = required ? least_plan_f32(M, N, K, 1, 1, kAnyRoom).splits
-                 : plan_fast_f32(M, N, K, 1, 1, kAnyRoom, rowsums).splits;
-  else
+  if constexpr (sizeof(T) == 4) {
+    if (required) {
+      s = least_plan_f32(M, N, K, 1, 1, kAnyRoom).splits;
+    } else {  // on whichever loads
+      s = plan_fast_f32(M, N, K, 1, 1, kAnyRoom, rowsums).splits;
+      for (const auto& costs : kCostRegF32) {
+        const int r = plan_fast_f32(M, N, K, 1, 1, kAnyRoom, rowsums, costs).splits;
+        if (r > s) s = r;
+      }
+    }
+  } else
     s = plan_fast_bf16(M, N, K, 1, 1).splits;
   return s > 1 ? static_cast<size_t>(s) * M * N : 0;
 }
@@ -1560,8 +1596,9 @@ inline hipError_t launch_fast_pair(GemmArgs g1, GemmArgs g2, hipStream_t stream)
 
 // Modelled time of fast_gemm_pair_kernel on fp32 operands, in us: its fixed
 // time, the longest tile or the tiles shared out over the chip, further rounds,
-// the loaded and the stored bytes (fitted to 152 layers on MI355X, within 8%).
-inline double pair_us_f32(const GemmArgs& g1, const GemmArgs& g2) {
+// the loaded and the stored bytes (fitted to 152 layers on direct and 297 on
+// register loads on MI355X, within 8%).
+inline double pair_us_f32(const GemmArgs& g1, const GemmArgs& g2, bool reg) {
   using C = FastCfgs<float>::Small;
   auto tiles = [](const GemmArgs& g) {
     return static_cast<double>((g.M + C::BM - 1) / C::BM) * ((g.N + C::BN - 1) / C::BN);
@@ -1571,8 +1608,11 @@ inline double pair_us_f32(const GemmArgs& g1, const GemmArgs& g2) {
   const double work = 2.0 * C::BM * C::BN * C::BK / 614e3, longest = q1 > q2 ? q1 : q2;
   const double share = (t1 * q1 + t2 * q2) / kTargetBlocks;
   const double rounds = static_cast<double>((static_cast<int64_t>(t1 + t2) + kTargetBlocks - 1) / kTargetBlocks);
-  return 4.9 + 1.14 * (longest > share ? longest : share) * work + 2.4 * (rounds - 1) +
-         0.22 * 4.0 * (t1 * q1 + t2 * q2) * (C::BM + C::BN) * C::BK / 5e6;
+  const double loads = 4.0 * (t1 * q1 + t2 * q2) * (C::BM + C::BN) * C::BK / 5e6;
+  const double outs = 4.0 * (static_cast<double>(g1.M) * g1.N + static_cast<double>(g2.M) * g2.N) / 5e6;
+  const double mma = (longest > share ? longest : share) * work;
+  return reg ? 4.0 + 2.73 * mma + 0.70 * (rounds - 1) + 0.084 * loads + 0.64 * outs
+             : 4.9 + 1.14 * mma + 2.42 * (rounds - 1) + 0.22 * loads;
 }
 
 // Whether bwd_data (g1) and bwd_weight (g2, with row sums) run as one
@@ -1583,7 +1623,8 @@ inline double pair_us_f32(const GemmArgs& g1, const GemmArgs& g2) {
 // that had run as one launch to two (batch 184, 364 -> 832: 10.5 -> 18.1 us; batch
 // 704, 512 -> 688: 22.7 -> 32.2).
 template <typename T>
-inline bool pair_ok(const GemmArgs& g1, const FastPlan& p1, const GemmArgs& g2, const FastPlan& p2, int64_t cap) {
+inline bool pair_ok(const GemmArgs& g1, const FastPlan& p1, const GemmArgs& g2, const FastPlan& p2, int64_t cap,
+                    bool reg) {
   if (g1.M <= 0 || g1.N <= 0 || g2.M <= 0 || g2.N <= 0) return false;
   if (p1.kind == FAST_SMALL && p2.kind == FAST_SMALL && p1.splits == 1 && p2.splits == 1) return true;
   if constexpr (sizeof(T) == 2) {
@@ -1593,13 +1634,13 @@ inline bool pair_ok(const GemmArgs& g1, const FastPlan& p1, const GemmArgs& g2, 
       const FastPlan l = least_plan_f32(g.M, g.N, g.K, 1, 1, cap);
       return l.kind == FAST_SMALL && l.splits == 1;
     };
-    return p1.us > 0.0 && p2.us > 0.0 && small(g1) && small(g2) && pair_us_f32(g1, g2) < p1.us + p2.us;
+    return p1.us > 0.0 && p2.us > 0.0 && small(g1) && small(g2) && pair_us_f32(g1, g2, reg) < p1.us + p2.us;
   }
 }
 template <typename T>
 inline bool fast_pair_ok(const GemmArgs& g1, const GemmArgs& g2, int64_t cap) {
   return pair_ok<T>(g1, plan_fast<T>(g1.M, g1.N, g1.K, 1, 1, cap), g2,
-                    plan_fast<T>(g2.M, g2.N, g2.K, 1, 1, cap, true), cap);
+                    plan_fast<T>(g2.M, g2.N, g2.K, 1, 1, cap, true), cap, false);
 }
 
 template <typename T, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM, int LD = LOAD_DMA>
@@ -1618,6 +1659,9 @@ inline hipError_t launch_planned(const GemmArgs& g, int kind, int batch, hipStre
       return launch_fast<typename C::Big, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
     case FAST_MID:  // fp32 only
       if constexpr (sizeof(T) == 4) return launch_fast<typename C::Mid, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
+      else return hipErrorNotSupported;
+    case FAST_DUO:  // fp32 only
+      if constexpr (sizeof(T) == 4) return launch_fast<typename C::Duo, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
       else return hipErrorNotSupported;
     case FAST_NARROW:  // fp32 only
       if constexpr (sizeof(T) == 4) return launch_fast<typename C::Narrow, AMC, BMC, OutT, EPI, RSUM, LD>(g, batch, stream);
@@ -1652,15 +1696,17 @@ inline hipError_t run_fast_gemm(GemmArgs g, int batch, hipStream_t stream, float
   return launch_planned<T, AMC, BMC, OutT, EPI, false>(g, p.kind, batch, stream);
 }
 
-// Plan of the register-load variant. fp32 takes the direct-load plan. bf16
-// has two tile sizes here: its 256-wide tiles leave no registers for two slabs
-// in flight. The split count never exceeds what the workspace of the problem
-// was sized for (the direct-load or the general kernel's plan).
+// Plan of the register-load variant. fp32: the cost model with this variant's
+// times. bf16 has two tile sizes here: its 256-wide tiles leave no registers for
+// two slabs in flight; its split count never exceeds what the workspace of the
+// problem was sized for (the direct-load or the general kernel's plan).
 template <typename T>
-inline FastPlan plan_any(int M, int N, int K, int kbatch, int batch, int64_t cap, bool rowsums = false) {
-  FastPlan p = plan_fast<T>(M, N, K, kbatch, batch, cap, rowsums);
-  if constexpr (sizeof(T) == 2) {
+inline FastPlan plan_any(int form, int M, int N, int K, int kbatch, int batch, int64_t cap, bool rowsums = false) {
+  if constexpr (sizeof(T) == 4) {
+    return plan_fast_f32(M, N, K, kbatch, batch, cap, rowsums, kCostRegF32[form]);
+  } else {
     using C = FastCfgs<bf16>;
+    FastPlan p = plan_fast_bf16(M, N, K, kbatch, batch);
     const int gs = plan_gemm<T>(M, N, K, kbatch, batch).splits;
     const int most = p.splits > gs ? p.splits : gs;
     const int64_t kb = kbatch > 0 ? kbatch : 1;
@@ -1669,11 +1715,34 @@ inline FastPlan plan_any(int M, int N, int K, int kbatch, int batch, int64_t cap
     const int b = p.kind == FAST_BIG ? C::Big::BM : C::Small::BM, bk = p.kind == FAST_BIG ? C::Big::BK : C::Small::BK;
     p.splits = fast_splits(tiles_of(b), kb * ((K + bk - 1) / bk));
     if (p.splits > most) p.splits = most;
+    return p;
   }
-  return p;
 }
 
-// Runs a GEMM whose operands are plain strided views (any_ok): on the direct
+// Whether a product on rows off 16 bytes is too short for the register loads,
+// whose pipeline and 128- or 64-deep slabs a contraction of at most 64 does not
+// fill: the general kernel (ard_gemm.hpp) then takes less time. Measured on
+// MI355X, general over register loads: fp32, up to 64 / 65 to 128 tiles of 64 x
+// 64, K up to 48: 0.98 / 0.90 (911 x 260 x 34: 5.7 / 7.1 us), up to 64: 1.05 /
+// 0.90, up to 96: 1.25 / 1.15, more tiles: 1.1 to 2; bf16 on 128 x 128 tiles, K up
+// to 64: 0.79 (2169 x 2797 x 17: 23 / 36 us), up to 128: 1.3, on 32 x 32 tiles:
+// 1.2. Not for products with row sums, which the general kernel does not take.
+template <typename T>
+inline bool short_contraction(int M, int N, int K) {
+  auto tiles_of = [&](int b) { return static_cast<int64_t>((M + b - 1) / b) * ((N + b - 1) / b); };
+  if constexpr (sizeof(T) == 4)
+    return K <= (tiles_of(64) > kTargetBlocks / 4 ? 64 : 48) && tiles_of(64) <= kTargetBlocks * 5 / 8;
+  else
+    return K <= 64 && tiles_of(FastCfgs<bf16>::Big::BM) >= kTargetBlocks / 2;
+}
+// Whether run_strided_gemm takes the product.
+template <typename T, bool AMC, bool BMC>
+inline bool strided_ok(const GemmArgs& g, bool rowsums = false) {
+  return fast_ok<AMC, BMC>(g, sizeof(T)) ||
+         (any_ok<AMC, BMC>(g, sizeof(T)) && (rowsums || !short_contraction<T>(g.M, g.N, g.K)));
+}
+
+// Runs a GEMM whose operands are plain strided views (strided_ok): on the direct
 // loads where the rows start on 16 bytes (fast_ok), else on register loads.
 template <typename T, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false>
 inline hipError_t run_strided_gemm(GemmArgs g, int batch, hipStream_t stream, float* partial, int64_t cap,
@@ -1683,7 +1752,7 @@ inline hipError_t run_strided_gemm(GemmArgs g, int batch, hipStream_t stream, fl
   if (rsum_done) *rsum_done = false;
   if (g.M <= 0 || g.N <= 0 || batch <= 0) return hipSuccess;
   FastPlan p = {FAST_SMALL, 1, 0.0};
-  if (!smallest) p = plan_any<T>(g.M, g.N, g.K, g.kbatch, batch, partial ? cap : 0, RSUM);
+  if (!smallest) p = plan_any<T>(reg_form(AMC, BMC), g.M, g.N, g.K, g.kbatch, batch, partial ? cap : 0, RSUM);
   const int64_t kb = g.kbatch > 0 ? g.kbatch : 1;
   if (!partial || kb * (g.K / 32 + 1) * p.splits >= int64_t{1} << 31) p.splits = 1;
   g.splits = p.splits;
@@ -1704,6 +1773,7 @@ inline hipError_t run_strided_gemm(GemmArgs g, int batch, hipStream_t stream, fl
     if (p.kind == FAST_HUGE) return go(typename C::Huge{});
     if (p.kind == FAST_NARROW) return go(typename C::Narrow{});
     if (p.kind == FAST_MID) return go(typename C::Mid{});
+    if (p.kind == FAST_DUO) return go(typename C::Duo{});
   }
   return go(typename C::Big{});
 }
@@ -1711,8 +1781,8 @@ inline hipError_t run_strided_gemm(GemmArgs g, int batch, hipStream_t stream, fl
 // Whether the pair runs as one launch of the register-load 32x32 tiles.
 template <typename T>
 inline bool any_pair_ok(const GemmArgs& g1, const GemmArgs& g2, int64_t cap) {
-  return pair_ok<T>(g1, plan_any<T>(g1.M, g1.N, g1.K, 1, 1, cap), g2,
-                    plan_any<T>(g2.M, g2.N, g2.K, 1, 1, cap, true), cap);
+  return pair_ok<T>(g1, plan_any<T>(reg_form(true, true), g1.M, g1.N, g1.K, 1, 1, cap), g2,
+                    plan_any<T>(reg_form(false, false), g2.M, g2.N, g2.K, 1, 1, cap, true), cap, true);
 }
 
 // A fp32 product over the columns of several steps at once (EPI_COLS): B's and

@@ -9,7 +9,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1805_08939_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-KINDS = ["HUGE", "WIDE", "TALL", "BIG", "SMALL", "NARROW", "MID"]
+KINDS = ["HUGE", "WIDE", "TALL", "BIG", "SMALL", "NARROW", "MID", "DUO"]
 
 SOURCE = r"""
 #include <hip/hip_runtime.h>
@@ -21,8 +21,8 @@ void plan_f32(int M, int N, int K, int kb, int batch, long cap, int* out) {
   const FastPlan p = plan_fast_f32(M, N, K, kb, batch, cap), l = least_plan_f32(M, N, K, kb, batch, cap);
   out[0] = p.kind, out[1] = p.splits, out[2] = l.kind, out[3] = l.splits;
 }
-void plan_reg(int bf, int M, int N, int K, long cap, int* out) {
-  const FastPlan p = bf ? plan_any<bf16>(M, N, K, 1, 1, cap) : plan_any<float>(M, N, K, 1, 1, cap);
+void plan_reg(int bf, int form, int M, int N, int K, long cap, int* out) {
+  const FastPlan p = bf ? plan_any<bf16>(form, M, N, K, 1, 1, cap) : plan_any<float>(form, M, N, K, 1, 1, cap);
   out[0] = p.kind, out[1] = p.splits;
 }
 static GemmArgs product(int M, int N, int K) {
@@ -54,7 +54,7 @@ class Planner:
 
     def __init__(self, lib):
         lib.plan_f32.argtypes = [ctypes.c_int] * 5 + [ctypes.c_long, ctypes.c_void_p]
-        lib.plan_reg.argtypes = [ctypes.c_int] * 4 + [ctypes.c_long, ctypes.c_void_p]
+        lib.plan_reg.argtypes = [ctypes.c_int] * 5 + [ctypes.c_long, ctypes.c_void_p]
         lib.pair_f32.argtypes = [ctypes.c_int] * 3 + [ctypes.c_long]
         self.lib = lib
 
@@ -64,10 +64,10 @@ class Planner:
         self.lib.plan_f32(M, N, K, kb, batch, cap, out)
         return (KINDS[out[0]], out[1]), (KINDS[out[2]], out[3])
 
-    def reg(self, dtype, M, N, K, cap=ROOM):
-        """(kind, splits) on register loads."""
+    def reg(self, dtype, form, M, N, K, cap=ROOM):
+        """(kind, splits) on register loads; form 0 forward, 1 dX, 2 dW."""
         out = (ctypes.c_int * 2)()
-        self.lib.plan_reg(int(dtype == "bf16"), M, N, K, cap, out)
+        self.lib.plan_reg(int(dtype == "bf16"), form, M, N, K, cap, out)
         return KINDS[out[0]], out[1]
 
     def pair(self, B, kin, kout, cap=ROOM):

@@ -7,7 +7,7 @@ import random
 from native_plan import planner  # noqa: F401  (fixture)
 
 # BK, waves that share a slab's k, accumulators per output: the plan's tiles, and the older plan's (one accumulator)
-TILES = {"HUGE": (32, 1, 2), "BIG": (64, 2, 4), "MID": (32, 1, 4), "SMALL": (128, 8, 1), "NARROW": (32, 2, 1)}
+TILES = {"HUGE": (32, 1, 2), "BIG": (64, 2, 4), "MID": (32, 1, 4), "DUO": (64, 2, 2), "SMALL": (128, 8, 1), "NARROW": (32, 2, 1)}
 LEAST = {k: (bk, ks, 1) for k, (bk, ks, _) in TILES.items()}
 
 
@@ -38,13 +38,16 @@ def test_no_longer_chains_of_additions(planner):
     for rng, (M, N, K) in products(4000, 1):
         kb, batch = rng.choice([(1, 1), (1, 1), (1, 4), (35, 4)])
         cap = rng.choice([planner.ROOM, 0, 1 << 20])
-        (kind, s), (lkind, ls) = planner.f32(M, N, K, kb, batch, cap)
-        got, was = chain(TILES[kind], K, kb, s), chain(LEAST[lkind], K, kb, ls)
-        assert got <= was, ((M, N, K, kb, batch, cap), kind, s, got, lkind, ls, was)
+        plan, (lkind, ls) = planner.f32(M, N, K, kb, batch, cap)
+        was = chain(LEAST[lkind], K, kb, ls)
+        reg = [planner.reg("f32", form, M, N, K, cap) for form in range(3)] if (kb, batch) == (1, 1) else []
+        for kind, s in [plan] + reg:
+            got = chain(TILES[kind], K, kb, s)
+            assert got <= was, ((M, N, K, kb, batch, cap), kind, s, got, lkind, ls, was)
 
 
 def test_splits_fit_the_room(planner):
     for rng, (M, N, K) in products(4000, 2):
         cap = round(math.exp(rng.uniform(0, math.log(1 << 26))))
-        for s in (planner.f32(M, N, K, 1, 1, cap)[0][1], planner.reg("f32", M, N, K, cap)[1]):
-            assert s == 1 or s * M * N <= cap, (M, N, K, cap, s)
+        plans = [planner.f32(M, N, K, 1, 1, cap)[0]] + [planner.reg("f32", form, M, N, K, cap) for form in range(3)]
+        assert all(s == 1 or s * M * N <= cap for _, s in plans), (M, N, K, cap, plans)
