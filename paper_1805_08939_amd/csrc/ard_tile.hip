@@ -915,26 +915,30 @@ bool tdp_fast_ok(const TdpArgs& a) {
 // pipeline rather than the wave kernels: where its tiles fill the chip, alone
 // (fwd) or together with the weight gradient that shares bwd_data's launch.
 // One workgroup walks a tile row's list alone, so with fewer of them the
-// longest list is the product's time. Measured on MI355X, layers at p = 0.5
-// unless noted (pipeline / wave kernels):
-//   fwd, workgroups 256: bf16 4096 x 4096 batch 512 19 / 25 us, fp32 102 / 108;
-//   128: bf16 2048 x 2048 batch 512 11.8 / 10.5; 64: fp32 2048 -> 1024 batch 512
-//   47 / 19; 55: bf16 256 -> 3520 batch 48 7.3 / 4.7; 32: fp32 2048 x 2048 batch
-//   128 50 / 12
-//   one-launch bwd, bwd_data workgroups 128: fp32 2048 -> 1024 batch 512 42 / 47,
-//   bf16 2048 x 2048 batch 512 19 / 20; 102: fp32 2176 -> 512 batch 304, p = 0.3,
-//   29 / 37; 64: bf16 4096 x 4096 batch 64 21.0 / 21.7, fp32 batch 128 115 / 68;
-//   36: fp32 1152 -> 3712 batch 176, p = 0.7, 71 / 31; 12: bf16 384 -> 3840 batch
-//   160, p = 0.7, 12.8 / 10.0
+// longest list is the product's time.
+// bf16: by the outputs, from 64 owners' rows of 64 samples on (fwd), from half of
+// them on (bwd). Measured on MI355X over 329 layers (batch 16 to 600, 3 to 64
+// tiles a side, p 0.3 to 0.7), pipeline over wave kernels: fwd 1.6 (up to 32
+// workgroups of 128 samples), 1.15 (to 64), 0.90 (to 96), 0.87 (to 128), 0.75;
+// bwd 1.15 (to 16), 1.06 (to 32), 0.93 (to 48), 0.82, with the batch as important
+// as the workgroups: 344 x 20 owners 13.4 / 23.0 us, 24 x 34 owners 11.4 / 9.4.
+// With these lines fwd is 0.1% and bwd 0.8% slower than the better one in the
+// mean; with lines at 256 and 96 workgroups one layer in five lost 10% or more.
+// fp32: by the workgroups, the pipeline from one per compute unit on (fwd, 4096 x
+// 4096 batch 512 102 / 108 us; over 171 layers of fewer the pipeline takes 1.26 to
+// 4.8 of the wave kernels' time), in the one-launch bwd from 3/8 of that on (2048
+// -> 1024 batch 512 42 / 47 us; below it 1.15 to 5.5).
 template <typename T>
 bool rows_on_pipeline(int pass, const TdpArgs& a, int owners) {
   using C = TdpFastCfgs<T>;
-  int bn = C::Rows::BN;
-  if constexpr (sizeof(T) == 4) {
-    if (a.B <= C::Narrow::BN) bn = C::Narrow::BN;
+  if (!tdp_fast_ok<T>(a)) return false;
+  if constexpr (sizeof(T) == 2) {
+    return static_cast<int64_t>(owners) * a.B >= (pass == TDP_FWD ? 4096 : 2048);
+  } else {
+    const int bn = a.B <= C::Narrow::BN ? C::Narrow::BN : C::Rows::BN;
+    const int64_t wgs = static_cast<int64_t>(owners) * ((a.B + bn - 1) / bn);
+    return wgs >= (pass == TDP_FWD ? kTargetBlocks : kTargetBlocks * 3 / 8);
   }
-  const int64_t wgs = static_cast<int64_t>(owners) * ((a.B + bn - 1) / bn);
-  return tdp_fast_ok<T>(a) && wgs >= (pass == TDP_FWD ? kTargetBlocks : kTargetBlocks * 3 / 8);
 }
 
 // Group records of a plan with nnz kept tiles in `rows` tile rows of tiles_k
