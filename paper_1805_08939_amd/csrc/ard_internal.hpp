@@ -35,6 +35,7 @@ struct TilePart {
   int32_t ldo, nb, nv;      // output addressing (see TileWaveArgs)
   int64_t bstride;
   float* partial;           // kTilePartSplits * own_count * tile * cols floats, or NULL
+  bool chains;              // add an output's terms in sixteen chains
 };
 // The plan's and W's checks of the tile-layer calls.
 int tile_part_check(const ard_tile_plan* p, int32_t cols, const void* W);

@@ -335,6 +335,15 @@ TilePart step_part(const TileLstm& s, const ard_tile_plan* p, const void* W, boo
   return q;
 }
 
+// Whether a product over all steps keeps the precision of lists split over four
+// workgroups or more: where a step's `rows` tile rows and batch columns alone
+// would leave most of the chip idle, on 64 x 64 tiles and batches that were never
+// padded (the others ran in one chain).
+bool split_chains(const TileLstm& s, const ard_tile_plan* p, int32_t rows) {
+  const int64_t wgs = static_cast<int64_t>(rows) * (s.B <= 64 ? 1 : (s.B + 127) / 128);
+  return p->tile == 64 && s.B == s.Bp && wgs <= 64;
+}
+
 }  // namespace
 }  // namespace ard
 
@@ -383,6 +392,7 @@ int ard_lstm_tile_fwd(const ard_lstm_tile_desc* desc, const void* X, const void*
     q.hi = s.I / p->tile;
     q.cols = q.ldo = q.nb = q.nv = static_cast<int32_t>(s.TB);
     q.partial = nullptr;
+    q.chains = split_chains(s, p, p->tiles_n);
     if ((st = tile_part_f32(true, p, q, stream, nullptr)) != ARD_OK) return st;
   }
   for (int32_t t = 0; t < s.T; ++t) {
@@ -433,6 +443,7 @@ int ard_lstm_tile_bwd(const ard_lstm_tile_desc* desc, const void* W, const void*
     q.nb = s.Bp;
     q.bstride = static_cast<int64_t>(s.I) * s.B;
     q.partial = nullptr;
+    q.chains = split_chains(s, p, p->tiles_k);
     if ((st = tile_part_f32(false, p, q, stream, nullptr)) != ARD_OK) return st;
   }
   if (dW) {

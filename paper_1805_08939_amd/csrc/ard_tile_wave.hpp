@@ -52,9 +52,9 @@ struct TileWaveArgs {
 enum { WAVE_FWD = 0, WAVE_BWD_DATA = 1 };
 constexpr int kAllTiles = 1 << 30;  // hi of an unrestricted list
 
-template <typename T, int BN_, int NWV_, int STAGES_>
+template <typename T, int BN_, int NWV_, int STAGES_, int CHAINS_ = 1>
 struct WaveCfg {
-  using Cfg = FastCfg<T, 32, BN_, 32, STAGES_, 1, 1, 1>;  // one wave's pipeline
+  using Cfg = FastCfg<T, 32, BN_, 32, STAGES_, 1, 1, 1, CHAINS_>;  // one wave's pipeline
   static constexpr int BN = BN_, NWV = NWV_, NT = 64 * NWV;
   static constexpr int ROW = BN * 4 + 32;                 // bytes of a reduction row (see fast_store)
   static constexpr int RED = NWV * 32 * ROW;
@@ -98,7 +98,7 @@ struct PartWalk {
 
 // MFMAs of one 32-deep part held in the wave's LDS stage.
 template <class Cfg, bool AMC, bool BMC>
-__device__ __forceinline__ void wave_part(const char* st, f32x16 (&acc)[Cfg::FM][Cfg::FN]) {
+__device__ __forceinline__ void wave_part(const char* st, AccChains<Cfg>& ch) {
   using Frags = StepFrags<Cfg, AMC, BMC>;
   constexpr int STEPS = Cfg::KW / Frags::KSTEP;
   Frags fr[2];
@@ -106,7 +106,7 @@ __device__ __forceinline__ void wave_part(const char* st, f32x16 (&acc)[Cfg::FM]
 #pragma unroll
   for (int s = 0; s < STEPS; ++s) {
     if (s + 1 < STEPS) fr[(s + 1) & 1].load(st, 0, 0, (s + 1) * Frags::KSTEP);
-    fr[s & 1].mma(acc);
+    ch.mma(fr[s & 1], s);
   }
 }
 
@@ -138,6 +138,7 @@ __device__ __forceinline__ void wave_walk_dma(const Src& da, const SrcB& db, Nex
     is = is + 1 == Cfg::STAGES ? 0 : is + 1;
     return kv;
   };
+  AccChains<Cfg> ch(acc);
   int kvs[Cfg::STAGES];  // valid k of the loaded parts, oldest first
 #pragma unroll
   for (int s = 0; s < Cfg::STAGES - 1; ++s) kvs[s] = issue();
@@ -162,9 +163,10 @@ __device__ __forceinline__ void wave_walk_dma(const Src& da, const SrcB& db, Nex
 #pragma unroll
       for (int s = 0; s + 1 < Cfg::STAGES; ++s) kvs[s] = kvs[s + 1];
     }
-    wave_part<Cfg, AMC, BMC>(st, acc);
+    wave_part<Cfg, AMC, BMC>(st, ch);
     cs = cs + 1 == Cfg::STAGES ? 0 : cs + 1;
   }
+  ch.sum();
   wait_vm<0>();  // no direct load may still write LDS past this point
 }
 
@@ -181,6 +183,7 @@ __device__ __forceinline__ void wave_walk_any(const Src& da, const SrcB& db, Nex
     da.load(a, kv, ra[i]);
     db.load(b, kv, rb[i]);
   };
+  AccChains<Cfg> ch(acc);
   load(0);
   if (nu > 1) load(1);
   auto part = [&](int j, int i) {
@@ -188,13 +191,14 @@ __device__ __forceinline__ void wave_walk_any(const Src& da, const SrcB& db, Nex
     db.store(smem + Cfg::ABYTES, 0, rb[i]);
     if (j + 2 < nu) load(i);
     asm volatile("" ::: "memory");
-    wave_part<Cfg, AMC, BMC>(smem, acc);
+    wave_part<Cfg, AMC, BMC>(smem, ch);
     asm volatile("" ::: "memory");
   };
   for (int j = 0; j < nu; j += 2) {
     part(j, 0);
     if (j + 1 < nu) part(j + 1, 1);
   }
+  ch.sum();
 }
 
 // The waves' accumulators (32 x BN each) added in wave order; every thread then
