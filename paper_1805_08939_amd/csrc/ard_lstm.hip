@@ -643,7 +643,13 @@ __global__ void __launch_bounds__(256) lstm_bwd_point_kernel(LstmStep s, const f
 // 8 stages measured the same or slower.
 using RecStepCfg = FastCfg<float, 16, 16, 128, 4, 1, 1, 4>;  // 64 KB LDS
 
-template <bool FINAL>
+// NACC accumulators take the k steps of a slab in turn, so that consecutive MFMAs
+// do not wait for each other's result and the chains of additions stay short: with
+// two, dh0 of a layer of 410 kept units was 1.8 times as far from its 64-bit values
+// as with the contraction split over workgroups, with four 1.4, with eight 1.0.
+// Eight take 1.5% more time than four (70 layers), so they serve contractions of
+// more than 1024 gate rows; below, four are within 1.2.
+template <bool FINAL, int NACC>
 __global__ void __launch_bounds__(RecStepCfg::NT) lstm_bwd_step_fused_kernel(LstmStep s) {
   using Cfg = RecStepCfg;
   constexpr int CPR = Cfg::BM * 4 / 16;  // 16-byte chunks per k-row of either operand
@@ -675,9 +681,9 @@ __global__ void __launch_bounds__(RecStepCfg::NT) lstm_bwd_step_fused_kernel(Lst
   ld.b_wrap = 0;
   ld.na = uniform_ptr(reinterpret_cast<const char*>(s.Wc + s.R));
   ld.nb = uniform_ptr(reinterpret_cast<const char*>(s.dA + static_cast<int64_t>(s.t) * s.G4 * s.Bp));
-  // two accumulators on alternate k steps, so that consecutive MFMAs do not
-  // wait for each other's result
-  f32x4 acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4 acc[NACC];
+#pragma unroll
+  for (int j = 0; j < NACC; ++j) acc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int q = 0; q < Cfg::STAGES - 1; ++q) ld.issue();
   // MFMA operands: lane l holds A[m][k] and B[k][n] for m = n = l % 16 and
@@ -695,16 +701,11 @@ __global__ void __launch_bounds__(RecStepCfg::NT) lstm_bwd_step_fused_kernel(Lst
     }
     ld.issue();  // slab q + STAGES - 1, into the stage slab q - 1 held
 #pragma unroll
-    for (int j = 0; j < Cfg::KW / 4; j += 2) {
-      const int k0 = w * Cfg::KW + 4 * j + kl;
-      const int o0 = mc_off<CPR, 4>(k0, mn >> 2) + (mn & 3) * 4;
-      const int o1 = mc_off<CPR, 4>(k0 + 4, mn >> 2) + (mn & 3) * 4;
-      const float a0 = *reinterpret_cast<const float*>(st + o0);
-      const float b0v = *reinterpret_cast<const float*>(st + Cfg::ABYTES + o0);
-      const float a1 = *reinterpret_cast<const float*>(st + o1);
-      const float b1v = *reinterpret_cast<const float*>(st + Cfg::ABYTES + o1);
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b0v, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b1v, acc1, 0, 0, 0);
+    for (int j = 0; j < Cfg::KW / 4; ++j) {
+      const int o = mc_off<CPR, 4>(w * Cfg::KW + 4 * j + kl, mn >> 2) + (mn & 3) * 4;
+      const float av = *reinterpret_cast<const float*>(st + o);
+      const float bv = *reinterpret_cast<const float*>(st + Cfg::ABYTES + o);
+      acc[j % NACC] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[j % NACC], 0, 0, 0);
     }
     cs = cs + 1 == Cfg::STAGES ? 0 : cs + 1;
     ck += Cfg::BK;
@@ -715,7 +716,11 @@ __global__ void __launch_bounds__(RecStepCfg::NT) lstm_bwd_step_fused_kernel(Lst
   float* red = reinterpret_cast<float*>(smem);
   lds_barrier();  // every wave is done with the stages
 #pragma unroll
-  for (int i = 0; i < 4; ++i) red[(w * 4 + i) * 64 + lane] = acc0[i] + acc1[i];
+  for (int n = 1; n < NACC; n *= 2)
+#pragma unroll
+    for (int j = 0; j < NACC; j += 2 * n) acc[j] += acc[j + n];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) red[(w * 4 + i) * 64 + lane] = acc[0][i];
   lds_barrier();
   const int src = (tm >> 2) * 16 + tn, reg = tm & 3;
   float v = 0.0f;
@@ -1038,26 +1043,27 @@ int ard_lstm_bwd(const ard_lstm_desc* desc, const void* X, const void* dHs, cons
                          int64_t{RecStepCfg::BK} * L.Bp * 4 < (int64_t{1} << 31) &&
                          static_cast<int64_t>(ns) * L.G4 * L.Bp / 2 <= (int64_t{16} << 20);
   if (rec_fused) {
-    static const hipError_t a0 = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(lstm_bwd_step_fused_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
-        RecStepCfg::LDS);
-    static const hipError_t a1 = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(lstm_bwd_step_fused_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-        RecStepCfg::LDS);
-    ARD_HIP_CHECK(a0);
-    ARD_HIP_CHECK(a1);
+    static const hipError_t attr = [] {
+      hipError_t e = hipSuccess;
+      for (auto k : {lstm_bwd_step_fused_kernel<false, 4>, lstm_bwd_step_fused_kernel<true, 4>,
+                     lstm_bwd_step_fused_kernel<false, 8>, lstm_bwd_step_fused_kernel<true, 8>})
+        if (e == hipSuccess)
+          e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  RecStepCfg::LDS);
+      return e;
+    }();
+    ARD_HIP_CHECK(attr);
   }
   const dim3 fgrid(static_cast<unsigned>((L.Bp + 15) / 16), static_cast<unsigned>((ns + 15) / 16));
   for (int t = static_cast<int>(L.T) - 1; t >= 0; --t) {
     if (t == 0 && !dh0) break;
     s.t = t;
     if (rec_fused) {
-      if (t > 0) {
-        hipLaunchKernelGGL(lstm_bwd_step_fused_kernel<false>, fgrid, dim3(RecStepCfg::NT), RecStepCfg::LDS, sm, s);
-      } else {
-        s.dh0 = static_cast<float*>(dh0);
-        hipLaunchKernelGGL(lstm_bwd_step_fused_kernel<true>, fgrid, dim3(RecStepCfg::NT), RecStepCfg::LDS, sm, s);
-      }
+      if (t == 0) s.dh0 = static_cast<float*>(dh0);
+      const bool longer = L.G4 > 1024;
+      auto kern = t > 0 ? (longer ? lstm_bwd_step_fused_kernel<false, 8> : lstm_bwd_step_fused_kernel<false, 4>)
+                        : (longer ? lstm_bwd_step_fused_kernel<true, 8> : lstm_bwd_step_fused_kernel<true, 4>);
+      hipLaunchKernelGGL(kern, fgrid, dim3(RecStepCfg::NT), RecStepCfg::LDS, sm, s);
       ARD_LAUNCH_CHECK();
       continue;
     }
