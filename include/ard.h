@@ -330,12 +330,14 @@ int ard_fc_bwd_data(const ard_fc_desc* desc, const void* dYt, const void* Yt, co
  * ard_fc_fwd for callers that cannot allocate device memory or pass a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc. The same computation, kernels and results, bit for bit,
- * as ard_fc_fwd with a workspace; the scratch the layer needs (the compact
- * weight copy of a gathered input side, split-contraction partial sums) comes
- * from a static device array of the library instead: 32 MiB per GPU, kept
- * from the first such call on that GPU until the process ends. A layer whose
- * ard_fc_workspace_bytes exceeds 32 MiB is rejected with ARD_ERR_WORKSPACE
- * before any launch. Nothing in the scratch needs to start at zero (a call
+ * as ard_fc_fwd with a workspace of ard_fc_workspace_bytes or more; the scratch
+ * the layer needs (the compact weight copy of a gathered input side,
+ * split-contraction partial sums) comes from a static device array of the
+ * library instead: 64 MiB per GPU, kept from the first such call on that GPU
+ * until the process ends. A layer that cannot do with 32 MiB (the compact copy
+ * and the least partial sums that ard_fc_fwd accepts) is rejected with
+ * ARD_ERR_WORKSPACE before any launch; one whose ard_fc_workspace_bytes is at
+ * most 32 MiB never is. Nothing in the scratch needs to start at zero (a call
  * reads only what it wrote), but every call on one GPU shares that GPU's
  * array: calls that overlap in time on one GPU (other streams, other threads)
  * race and must be serialised by the caller. No call allocates or frees.

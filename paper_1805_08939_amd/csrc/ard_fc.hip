@@ -258,21 +258,35 @@ int check_desc(const ard_fc_desc* d, FcShape* s) {
 
 size_t al256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
-constexpr size_t kNoAllocScratchBytes = size_t{32} << 20;  // scratch of ard_fc_fwd_noalloc
+// Most partial sums that the forward's plan makes use of, whatever workspace it
+// is given (where least_plan_f32 does not need more), so that its splits, and with
+// them the order of its sums, follow from the descriptor alone.
+constexpr int64_t kFwdSplitFloats = int64_t{8} << 20;
+// ard_fc_fwd_noalloc: the largest workspace that a layer may need, and the scratch,
+// which holds that and the forward's partial sums behind it
+constexpr size_t kNoAllocLimitBytes = size_t{32} << 20;
+constexpr size_t kNoAllocScratchBytes = kNoAllocLimitBytes + 4 * kFwdSplitFloats;
 
 size_t compact_bytes(const FcShape& s) { return static_cast<size_t>(s.kout) * s.ldc * s.esize; }
 
 // Split-K partial floats of one problem under whichever kernel may run it.
 template <typename T>
-size_t problem_partials(int M, int N, int K, bool required, bool rowsums = false) {
+size_t problem_partials(int M, int N, int K, bool required, bool rowsums = false, int64_t room = kAnyRoom) {
   size_t f = gemm_partial_floats<T>(M, N, K, 1, 1);
-  const size_t h = fast_partial_floats<T>(M, N, K, required, rowsums);
+  const size_t h = fast_partial_floats<T>(M, N, K, required, rowsums, room);
   return f > h ? f : h;
+}
+
+// Floats of partial sums that the forward may use.
+template <typename T>
+int64_t fwd_room(const FcShape& s) {
+  const int64_t least = static_cast<int64_t>(problem_partials<T>(s.kout, s.B, s.kin, true));
+  return least > kFwdSplitFloats ? least : kFwdSplitFloats;
 }
 
 template <typename T>
 size_t partial_bytes(const FcShape& s, bool required) {
-  size_t f = problem_partials<T>(s.kout, s.B, s.kin, required);                 // fwd
+  size_t f = problem_partials<T>(s.kout, s.B, s.kin, required, false, fwd_room<T>(s));  // fwd
   const size_t d = problem_partials<T>(s.kin, s.B, s.kout, required);           // bwd_data
   const size_t w = problem_partials<T>(s.kout, s.kin, s.B, required, !s.input_major);  // bwd_weight
   f = f > d ? f : d;
@@ -427,12 +441,7 @@ int fc_fwd_impl(const ard_fc_desc* d, const FcShape& s, const void* Xt, const vo
   WeightView wv;
   int st = weight_view<T>(s, W, ws, stream, &wv);
   if (st != ARD_OK) return st;
-  // no more room than ard_fc_fwd_noalloc has, so that its results are these bit for bit
-  const size_t skip = s.needs_compact ? al256(compact_bytes(s)) : 0;
-  if (skip < kNoAllocScratchBytes) {
-    const int64_t most = static_cast<int64_t>(kNoAllocScratchBytes - skip) / 4;
-    if (wv.cap > most) wv.cap = most;
-  }
+  if (wv.cap > fwd_room<T>(s)) wv.cap = fwd_room<T>(s);
   GemmArgs g = {};
   g.M = s.kout;
   g.N = s.B;
@@ -751,10 +760,10 @@ int ard_fc_fwd_noalloc(const ard_fc_desc* desc, const void* Xt, const void* W, c
     return st;
   if (bias && !aligned16(bias)) return fail(ARD_ERR_INVALID_ARG, "bias is not 16-byte aligned");
   const size_t need = workspace_bytes(s, desc->dtype, true);
-  if (need > kNoAllocScratchBytes)
+  if (need > kNoAllocLimitBytes)
     return fail(ARD_ERR_WORKSPACE,
-                "the layer needs %zu bytes of scratch, the static scratch holds %zu (use ard_fc_fwd with a workspace)",
-                need, kNoAllocScratchBytes);
+                "the layer needs %zu bytes of scratch, the static scratch is for %zu (use ard_fc_fwd with a workspace)",
+                need, kNoAllocLimitBytes);
   Workspace ws = {nullptr, 0};
   if (workspace_bytes(s, desc->dtype, false) > 0) {
     if ((st = device_scratch(&ws.p)) != ARD_OK) return st;

@@ -1530,17 +1530,17 @@ inline FastPlan plan_fast(int M, int N, int K, int kbatch, int batch, int64_t ca
 constexpr int64_t kAnyRoom = int64_t{1} << 60;
 
 // Floats of split-K partials of a product: what a call must be given room for
-// (required), and what it makes use of.
+// (required), and what it makes use of if it has room floats.
 template <typename T>
-inline size_t fast_partial_floats(int M, int N, int K, bool required, bool rowsums) {
+inline size_t fast_partial_floats(int M, int N, int K, bool required, bool rowsums, int64_t room) {
   int64_t s;
   if constexpr (sizeof(T) == 4) {
     if (required) {
       s = least_plan_f32(M, N, K, 1, 1, kAnyRoom).splits;
     } else {  // on whichever loads
-      s = plan_fast_f32(M, N, K, 1, 1, kAnyRoom, rowsums).splits;
+      s = plan_fast_f32(M, N, K, 1, 1, room, rowsums).splits;
       for (const auto& costs : kCostRegF32) {
-        const int r = plan_fast_f32(M, N, K, 1, 1, kAnyRoom, rowsums, costs).splits;
+        const int r = plan_fast_f32(M, N, K, 1, 1, room, rowsums, costs).splits;
         if (r > s) s = r;
       }
     }
