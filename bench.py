@@ -421,8 +421,10 @@ class FcLayer:
         self.plan = api.ard_row_plan()
         self.desc = api.fc_desc(self.ard_dtype, batch, n_in, n_out, None, self.plan, 1.0, api.ARD_ACT_NONE,
                                 api.ARD_DROPPED_SKIP)
-        self.ws = torch.empty(max(api.ard_fc_workspace_bytes(
-            api.fc_desc(self.ard_dtype, batch, n_in, n_out)), 16) // 4, device=dev)
+        # a workspace for any pattern of the step (n_max 16): sparse ones may use more than the dense one
+        self.ws = torch.empty(max([16] + [api.ard_fc_workspace_bytes(api.fc_desc(
+            self.ard_dtype, batch, n_in, n_out, None, api.ard_plan_rows(n_out, q, 0, None)))
+            for q in range(1, 17)]) // 4 + 4, device=dev)
         self.stream = torch.cuda.current_stream().cuda_stream
         self.order = [("fwd", 0), ("bwd", 0)]
         self.config = {"workload": name, "global_batch": batch, "layer": [n_in, n_out],

@@ -45,7 +45,7 @@ typedef enum {
   ARD_ERR_UNSUPPORTED = 2,   /* valid but not implemented (e.g. a dtype) */
   ARD_ERR_HIP = 3,           /* the HIP runtime reported an error */
   ARD_ERR_NOT_CONVERGED = 4, /* the search hit max_iters; its output is the last iterate */
-  ARD_ERR_WORKSPACE = 5      /* ws is NULL or smaller than the queried size */
+  ARD_ERR_WORKSPACE = 5      /* ws is NULL or too small (no call refuses the queried size) */
 } ard_status;
 
 typedef enum { ARD_F32 = 0, ARD_BF16 = 1 } ard_dtype;
@@ -155,7 +155,8 @@ int32_t ard_bitmap_popcount(const uint32_t* bits, int32_t total);
  * NULL for a list-free plan (nothing is launched). The kept set of a row pattern
  * is the arithmetic progression offset + period * i, so the FC calls fold it
  * into strided operand and output views and never read the list: they accept
- * list-free plans. The LSTM calls read the list and reject a list-free plan
+ * list-free plans. The LSTM calls take the units by the same arithmetic but read
+ * the list for some shapes of the weight gradient, and reject a list-free plan
  * that drops units (ARD_ERR_INVALID_ARG).
  */
 typedef struct {
@@ -268,9 +269,9 @@ typedef enum { ARD_DROPPED_ZERO = 0, ARD_DROPPED_SKIP = 1 } ard_dropped;
  * compact copy in their workspace themselves; a training step that compacts
  * once and passes COMPACT to both saves one pass over W. With an ungathered
  * input side FULL reads the kept rows of W in place, and where those rows do
- * not start on a 16-byte boundary the products run on the general kernel:
- * Y and dX of FULL and COMPACT then agree up to the order of rounding, not
- * bit for bit.
+ * not start on a 16-byte boundary the products run on other kernels than on
+ * the compact copy: Y and dX of FULL and COMPACT then agree up to the order of
+ * rounding, not bit for bit.
  */
 typedef enum {
   ARD_WEIGHTS_FULL = 0,
@@ -307,11 +308,17 @@ int ard_fc_compact_weights(const ard_fc_desc* desc, const void* W, void* Wc, voi
 int ard_fc_compact_weights_batch(int32_t count, const ard_fc_desc* const* descs, const void* const* W,
                                  void* const* Wc, void* stream);
 
-/* Workspace (bytes) that fwd, bwd_data and bwd_weight of this descriptor need:
- * split-contraction partial sums for small output grids and, for FULL weights
- * with a gathered input side, the compact weight copy. Depends on the kept
- * counts, so query it per pattern (or once for the dense pattern, which bounds
- * every other one of the same layer). ws may be NULL when this is 0. */
+/* Workspace (bytes) that fwd, bwd_data, bwd_weight and bwd of this descriptor
+ * make use of: split-contraction partial sums for small output grids and, for
+ * FULL weights with a gathered input side, the compact weight copy. Depends on
+ * the kept counts (a pattern's size may exceed that of the dense layer), so
+ * query it per pattern. ws may be NULL when this is 0.
+ * With this much or more a call's results are the same bits whatever the size.
+ * A call also accepts a smaller workspace down to what it cannot do without
+ * (the compact copy and, for some shapes, the partial sums of a coarser split;
+ * NULL where that is nothing) and is refused with ARD_ERR_WORKSPACE below it:
+ * ARD_F32 contractions are then split less, so that times and the order of
+ * rounding depend on ws_bytes. */
 size_t ard_fc_workspace_bytes(const ard_fc_desc* desc);
 
 int ard_fc_fwd(const ard_fc_desc* desc, const void* Xt, const void* W, const float* bias,
@@ -427,9 +434,9 @@ int ard_tile_bwd_weight(const ard_tile_desc* desc, const ard_tile_plan* plan, co
 /*
  * The layer's backward in one call: ard_tile_bwd_data and
  * ard_tile_bwd_weight on the same arguments, with the same results bit for
- * bit. Where both products take the direct-load kernels they run as one
- * launch, the weight-gradient work starting on each compute unit as soon as
- * its bwd_data tile is done; otherwise the two calls one after the other.
+ * bit. They run as one launch, the weight-gradient work starting on each
+ * compute unit as soon as its bwd_data tile is done; where an operand reaches
+ * past 2 GiB, as the two calls one after the other.
  */
 int ard_tile_bwd(const ard_tile_desc* desc, const ard_tile_plan* plan, const void* Xt, const void* dYt,
                  const void* W, void* dXt, float* dW, void* stream);
