@@ -741,6 +741,8 @@ int check_lstm(const ard_lstm_desc* d, int32_t* ns, int32_t* period, int32_t* of
   if (d->dtype != ARD_F32) return fail(ARD_ERR_UNSUPPORTED, "LSTM supports ARD_F32 only");
   if (d->seq_len < 1 || d->batch < 1 || d->input_size < 1 || d->hidden_size < 1)
     return fail(ARD_ERR_INVALID_ARG, "sizes must be >= 1");
+  if (d->batch > INT32_MAX / 4 * 4)  // the batch is padded to a multiple of 4
+    return fail(ARD_ERR_UNSUPPORTED, "batch must be < 2^31 padded to a multiple of 4");
   int st = check_row_plan(d->hidden_plan, d->hidden_size, "hidden_plan", true);
   if (st != ARD_OK) return st;
   if ((st = check_row_plan(d->input_plan, d->input_size, "input_plan", false)) != ARD_OK) return st;

@@ -216,3 +216,10 @@ def test_tile_call_validation_on_host():
         nargs = 6 if name == "bwd" else 4
         assert fn(None, ctypes.byref(plan()), *([None] * nargs)) == _ffi.ARD_ERR_INVALID_ARG  # NULL descriptor
         assert fn(ctypes.byref(desc()), None, *([None] * nargs)) == _ffi.ARD_ERR_INVALID_ARG  # NULL plan
+
+
+def test_lstm_batch_that_cannot_be_padded_is_refused():
+    """The LSTM pads its batch to a multiple of 4: one that has none below 2^31 is refused, the largest other is not."""
+    for batch, ok in ((2**31 - 1, False), (2**31 - 3, False), (2**31 - 4, True)):
+        desc = api.lstm_desc(api.ARD_F32, 1, batch, 1, 1, None, None)
+        assert (api.ard_lstm_workspace_bytes(desc) > 0) == ok

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import device
+from gpu_util import ard_dtype, device
 from oracle import lstm as olstm
 from paper_1805_08939_amd import api
 
@@ -19,52 +19,133 @@ def some_columns(B):
     return torch.tensor(c, device=device())
 
 
-def random_on_gpu(seed, *shape):
+def random_on_gpu(seed, *shape, dtype=torch.float32):
     g = torch.Generator(device=device())
     g.manual_seed(seed)
-    return torch.empty(*shape, device=device()).uniform_(-0.5, 0.5, generator=g)
+    return torch.empty(*shape, dtype=dtype, device=device()).uniform_(-0.5, 0.5, generator=g)
 
 
-def lstm_reference(X, W, b, h0, c0, dHs, cols, mask=None):
-    """The oracle's forward and backward (without weight gradients) of the samples
-    cols of X[T][I][B] and the others, in the library's layouts."""
+def gradients_at(cols, *shape):
+    """Output gradients that are zero but at the samples cols: the weight
+    gradients are then those of these samples."""
+    g = torch.zeros(*shape, device=device())
+    g[..., cols] = random_on_gpu(4, *shape[:-1], len(cols))
+    return g
+
+
+def lstm_reference(X, W, b, h0, c0, dHs, cols, tile_mask=None, kept=None):
+    """The oracle's forward and backward on the samples cols, in the library's layouts."""
     def take(t):
         return t[..., cols].transpose(-1, -2).double().cpu().numpy()
-    w = W.double().cpu().numpy() * (1.0 if mask is None else mask)
-    ones = np.ones(w.shape[0] // 4)
-    Hs, hT, cT, cache = olstm.lstm_forward(take(X), w, b.double().cpu().numpy(), ones, take(h0), take(c0))
-    dX, _, _, dh0, dc0 = olstm.lstm_backward(take(X), w, ones, cache, take(dHs), None, None)
+    w = W.double().cpu().numpy() * (1.0 if tile_mask is None else tile_mask)
+    m = np.ones(w.shape[0] // 4) if kept is None else kept
+    Hs, hT, cT, cache = olstm.lstm_forward(take(X), w, b.double().cpu().numpy(), m, take(h0), take(c0))
+    dX, dW, db, dh0, dc0 = olstm.lstm_backward(take(X), w, m, cache, take(dHs), None, None)
+    if tile_mask is not None:
+        dW = dW * tile_mask
     return {"Hs": Hs.transpose(0, 2, 1), "hT": hT.T, "cT": cT.T, "dX": dX.transpose(0, 2, 1), "dh0": dh0.T,
-            "dc0": dc0.T}
+            "dc0": dc0.T}, {"dW": dW, "db": db}
 
 
 def check(got, want, cols):
-    for name, w in want.items():
-        v = got[name][..., cols].double().cpu().numpy()
-        # fp32 gates and sums of at most some tens of terms: a few roundings of 2^-24 of the largest value
-        assert np.abs(v - w).max() <= 1e-5 * max(np.abs(w).max(), 1e-3), name
+    for name, w in list(want[0].items()) + list(want[1].items()):
+        v = got[name][..., cols] if name in want[0] else got[name]
+        # fp32 gates and sums of at most some hundred terms: a few roundings of 2^-24 of the largest value
+        assert np.abs(v.double().cpu().numpy() - w).max() <= 1e-5 * max(np.abs(w).max(), 1e-3), name
 
 
-# Step products on contiguous copies of a step's columns, whose rows are Bp
-# floats: row 31 of a tile passes 2^31 bytes from Bp = 2^24 on, and 2^32 bytes
-# at the last columns of 2^25 + 8.
-@pytest.mark.parametrize("T,B", [(1, (1 << 25) + 6)])
-def test_lstm_tile_long_rows(T, B):
-    I, H, tile = 24, 8, 32
-    print(T, B, I, H, tile, flush=True)
-    W, b = random_on_gpu(1, 4 * H, I + H), random_on_gpu(2, 4 * H)
-    X, dHs = random_on_gpu(3, T, I, B), random_on_gpu(4, T, H, B)
-    h0, c0 = random_on_gpu(5, H, B), random_on_gpu(6, H, B)
-    bits = torch.ones(1, dtype=torch.int32, device=device())
-    plan_ws = torch.empty(api.ard_tile_plan_workspace_bytes(1, 1) // 4, dtype=torch.int32, device=device())
-    plan = api.ard_plan_tiles(4 * H, I + H, tile, bits, 1, plan_ws)
-    desc = api.lstm_tile_desc(api.ARD_F32, T, B, I, H, plan)
-    ws = torch.empty(api.ard_lstm_tile_workspace_bytes(desc) // 4 + 4, device=device())
-    got = {"Hs": torch.empty(T, H, B, device=device()), "dX": torch.empty(T, I, B, device=device())}
+def outputs(T, B, I, H):
+    got = {"Hs": torch.empty(T, H, B, device=device()), "dX": torch.empty(T, I, B, device=device()),
+           "dW": torch.empty(4 * H, I + H, device=device()), "db": torch.empty(4 * H, device=device())}
     for n in ("hT", "cT", "dh0", "dc0"):
         got[n] = torch.empty(H, B, device=device())
-    api.ard_lstm_tile_fwd(desc, X, W, b, h0, c0, got["Hs"], got["hT"], got["cT"], ws)
-    api.ard_lstm_tile_bwd(desc, W, dHs, None, None, ws, got["dX"], None, None, got["dh0"], got["dc0"])
-    torch.cuda.synchronize()
+    return got
+
+
+# Step products on contiguous copies of a step's columns (T Bp of 2^23 and more), whose rows are Bp floats: row 31
+# of a tile passes 2^31 bytes from Bp = 2^24 on, and 2^32 bytes at the last columns of 2^25 + 8
+@pytest.mark.parametrize("T,B,I,H", [(1, (1 << 25) + 6, 24, 8), (2, (1 << 22) + 2, 24, 8), (2, (1 << 22) + 3, 32, 32)])
+def test_lstm_tile_long_rows(T, B, I, H):
+    tile = 32
+    print(T, B, I, H, flush=True)
     cols = some_columns(B)
-    check(got, lstm_reference(X, W, b, h0, c0, dHs, cols), cols)
+    W, b = random_on_gpu(1, 4 * H, I + H), random_on_gpu(2, 4 * H)
+    X, dHs = random_on_gpu(3, T, I, B), gradients_at(cols, T, H, B)
+    h0, c0 = random_on_gpu(5, H, B), random_on_gpu(6, H, B)
+    tn, tk = 4 * H // tile, (I + H) // tile
+    keep = np.ones((tn, tk), dtype=np.uint32)
+    if keep.size > 1:
+        keep[1, 0] = 0
+    word = int(sum(int(v) << i for i, v in enumerate(keep.reshape(-1))))
+    bits = torch.tensor([word], dtype=torch.int32, device=device())
+    plan_ws = torch.empty(api.ard_tile_plan_workspace_bytes(tn, tk) // 4, dtype=torch.int32, device=device())
+    plan = api.ard_plan_tiles(4 * H, I + H, tile, bits, int(keep.sum()), plan_ws)
+    desc = api.lstm_tile_desc(api.ARD_F32, T, B, I, H, plan)
+    ws = torch.empty(api.ard_lstm_tile_workspace_bytes(desc) // 4 + 4, device=device())
+    got = outputs(T, B, I, H)
+    api.ard_lstm_tile_fwd(desc, X, W, b, h0, c0, got["Hs"], got["hT"], got["cT"], ws)
+    api.ard_lstm_tile_bwd(desc, W, dHs, None, None, ws, got["dX"], got["dW"], got["db"], got["dh0"], got["dc0"])
+    torch.cuda.synchronize()
+    mask = np.kron(keep, np.ones((tile, tile)))
+    check(got, lstm_reference(X, W, b, h0, c0, dHs, cols, tile_mask=mask), cols)
+
+
+# A batch whose rows no slab's offsets reach over: the step kernels with register loads, the split recurrent kernel and
+# the general products, with a kept list in the weight gradient; and an X of more than 2^31 bytes whose steps are
+# small: products step by step (batched) on the direct loads
+@pytest.mark.parametrize("T,B,I,H,period", [(2, (1 << 23) + 2, 8, 64, 2), (64, 8192, 1024, 8, 1)])
+def test_lstm_past_the_offsets(T, B, I, H, period):
+    print(T, B, I, H, period, flush=True)
+    cols = some_columns(B)
+    W, b = random_on_gpu(1, 4 * H, I + H) * 0.2, random_on_gpu(2, 4 * H)
+    X, dHs = random_on_gpu(3, T, I, B), gradients_at(cols, T, H, B)
+    h0, c0 = random_on_gpu(5, H, B), random_on_gpu(6, H, B)
+    offset = period - 1
+    idx = torch.zeros(H, dtype=torch.int32, device=device())
+    plan = api.ard_plan_rows(H, period, offset, idx)
+    desc = api.lstm_desc(api.ARD_F32, T, B, I, H, plan, None)
+    ws = torch.empty(api.ard_lstm_workspace_bytes(desc) // 4 + 4, device=device())
+    got = outputs(T, B, I, H)
+    api.ard_lstm_fwd(desc, X, W, b, h0, c0, got["Hs"], got["hT"], got["cT"], ws)
+    api.ard_lstm_bwd(desc, X, dHs, None, None, ws, got["dX"], got["dW"], got["db"], got["dh0"], got["dc0"])
+    torch.cuda.synchronize()
+    kept = np.zeros(H)
+    kept[offset::period] = 1
+    check(got, lstm_reference(X, W, b, h0, c0, dHs, cols, kept=kept), cols)
+
+
+# Activations of 2^31 bytes and more: the tile layer's register-staged kernel, each pass, tile size and type, on rows of
+# whole 16-byte chunks and not
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("tile,odd", [(32, 0), (64, 0), (32, 1), (64, 3)])
+def test_tile_layer_past_the_offsets(dtype, tile, odd):
+    sdt, es = (torch.float32, 4) if dtype == "f32" else (torch.bfloat16, 2)
+    N = K = 64
+    B = (1 << 31) // (K * es) + 16 + odd
+    print(dtype, tile, B, flush=True)
+    cols = some_columns(B)
+    X, W = random_on_gpu(1, K, B, dtype=sdt), random_on_gpu(2, N, K, dtype=sdt)
+    dY = torch.zeros(N, B, dtype=sdt, device=device())
+    dY[:, cols] = random_on_gpu(3, N, len(cols), dtype=sdt)
+    tn, tk = N // tile, K // tile
+    keep = torch.ones(tn, tk)
+    if tn > 1:
+        keep[0, 1] = 0
+    word = int(sum(int(v) << i for i, v in enumerate(keep.reshape(-1))))
+    bits = torch.tensor([word], dtype=torch.int32, device=device())
+    pw = torch.empty(api.ard_tile_plan_workspace_bytes(tn, tk) // 4, dtype=torch.int32, device=device())
+    plan = api.ard_plan_tiles(N, K, tile, bits, int(keep.sum()), pw)
+    desc = api.tile_desc(ard_dtype(dtype), B, K, N, 0.5, api.ARD_DROPPED_ZERO)
+    Y, dX = torch.empty(N, B, dtype=sdt, device=device()), torch.empty(K, B, dtype=sdt, device=device())
+    dW = torch.full((N, K), 7.0, device=device())
+    api.ard_tile_fwd(desc, plan, X, W, Y)
+    api.ard_tile_bwd(desc, plan, X, dY, W, dX, dW)
+    torch.cuda.synchronize()
+    m = keep.repeat_interleave(tile, 0).repeat_interleave(tile, 1).double().to(device())
+    w, x, dy = W.double() * m, X[:, cols].double(), dY[:, cols].double()
+    out = 1e-5 if dtype == "f32" else 2.0 ** -8  # fp32 sums; bf16 outputs round by 2^-9
+    for v, a, c, tol in ((Y[:, cols], w, x, out), (dX[:, cols], w.t(), dy, out), (dW, dy, x.t(), 1e-5)):
+        want, norm = 0.5 * (a @ c), 0.5 * (a.abs() @ c.abs())
+        if v is dW:
+            want, norm = want * m, norm * m
+        assert ((v.double() - want).abs() <= tol * norm + 1e-30).all()
