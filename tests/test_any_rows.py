@@ -7,9 +7,8 @@ import pytest
 import torch
 
 from gpu_util import ard_dtype, device, workspace
+from native_plan import planner  # noqa: F401  (fixture)
 from paper_1805_08939_amd import api, synth
-
-pytestmark = pytest.mark.gpu
 
 # largest |error| over |A| |B| of one product: fp32 sums of K terms round each
 # partial sum by 2^-24 of the terms so far (K / 8 sequential steps of the matrix
@@ -32,12 +31,25 @@ def close(got, a, b, tol, rows=None):
     assert (err <= tol * norm + 1e-30).all(), float((err / (norm + 1e-30)).max())
 
 
-# (batch, inputs, outputs): 128x128, 64x64, 128x32 and 32x32 tiles of the three
-# products, K of one element to many slabs, and split contractions
+# (batch, inputs, outputs): K of one element to many slabs, and split contractions; with the second part every
+# fp32 tile in each of the three products (the full layout; see test_shapes_reach_every_tile)
 SHAPES = [(1501, 1700, 1703), (833, 834, 835), (31, 45, 20481), (17, 1501, 33), (1, 1, 1), (129, 33, 65),
-          (7, 255, 130)]
+          (7, 255, 130),
+          (1507, 137, 2071), (582, 5194, 82), (107, 1994, 1547), (274, 70, 3660), (63, 798, 1120), (46, 585, 987),
+          (71, 4327, 106), (1190, 781, 33), (33, 522, 1603), (38, 35, 5042), (19, 18, 510)]
 
 
+def test_shapes_reach_every_tile(planner):
+    reached = set()
+    for B, K, N in SHAPES:
+        if B % 4 and K % 4:  # both operands' rows off 16 bytes in every product
+            for form, (m, n, k) in enumerate([(N, B, K), (K, B, N), (N, K, B)]):
+                reached.add((form, planner.reg("f32", form, m, n, k)[0]))
+    want = {(form, kind) for form in range(3) for kind in ("HUGE", "BIG", "DUO", "MID", "SMALL")} | {(0, "NARROW")}
+    assert want <= reached, want - reached
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", SHAPES)
 @pytest.mark.parametrize("layout", ["full", "gathered", "compact_grad", "input_major"])

@@ -81,7 +81,7 @@ def run_lstm(T, B, I, H, pattern, seed, with_state=True, with_final_grads=True, 
 
 
 @pytest.mark.parametrize("shape,pattern,in_pattern", [
-    ((3, 5, 6, 10), (2, 1), (3, 1)),         # unaligned: the register-staged paths
+    ((3, 5, 6, 10), (2, 1), (3, 1)),         # a ragged batch and a compact width off 16 bytes
     ((2, 8, 12, 10), (3, 0), (2, 1)),
     ((2, 8, 12, 10), (1, 0), (4, 3)),
     ((4, 64, 96, 200), (2, 1), (3, 2)),      # aligned: the direct-load GEMMs and step kernels
@@ -101,7 +101,7 @@ def test_tiny_patterns(pattern):
 
 @pytest.mark.parametrize("shape,pattern", [((4, 40, 68, 100), (3, 1)), ((3, 37, 33, 70), (2, 0)),
                                            ((5, 96, 128, 160), (4, 3)), ((1, 8, 12, 64), (5, 2)),
-                                           # split forward recurrence on unaligned operands (KW = 370)
+                                           # a compact row of 370 entries, padded to 372
                                            ((3, 36, 70, 600), (2, 1))])
 def test_multi_tile_and_unaligned(shape, pattern):
     T, B, I, H = shape
@@ -118,9 +118,8 @@ def test_all_units_kept_wide_recurrence_tiles(shape):
 @pytest.mark.parametrize("shape,pattern,in_pattern", [((35, 20, 640, 320), (2, 1), (1, 0)),
                                                       ((35, 20, 768, 320), (2, 0), (2, 1))])
 def test_small_batch_steps_on_narrow_tiles(shape, pattern, in_pattern):
-    """Batch 20 over 35 steps: the step-batched input projection (and, with
-    every input kept, the input gradient) has 20 columns per step and at
-    least 160 row tiles of 128, so it runs on 128 x 32 tiles."""
+    """Batch 20 over 35 steps: the input projection and the input gradient of
+    all steps are one product of 700 columns each, in blocks of 20."""
     run_lstm(*shape, pattern, seed=sum(shape), in_pattern=in_pattern)
 
 

@@ -5,21 +5,40 @@ import pytest
 import torch
 
 from gpu_util import device
+from native_plan import planner  # noqa: F401  (fixture)
 from paper_1805_08939_amd import api, synth
 from test_lstm_parity import run_lstm
 
-pytestmark = pytest.mark.gpu
-
-
 # (T, B, I, H), hidden pattern, input pattern: padded batches of one sample to
-# more than one tile; 32-, 64- and 128-wide tiles of T * Bp columns that end
-# inside a step; flat contractions over T * Bp with remainders of a slab, in the
-# gathered and the identity layout; rows of X that are no multiple of 16 bytes
+# more than one tile; tiles of T * Bp columns that end inside a step; flat
+# contractions over T * Bp with remainders of a slab, in the gathered and the
+# identity layout; rows of X that are no multiple of 16 bytes. With the shapes
+# below them every tile in each product (test_lstm_shapes_reach_every_tile).
 LSTM = [((1, 1, 3, 5), (1, 0), (1, 0)), ((7, 1, 40, 64), (2, 1), (1, 0)), ((35, 5, 96, 130), (2, 0), (3, 1)),
         ((9, 10, 300, 512), (2, 1), (1, 0)), ((5, 20, 256, 1024), (2, 1), (2, 0)), ((3, 66, 130, 96), (3, 2), (1, 0)),
         ((2, 129, 512, 256), (1, 0), (4, 1)), ((20, 64, 768, 640), (2, 0), (1, 0))]
+LSTM += [(shape, (1, 0), (1, 0)) for shape in
+         [(8, 121, 658, 25), (20, 72, 2278, 5), (11, 10, 1718, 5), (7, 13, 2476, 19), (14, 132, 74, 35),
+          (18, 65, 114, 122), (18, 103, 6, 402), (17, 121, 13, 28), (17, 1, 5, 272), (13, 6, 6, 398), (1, 1, 4, 861),
+          (1, 1, 5, 264), (20, 1, 2238, 6), (9, 10, 2497, 13), (1, 1, 1801, 420), (3, 1, 2360, 5), (1, 5, 33, 5125),
+          (1, 30, 20490, 16)]]
 
 
+def test_lstm_shapes_reach_every_tile(planner):
+    reached = set()
+    for (T, B, I, H), pattern, in_pattern in LSTM:
+        n, cols = len(range(pattern[1], H, pattern[0])), T * ((B + 3) // 4 * 4)
+        k = len(range(in_pattern[1], I, in_pattern[0]))
+        # input projection, dX, and the two parts of dW (four gates in one launch), none split
+        for name, m, w, depth, batch in (("zx", 4 * n, cols, k, 1), ("dx", k, cols, 4 * n, 1), ("dw", n, k, cols, 4),
+                                         ("dwh", n, n, cols, 4)):
+            reached.add((name, planner.f32(m, w, depth, 1, batch, 0)[0][0]))
+    want = {(p, t) for p in ("zx", "dx", "dw", "dwh") for t in ("HUGE", "BIG", "DUO", "MID", "SMALL")}
+    want |= {("zx", "NARROW"), ("dx", "NARROW")}
+    assert want <= reached, want - reached
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("shape,pattern,in_pattern", LSTM)
 @pytest.mark.parametrize("states", [True, False])
 def test_products_over_all_steps(shape, pattern, in_pattern, states):
@@ -27,11 +46,17 @@ def test_products_over_all_steps(shape, pattern, in_pattern, states):
     run_lstm(*shape, pattern, seed=sum(shape), with_state=states, with_final_grads=states, in_pattern=in_pattern)
 
 
-# (batch, inputs, outputs): 128x128, 64x64 (two depths) and 32x32 tiles of the
-# three products, with and without a split contraction, remainders of each
+# (batch, inputs, outputs): every tile, with and without a split contraction, remainders of each
 FC = [(2048, 1536, 2240), (1028, 2052, 1028), (260, 4100, 516), (20, 9000, 1500), (700, 3004, 1500), (64, 8200, 68)]
 
 
+def test_fc_shapes_reach_every_tile(planner):
+    plans = [planner.f32(*p)[0] for B, K, N in FC for p in ((N, B, K), (K, B, N), (N, K, B))]
+    assert {k for k, _ in plans} >= {"HUGE", "BIG", "DUO", "MID", "SMALL"}
+    assert {k for k, s in plans if s > 1} >= {"DUO", "MID", "SMALL"}
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("shape", FC)
 def test_f32_tiles_and_workspaces(shape):
     B, K, N = shape
@@ -70,6 +95,7 @@ def test_f32_tiles_and_workspaces(shape):
     assert ran > 0
 
 
+@pytest.mark.gpu
 def test_initial_state_gradient_precision():
     """dh0 through the one-kernel backward step, 1640 gate rows deep."""
     import numpy as np
