@@ -43,6 +43,13 @@ namespace ard {
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
+// LD: how the operands are loaded.
+enum FastLoad {
+  LOAD_DMA = 0,   // direct loads
+  LOAD_ANY = 1,   // rows starting at any element (register loads)
+  LOAD_FLAT = 2   // direct loads of a flat contraction (FlatLoader)
+};
+
 template <typename T_, int BM_, int BN_, int BK_, int STAGES_, int WGM_, int WGN_, int KSPLIT_, int CHAINS_ = 1>
 struct FastCfg {
   using T = T_;
@@ -387,19 +394,29 @@ struct StepFrags {
 // A lane's sums of the A values that it reads (StepFrags::rowsum): a slab's in 32
 // bits, those of the slabs in 64, for one lane adds an eighth or more of the
 // whole contraction. A bias gradient over 1450 samples is then 6e-8 off its
-// 64-bit value, 2.6e-7 with one chain in 32 bits.
-template <class Cfg>
+// 64-bit value, 2.6e-7 with one chain in 32 bits. bf16 on direct loads keeps one
+// chain in 32 bits: its values have 8 bits, its sums are 1e-8 off, and the 8192 x
+// 8192 layer at batch 2048 takes 1% more time with a sum per slab.
+template <class Cfg, int LD>
 struct RowSums {
-  double all[Cfg::FM];
+  static constexpr bool BY_SLAB = Cfg::ES == 4 || LD == LOAD_ANY;
+  typename std::conditional<BY_SLAB, double, float>::type all[Cfg::FM];
   float slab[Cfg::FM];
 
   __device__ __forceinline__ void clear() {
 #pragma unroll
-    for (int i = 0; i < Cfg::FM; ++i) all[i] = 0.0, slab[i] = 0.0f;
+    for (int i = 0; i < Cfg::FM; ++i) all[i] = 0, slab[i] = 0.0f;
+  }
+  template <class Frags>
+  __device__ __forceinline__ void add(const Frags& fr) {  // a k step's values
+    if constexpr (BY_SLAB) fr.rowsum(slab);
+    else fr.rowsum(all);
   }
   __device__ __forceinline__ void end_slab() {
+    if constexpr (BY_SLAB) {
 #pragma unroll
-    for (int i = 0; i < Cfg::FM; ++i) all[i] += slab[i], slab[i] = 0.0f;
+      for (int i = 0; i < Cfg::FM; ++i) all[i] += slab[i], slab[i] = 0.0f;
+    }
   }
 };
 
@@ -591,7 +608,7 @@ __device__ __forceinline__ void grouped_tile(int bid, int nx, int ny, int& row, 
 // flight.
 template <class Cfg, bool AMC, bool BMC, bool TAIL, bool RSUM = false, class Loader>
 __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, f32x16 (&acc)[Cfg::FM][Cfg::FN],
-                                          int wm, int wn, int kw0, char* smem, RowSums<Cfg>* rs = nullptr) {
+                                          int wm, int wn, int kw0, char* smem, RowSums<Cfg, LOAD_DMA>* rs = nullptr) {
   using Frags = StepFrags<Cfg, AMC, BMC>;
   constexpr int STEPS = Cfg::KW / Frags::KSTEP;
   static_assert(STEPS % 2 == 0, "a slab holds an even number of k steps");
@@ -638,7 +655,7 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
       }
       ch.mma(fr[s & 1], s);
       if constexpr (RSUM) {
-        fr[s & 1].rowsum(rs->slab);
+        rs->add(fr[s & 1]);
         if (s + 1 == STEPS) rs->end_slab();
       }
       if (s == 0) ld.issue_b();
@@ -650,7 +667,7 @@ __device__ __forceinline__ void run_slabs(Loader& ld, int nslab, int K, int ck, 
       if (s + 1 < STEPS) fr[(s + 1) & 1].load(st, wm, wn, kw0 + (s + 1) * Frags::KSTEP);
       ch.mma(fr[s & 1], s);
       if constexpr (RSUM) {
-        fr[s & 1].rowsum(rs->slab);
+        rs->add(fr[s & 1]);
         if (s + 1 == STEPS) rs->end_slab();
       }
       if (s == 0) ld.issue_b();
@@ -806,7 +823,7 @@ struct RegLoader {
 template <class Cfg, bool AMC, bool BMC, bool RSUM>
 __device__ __forceinline__ void run_slabs_reg(RegLoader<Cfg, AMC, BMC>& ld, int nslab,
                                               f32x16 (&acc)[Cfg::FM][Cfg::FN], int wm, int wn, int kw0, char* smem,
-                                              RowSums<Cfg>* rs) {
+                                              RowSums<Cfg, LOAD_ANY>* rs) {
   using Frags = StepFrags<Cfg, AMC, BMC>;
   constexpr int STEPS = Cfg::KW / Frags::KSTEP;
   static_assert(Cfg::STAGES >= 2, "two LDS stages");
@@ -828,7 +845,7 @@ __device__ __forceinline__ void run_slabs_reg(RegLoader<Cfg, AMC, BMC>& ld, int 
       if (s + 1 < STEPS) fr[(s + 1) & 1].load(st, wm, wn, kw0 + (s + 1) * Frags::KSTEP);
       ch.mma(fr[s & 1], s);
       if constexpr (RSUM) {
-        fr[s & 1].rowsum(rs->slab);
+        rs->add(fr[s & 1]);
         if (s + 1 == STEPS) rs->end_slab();
       }
     }
@@ -980,12 +997,6 @@ __device__ __forceinline__ void fast_store(const GemmArgs& g, f32x16 (&acc)[Cfg:
 // row 32 i + l % 32, the waves of a k split are added in LDS in split order.
 // One workgroup's output tile: position bid of an nx x ny tile grid in the
 // grouped order, batch-and-split index bzs.
-// LD: how the operands are loaded.
-enum FastLoad {
-  LOAD_DMA = 0,   // direct loads
-  LOAD_ANY = 1,   // rows starting at any element (register loads)
-  LOAD_FLAT = 2   // direct loads of a flat contraction (LOAD_FLAT)
-};
 template <class Cfg, bool AMC, bool BMC, typename OutT, int EPI, bool RSUM = false, int LD = LOAD_DMA>
 __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, int tile_col, int bzs, char* smem) {
   using T = typename Cfg::T;
@@ -1024,7 +1035,7 @@ __device__ __forceinline__ void fast_gemm_tile(const GemmArgs& g, int tile_row, 
   // slabs q0 .. q1 - 1 of this split
   static_assert(DmaSrc<Cfg, Cfg::BM, AMC>::PER_WAVE + DmaSrc<Cfg, Cfg::BN, BMC>::PER_WAVE == Cfg::LPW, "load count");
   constexpr int ES = Cfg::ES;
-  RowSums<Cfg> rs;
+  RowSums<Cfg, LD == LOAD_ANY ? LOAD_ANY : LOAD_DMA> rs;
   rs.clear();
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (LD == LOAD_FLAT) {
@@ -1371,9 +1382,12 @@ struct CostF32 {
 // most; the constants before, from eleven products, were 3.2% and 83%, and left
 // one layer in ten slower than the fill rule that they had replaced (batch 32,
 // 1952 -> 2604 forward 13.4 -> 19.2 us; batch 1652, 80 -> 3252 backward 35 -> 56).
+// Mid has 0.4 us more than fitted: with operands out of the caches, as between a
+// network's layers, its 32-deep slabs wait longer than Duo's (the 784-2048-2048-10
+// network's step at batch 128 88.7 us without, 86.7 with; the pick 0.2% over the best).
 constexpr CostF32 kCostF32[5] = {
     {FAST_HUGE, 6.98, 1.11, 1.06, 1.03, 1.84, 0.083, 1.06, 3.07, 1.45},
-    {FAST_MID, 5.80, 1.46, 1.19, 1.13, 0.95, 0.056, 0.63, 2.45, 1.78},
+    {FAST_MID, 6.20, 1.46, 1.19, 1.13, 0.95, 0.056, 0.63, 2.45, 1.78},
     {FAST_BIG, 6.17, 1.26, 1.23, 1.20, 3.71, 0.052, 1.07, 1.96, 1.30},
     {FAST_DUO, 5.96, 1.29, 1.10, 1.09, 1.78, 0.051, 0.89, 1.88, 1.55},
     {FAST_SMALL, 4.85, 1.45, 1.42, 1.34, 2.80, 0.059, 1.19, 2.43, 2.07},
@@ -1724,16 +1738,18 @@ inline FastPlan plan_any(int form, int M, int N, int K, int kbatch, int batch, i
 // fill: the general kernel (ard_gemm.hpp) then takes less time. Measured on
 // MI355X, general over register loads: fp32, up to 64 / 65 to 128 tiles of 64 x
 // 64, K up to 48: 0.98 / 0.90 (911 x 260 x 34: 5.7 / 7.1 us), up to 64: 1.05 /
-// 0.90, up to 96: 1.25 / 1.15, more tiles: 1.1 to 2; bf16 on 128 x 128 tiles, K up
-// to 64: 0.79 (2169 x 2797 x 17: 23 / 36 us), up to 128: 1.3, on 32 x 32 tiles:
-// 1.2. Not for products with row sums, which the general kernel does not take.
+// 0.90, up to 96: 1.25 / 1.15, more tiles: 1.1 to 2; bf16 on 128 x 128 tiles whose
+// output rows hold no whole 4-element pieces, K below 64: 0.79 (2169 x 2797 x 17:
+// 23 / 36 us), with whole pieces, which only the register-load kernel stores at
+// once, 1.5 (4612 x 596 x 64: 22.7 / 12.4), K up to 128: 1.3, on 32 x 32 tiles: 1.2.
+// Not for products with row sums, which the general kernel does not take.
 template <typename T>
 inline bool short_contraction(int M, int N, int K) {
   auto tiles_of = [&](int b) { return static_cast<int64_t>((M + b - 1) / b) * ((N + b - 1) / b); };
   if constexpr (sizeof(T) == 4)
     return K <= (tiles_of(64) > kTargetBlocks / 4 ? 64 : 48) && tiles_of(64) <= kTargetBlocks * 5 / 8;
   else
-    return K <= 64 && tiles_of(FastCfgs<bf16>::Big::BM) >= kTargetBlocks / 2;
+    return K < 64 && N % 4 != 0 && tiles_of(FastCfgs<bf16>::Big::BM) >= kTargetBlocks / 2;
 }
 // Whether run_strided_gemm takes the product.
 template <typename T, bool AMC, bool BMC>
