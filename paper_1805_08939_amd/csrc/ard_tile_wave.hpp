@@ -18,7 +18,7 @@
 //
 // Measured on MI355X, a layer's plan, forward and backward at p = 0.5, against
 // the register-staged one-buffer kernel these sizes ran on: fp32 2048 x 2048,
-// batch 128, 32 x 32 tiles 173 -> 44 us (forward 69 -> 12); bf16 2816 x 384,
+// batch 128, 32 x 32 tiles 172 -> 38 us (forward 69 -> 12); bf16 2816 x 384,
 // batch 391, 64 x 64 tiles 296 -> 56 us.
 #pragma once
 
